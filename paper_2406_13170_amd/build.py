@@ -8,13 +8,13 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libamph.so")
-SOURCES = ["gemv.hip", "small.hip", "gemm_skinny.hip", "verify_attn.hip", "amph_api.hip"]
+SOURCES = ["gemv.hip", "draft_mm.hip", "small.hip", "gemm_skinny.hip", "verify_attn.hip", "amph_api.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          # packed-fp32 VALU forms are kept off on the test machines
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
-def build_library(verbose: bool = True, jobs: int = 5) -> str:
+def build_library(verbose: bool = True, jobs: int = 6) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)

@@ -232,18 +232,9 @@ amph_status draft_impl(amph_ctx *ctx, const amph_draft_w *w, const float *h_new,
   // Eq. 5, once or twice: q/k/v projections of the K rows, K x K attention per head, output projection
   auto self_attention = [&](const void *wq, const void *wk, const void *wv, const void *wo, const float *in,
                             float *out_rows) -> amph_status {
-    for (int r0 = 0; r0 < BK; r0 += 8) {
-      const int m = std::min(8, BK - r0);
-      const size_t o = (size_t)r0 * d;
-      PROF_TRY(ctx, AMPH_K_AEB_QKV, launch_linear<T>(st, wq, wk, wv, 3, d, d, in + o, d, m, nullptr, Qa + o, Ka + o, Va + o, d));
-    }
+    PROF_TRY(ctx, AMPH_K_AEB_QKV, launch_linear<T>(st, wq, wk, wv, 3, d, d, in, d, BK, nullptr, Qa, Ka, Va, d));
     PROF_TRY(ctx, AMPH_K_AEB_ATTN, launch_aeb_attn(st, Qa, Ka, Va, B, K, n_h, d_h, ctxa));
-    for (int r0 = 0; r0 < BK; r0 += 8) {
-      const int m = std::min(8, BK - r0);
-      const size_t o = (size_t)r0 * d;
-      PROF_TRY(ctx, AMPH_K_AEB_WO, launch_linear<T>(st, wo, nullptr, nullptr, 1, d, d, ctxa + o, d, m, nullptr, out_rows + o,
-                                    nullptr, nullptr, d));
-    }
+    PROF_TRY(ctx, AMPH_K_AEB_WO, launch_linear<T>(st, wo, nullptr, nullptr, 1, d, d, ctxa, d, BK, nullptr, out_rows, nullptr, nullptr, d));
     return AMPH_OK;
   };
   if (amph_status s1 = self_attention(w->aeb_wq, w->aeb_wk, w->aeb_wv, w->aeb_wo, Hp, attn_o)) return s1;
@@ -255,11 +246,8 @@ amph_status draft_impl(amph_ctx *ctx, const amph_draft_w *w, const float *h_new,
   const void *lm_w = w->lm_head;
   int lm_k = d;
   if (c.lm_rank > 0) {                      // low-rank head: [K rows, r] = lm_a x first, then the [V, r] matrix
-    for (int r0 = 0; r0 < BK; r0 += 8) {
-      const int m = std::min(8, BK - r0);
-      PROF_TRY(ctx, AMPH_K_LM_HEAD, launch_linear<T>(st, w->lm_a, nullptr, nullptr, 1, c.lm_rank, d, head_in + (size_t)r0 * d, d, m,
-                                    nullptr, Qa + (size_t)r0 * c.lm_rank, nullptr, nullptr, c.lm_rank));
-    }
+    PROF_TRY(ctx, AMPH_K_LM_HEAD, launch_linear<T>(st, w->lm_a, nullptr, nullptr, 1, c.lm_rank, d, head_in, d, BK, nullptr, Qa, nullptr,
+                                  nullptr, c.lm_rank));
     head_in = Qa; lm_w = w->lm_b; lm_k = c.lm_rank;
   }
   // Eq. 6: the LM head's launches leave per-workgroup top-k candidates (and the logits only if the caller wants them);

@@ -1,5 +1,6 @@
 // Weight-streaming GEMV family for the draft path (Sec. 3.1 Eq. 1, Sec. 3.2 Eq. 2-6): M <= 8
-// activation rows against a [N, Kd] weight matrix that is read exactly once from HBM.
+// activation rows against a [N, Kd] weight matrix that is read exactly once from HBM.  It serves float32 weights and,
+// in bf16, one or two rows (use_mm below says where the matrix-core form of draft_mm.hip takes over).
 //
 // Shape of every kernel here: a 256-thread workgroup first parks the M activation rows in LDS as
 // float32 (after the prologue: concat with the token embedding, or RMSNorm scaling), then each of
@@ -86,7 +87,7 @@ template <typename P> __device__ __forceinline__ P *pick3(int i, P *a, P *b, P *
 // With five or more activation rows a batch of fragments takes about as long to multiply as to fetch, and the rows
 // in LDS leave room for one workgroup per compute unit only, so nothing else would cover the fetch: those
 // instantiations keep two batches per wave and always have the next one on its way, across row groups as well
-// (measured with 5 rows at 7B shapes: gate/up 77.8 -> 62.7 us, the three SAL projections 45.2 -> 46.7, Wo / down
+// (measured with 5 bf16 rows at 7B shapes: gate/up 77.8 -> 62.7 us, the three SAL projections 45.2 -> 46.7, Wo / down
 // 17.5 -> 16.5).  With fewer rows several workgroups share a compute unit and a second batch per wave gains nothing
 // (1 row) or loses (4 rows: the LM head 52.9 -> 60.5 us).
 template <int M> struct GvPipe { static constexpr bool on = (M >= 5); };
@@ -688,6 +689,38 @@ template <typename T, typename Kern> static hipError_t gv_set_smem(Kern kern, si
   return hipSuccess;
 }
 
+// Whether a bf16 projection of M rows runs on the matrix cores (draft_mm.hip).  From three rows on it does (us per launch
+// over 4 rows, here / there: 4096 x 4096 12.7 / 12.9, 4096 x 11008 34 / 27, 22016 x 4096 34 / 32, 5120 x 13824 54 / 38,
+// 6656 x 17920 67 / 50, 35840 x 6656 89 / 78; over 2 rows 10.9 / 13.0, 22 / 27, 33 / 32, 36 / 36, 53 / 52, 76 / 77), and
+// a small matrix always, which is all fixed costs (2752 x 512 over 1 row 5.6 / 4.0, 4096 x 1024 6.2 / 5.3, 8192 x 1024
+// 6.3 / 6.9).
+constexpr int DRAFT_MM_MIN = 3;
+constexpr size_t DRAFT_MM_SMALL = (size_t)4 << 20;         // weights
+template <typename T> static inline bool use_mm(int M, size_t weights) {
+  return sizeof(T) == 2 && (M >= DRAFT_MM_MIN || weights <= DRAFT_MM_SMALL);
+}
+// The LM head: its vector kernel stays ahead up to four rows as long as they leave room for two workgroups in a compute
+// unit's LDS (us over 4 rows, here / there: 32000 x 4096 45 / 52, 32000 x 6656 81 / 64).
+template <typename T> static inline bool use_mm_head(int M, int V, int Kd) {
+  return use_mm<T>(M, (size_t)V * Kd) && draft_mm_lmhead_wgs(V) <= LMTK_MAX_WG &&
+         (M > 4 || (size_t)V * Kd <= DRAFT_MM_SMALL || (size_t)M * Kd * 4 > 80 * 1024);
+}
+// rows of every launch when M rows are served in as few launches as possible, evenly
+static inline int mm_chunk(int M) {
+  const int n = (M + DRAFT_MM_ROWS - 1) / DRAFT_MM_ROWS;
+  return (M + n - 1) / n;
+}
+#define MM_CHUNKS(CALL)                                      \
+  do {                                                       \
+    const int ch_ = mm_chunk(M);                             \
+    for (int m0 = 0; m0 < M; m0 += ch_) {                    \
+      const int m = std::min(ch_, M - m0);                   \
+      hipError_t e_ = (CALL);                                \
+      if (e_ != hipSuccess) return e_;                       \
+    }                                                        \
+    return hipSuccess;                                       \
+  } while (0)
+
 // Rows per launch: the activation rows of a launch sit in LDS as float32 and a wave keeps at most 8 rows of
 // accumulators, so a call with more rows than that (catch-up positions of several sequences), or more than fit
 // in LDS (wide models), is served in several launches over row ranges; every launch then streams the weights
@@ -703,6 +736,8 @@ template <typename T>
 hipError_t launch_fc_concat(hipStream_t st, const void *W, const float *u, const void *embed, const int32_t *tok,
                             int vocab, int d, int M, float *out, uint32_t *dev_status) {
   if (M < 1 || d % 8) return hipErrorInvalidValue;
+  if (use_mm<T>(M, (size_t)d * 2 * d) && d % 256 == 0)
+    MM_CHUNKS(draft_mm_fc(st, W, u + (size_t)m0 * d, embed, tok + m0, vocab, d, m, out + (size_t)m0 * d, dev_status));
   int mc = gv_rows_per_launch(M, gv_xs_bytes<T>(1, 2 * d), 0);
   // rows that fit only without their other half: two launches over d columns each
   const int mch = gv_rows_per_launch(M, gv_xs_bytes<T>(1, d), 0);
@@ -728,6 +763,9 @@ hipError_t launch_sal_qkv(hipStream_t st, const amph_layer_w &lw, const float *x
                           float eps, float theta, const int32_t *sal_len, int max_kv, void *kv_stage, float *qbuf,
                           uint32_t *dev_status, int R, const int32_t *n_valid) {
   if (M < 1 || d % 8 || d_h % 4) return hipErrorInvalidValue;
+  if (use_mm<T>(M, (size_t)3 * d * d) && d % 16 == 0 && d_h % 16 == 0)
+    MM_CHUNKS(draft_mm_sal_qkv(st, lw, x + (size_t)m0 * d, d, n_heads, d_h, m, eps, theta, sal_len, max_kv, kv_stage,
+                               qbuf + (size_t)m0 * d, dev_status, m0, R, n_valid));
   const int mc = gv_rows_per_launch(M, gv_xs_bytes<T>(1, d), 16);
   if (mc < 1) return hipErrorInvalidValue;
   for (int m0 = 0; m0 < M; m0 += mc) {
@@ -747,6 +785,9 @@ template <typename T>
 hipError_t launch_linear(hipStream_t st, const void *w0, const void *w1, const void *w2, int n_seg, int seg_rows, int Kd,
                          const float *x, int ldx, int M, const float *res, float *o0, float *o1, float *o2, int ldo) {
   if (M < 1 || Kd % 8) return hipErrorInvalidValue;
+  if (use_mm<T>(M, (size_t)n_seg * seg_rows * Kd))
+    MM_CHUNKS(draft_mm_linear(st, w0, w1, w2, n_seg, seg_rows, Kd, x + (size_t)m0 * ldx, ldx, m, res ? res + (size_t)m0 * ldo : nullptr,
+                              o0 + (size_t)m0 * ldo, o1 ? o1 + (size_t)m0 * ldo : nullptr, o2 ? o2 + (size_t)m0 * ldo : nullptr, ldo));
   int mc = gv_rows_per_launch(M, gv_xs_bytes<T>(1, Kd), 0);
   // Rows too wide for all of them (up to 8) to sit in LDS whole: cut the reduction axis into ks slices instead of
   // the rows into more launches, each of which would read the matrix again.
@@ -781,6 +822,7 @@ template <typename T>
 hipError_t launch_gate_up(hipStream_t st, const amph_layer_w &lw, const float *x, int d, int f, int M, float eps,
                           float *act) {
   if (M < 1 || d % 8) return hipErrorInvalidValue;
+  if (use_mm<T>(M, (size_t)2 * f * d)) MM_CHUNKS(draft_mm_gate_up(st, lw, x + (size_t)m0 * d, d, f, m, eps, act + (size_t)m0 * f));
   const int mc = gv_rows_per_launch(M, gv_xs_bytes<T>(1, d), 16);
   if (mc < 1) return hipErrorInvalidValue;
   for (int m0 = 0; m0 < M; m0 += mc) {
@@ -799,6 +841,8 @@ template <typename T>
 hipError_t launch_head_mlp(hipStream_t st, const void *w_mlp, const void *pe, const float *h1, const float *h2, int d,
                            int K, int M, float *Hp) {
   if (M < 1 || d % 8) return hipErrorInvalidValue;
+  if (use_mm<T>(M, (size_t)K * d * d))
+    MM_CHUNKS(draft_mm_head_mlp(st, w_mlp, pe, h1 + (size_t)m0 * d, h2 + (size_t)m0 * d, d, K, m, Hp + (size_t)m0 * K * d));
   int mc = gv_rows_per_launch(M, 2 * gv_xs_bytes<T>(1, d), 0);
   // rows that fit only with one of the two sources staged: one launch for the heads of each source
   const int mch = gv_rows_per_launch(M, gv_xs_bytes<T>(1, d), 0);
@@ -838,6 +882,13 @@ template <typename T>
 hipError_t launch_lmhead_cands(hipStream_t st, const void *W, int V, int Kd, const float *x, int M, int k, float *logits,
                                float *ws, int *n_cand) {
   if (M < 1 || Kd % 8 || k < 1 || k > AMPH_MAX_TOPK || k > V) return hipErrorInvalidValue;
+  if (use_mm_head<T>(M, V, Kd)) {
+    const int wgs = draft_mm_lmhead_wgs(V);
+    int *ci = reinterpret_cast<int *>(ws + (size_t)M * wgs * k);
+    *n_cand = wgs * k;
+    MM_CHUNKS(draft_mm_lmhead(st, W, V, Kd, x + (size_t)m0 * Kd, m, k, logits ? logits + (size_t)m0 * V : nullptr,
+                              ws + (size_t)m0 * wgs * k, ci + (size_t)m0 * wgs * k));
+  }
   const int mc = gv_rows_per_launch(M, gv_xs_bytes<T>(1, Kd), 8 * 64 * LMTK_NPT * sizeof(float));
   if (mc < 1) return hipErrorInvalidValue;
   // every launch uses the shape of a full launch of mc rows, so that all rows have the same number of candidates

@@ -34,6 +34,22 @@ template <typename T>
 hipError_t launch_lmhead_cands(hipStream_t st, const void *W, int V, int Kd, const float *x, int M, int k, float *logits,
                                float *ws, int *n_cand);
 
+// ---- draft_mm.hip (draft path on the matrix cores: bf16 weights, up to DRAFT_MM_ROWS rows a launch) ----
+constexpr int DRAFT_MM_ROWS = 48;
+hipError_t draft_mm_fc(hipStream_t st, const void *W, const float *u, const void *embed, const int32_t *tok, int vocab, int d, int M,
+                       float *out, uint32_t *dev_status);
+hipError_t draft_mm_sal_qkv(hipStream_t st, const amph_layer_w &lw, const float *x, int d, int n_heads, int d_h, int M, float eps,
+                            float theta, const int32_t *sal_len, int max_kv, void *kv_stage, float *qbuf, uint32_t *dev_status,
+                            int row0, int R, const int32_t *n_valid);
+hipError_t draft_mm_linear(hipStream_t st, const void *w0, const void *w1, const void *w2, int n_seg, int seg_rows, int Kd,
+                           const float *x, int ldx, int M, const float *res, float *o0, float *o1, float *o2, int ldo);
+hipError_t draft_mm_gate_up(hipStream_t st, const amph_layer_w &lw, const float *x, int d, int f, int M, float eps, float *act);
+hipError_t draft_mm_head_mlp(hipStream_t st, const void *w_mlp, const void *pe, const float *h1, const float *h2, int d, int K, int M,
+                             float *Hp);
+int draft_mm_lmhead_wgs(int V);               // workgroups of draft_mm_lmhead, each leaving k candidates per row
+hipError_t draft_mm_lmhead(hipStream_t st, const void *W, int V, int Kd, const float *x, int M, int k, float *logits, float *cand_v,
+                           int *cand_i);
+
 // ---- small.hip (attention of the draft path, top-k, tree, accept, norms) ----
 template <typename T>
 hipError_t launch_sal_attn(hipStream_t st, const float *qbuf, const void *kv_stage, const int32_t *sal_len, int B,

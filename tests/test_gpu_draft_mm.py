@@ -1,0 +1,101 @@
+"""The draft's projections on the matrix cores (float32 rows against bf16 weights): their error against 64 bits at the edges
+of blocks, tiles and stages, non-finite activations, and whole drafts over row counts around the edges of a launch."""
+import numpy as np
+import pytest
+import torch
+
+import synth_inputs as si
+from oracle import amphista_oracle as orc
+from paper_2406_13170_amd import binding as B
+from paper_2406_13170_amd import device as D
+
+from gpu_common import DEV, TOL, assert_rows_close, draft_f32, f32_to_dev, i32_to_dev, make_ctx, np_of, say, topk_consistent
+
+pytestmark = pytest.mark.gpu
+
+
+# N: one block, a ragged one, ragged last workgroups of every height; K: one piece, ragged and whole stages, long axes
+@pytest.mark.parametrize("M", [1, 3, 5, 8])
+@pytest.mark.parametrize("N,K", [(16, 8), (5, 40), (40, 264), (515, 520), (4096, 1032), (4100, 1016), (6000, 4096), (12300, 1024),
+                                 (1024, 17920), (22016, 512)])
+def test_projection_error_against_64_bits(M, N, K):
+    say(f"projection M={M} N={N} K={K}")
+    g = torch.Generator(device=DEV).manual_seed(N * 31 + K)
+    W = (torch.randn((N, K), generator=g, device=DEV) * 0.02).bfloat16()
+    x = torch.randn((M, K), generator=g, device=DEV)
+    y = torch.full((M, N), float("nan"), device=DEV)
+    make_ctx(si.MINI).amph_gemv(x, W, y, M, N, K)
+    ref = x.double() @ W.double().t()
+    # float32 sums of K random terms in chains of at most 280: about sqrt(280) / 2 half-ulps of the running sum
+    err = float((y.double() - ref).norm() / ref.norm())
+    assert err < 5e-7, err
+
+
+@pytest.mark.parametrize("M", [5])
+def test_projection_of_infinities_and_nan(M):
+    N, K = 48, 520
+    W = si.normal(si.MINI, 3, "dm.inf", (N, K), 0.02).f32
+    x = si.as_f32_exact(si.MINI, 3, "dm.x", (M, K), 1.0)
+    x[0, 7], x[1, 300], x[2, 519], x[3, 0], x[3, 1] = np.inf, -np.inf, np.nan, 3.0e38, 1.0e-38
+    W[0, 7] = 0.0                                             # 0 * inf
+    y = torch.zeros((M, N), device=DEV)
+    ctx = make_ctx(si.MINI)
+    ctx.amph_gemv(f32_to_dev(x), torch.from_numpy(W).to(DEV).bfloat16(), y, M, N, K)
+    got = np_of(y).astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        ref = x.astype(np.float64) @ W.astype(np.float64).T
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    fin = np.isfinite(ref)
+    assert np.all(np.abs(got - ref)[fin] <= 1e-5 * np.maximum(np.abs(ref[fin]), 1.0))
+
+
+# rows of a launch: one tile exactly, one more than a tile, three tiles, more than a launch takes; 4 * B rows in the heads
+@pytest.mark.parametrize("batch,n_new", [(4, 4), (17, 1), (9, 5), (10, 5), (13, 4)])
+def test_draft_over_many_rows_matches_the_oracle(batch, n_new):
+    cfg = si.with_(si.MINI, batch=batch)
+    seed, Ls = 13, 21
+    n_h, d_h, d, V, K = cfg.n_heads, cfg.head_dim, cfg.d_model, cfg.vocab, cfg.K
+    max_kv = 64
+    ctx = make_ctx(cfg, max_kv=max_kv)
+    dw = si.draft_weights(cfg, seed)
+    dwd, dwo = D.draft_to_device(dw, DEV), draft_f32(dw)
+    h = si.as_f32_exact(cfg, seed, "dm.h", (batch, n_new, d), 1.0)
+    tok = si.tokens(cfg, seed, "dm.tok", (batch, n_new))
+    live = [1 + (3 * b) % n_new for b in range(batch)]
+    lens = [Ls - b % 5 for b in range(batch)]
+    rows = [[si.normal(cfg, seed, f"dm.sal{s}.{kv}", (batch, n_h, Ls, d_h), 1.0) for kv in "kv"] for s in range(2)]
+    sal = torch.zeros((2, batch, 2, n_h, max_kv, d_h), dtype=torch.bfloat16, device=DEV)
+    for s in range(2):
+        for kv in range(2):
+            sal[s, :, kv, :, :Ls] = D.to_device(rows[s][kv], DEV)
+    before = np_of(sal)
+    sal_len = i32_to_dev(lens)
+    idx = torch.zeros((batch, K, cfg.topk), dtype=torch.int32, device=DEV)
+    val = torch.zeros((batch, K, cfg.topk), device=DEV)
+    logits = torch.zeros((batch, K, V), device=DEV)
+    args = (B.Context.draft_struct(dwd), f32_to_dev(h), i32_to_dev(tok), sal, sal_len, idx, val, logits)
+    ctx.amph_draft(*args, n_new=n_new, n_valid=i32_to_dev(live))
+    assert ctx.device_status() == 0
+    assert list(np_of(sal_len)) == [n + r for n, r in zip(lens, live)]
+    after, lg = np_of(sal), np_of(logits)
+    for b in sorted({0, 1, batch // 2, batch - 1}):
+        say(f"batch {batch} n_new {n_new} element {b} live {live[b]}")
+        k0 = [rows[s][0].f32[b][:, :lens[b]] for s in range(2)]
+        v0 = [rows[s][1].f32[b][:, :lens[b]] for s in range(2)]
+        ref, k1, v1 = orc.draft_catchup(dwo, h[b, :live[b]], tok[b, :live[b]], k0, v0, n_h, cfg.topk, cfg.rms_eps, cfg.rope_theta)
+        assert_rows_close(lg[b], ref["logits"], TOL["bf16"], "logits")
+        for r in range(K):
+            ok, bad = topk_consistent(np_of(idx)[b, r], np.asarray(ref["logits"][r]), cfg.topk, 1e-2 * np.abs(ref["logits"][r]).max())
+            assert ok, bad
+        end = lens[b] + live[b]
+        for s in range(2):
+            assert_rows_close(after[s, b, 0, :, lens[b]:end].reshape(-1, d_h), k1[s][:, lens[b]:].reshape(-1, d_h), TOL["bf16"], "keys")
+            assert_rows_close(after[s, b, 1, :, lens[b]:end].reshape(-1, d_h), v1[s][:, lens[b]:].reshape(-1, d_h), TOL["bf16"], "values")
+        assert np.array_equal(after[:, b, :, :, end:], before[:, b, :, :, end:])          # rows of dead positions stay
+    # a token outside the vocabulary is reported
+    tok[batch - 1, 0] = V
+    sal_len.copy_(i32_to_dev(lens))
+    args = (*args[:2], i32_to_dev(tok), *args[3:])
+    ctx.amph_draft(*args, n_new=n_new, n_valid=i32_to_dev(live))
+    assert ctx.device_status() == B.AMPH_DEV_BAD_TOKEN
