@@ -499,6 +499,7 @@ hipError_t launch_accept(hipStream_t st, const int32_t *parent, const int32_t *d
 //     above the total), the last token of non-zero probability is taken.
 // =====================================================================================================
 constexpr int AT_THREADS = 1024, AT_WAVES = AT_THREADS / WAVE;
+constexpr int AT_RUN = 32;                               // tokens of every run that sit in LDS at a time
 
 __device__ __forceinline__ float at_block_max(float v, float *sm) {
   #pragma unroll
@@ -521,18 +522,29 @@ __device__ __forceinline__ float at_block_sum(float v, float *sm) {      // fixe
   return r;
 }
 
+// A row is read once: its NPT * 1024 logits are all requested before the first is used and stay in registers between the
+// maximum and the sums (two strided loops over memory took 23.5 us for 256 rows of 32000, this 12.8; the rows' 33 MB
+// are 7 us).  Threads keep the elements they always had (t, t + 1024, ...), so the sums' bits do not change.
+template <int NPT>
 __global__ __launch_bounds__(AT_THREADS) void k_row_softmax_stats(const float *logits, int V, float inv_temp, float4 *stats) {
   __shared__ float sm[AT_WAVES];
   const float *l = logits + (size_t)blockIdx.x * V;
   const int t = threadIdx.x;
+  float x[NPT];
+  #pragma unroll
+  for (int j = 0; j < NPT; ++j) x[j] = l[min(j * AT_THREADS + t, V - 1)];          // unconditional loads from clamped addresses
   float m = -__builtin_huge_valf();
-  for (int v = t; v < V; v += AT_THREADS) m = fmaxf(m, l[v]);
+  #pragma unroll
+  for (int j = 0; j < NPT; ++j) m = fmaxf(m, x[j]);       // (the clamped repeats change no maximum)
   m = at_block_max(m, sm);
   float z = 0.f, sx = 0.f;
-  for (int v = t; v < V; v += AT_THREADS) {
-    const float x = (l[v] - m) * inv_temp, e = expf(x);
-    z += e;
-    if (e > 0.f) sx += e * x;                             // a token of probability zero adds nothing (0 * -inf)
+  #pragma unroll
+  for (int j = 0; j < NPT; ++j) {
+    if (j * AT_THREADS + t < V) {
+      const float y = (x[j] - m) * inv_temp, e = expf(y);
+      z += e;
+      if (e > 0.f) sx += e * y;                           // a token of probability zero adds nothing (0 * -inf)
+    }
   }
   z = at_block_sum(z, sm);
   sx = at_block_sum(sx, sm);
@@ -545,15 +557,18 @@ __global__ __launch_bounds__(AT_THREADS) void k_accept_typical(const int32_t *pa
                                                                int32_t *accept_len, int32_t *accept_path, int32_t *next_tok,
                                                                int32_t *best_node) {
   __shared__ float sm[AT_WAVES];
-  __shared__ int s_pass[AMPH_MAX_TREE];
+  __shared__ int s_pass[AMPH_MAX_TREE], s_parent[AMPH_MAX_TREE];
   __shared__ int s_key[AT_WAVES];
   __shared__ int s_best, s_found;
+  __shared__ float s_e[AT_THREADS][AT_RUN + 1];           // one piece of every thread's run (pitch: no two lanes in one bank)
   const int b = blockIdx.x, t = threadIdx.x;
   const int32_t *tok = tree_tok + (size_t)b * T;
   if (t < T) {
     int pass = 1;                                          // the root
+    const int j = parent[t];
+    s_parent[t] = j;                                       // (the walks up the tree below would each be a chain of global loads)
     if (t > 0) {
-      const int j = parent[t], tk = tok[t];
+      const int tk = tok[t];
       const size_t row = (size_t)b * T + j;
       const float4 st = stats[row];
       pass = 0;
@@ -572,7 +587,7 @@ __global__ __launch_bounds__(AT_THREADS) void k_accept_typical(const int32_t *pa
     int j = t;
     for (int hop = 0; hop <= AMPH_MAX_HEADS_K && j > 0; ++hop) {
       if (!s_pass[j]) { ok = false; break; }
-      j = parent[j];
+      j = s_parent[j];
     }
     if (ok) key = depth[t] * 256 + (255 - t);
   }
@@ -589,7 +604,7 @@ __global__ __launch_bounds__(AT_THREADS) void k_accept_typical(const int32_t *pa
     s_best = best;
     for (int dd = 0; dd <= K; ++dd) accept_path[(size_t)b * (K + 1) + dd] = -1;
     int j = best;
-    for (int dd = a; dd >= 0 && j >= 0; --dd) { accept_path[(size_t)b * (K + 1) + dd] = j; j = parent[j]; }
+    for (int dd = a; dd >= 0 && j >= 0; --dd) { accept_path[(size_t)b * (K + 1) + dd] = j; j = s_parent[j]; }
   }
   __syncthreads();
   // ---- the draw from p_best
@@ -598,12 +613,33 @@ __global__ __launch_bounds__(AT_THREADS) void k_accept_typical(const int32_t *pa
   const float4 st = stats[row];
   const float target = u[b] * st.y;
   const int C = (V + AT_THREADS - 1) / AT_THREADS, v0 = min(t * C, V), v1 = min(v0 + C, V);
+  // Thread t's run is C consecutive tokens, added up in order; read that way every load would touch 64 lines (with the
+  // walks above through global memory 21.3 us for 4 rows, this 11.8).  So the runs come in pieces of AT_RUN tokens through
+  // LDS: consecutive lanes fetch consecutive tokens, then each thread adds its own.
   float run = 0.f;
   int last_live = -1;
-  for (int v = v0; v < v1; ++v) {
-    const float e = expf((l[v] - st.x) * inv_temp);
-    run += e;
-    if (e > 0.f) last_live = v;
+  for (int c0 = 0; c0 < C; c0 += AT_RUN) {
+    if (c0 > 0) __syncthreads();
+    float x[AT_RUN];
+    #pragma unroll
+    for (int i = 0; i < AT_RUN; ++i) {
+      const int q = i * AT_THREADS + t;                    // piece of run q / AT_RUN, token q % AT_RUN of it
+      x[i] = l[min((q / AT_RUN) * C + c0 + q % AT_RUN, V - 1)];
+    }
+    #pragma unroll
+    for (int i = 0; i < AT_RUN; ++i) {
+      const int q = i * AT_THREADS + t;
+      s_e[q / AT_RUN][q % AT_RUN] = expf((x[i] - st.x) * inv_temp);
+    }
+    __syncthreads();
+    for (int i = 0; i < AT_RUN; ++i) {
+      const int v = v0 + c0 + i;
+      if (c0 + i < C && v < v1) {
+        const float e = s_e[t][i];
+        run += e;
+        if (e > 0.f) last_live = v;
+      }
+    }
   }
   // inclusive scan of the runs: inside a wave, then over the wave totals (ascending)
   float inc = run;
@@ -624,7 +660,7 @@ __global__ __launch_bounds__(AT_THREADS) void k_accept_typical(const int32_t *pa
     float acc = exc;
     int pick = -1;
     for (int v = v0; v < v1; ++v) {
-      acc += expf((l[v] - st.x) * inv_temp);
+      acc += C <= AT_RUN ? s_e[t][v - v0] : expf((l[v] - st.x) * inv_temp);
       if (acc > target) { pick = v; break; }
     }
     if (pick < 0) pick = max(last_live, v0);              // (acc and inc differ by rounding order only)
@@ -651,7 +687,10 @@ hipError_t launch_accept_typical(hipStream_t st, const int32_t *parent, const in
                                  int32_t *best_node, float *stats_ws) {
   if (T < 1 || T > AMPH_MAX_TREE || V < 1 || !(temperature > 0.f)) return hipErrorInvalidValue;
   const float inv_temp = 1.0f / temperature;
-  hipLaunchKernelGGL(k_row_softmax_stats, dim3(B * T), dim3(AT_THREADS), 0, st, logits, V, inv_temp, (float4 *)stats_ws);
+  if (V > 64 * AT_THREADS) return hipErrorInvalidValue;
+  #define AT_STATS(N) hipLaunchKernelGGL((k_row_softmax_stats<N>), dim3(B * T), dim3(AT_THREADS), 0, st, logits, V, inv_temp, (float4 *)stats_ws)
+  if (V <= 8 * AT_THREADS) AT_STATS(8); else if (V <= 32 * AT_THREADS) AT_STATS(32); else AT_STATS(64);
+  #undef AT_STATS
   hipLaunchKernelGGL(k_accept_typical, dim3(B), dim3(AT_THREADS), 0, st, parent, depth, T, K, V, tree_tok, logits,
                      (const float4 *)stats_ws, inv_temp, eps, delta, u, accept_len, accept_path, next_tok, best_node);
   return hipGetLastError();
@@ -663,9 +702,9 @@ hipError_t launch_accept_typical(hipStream_t st, const int32_t *parent, const in
 //   k_kv_commit: for one (layer, batch element, head), the K/V rows of the accepted path's nodes 1..a move
 //     from tree slots kv_len + node to kv_len + j (node 0, the root, already sits at kv_len).  All sources
 //     are read before the first write (a destination may be another node's source).
-//   k_gather_accepted: row j <= a of h_new is the target's hidden state at path node j, tok_new[j] the
-//     token that follows it (the next path node's token, or next_tok after the last); n_new = a + 1.
-//   k_advance_len: kv_len += a + 1, as its own launch, after every workgroup above has read kv_len.
+//   k_gather_advance: row j <= a of h_new is the target's hidden state at path node j, tok_new[j] the
+//     token that follows it (the next path node's token, or next_tok after the last); n_new = a + 1; and
+//     kv_len += a + 1: a launch after the one above, whose workgroups have all read kv_len by then.
 //   k_gather_rows: out[b] = rows[b * R + (n_valid ? n_valid[b] : R) - 1] (the last live row of each element).
 // =====================================================================================================
 template <typename T>
@@ -702,12 +741,17 @@ __global__ __launch_bounds__(256) void k_kv_commit(T *k_caches, T *v_caches, int
   }
 }
 
-__global__ __launch_bounds__(256) void k_gather_accepted(const float *hidden, const int32_t *tree_tok, int T_nodes, int d,
-                                                         int K, const int32_t *accept_len, const int32_t *accept_path,
-                                                         const int32_t *next_tok, float *h_new, int32_t *tok_new,
-                                                         int32_t *n_new) {
+__global__ __launch_bounds__(256) void k_gather_advance(const float *hidden, const int32_t *tree_tok, int T_nodes, int d,
+                                                        int K, const int32_t *accept_len, const int32_t *accept_path,
+                                                        const int32_t *next_tok, float *h_new, int32_t *tok_new,
+                                                        int32_t *n_new, int32_t *kv_len, int max_kv) {
   const int j = blockIdx.x, b = blockIdx.y;
   const int a = min(max(accept_len[b], 0), K);
+  if (j == 0 && threadIdx.x == 0) {
+    const int L = kv_len[b];
+    if (L >= 0 && L + T_nodes <= max_kv) kv_len[b] = L + a + 1;
+  }
+  if (!h_new) return;
   const int32_t *path = accept_path + (size_t)b * (K + 1);
   float *dst = h_new + ((size_t)b * (K + 1) + j) * d;
   if (j <= a) {
@@ -721,14 +765,6 @@ __global__ __launch_bounds__(256) void k_gather_accepted(const float *hidden, co
     if (threadIdx.x == 0) tok_new[(size_t)b * (K + 1) + j] = 0;
   }
   if (j == 0 && threadIdx.x == 0) n_new[b] = a + 1;
-}
-
-__global__ void k_advance_len(int32_t *kv_len, const int32_t *accept_len, int B, int K, int T_nodes, int max_kv) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  const int L = kv_len[b];
-  if (L < 0 || L + T_nodes > max_kv) return;
-  kv_len[b] = L + min(max(accept_len[b], 0), K) + 1;
 }
 
 __global__ __launch_bounds__(256) void k_gather_rows(const float *rows, int R, int d, const int32_t *n_valid, float *out) {
@@ -749,10 +785,8 @@ hipError_t launch_commit(hipStream_t st, void *k_caches, void *v_caches, int n_l
   if (n_layers > 0)
     hipLaunchKernelGGL((k_kv_commit<T>), dim3(n_heads, B, n_layers), dim3(256), 0, st, (T *)k_caches, (T *)v_caches, B, n_heads,
                        d_h, max_kv, T_nodes, kv_len, accept_len, accept_path, K);
-  if (h_new)
-    hipLaunchKernelGGL(k_gather_accepted, dim3(K + 1, B), dim3(256), 0, st, hidden, tree_tok, T_nodes, d, K, accept_len,
-                       accept_path, next_tok, h_new, tok_new, n_new);
-  hipLaunchKernelGGL(k_advance_len, dim3((B + 63) / 64), dim3(64), 0, st, kv_len, accept_len, B, K, T_nodes, max_kv);
+  hipLaunchKernelGGL(k_gather_advance, dim3(h_new ? K + 1 : 1, B), dim3(256), 0, st, hidden, tree_tok, T_nodes, d, K, accept_len,
+                     accept_path, next_tok, h_new, tok_new, n_new, kv_len, max_kv);
   return hipGetLastError();
 }
 template hipError_t launch_commit<float>(hipStream_t, void *, void *, int, int, int, int, int, int, int, int, int32_t *,
