@@ -42,7 +42,7 @@ hipError_t scratch_for_current_device(int *dev_out, void **ptr_out) {
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 struct WsLayout {   // byte offsets into the caller's workspace
-  size_t x, q, att, y, act, h[2], Hp, Qa, Ka, Va, ctxa, attn_o, logits, topk_ws;                 // draft
+  size_t x, q, att, y, act, h[2], Hp, Qa, Ka, Va, ctxa, attn_o, logits, topk_ws, sal_part;       // draft
   size_t xres, xn, qb, attb, actb, slabs, amax_val, amax_idx, ver_part, tgt_tmp, row_stats, rope_cs, xt;  // target
   size_t slabs_floats, ver_part_floats;
   size_t total;
@@ -136,6 +136,7 @@ WsLayout make_layout(const amph_config &c) {
   w.ctxa = take(BK * d * 4); w.attn_o = take(BK * d * 4); w.logits = take(BK * V * 4);
   w.topk_ws = take(std::max(std::max(topk_ws_floats((int)BK, c.vocab, c.topk), topk_ws_floats((int)M, c.vocab, 1)),
                             lmtk_ws_floats((int)BK, c.topk)) * 4);
+  w.sal_part = take(sal_part_floats(c.batch, c.K + 1, c.n_heads, c.head_dim, c.max_kv) * 4);
   const size_t Mp = (M + 31) / 32 * 32;         // activations may be kept in 32-row tiles for the wide GEMM
   w.xres = take(M * d * 4); w.xn = take(Mp * d * esz); w.qb = take(M * d * esz); w.attb = take(Mp * d * esz);
   w.actb = take(Mp * f * esz);
@@ -209,7 +210,7 @@ amph_status draft_impl(amph_ctx *ctx, const amph_draft_w *w, const float *h_new,
       res = x_last;
     }
     PROF_TRY(ctx, AMPH_K_SAL_ATTN, launch_sal_attn<T>(st, q, kv_stage, sal_len, B, n_h, d_h, c.max_kv, att, R, n_valid,
-                                                      last_rows_only ? 1 : 0));
+                                                      last_rows_only ? 1 : 0, F(ctx->ws.sal_part)));
     PROF_TRY(ctx, AMPH_K_SAL_WO, launch_linear<T>(st, w->sal[s].wo, nullptr, nullptr, 1, d, d, att, d, Ms, res, y, nullptr, nullptr, d));
     PROF_TRY(ctx, AMPH_K_SAL_GATEUP, launch_gate_up<T>(st, w->sal[s], y, d, f, Ms, c.rms_eps, act));
     PROF_TRY(ctx, AMPH_K_SAL_DOWN, launch_linear<T>(st, w->sal[s].w_down, nullptr, nullptr, 1, d, f, act, f, Ms, y, h[s], nullptr, nullptr, d));

@@ -51,9 +51,12 @@ hipError_t draft_mm_lmhead(hipStream_t st, const void *W, int V, int Kd, const f
                            int *cand_i);
 
 // ---- small.hip (attention of the draft path, top-k, tree, accept, norms) ----
+// part: sal_part_floats(B, R, ...) floats for the key splits' partial results
+constexpr int SAL_MAX_SPLITS = 8;
+size_t sal_part_floats(int B, int R, int n_heads, int d_h, int max_kv);      // for any number of new positions up to R
 template <typename T>
 hipError_t launch_sal_attn(hipStream_t st, const float *qbuf, const void *kv_stage, const int32_t *sal_len, int B,
-                           int n_heads, int d_h, int max_kv, float *out, int R, const int32_t *n_valid, int last_only = 0);
+                           int n_heads, int d_h, int max_kv, float *out, int R, const int32_t *n_valid, int last_only, float *part);
 hipError_t launch_aeb_attn(hipStream_t st, const float *Q, const float *Kk, const float *V, int B, int K, int n_heads,
                            int d_h, float *ctx);
 // ws: topk_ws_floats(rows, V, k) floats of scratch for the per-wave candidates

@@ -7,136 +7,268 @@
 namespace amph {
 
 // =====================================================================================================
-// Single-query attention over a SAL cache: query row (b, j) = new position j of batch element b against
-// rows [0, sal_len[b] + j] of the cache (its own new row included, later new rows excluded: causal among
-// the new positions).  grid = (heads, batch * R), 1024 threads: the 16
-// waves of a workgroup stride over the rows.  Each 16-byte fragment of a key/value row belongs to one
-// lane; LPR lanes share a row, so a wave covers 64/LPR rows per load.  Running (max, sum, weighted
-// values) are merged lane group -> wave -> workgroup; no workgroup depends on another.
-// kv_stage: [B, 2, n_heads, max_kv, DH] T.   out: [B, d] float32.
+// Attention of the adaptation layers over their caches: query row (b, j) = new position j of batch element b against
+// rows [0, sal_len[b] + j] of the cache (its own new row included, later new rows excluded: causal among the new
+// positions).  A stream of the caches with little arithmetic, so what counts is that every row is read once and that
+// enough compute units read:
+//   * a workgroup serves up to RT new positions of a (head, batch element) together, from the same key and value
+//     fragments (one workgroup per position read the cache R times: 33B widths, batch 4, 6 positions, 2047 rows 99 us,
+//     now 58; 7B, batch 8, 5 positions 40 us, now 32);
+//   * with few heads the cache rows are split over S workgroups, whose (max, sum, weighted values) k_sal_fold merges in
+//     ascending order (7B, batch 1, 1024 rows, one workgroup per head 15.8 us, now 6.1 + 4.7 us).
+// grid = (heads, batch * row groups, S), 512 threads: the 8 waves stride over the rows.  Each 16-byte fragment of a
+// key/value row belongs to one lane; LPR lanes share a row, so a wave covers 64 / LPR rows per load.  Running (max, sum,
+// weighted values) are merged lane group -> wave -> workgroup.
+// kv_stage: [B, 2, n_heads, max_kv, DH] T.   out: [rows, d] float32.
 // =====================================================================================================
-constexpr int SA_WAVES = 16;
+constexpr int SA_WAVES = 8;
 
-template <typename T, int DH>
+// 2^x by the hardware instruction alone: arguments here are at most 0, and what would be below the normal range may be 0
+__device__ __forceinline__ float sa_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// sum over groups of LPR adjacent lanes, in every lane: neighbour at distance 1, 2, then mirror inside 8 and inside 16
+// lanes, each one vector instruction (a cross-lane permute goes through LDS)
+template <bool V> struct BoolTag { static constexpr bool value = V; };
+// op of a lane's value and the one 16 (32) lanes further on, modulo 32 (64): the row swap of a register with itself leaves
+// the even rows (the lower half) in one result and the odd ones (the upper half) in the other
+template <typename F> __device__ __forceinline__ float sa_xor16(float v, F op) {
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return op(__uint_as_float(p[0]), __uint_as_float(p[1]));
+}
+template <typename F> __device__ __forceinline__ float sa_xor32(float v, F op) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return op(__uint_as_float(p[0]), __uint_as_float(p[1]));
+}
+template <int LPR> __device__ __forceinline__ float sa_group_sum(float v) {
+  #define SA_DPP(CTRL) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true))
+  SA_DPP(0xb1);                          // quad_perm [1, 0, 3, 2]
+  SA_DPP(0x4e);                          // quad_perm [2, 3, 0, 1]
+  if (LPR >= 8) SA_DPP(0x141);           // row_half_mirror
+  if (LPR >= 16) SA_DPP(0x140);          // row_mirror
+  #undef SA_DPP
+  if (LPR >= 32) v = sa_xor16(v, [](float a, float b) { return a + b; });
+  return v;
+}
+// op over the lane groups of LPR lanes (the same lane of each), in every lane
+template <int LPR, typename F> __device__ __forceinline__ float sa_across(float v, F op) {
+  if (LPR <= 8) v = op(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, true)));   // row_ror:8
+  if (LPR <= 16) v = sa_xor16(v, op);
+  return sa_xor32(v, op);
+}
+
+template <typename T, int DH, int RT>
 __global__ __launch_bounds__(SA_WAVES * 64) void k_sal_attn(const float *qbuf, const T *kv_stage, const int32_t *sal_len,
                                                             int n_heads, int max_kv, float *out, int R,
-                                                            const int32_t *n_valid, int last_only) {
+                                                            const int32_t *n_valid, int last_only, int n_groups, float *part) {
   constexpr int PER = Elem<T>::PER;
   constexpr int LPR = DH / PER;          // lanes per row
   constexpr int G = WAVE / LPR;          // rows per wave load
   constexpr int U = 4;
-  __shared__ float sm_m[SA_WAVES], sm_l[SA_WAVES];
-  __shared__ float sm_o[SA_WAVES][DH];
-  // last_only: one workgroup row per batch element, serving its last live position (query row b * R + jn of qbuf,
-  // output row b); otherwise one per (element, position)
-  const int h = blockIdx.x;
-  int row = blockIdx.y, b, jn, out_row;
-  if (last_only) {
-    b = row;
-    jn = min(max(n_valid ? n_valid[b] : R, 1), R) - 1;
-    out_row = b;
-    row = b * R + jn;
-  } else {
-    b = row / R; jn = row % R; out_row = row;
-  }
+  __shared__ float sm_m[SA_WAVES][RT], sm_l[SA_WAVES][RT];
+  __shared__ float sm_o[SA_WAVES][RT][DH];
+  // last_only: one row per batch element, its last live position (query row b * R + jn of qbuf, output row b);
+  // otherwise rows j0 .. j0 + RT - 1 of the element
+  const int h = blockIdx.x, b = blockIdx.y / n_groups, j0 = (blockIdx.y % n_groups) * RT;
+  const int S = gridDim.z, split = blockIdx.z;
   const int d = n_heads * DH;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int grp = lane / LPR, li = lane % LPR;
-  const int len = sal_len[b] + jn;
-  const bool live = !(n_valid && jn >= n_valid[b]);
-  const int n = (!live || sal_len[b] < 0 || len + 1 > max_kv) ? 0 : len + 1;
+  const int sl = sal_len[b], nv = n_valid ? n_valid[b] : R;
+  int n[RT], n_max = 0, n_all = 0x7fffffff;               // rows of the cache that each query sees (0: dead); rows that all live ones see
+  float qv[RT][PER];
   const float scale = 1.4426950408889634f * rsqrtf((float)DH);
-  float qv[PER];
   #pragma unroll
-  for (int j = 0; j < PER; ++j) qv[j] = qbuf[(size_t)row * d + h * DH + li * PER + j] * scale;
+  for (int r = 0; r < RT; ++r) {
+    const int jn = last_only ? min(max(nv, 1), R) - 1 : j0 + r;
+    const bool live = jn < R && !(n_valid && jn >= nv);
+    n[r] = (!live || sl < 0 || sl + jn + 1 > max_kv) ? 0 : sl + jn + 1;
+    n_max = max(n_max, n[r]);
+    if (n[r] > 0) n_all = min(n_all, n[r]);
+    const float *q = qbuf + (size_t)(b * R + min(jn, R - 1)) * d + h * DH + li * PER;
+    #pragma unroll
+    for (int j = 0; j < PER; ++j) qv[r][j] = q[j] * scale;
+  }
   const T *kbase = kv_stage + (((size_t)b * 2 + 0) * n_heads + h) * (size_t)max_kv * DH;
   const T *vbase = kv_stage + (((size_t)b * 2 + 1) * n_heads + h) * (size_t)max_kv * DH;
-  float m = NEG_BIG, l = 0.f, o[PER];
+  float m[RT], l[RT], o[RT][PER];
   #pragma unroll
-  for (int j = 0; j < PER; ++j) o[j] = 0.f;
-  for (int jb = wave * (U * G); jb < n; jb += SA_WAVES * U * G) {
+  for (int r = 0; r < RT; ++r) {
+    m[r] = NEG_BIG; l[r] = 0.f;
+    #pragma unroll
+    for (int j = 0; j < PER; ++j) o[r][j] = 0.f;
+  }
+  const int per = (n_max + S - 1) / S, k0 = split * per, k1 = min(k0 + per, n_max);
+  // U rows per lane group against all queries: scores, one move of the running maxima, probabilities, values.  MASKED:
+  // some of the rows lie past the range or are hidden from some query (the last batch of a range only).
+  auto batch = [&](auto tag, int jb, const uint4 (&kf)[U], const uint4 (&vf)[U]) {
+    constexpr bool MASKED = decltype(tag)::value;
+    float sc[RT][U];
+    #pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float kk[PER];
+      Elem<T>::unpack(kf[u], kk);
+      const int j = jb + u * G + grp;
+      #pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        float s = 0.f;
+        #pragma unroll
+        for (int e = 0; e < PER; ++e) s = fmaf(qv[r][e], kk[e], s);
+        s = sa_group_sum<LPR>(s);
+        sc[r][u] = (MASKED && !(j < k1 && j < n[r])) ? -__builtin_huge_valf() : s;
+      }
+    }
+    #pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      float mn = m[r];
+      #pragma unroll
+      for (int u = 0; u < U; ++u) mn = fmaxf(mn, sc[r][u]);
+      const float corr = sa_exp2(m[r] - mn);               // (mn is at least NEG_BIG: masked scores give 2^-inf = 0)
+      m[r] = mn;
+      l[r] *= corr;
+      #pragma unroll
+      for (int e = 0; e < PER; ++e) o[r][e] *= corr;
+      #pragma unroll
+      for (int u = 0; u < U; ++u) { sc[r][u] = sa_exp2(sc[r][u] - mn); l[r] += sc[r][u]; }
+    }
+    #pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float vv[PER];
+      Elem<T>::unpack(vf[u], vv);
+      const int j = jb + u * G + grp;
+      #pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        const bool in = !MASKED || (j < k1 && j < n[r]);   // a hidden row is left out whatever it holds (0 * NaN)
+        #pragma unroll
+        for (int e = 0; e < PER; ++e) o[r][e] = in ? fmaf(sc[r][u], vv[e], o[r][e]) : o[r][e];
+      }
+    }
+  };
+  for (int jb = k0 + wave * (U * G); jb < k1; jb += SA_WAVES * U * G) {
     uint4 kf[U], vf[U];
     #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int j = min(jb + u * G + grp, n - 1);     // unconditional loads; rows past the end are skipped below
+      const int j = min(jb + u * G + grp, k1 - 1);         // unconditional loads; rows past the end are masked
       kf[u] = ldg16_stream(kbase + (size_t)j * DH + li * PER);
       vf[u] = ldg16_stream(vbase + (size_t)j * DH + li * PER);
     }
-    #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int j = jb + u * G + grp;
-      float kk[PER], vv[PER];
-      Elem<T>::unpack(kf[u], kk);
-      Elem<T>::unpack(vf[u], vv);
-      float sc = 0.f;
-      #pragma unroll
-      for (int e = 0; e < PER; ++e) sc = fmaf(qv[e], kk[e], sc);
-      #pragma unroll
-      for (int off = 1; off < LPR; off <<= 1) sc += __shfl_xor(sc, off, WAVE);
-      if (j < n) {
-        const float mn = fmaxf(m, sc);
-        const float corr = exp2f(m - mn), p = exp2f(sc - mn);
-        l = l * corr + p;
-        #pragma unroll
-        for (int e = 0; e < PER; ++e) o[e] = o[e] * corr + p * vv[e];
-        m = mn;
-      }
-    }
+    if (jb + U * G <= min(k1, n_all)) batch(BoolTag<false>{}, jb, kf, vf);        // (uniform over the wave)
+    else batch(BoolTag<true>{}, jb, kf, vf);
   }
+  #pragma unroll
+  for (int r = 0; r < RT; ++r)
+    if (n[r] == 0) { m[r] = NEG_BIG; l[r] = 0.f; }         // a dead position (its output is zero)
   // lane groups -> wave
   #pragma unroll
-  for (int off = LPR; off < WAVE; off <<= 1) {
-    const float m2 = __shfl_xor(m, off, WAVE), l2 = __shfl_xor(l, off, WAVE);
-    const float mn = fmaxf(m, m2);
-    const float c1 = exp2f(m - mn), c2 = exp2f(m2 - mn);
-    l = l * c1 + l2 * c2;
+  for (int r = 0; r < RT; ++r) {
+    const float mw = sa_across<LPR>(m[r], [](float x, float y) { return fmaxf(x, y); });
+    const float f = sa_exp2(m[r] - mw);
+    m[r] = mw;
+    l[r] = sa_across<LPR>(l[r] * f, [](float x, float y) { return x + y; });
     #pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      const float o2 = __shfl_xor(o[e], off, WAVE);
-      o[e] = o[e] * c1 + o2 * c2;
+    for (int e = 0; e < PER; ++e) o[r][e] = sa_across<LPR>(o[r][e] * f, [](float x, float y) { return x + y; });
+    if (grp == 0) {
+      #pragma unroll
+      for (int e = 0; e < PER; ++e) sm_o[wave][r][li * PER + e] = o[r][e];
+      if (li == 0) { sm_m[wave][r] = m[r]; sm_l[wave][r] = l[r]; }
     }
-    m = mn;
-  }
-  if (grp == 0) {
-    #pragma unroll
-    for (int e = 0; e < PER; ++e) sm_o[wave][li * PER + e] = o[e];
-    if (li == 0) { sm_m[wave] = m; sm_l[wave] = l; }
   }
   __syncthreads();
   // waves -> workgroup
-  if (threadIdx.x < DH) {
-    float mw = sm_m[0];
+  for (int idx = threadIdx.x; idx < RT * DH; idx += SA_WAVES * 64) {
+    const int r = idx / DH, e = idx % DH;
+    if (!last_only && j0 + r >= R) break;
+    const int row = last_only ? b : b * R + j0 + r;
+    float mw = sm_m[0][r];
     #pragma unroll
-    for (int w = 1; w < SA_WAVES; ++w) mw = fmaxf(mw, sm_m[w]);
+    for (int w = 1; w < SA_WAVES; ++w) mw = fmaxf(mw, sm_m[w][r]);
     float lw = 0.f, ow = 0.f;
     #pragma unroll
     for (int w = 0; w < SA_WAVES; ++w) {
-      const float f = exp2f(sm_m[w] - mw);
-      lw += sm_l[w] * f;
-      ow += sm_o[w][threadIdx.x] * f;
+      const float f = sa_exp2(sm_m[w][r] - mw);
+      lw += sm_l[w][r] * f;
+      ow += sm_o[w][r][e] * f;
     }
-    out[(size_t)out_row * d + h * DH + threadIdx.x] = (lw > 0.f) ? ow / lw : 0.f;
+    if (S == 1) {
+      out[(size_t)row * d + h * DH + e] = (lw > 0.f) ? ow / lw : 0.f;
+    } else {
+      float *p = part + (((size_t)row * n_heads + h) * S + split) * (DH + 2);
+      p[e] = ow;
+      if (e == 0) { p[DH] = mw; p[DH + 1] = lw; }
+    }
   }
+}
+
+// out[row] of one head = sum_s o_s 2^(m_s - m) / sum_s l_s 2^(m_s - m), s ascending; every split's values are requested
+// before the first is used.  grid = (heads, rows), DH threads.
+template <int DH>
+__global__ __launch_bounds__(DH) void k_sal_fold(const float *part, int n_heads, int S, float *out) {
+  const int h = blockIdx.x, row = blockIdx.y, e = threadIdx.x;
+  const float *p = part + ((size_t)row * n_heads + h) * S * (DH + 2);
+  float ov[SAL_MAX_SPLITS], mv[SAL_MAX_SPLITS], lv[SAL_MAX_SPLITS];
+  #pragma unroll
+  for (int s = 0; s < SAL_MAX_SPLITS; ++s) {
+    const float *ps = p + (size_t)min(s, S - 1) * (DH + 2);
+    ov[s] = ps[e]; mv[s] = ps[DH]; lv[s] = ps[DH + 1];
+  }
+  float mw = NEG_BIG;
+  #pragma unroll
+  for (int s = 0; s < SAL_MAX_SPLITS; ++s) if (s < S) mw = fmaxf(mw, mv[s]);
+  float lw = 0.f, ow = 0.f;
+  #pragma unroll
+  for (int s = 0; s < SAL_MAX_SPLITS; ++s)
+    if (s < S) {
+      const float f = exp2f(mv[s] - mw);
+      lw += lv[s] * f;
+      ow += ov[s] * f;
+    }
+  out[((size_t)row * n_heads + h) * DH + e] = (lw > 0.f) ? ow / lw : 0.f;
+}
+
+// New positions per workgroup: one where that leaves fewer workgroups than compute units (their caches then come from L2
+// for all but the first, and six queries' arithmetic would be the longest part: 32 heads, 5 positions, 1024 rows: five
+// workgroups per head 15.1 us, one with 8 key splits 11.8 + 4.8 for the fold), else as many as go together.
+static int sal_group(int B, int n_heads, int R) { return (R <= 1 || B * n_heads * R <= 256) ? 1 : R <= 3 ? 3 : 6; }
+// Key splits, of 128 rows or more, where they pay for the fold's launch: one workgroup per compute unit, of the small
+// ones (one position) two, from five splits on (one position, 208 workgroups of 2047 rows: 33.8 us whole, 35.6 + 4.9 in
+// two splits; 160 of 1024 rows 15.1, 11.2 + 4.9 in three; 32 of 1024 rows 15.8, 6.1 + 4.7 in eight).
+static int sal_splits(int B, int n_groups, int n_heads, int max_kv, int rt) {
+  const int s = std::min((rt == 1 ? 480 : 256) / (B * n_groups * n_heads), max_kv / 128);
+  return (rt == 1 && s < 5) ? 1 : std::max(1, std::min(s, SAL_MAX_SPLITS));
+}
+size_t sal_part_floats(int B, int R, int n_heads, int d_h, int max_kv) {
+  size_t most = 0;
+  for (int r = 1; r <= R; ++r) {                            // any number of new positions up to R may be asked for
+    const int rt = sal_group(B, n_heads, r), s = sal_splits(B, (r + rt - 1) / rt, n_heads, max_kv, rt);
+    if (s > 1) most = std::max(most, (size_t)B * r * n_heads * s * (d_h + 2));
+  }
+  return most;
+}
+
+template <typename T, int DH>
+static hipError_t launch_sal_attn_dh(hipStream_t st, const float *qbuf, const T *kv_stage, const int32_t *sal_len, int B, int n_heads,
+                                     int max_kv, float *out, int R, const int32_t *n_valid, int last_only, float *part) {
+  const int rt = last_only ? 1 : sal_group(B, n_heads, R), n_groups = last_only ? 1 : (R + rt - 1) / rt;
+  const int S = sal_splits(B, n_groups, n_heads, max_kv, rt);
+  const dim3 grid(n_heads, B * n_groups, S), block(SA_WAVES * 64);
+  #define SA(RT_) hipLaunchKernelGGL((k_sal_attn<T, DH, RT_>), grid, block, 0, st, qbuf, kv_stage, sal_len, n_heads, max_kv, out, R, n_valid, \
+                                     last_only, n_groups, part)
+  if (rt == 1) SA(1); else if (rt == 3) SA(3); else SA(6);
+  #undef SA
+  if (S > 1) hipLaunchKernelGGL((k_sal_fold<DH>), dim3(n_heads, last_only ? B : B * R), dim3(DH), 0, st, part, n_heads, S, out);
+  return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_sal_attn(hipStream_t st, const float *qbuf, const void *kv_stage, const int32_t *sal_len, int B,
-                           int n_heads, int d_h, int max_kv, float *out, int R, const int32_t *n_valid, int last_only) {
-  const dim3 grid(n_heads, last_only ? B : B * R), block(SA_WAVES * 64);
-  if (d_h == 64)
-    hipLaunchKernelGGL((k_sal_attn<T, 64>), grid, block, 0, st, qbuf, (const T *)kv_stage, sal_len, n_heads, max_kv, out, R,
-                       n_valid, last_only);
-  else if (d_h == 128)
-    hipLaunchKernelGGL((k_sal_attn<T, 128>), grid, block, 0, st, qbuf, (const T *)kv_stage, sal_len, n_heads, max_kv, out, R,
-                       n_valid, last_only);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
+                           int n_heads, int d_h, int max_kv, float *out, int R, const int32_t *n_valid, int last_only, float *part) {
+  if (d_h == 64) return launch_sal_attn_dh<T, 64>(st, qbuf, (const T *)kv_stage, sal_len, B, n_heads, max_kv, out, R, n_valid, last_only, part);
+  if (d_h == 128) return launch_sal_attn_dh<T, 128>(st, qbuf, (const T *)kv_stage, sal_len, B, n_heads, max_kv, out, R, n_valid, last_only, part);
+  return hipErrorInvalidValue;
 }
 template hipError_t launch_sal_attn<float>(hipStream_t, const float *, const void *, const int32_t *, int, int, int, int,
-                                           float *, int, const int32_t *, int);
+                                           float *, int, const int32_t *, int, float *);
 template hipError_t launch_sal_attn<bf16_t>(hipStream_t, const float *, const void *, const int32_t *, int, int, int,
-                                            int, float *, int, const int32_t *, int);
+                                            int, float *, int, const int32_t *, int, float *);
 
 // =====================================================================================================
 // Eq. 5 core: for one (batch, head) the K x K score matrix of the K head positions, a row softmax
