@@ -134,8 +134,7 @@ WsLayout make_layout(const amph_config &c) {
   w.act = take(Mr * f * 4); w.h[0] = take(Mr * d * 4); w.h[1] = take(Mr * d * 4);
   w.Hp = take(BK * d * 4); w.Qa = take(BK * d * 4); w.Ka = take(BK * d * 4); w.Va = take(BK * d * 4);
   w.ctxa = take(BK * d * 4); w.attn_o = take(BK * d * 4); w.logits = take(BK * V * 4);
-  w.topk_ws = take(std::max(std::max(topk_ws_floats((int)BK, c.vocab, c.topk), topk_ws_floats((int)M, c.vocab, 1)),
-                            lmtk_ws_floats((int)BK, c.topk)) * 4);
+  w.topk_ws = take(lmtk_ws_floats((int)BK, c.topk) * 4);
   w.sal_part = take(sal_part_floats(c.batch, c.K + 1, c.n_heads, c.head_dim, c.max_kv) * 4);
   const size_t Mp = (M + 31) / 32 * 32;         // activations may be kept in 32-row tiles for the wide GEMM
   w.xres = take(M * d * 4); w.xn = take(Mp * d * esz); w.qb = take(M * d * esz); w.attb = take(Mp * d * esz);
@@ -617,8 +616,7 @@ amph_status amph_accept(amph_ctx *ctx, const amph_tree *tree, const int32_t *tre
   if (tgt_logits) {
     if (!workspace) return fail(ctx, AMPH_EINVAL, "amph_accept: workspace needed with tgt_logits");
     int32_t *tmp = (int32_t *)((char *)workspace + ctx->ws.tgt_tmp);
-    HIP_TRY(ctx, launch_row_argmax(ctx->stream, tgt_logits, ctx->cfg.batch * tree->T, ctx->cfg.vocab, tmp,
-                                   (float *)((char *)workspace + ctx->ws.topk_ws)));
+    HIP_TRY(ctx, launch_row_argmax(ctx->stream, tgt_logits, ctx->cfg.batch * tree->T, ctx->cfg.vocab, tmp));
     tgt = tmp;
   }
   HIP_TRY(ctx, launch_accept(ctx->stream, tree->d_parent, tree->d_depth, tree->T, ctx->cfg.batch, ctx->cfg.K, tree_tok, tgt,

@@ -167,55 +167,50 @@ __device__ __forceinline__ bool better(float v1, int i1, float v2, int i2) {
   return (v1 > v2) || (v1 == v2 && i1 < i2);
 }
 
-// The best (value, index) pair of the wave, in every lane.  Six data-parallel-primitive steps instead of a
-// butterfly of cross-lane permutes through the LDS crossbar (twelve dependent permutes cost about 1400 clocks per
-// selection round, which made a ten-round top-k the longest part of its kernel): inside each row of 16 lanes
-// the pair is folded with its neighbour at distance 1, 2, then its mirror inside 8 and inside 16 lanes (after which
-// every lane of a row holds the row's best); lane 15 of rows 0 and 2 is then broadcast into rows 1 and 3, lane 31
-// into rows 2 and 3, so lane 63 ends with the wave's best, which a lane read hands to everybody.  A lane that a
-// step does not write keeps its own pair, which never beats itself.  All 64 lanes must be active.
-__device__ __forceinline__ void wave_best(float &v, int &i) {
-  #define AMPH_DPP_STEP(CTRL, ROWS)                                                                              \
-    {                                                                                                            \
-      const int ovb = __builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, ROWS, 0xf, false); \
-      const int oi = __builtin_amdgcn_update_dpp(i, i, CTRL, ROWS, 0xf, false);                                  \
-      const float ov = __int_as_float(ovb);                                                                      \
-      if (better(ov, oi, v, i)) { v = ov; i = oi; }                                                              \
-    }
-  AMPH_DPP_STEP(0xb1, 0xf)       // quad_perm [1, 0, 3, 2]
-  AMPH_DPP_STEP(0x4e, 0xf)       // quad_perm [2, 3, 0, 1]
-  AMPH_DPP_STEP(0x141, 0xf)      // row_half_mirror
-  AMPH_DPP_STEP(0x140, 0xf)      // row_mirror
-  AMPH_DPP_STEP(0x142, 0xa)      // row_bcast:15 into rows 1 and 3
-  AMPH_DPP_STEP(0x143, 0xc)      // row_bcast:31 into rows 2 and 3
-  #undef AMPH_DPP_STEP
-  v = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-  i = __builtin_amdgcn_readlane(i, 63);
+// Selection by counting: an element's place among the best is the number of better ones, which every lane counts for its
+// own elements against all of them, one broadcast at a time.  The k places come out at once.  (In k rounds of a wave-wide
+// maximum, each a chain of six cross-lane steps and a rescan of about 1000 clocks, ten places among 64 logits made the
+// LM head's epilogue 4 us long; this takes less than one round did.)
+// Order-preserving integer of a float, at least 1; 0 for NaN (never selected).  +0 and -0 are equal.
+__device__ __forceinline__ unsigned rank_key(float v) {
+  const unsigned b = __float_as_uint(v + 0.0f);
+  return (v == v) ? b ^ (((int)b < 0) ? 0xffffffffu : 0x80000000u) : 0u;
 }
-
-// Select k times from NPT per-lane (value, index) pairs spread over a wave.  Lane 0 writes the results.
+// number of the NPT * 64 keys (element j * 64 + lane; 0 = none) that come before own key at place own_e: larger, or equal
+// at a lower place.  Elements from n on are not looked at.  All 64 lanes must be active.
 template <int NPT>
-__device__ __forceinline__ void wave_select(float (&x)[NPT], int (&id)[NPT], int k, int none, float *out_v, int *out_i) {
-  const float NEG_INF = -__builtin_huge_valf();
-  const int lane = threadIdx.x & 63;
-  float bv = NEG_INF; int bi = none, bj = -1;
+__device__ __forceinline__ int rank_among(const unsigned (&key)[NPT], int n, unsigned own, int own_e) {
+  int rank = 0;
   #pragma unroll
-  for (int j = 0; j < NPT; ++j)
-    if (id[j] != none && better(x[j], id[j], bv, bi)) { bv = x[j]; bi = id[j]; bj = j; }
-  for (int r = 0; r < k; ++r) {
-    float wv = bv; int wi = bi;
-    wave_best(wv, wi);
-    if (lane == 0) { out_v[r] = wv; out_i[r] = (wi == none) ? -1 : wi; }
-    if (wi != none && wi == bi) {              // this lane owned the winner: retire it and rescan
-      bv = NEG_INF; bi = none;
-      const int gone = bj; bj = -1;
-      #pragma unroll
-      for (int j = 0; j < NPT; ++j) {
-        if (j == gone) id[j] = none;
-        if (id[j] != none && better(x[j], id[j], bv, bi)) { bv = x[j]; bi = id[j]; bj = j; }
+  for (int j = 0; j < NPT; ++j) {
+    if (j * WAVE < n) {
+      #pragma unroll 8
+      for (int s = 0; s < WAVE; ++s) {                     // (unrolled whole, the broadcast values fill the scalar registers)
+        const unsigned o = (unsigned)__builtin_amdgcn_readlane((int)key[j], s);
+        rank += (o > own || (o == own && j * WAVE + s < own_e)) ? 1 : 0;
       }
     }
   }
+  return rank;
+}
+// The k best of NPT values per lane (element e = j * 64 + lane, token id0 + e, e < n_live) into out_v / out_i, best first, ties
+// to the lower token; (-inf, -1) past the last one.
+template <int NPT>
+__device__ __forceinline__ void rank_select(const float (&x)[NPT], int id0, int n_live, int k, float *out_v, int *out_i) {
+  const int lane = threadIdx.x & 63;
+  unsigned key[NPT];
+  int n_valid = 0;
+  #pragma unroll
+  for (int j = 0; j < NPT; ++j) {
+    key[j] = (j * WAVE + lane < n_live) ? rank_key(x[j]) : 0u;
+    n_valid += __popcll(__ballot(key[j] != 0u));
+  }
+  #pragma unroll
+  for (int j = 0; j < NPT; ++j) {
+    const int r = rank_among<NPT>(key, n_live, key[j], j * WAVE + lane);
+    if (key[j] != 0u && r < k) { out_v[r] = x[j]; out_i[r] = id0 + j * WAVE + lane; }
+  }
+  if (lane >= n_valid && lane < k) { out_v[lane] = -__builtin_huge_valf(); out_i[lane] = -1; }
 }
 
 }  // namespace amph

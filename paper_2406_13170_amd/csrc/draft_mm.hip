@@ -448,15 +448,11 @@ __global__ __launch_bounds__((DmStage<NB, NT, CB_>::THREADS)) void k_draft_mm(co
     constexpr int NPT = (16 * NB + 63) / 64;
     const int n_live = min(16 * NB, a.seg_rows - b0 * 16);
     for (int m = wave; m < a.M; m += KW + DM_NL) {
-      float xv[NPT]; int id[NPT];
+      float xv[NPT];
       #pragma unroll
-      for (int j = 0; j < NPT; ++j) {
-        const int e = j * WAVE + lane;
-        id[j] = (e < n_live) ? b0 * 16 + e : a.seg_rows;
-        xv[j] = lg[m * (16 * NB) + min(e, 16 * NB - 1)];
-      }
+      for (int j = 0; j < NPT; ++j) xv[j] = lg[m * (16 * NB) + min(j * WAVE + lane, 16 * NB - 1)];
       const size_t o = ((size_t)m * gridDim.x + blockIdx.x) * a.topk;
-      wave_select<NPT>(xv, id, a.topk, a.seg_rows, a.cand_v + o, a.cand_i + o);
+      rank_select<NPT>(xv, b0 * 16, n_live, a.topk, a.cand_v + o, a.cand_i + o);
     }
   }
 }

@@ -624,15 +624,16 @@ __global__ __launch_bounds__(GV_THREADS) void k_lmhead_topk(const T *W, int V, i
   __syncthreads();
   const int n_live = min((g1 - g0) * GV_R, V - g0 * GV_R);       // this workgroup's rows inside the vocabulary
   for (int m = wave; m < m_valid; m += 4) {
-    float xv[LMTK_NPT]; int id[LMTK_NPT];
-    #pragma unroll
-    for (int j = 0; j < LMTK_NPT; ++j) {
-      const int e = j * WAVE + lane;
-      id[j] = (e < n_live) ? g0 * GV_R + e : V;
-      xv[j] = lg[m * RP + min(e, RP - 1)];
-    }
     const size_t o = ((size_t)m * gridDim.x + blockIdx.x) * k;
-    wave_select<LMTK_NPT>(xv, id, k, V, cand_v + o, cand_i + o);
+    if (RP <= WAVE) {                                      // as at 32000 tokens: one logit per lane
+      const float xv[1] = {lg[m * RP + min(lane, RP - 1)]};
+      rank_select<1>(xv, g0 * GV_R, n_live, k, cand_v + o, cand_i + o);
+    } else {
+      float xv[LMTK_NPT];
+      #pragma unroll
+      for (int j = 0; j < LMTK_NPT; ++j) xv[j] = lg[m * RP + min(j * WAVE + lane, RP - 1)];
+      rank_select<LMTK_NPT>(xv, g0 * GV_R, n_live, k, cand_v + o, cand_i + o);
+    }
   }
 }
 

@@ -59,16 +59,11 @@ hipError_t launch_sal_attn(hipStream_t st, const float *qbuf, const void *kv_sta
                            int n_heads, int d_h, int max_kv, float *out, int R, const int32_t *n_valid, int last_only, float *part);
 hipError_t launch_aeb_attn(hipStream_t st, const float *Q, const float *Kk, const float *V, int B, int K, int n_heads,
                            int d_h, float *ctx);
-// ws: topk_ws_floats(rows, V, k) floats of scratch for the per-wave candidates
-size_t topk_ws_floats(int rows, int V, int k);
-hipError_t launch_topk_rows(hipStream_t st, const float *logits, int rows, int V, int k, int32_t *idx, float *val,
-                            int32_t *advance, int n_advance, int advance_by, const int32_t *advance_each, int advance_limit,
-                            float *ws);   // advance[i] += advance_each ? advance_each[i] : advance_by where the sum stays <= advance_limit
-// top-k of n_cand (value, token) candidates per row (cand_i < 0: no candidate), one workgroup per row
+// top-k of n_cand / k sorted lists of k (value, token) candidates per row (token < 0: none), one workgroup per row
 hipError_t launch_topk_merge(hipStream_t st, const float *cand_v, const int *cand_i, int rows, int n_cand, int V, int k,
                              int32_t *idx, float *val, int32_t *advance, int n_advance, int advance_by,
                              const int32_t *advance_each, int advance_limit);
-hipError_t launch_row_argmax(hipStream_t st, const float *logits, int rows, int V, int32_t *out, float *ws);
+hipError_t launch_row_argmax(hipStream_t st, const float *logits, int rows, int V, int32_t *out);
 hipError_t launch_tree_build(hipStream_t st, const int32_t *depth, const int32_t *rank, int T, int B, int K, int topk,
                              const int32_t *root_tok, const int32_t *topk_idx, const int32_t *kv_len, int32_t *tree_tok,
                              int32_t *tree_pos);

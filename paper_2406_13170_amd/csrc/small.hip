@@ -323,17 +323,9 @@ hipError_t launch_aeb_attn(hipStream_t st, const float *Q, const float *Kk, cons
 }
 
 // =====================================================================================================
-// Per-row top-k (Eq. 6) by repeated selection inside single waves (no workgroup barriers).
-// "Better" means a larger value, or the same value and a smaller index, so results are sorted and
-// ties deterministic.
-//   pass 1: every wave owns TK_CHUNK consecutive logits of one row (TK_NPT per lane) and emits its own
-//           top-k as (value, index) candidates;
-//   pass 2: one wave per row selects the top-k of all candidates of the row.
-// The top-k of a union is the top-k of the parts' top-k, so the result is exact.
+// Per-row top-k (Eq. 6).  "Better" means a larger value, or the same value and a smaller index, so results are sorted
+// and ties deterministic.
 // =====================================================================================================
-constexpr int TK_NPT = 8, TK_CHUNK = TK_NPT * WAVE;      // 512 logits per wave
-constexpr int TK_MAXC = 32;                              // pass 2: candidates per lane
-
 // Cache length of element i after its new rows: advanced only when every new row fitted (the kernels that write
 // the rows skipped those past the limit and raised the overflow flag; the length then stays where it was).
 __device__ __forceinline__ void advance_one(int32_t *len, int i, int by, int limit) {
@@ -341,53 +333,9 @@ __device__ __forceinline__ void advance_one(int32_t *len, int i, int by, int lim
   if (v >= 0 && by >= 0 && v + by <= limit) len[i] = v + by;
 }
 
-__global__ __launch_bounds__(256) void k_topk_pass1(const float *logits, int V, int k, int chunks_per_row, float *cand_v,
-                                                    int *cand_i) {
-  const int row = blockIdx.y, chunk = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (chunk >= chunks_per_row) return;                    // whole wave leaves together
-  const float *src = logits + (size_t)row * V;
-  float x[TK_NPT]; int id[TK_NPT];
-  #pragma unroll
-  for (int j = 0; j < TK_NPT; ++j) {
-    // unconditional loads from clamped addresses (a predicated load makes the compiler wait for each one)
-    const int e = chunk * TK_CHUNK + j * WAVE + lane;
-    id[j] = (e < V) ? e : V;
-    x[j] = src[min(e, V - 1)];
-  }
-  const size_t o = ((size_t)row * chunks_per_row + chunk) * k;
-  wave_select<TK_NPT>(x, id, k, V, cand_v + o, cand_i + o);
-}
-
-__global__ __launch_bounds__(64) void k_topk_pass2(const float *cand_v, const int *cand_i, int n_cand, int V, int k,
-                                                   int32_t *idx, float *val, int32_t *advance, int n_advance,
-                                                   int advance_by, const int32_t *advance_each, int advance_limit) {
-  const int row = blockIdx.x, lane = threadIdx.x;
-  float x[TK_MAXC]; int id[TK_MAXC];
-  #pragma unroll
-  for (int j = 0; j < TK_MAXC; ++j) {
-    const int c = min(j * WAVE + lane, n_cand - 1);
-    id[j] = cand_i[(size_t)row * n_cand + c];
-    x[j] = cand_v[(size_t)row * n_cand + c];
-  }
-  #pragma unroll
-  for (int j = 0; j < TK_MAXC; ++j)
-    if (j * WAVE + lane >= n_cand || id[j] < 0) id[j] = V;
-  __shared__ float sv[AMPH_MAX_TOPK];
-  __shared__ int si[AMPH_MAX_TOPK];
-  wave_select<TK_MAXC>(x, id, k, V, sv, si);
-  __syncthreads();
-  if (lane < k) {
-    if (idx) idx[(size_t)row * k + lane] = si[lane];
-    if (val) val[(size_t)row * k + lane] = sv[lane];
-  }
-  if (row == 0 && advance)
-    for (int i = lane; i < n_advance; i += WAVE) advance_one(advance, i, advance_each ? advance_each[i] : advance_by, advance_limit);
-}
-
 // One workgroup of 1024 threads per row for vocabularies up to 65536: every thread keeps NPT logits (element
 // j * 1024 + tid in slot j) and its own best; k rounds of (wave butterfly, 16 wave winners through LDS, every wave
-// folds them again) pick the winners, and only the thread that owned a winner rescans its slots.  Same order and
-// tie rule as the two-pass version, one launch instead of two.
+// folds them again) pick the winners, and only the thread that owned a winner rescans its slots.
 template <int NPT>
 __global__ __launch_bounds__(1024) void k_topk_row(const float *logits, int V, int k, int32_t *idx, float *val,
                                                    int32_t *advance, int n_advance, int advance_by,
@@ -448,101 +396,97 @@ __global__ __launch_bounds__(1024) void k_topk_row(const float *logits, int V, i
     for (int i = tid; i < n_advance; i += 1024) advance_one(advance, i, advance_each ? advance_each[i] : advance_by, advance_limit);
 }
 
-// Top-k of the candidates the fused LM head left: one 1024-thread workgroup per row.  Every wave selects the top k
-// of its share (NPT candidates per lane), the 16 x k survivors go through LDS, and the first wave selects among them.
-template <int NPT>
-__global__ __launch_bounds__(1024) void k_topk_merge(const float *cand_v, const int *cand_i, int n_cand, int V, int k,
-                                                     int32_t *idx, float *val, int32_t *advance, int n_advance, int advance_by,
-                                                     const int32_t *advance_each, int advance_limit) {
-  __shared__ float sv[16 * AMPH_MAX_TOPK];
-  __shared__ int si[16 * AMPH_MAX_TOPK];
-  __shared__ float fv[AMPH_MAX_TOPK];
-  __shared__ int fi[AMPH_MAX_TOPK];
+// Top-k of the candidates the fused LM head left: per row n_lists lists of k (value, token) pairs, each sorted (best
+// first, token -1 past its end), the lists in ascending token order.  One workgroup per row, three selections by counting
+// the better ones:
+//   1. every wave takes the k best heads of 64 lists;
+//   2. of those the k best heads of all (ties to the lower list, which holds the lower tokens): a list whose head is not
+//      among them has k better candidates elsewhere;
+//   3. the k best of those lists' k * k candidates.
+// (Sixteen waves selecting in rounds over all 5000 candidates of 500 lists: 14.6 us, one wave in rounds over the heads and
+// then the chosen lists 13.7, this 7.9; a launch that loads, loads what that names and stores is 4.8.)
+template <int W>
+__global__ __launch_bounds__(W * 64) void k_topk_merge(const float *cand_v, const int *cand_i, int n_lists, int V, int k,
+                                                       int32_t *idx, float *val, int32_t *advance, int n_advance, int advance_by,
+                                                       const int32_t *advance_each, int advance_limit) {
+  constexpr int MK = AMPH_MAX_TOPK;
+  static_assert(W * 64 >= MK * MK, "one thread per candidate of the chosen lists");
+  __shared__ float hv[W * MK];
+  __shared__ int hi[W * MK], sel[MK];
+  __shared__ unsigned long long key[W * 64];
   const int row = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const float *cv = cand_v + (size_t)row * n_cand;
-  const int *ci = cand_i + (size_t)row * n_cand;
-  float x[NPT]; int id[NPT];
-  #pragma unroll
-  for (int j = 0; j < NPT; ++j) {                          // unconditional loads from clamped addresses
-    const int c = j * 1024 + tid, cc = min(c, n_cand - 1);
-    const int t = ci[cc];
-    x[j] = cv[cc];
-    id[j] = (c < n_cand && t >= 0 && t < V) ? t : V;
+  const float *cv = cand_v + (size_t)row * n_lists * k;
+  const int *ci = cand_i + (size_t)row * n_lists * k;
+  // a key of its own for every (value, id): larger is better, ties to the lower id; 0 = none
+  auto key_of = [](float v, int id) {
+    const unsigned q = rank_key(v);
+    return (id >= 0 && q != 0u) ? ((unsigned long long)q << 32) | (unsigned)~id : 0ull;
+  };
+  auto place = [&](unsigned long long own, int n) {
+    int r = 0;
+    for (int e = 0; e < n; ++e) r += key[e] > own ? 1 : 0;
+    return r;
+  };
+  {
+    const int li = tid, lc = min(li, n_lists - 1), t = ci[(size_t)lc * k];
+    float x[1] = {cv[(size_t)lc * k]};
+    if (t < 0 || t >= V) x[0] = __builtin_nanf("");        // no candidate
+    rank_select<1>(x, wave * WAVE, min(max(n_lists - wave * WAVE, 0), WAVE), k, hv + wave * k, hi + wave * k);
   }
-  wave_select<NPT>(x, id, k, V, sv + wave * k, si + wave * k);
+  if (tid < k) sel[tid] = -1;
   __syncthreads();
-  if (wave == 0) {
-    constexpr int NP2 = (16 * AMPH_MAX_TOPK) / WAVE;       // 4
-    float y[NP2]; int jd[NP2];
-    #pragma unroll
-    for (int j = 0; j < NP2; ++j) {
-      const int c = j * WAVE + lane, cc = min(c, 16 * k - 1);
-      y[j] = sv[cc];
-      jd[j] = (c < 16 * k && si[cc] >= 0) ? si[cc] : V;
+  unsigned long long own = 0ull;
+  if (tid < W * k) key[tid] = own = key_of(hv[tid], hi[tid]);
+  __syncthreads();
+  if (own != 0ull) {
+    const int r = place(own, W * k);
+    if (r < k) sel[r] = hi[tid];
+  }
+  __syncthreads();
+  const int list = tid < k * k ? sel[tid / k] : -1;
+  float y = 0.f;
+  int tk = -1;
+  if (list >= 0) {
+    y = cv[(size_t)list * k + tid % k];
+    tk = ci[(size_t)list * k + tid % k];
+  }
+  own = key_of(y, tk < V ? tk : -1);
+  key[tid] = own;
+  const int n_valid = __syncthreads_count(own != 0ull);
+  if (own != 0ull) {
+    const int r = place(own, k * k);
+    if (r < k) {
+      if (idx) idx[(size_t)row * k + r] = tk;
+      if (val) val[(size_t)row * k + r] = y;
     }
-    wave_select<NP2>(y, jd, k, V, fv, fi);
   }
-  __syncthreads();
-  if (tid < k) {
-    if (idx) idx[(size_t)row * k + tid] = fi[tid];
-    if (val) val[(size_t)row * k + tid] = fv[tid];
+  if (tid >= n_valid && tid < k) {
+    if (idx) idx[(size_t)row * k + tid] = -1;
+    if (val) val[(size_t)row * k + tid] = -__builtin_huge_valf();
   }
   if (row == 0 && advance)
-    for (int i = tid; i < n_advance; i += 1024) advance_one(advance, i, advance_each ? advance_each[i] : advance_by, advance_limit);
+    for (int i = tid; i < n_advance; i += W * 64) advance_one(advance, i, advance_each ? advance_each[i] : advance_by, advance_limit);
 }
 
 hipError_t launch_topk_merge(hipStream_t st, const float *cand_v, const int *cand_i, int rows, int n_cand, int V, int k,
                              int32_t *idx, float *val, int32_t *advance, int n_advance, int advance_by,
                              const int32_t *advance_each, int advance_limit) {
-  if (rows < 1 || n_cand < 1 || k < 1 || k > AMPH_MAX_TOPK || n_cand > 16 * 1024) return hipErrorInvalidValue;
-  #define TM_LAUNCH(N) hipLaunchKernelGGL((k_topk_merge<N>), dim3(rows), dim3(1024), 0, st, cand_v, cand_i, n_cand, V, k, idx, val, \
+  if (rows < 1 || n_cand < 1 || k < 1 || k > AMPH_MAX_TOPK || n_cand % k || n_cand / k > LMTK_MAX_WG) return hipErrorInvalidValue;
+  const int n_lists = n_cand / k;
+  #define TM_LAUNCH(W) hipLaunchKernelGGL((k_topk_merge<W>), dim3(rows), dim3(W * 64), 0, st, cand_v, cand_i, n_lists, V, k, idx, val, \
                                           advance, n_advance, advance_by, advance_each, advance_limit)
-  // as few candidates per lane as cover the row: a selection round rescans a lane's candidates, and with ten rounds
-  // that is most of the kernel (5000 candidates: 8 per lane 16.4 us, 5 per lane 14.9; half the waves with 10 per lane
-  // 15.6, a quarter with 20 per lane 26.6)
-  switch ((n_cand + 1023) / 1024) {
-    case 1: TM_LAUNCH(1); break;
-    case 2: TM_LAUNCH(2); break;
-    case 3: TM_LAUNCH(3); break;
-    case 4: TM_LAUNCH(4); break;
-    case 5: TM_LAUNCH(5); break;
-    case 6: TM_LAUNCH(6); break;
-    case 7: case 8: TM_LAUNCH(8); break;
-    default: TM_LAUNCH(16); break;
-  }
+  if (n_lists <= 4 * WAVE) TM_LAUNCH(4); else if (n_lists <= 8 * WAVE) TM_LAUNCH(8); else TM_LAUNCH(16);
   #undef TM_LAUNCH
   return hipGetLastError();
 }
 
-size_t topk_ws_floats(int rows, int V, int k) {
-  const int chunks = (V + TK_CHUNK - 1) / TK_CHUNK;
-  return 2 * (size_t)rows * chunks * k;
-}
-
-hipError_t launch_topk_rows(hipStream_t st, const float *logits, int rows, int V, int k, int32_t *idx, float *val,
-                            int32_t *advance, int n_advance, int advance_by, const int32_t *advance_each, int advance_limit,
-                            float *ws) {
-  if (rows < 1 || V < 1 || k < 1 || k > V || k > AMPH_MAX_TOPK) return hipErrorInvalidValue;
-  if (V <= 65536) {
-    #define TK_ROW(N) hipLaunchKernelGGL((k_topk_row<N>), dim3(rows), dim3(1024), 0, st, logits, V, k, idx, val, advance, \
-                                         n_advance, advance_by, advance_each, advance_limit)
-    if (V <= 8192) TK_ROW(8); else if (V <= 16384) TK_ROW(16); else if (V <= 32768) TK_ROW(32); else TK_ROW(64);
-    #undef TK_ROW
-    return hipGetLastError();
-  }
-  const int chunks = (V + TK_CHUNK - 1) / TK_CHUNK;
-  const int n_cand = chunks * k;
-  if (n_cand > TK_MAXC * WAVE) return hipErrorInvalidValue;
-  float *cand_v = ws;
-  int *cand_i = reinterpret_cast<int *>(ws + (size_t)rows * n_cand);
-  hipLaunchKernelGGL(k_topk_pass1, dim3((chunks + 3) / 4, rows), dim3(256), 0, st, logits, V, k, chunks, cand_v, cand_i);
-  hipLaunchKernelGGL(k_topk_pass2, dim3(rows), dim3(64), 0, st, cand_v, cand_i, n_cand, V, k, idx, val, advance, n_advance,
-                     advance_by, advance_each, advance_limit);
+hipError_t launch_row_argmax(hipStream_t st, const float *logits, int rows, int V, int32_t *out) {
+  if (rows < 1 || V < 1 || V > 65536) return hipErrorInvalidValue;
+  #define TK_ROW(N) hipLaunchKernelGGL((k_topk_row<N>), dim3(rows), dim3(1024), 0, st, logits, V, 1, out, (float *)nullptr, \
+                                       (int32_t *)nullptr, 0, 0, (const int32_t *)nullptr, 0)
+  if (V <= 8192) TK_ROW(8); else if (V <= 16384) TK_ROW(16); else if (V <= 32768) TK_ROW(32); else TK_ROW(64);
+  #undef TK_ROW
   return hipGetLastError();
-}
-
-hipError_t launch_row_argmax(hipStream_t st, const float *logits, int rows, int V, int32_t *out, float *ws) {
-  return launch_topk_rows(st, logits, rows, V, 1, out, nullptr, nullptr, 0, 0, nullptr, 0, ws);
 }
 
 // =====================================================================================================
