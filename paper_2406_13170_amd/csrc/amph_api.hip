@@ -42,7 +42,7 @@ hipError_t scratch_for_current_device(int *dev_out, void **ptr_out) {
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 struct WsLayout {   // byte offsets into the caller's workspace
-  size_t x, q, att, y, act, h[2], Hp, Qa, Ka, Va, ctxa, attn_o, logits, topk_ws, sal_part;       // draft
+  size_t x, q, att, y, act, h[2], Hp, Qa, Ka, Va, ctxa, attn_o, logits, topk_ws, sal_part, dslabs;  // draft
   size_t xres, xn, qb, attb, actb, slabs, amax_val, amax_idx, ver_part, tgt_tmp, row_stats, rope_cs, xt;  // target
   size_t slabs_floats, ver_part_floats;
   size_t total;
@@ -136,6 +136,7 @@ WsLayout make_layout(const amph_config &c) {
   w.ctxa = take(BK * d * 4); w.attn_o = take(BK * d * 4); w.logits = take(BK * V * 4);
   w.topk_ws = take(lmtk_ws_floats((int)BK, c.topk) * 4);
   w.sal_part = take(sal_part_floats(c.batch, c.K + 1, c.n_heads, c.head_dim, c.max_kv) * 4);
+  w.dslabs = take(c.dtype == AMPH_BF16 ? DRAFT_MM_SPLITS * std::min(Mr, (size_t)DRAFT_MM_ROWS) * d * 4 : 0);
   const size_t Mp = (M + 31) / 32 * 32;         // activations may be kept in 32-row tiles for the wide GEMM
   w.xres = take(M * d * 4); w.xn = take(Mp * d * esz); w.qb = take(M * d * esz); w.attb = take(Mp * d * esz);
   w.actb = take(Mp * f * esz);
@@ -189,12 +190,12 @@ amph_status draft_impl(amph_ctx *ctx, const amph_draft_w *w, const float *h_new,
   char *ws = (char *)workspace;
   auto F = [&](size_t off) { return (float *)(ws + off); };
   float *x = F(ctx->ws.x), *q = F(ctx->ws.q), *att = F(ctx->ws.att), *y = F(ctx->ws.y), *act = F(ctx->ws.act);
-  float *h[2] = {F(ctx->ws.h[0]), F(ctx->ws.h[1])};
+  float *h[2] = {F(ctx->ws.h[0]), F(ctx->ws.h[1])}, *slabs = F(ctx->ws.dslabs);
   const size_t stage_stride = (size_t)B * 2 * n_h * c.max_kv * d_h;      // elements of T
   for (int s = 0; s < c.n_stages; ++s) {
     const float *u = (s == 0) ? h_new : h[0];
     void *kv_stage = (T *)sal_kv + s * stage_stride;
-    PROF_TRY(ctx, AMPH_K_FC, launch_fc_concat<T>(st, w->fc[s], u, w->embed, tok_new, V, d, M, x, ctx->dev_status));
+    PROF_TRY(ctx, AMPH_K_FC, launch_fc_concat<T>(st, w->fc[s], u, w->embed, tok_new, V, d, M, x, ctx->dev_status, slabs));
     PROF_TRY(ctx, AMPH_K_SAL_QKV, launch_sal_qkv<T>(st, w->sal[s], x, d, n_h, d_h, M, c.rms_eps, c.rope_theta, sal_len, c.max_kv, kv_stage,
                                    q, ctx->dev_status, R, n_valid));
     // Nothing reads the LAST stage's output at any but the last live position of a sequence (the heads read that one;
@@ -210,9 +211,9 @@ amph_status draft_impl(amph_ctx *ctx, const amph_draft_w *w, const float *h_new,
     }
     PROF_TRY(ctx, AMPH_K_SAL_ATTN, launch_sal_attn<T>(st, q, kv_stage, sal_len, B, n_h, d_h, c.max_kv, att, R, n_valid,
                                                       last_rows_only ? 1 : 0, F(ctx->ws.sal_part)));
-    PROF_TRY(ctx, AMPH_K_SAL_WO, launch_linear<T>(st, w->sal[s].wo, nullptr, nullptr, 1, d, d, att, d, Ms, res, y, nullptr, nullptr, d));
+    PROF_TRY(ctx, AMPH_K_SAL_WO, launch_linear<T>(st, w->sal[s].wo, nullptr, nullptr, 1, d, d, att, d, Ms, res, y, nullptr, nullptr, d, slabs));
     PROF_TRY(ctx, AMPH_K_SAL_GATEUP, launch_gate_up<T>(st, w->sal[s], y, d, f, Ms, c.rms_eps, act));
-    PROF_TRY(ctx, AMPH_K_SAL_DOWN, launch_linear<T>(st, w->sal[s].w_down, nullptr, nullptr, 1, d, f, act, f, Ms, y, h[s], nullptr, nullptr, d));
+    PROF_TRY(ctx, AMPH_K_SAL_DOWN, launch_linear<T>(st, w->sal[s].w_down, nullptr, nullptr, 1, d, f, act, f, Ms, y, h[s], nullptr, nullptr, d, slabs));
   }
   // the heads (Eq. 2-6) read the last live position of every batch element; with one adaptation layer every
   // head reads that layer's output.  After a catch-up the last stage's output already is one row per sequence.
@@ -234,7 +235,7 @@ amph_status draft_impl(amph_ctx *ctx, const amph_draft_w *w, const float *h_new,
                             float *out_rows) -> amph_status {
     PROF_TRY(ctx, AMPH_K_AEB_QKV, launch_linear<T>(st, wq, wk, wv, 3, d, d, in, d, BK, nullptr, Qa, Ka, Va, d));
     PROF_TRY(ctx, AMPH_K_AEB_ATTN, launch_aeb_attn(st, Qa, Ka, Va, B, K, n_h, d_h, ctxa));
-    PROF_TRY(ctx, AMPH_K_AEB_WO, launch_linear<T>(st, wo, nullptr, nullptr, 1, d, d, ctxa, d, BK, nullptr, out_rows, nullptr, nullptr, d));
+    PROF_TRY(ctx, AMPH_K_AEB_WO, launch_linear<T>(st, wo, nullptr, nullptr, 1, d, d, ctxa, d, BK, nullptr, out_rows, nullptr, nullptr, d, slabs));
     return AMPH_OK;
   };
   if (amph_status s1 = self_attention(w->aeb_wq, w->aeb_wk, w->aeb_wv, w->aeb_wo, Hp, attn_o)) return s1;

@@ -58,6 +58,7 @@ struct DmArgs {
   // DM_LMTOPK
   float *logits, *cand_v; int *cand_i; int topk;
   uint32_t *dev_status;
+  float *slabs;                   // DM_LINEAR, DM_FC with split axis: [S][M][seg_rows] partial sums, or NULL: the axis stays whole
   int blocks, ring, stage_bytes;  // row blocks of the launch; stages in the LDS ring and their bytes
 };
 
@@ -152,8 +153,9 @@ __global__ __launch_bounds__((DmStage<NB, NT, CB_>::THREADS)) void k_draft_mm(co
   const int b0 = blockIdx.x * NB;                          // first block (of the head)
   const int bl_last = (EPI == DM_HEADMLP ? bps : a.blocks) - 1;
   const int Kb = a.Kd * 2;
-  const int P = (Kb + CB - 1) / CB;                        // stages
-  const int Pu = EPI == DM_FC ? P / 2 : P;                 // stages whose activations are float32 (DM_FC: then the embeddings, bf16)
+  const int P_all = (Kb + CB - 1) / CB;                    // stages of the whole axis; this workgroup's are [Pa, P)
+  const int S = gridDim.z, Pa = (int)((unsigned)(P_all * blockIdx.z) / (unsigned)S), P = (int)((unsigned)(P_all * (blockIdx.z + 1)) / (unsigned)S);
+  const int Pu = EPI == DM_FC ? P_all / 2 : P_all;         // stages whose activations are float32 (DM_FC: then the embeddings, bf16)
   const int R = a.ring, SB = a.stage_bytes;
   auto blk_of = [&](int b) { return head * bps + min(b0 + b, bl_last); };
   const float *xbase = (EPI == DM_HEADMLP && head >= a.K / 2) ? a.x2 : a.x;
@@ -230,10 +232,10 @@ __global__ __launch_bounds__((DmStage<NB, NT, CB_>::THREADS)) void k_draft_mm(co
         }
       }
     };
-    const int pro = P < R - 1 ? P : R - 1;
-    for (int p = 0; p < pro; ++p) issue(p, p);
+    const int pro = P - Pa < R - 1 ? P - Pa : R - 1;
+    for (int p = 0; p < pro; ++p) issue(Pa + p, p);
     int fill = pro;                                        // slot of the next stage to request
-    for (int p = 0; p < P; ++p) {
+    for (int p = Pa; p < P; ++p) {
       const int newest = (p + R - 2 < P - 1) ? p + R - 2 : P - 1;
       const int nu = max(min(newest, Pu - 1) - p, 0), nn = newest - p;     // stages requested after p: float32 ones, all
       dm_wait_at_most(nu * cu + (nn - nu) * ce);           // stage p has landed
@@ -256,7 +258,7 @@ __global__ __launch_bounds__((DmStage<NB, NT, CB_>::THREADS)) void k_draft_mm(co
     }
     const unsigned sgn = (wave & 1) ? 0x80008000u : 0u;
     int slot = 0;
-    for (int p = 0; p < P; ++p) {
+    for (int p = Pa; p < P; ++p) {
       // A bare barrier; the LDS reads of the stage before are waited for first, since its slot is refilled behind it.
       asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
       const unsigned char *sb = dm_lds + slot * SB, *sx = sb + C::WB;
@@ -433,6 +435,10 @@ __global__ __launch_bounds__((DmStage<NB, NT, CB_>::THREADS)) void k_draft_mm(co
             a.o0[((size_t)m * a.K + head) * a.ldx + n0 + j] = src[n0 + j] + silu_f(v[j]) + pek;
           }
       } else {
+        if (S > 1) {                                       // partial sums, added up by k_draft_fold (seg_rows is a multiple of 4)
+          if (n0 < a.seg_rows) *reinterpret_cast<f32x4 *>(a.slabs + ((size_t)blockIdx.z * a.M + m) * a.seg_rows + n0) = v;
+          continue;
+        }
         float *out = (seg == 0 ? a.o0 : seg == 1 ? a.o1 : a.o2) + (size_t)m * a.ldo + n0;
         const float *res = a.res ? a.res + (size_t)m * a.ldo + n0 : nullptr;
         #pragma unroll
@@ -457,6 +463,20 @@ __global__ __launch_bounds__((DmStage<NB, NT, CB_>::THREADS)) void k_draft_mm(co
   }
 }
 
+// out[m][n] = (res ? res[m][n] : 0) + sum_s slabs[s][m][n], s ascending; everything is requested before the first use.
+template <int S>
+__global__ __launch_bounds__(256) void k_draft_fold(const float *slabs, int n, const float *res, float *out) {
+  const int i = (blockIdx.x * 256 + threadIdx.x) * 4;
+  if (i >= n) return;
+  f32x4 v[S], r = (f32x4){0.f, 0.f, 0.f, 0.f};
+  #pragma unroll
+  for (int s = 0; s < S; ++s) v[s] = *reinterpret_cast<const f32x4 *>(slabs + (size_t)s * n + i);
+  if (res) r = *reinterpret_cast<const f32x4 *>(res + i);
+  #pragma unroll
+  for (int s = 1; s < S; ++s) v[0] += v[s];
+  *reinterpret_cast<f32x4 *>(out + i) = v[0] + r;
+}
+
 // ---- host side --------------------------------------------------------------------------------------
 constexpr int DM_LDS = 160 * 1024;
 
@@ -465,12 +485,12 @@ template <int NB, int NT, int CB> static size_t dm_tail_bytes(bool lm) {       /
 }
 
 template <int EPI, int NB, int NT, int CB>
-static hipError_t dm_launch_cb(hipStream_t st, DmArgs a, int grid_x, int grid_y) {
+static hipError_t dm_launch_cb(hipStream_t st, DmArgs a, int grid_x, int grid_y, int S) {
   using C = DmStage<NB, NT, CB>;
   constexpr bool NORM = EPI == DM_SALQKV || EPI == DM_SWIGLU;
   // two workgroups share a compute unit when there are more than one per unit; otherwise one has the LDS to itself
   const size_t tail = dm_tail_bytes<NB, NT, CB>(EPI == DM_LMTOPK);
-  const size_t budget = (long long)grid_x * grid_y > 256 ? 80 * 1024 : 160 * 1024;
+  const size_t budget = (long long)grid_x * grid_y * S > 256 ? 80 * 1024 : 160 * 1024;
   const int nx = (a.M + C::RPX - 1) / C::RPX * C::LPX;
   a.stage_bytes = C::WB + nx * 1024 + (NORM ? DM_GAIN_B : 0);
   const int loads = C::LPW + (nx + 1) / 2 + 1;             // of one loader wave and stage
@@ -480,7 +500,7 @@ static hipError_t dm_launch_cb(hipStream_t st, DmArgs a, int grid_x, int grid_y)
   if (smem > (size_t)DM_LDS) return hipErrorInvalidValue;
   hipError_t e = hipFuncSetAttribute((const void *)k_draft_mm<EPI, NB, NT, CB>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_draft_mm<EPI, NB, NT, CB>), dim3(grid_x, grid_y), dim3(C::THREADS), smem, st, a);
+  hipLaunchKernelGGL((k_draft_mm<EPI, NB, NT, CB>), dim3(grid_x, grid_y, S), dim3(C::THREADS), smem, st, a);
   return hipGetLastError();
 }
 
@@ -489,72 +509,94 @@ static hipError_t dm_launch_cb(hipStream_t st, DmArgs a, int grid_x, int grid_y)
 // 256 / 512 bytes 43.0 / 30.6 us, 12288 x 4096 22.4 / 20.5); with two workgroups on a compute unit one's fixed part
 // hides behind the other's, and the smaller stages leave the ring deep enough (22016 x 4096: 32.0 / 32.8 us).
 template <int EPI, int NB, int NT>
-static hipError_t dm_launch_nt(hipStream_t st, const DmArgs &a, int grid_x, int grid_y) {
-  const bool alone = (long long)grid_x * grid_y <= 256;
+static hipError_t dm_launch_nt(hipStream_t st, const DmArgs &a, int grid_x, int grid_y, int S) {
+  const bool alone = (long long)grid_x * grid_y * S <= 256;
   if constexpr (NT == 1 && NB == 1 && EPI != DM_FC)
-    if (alone) return dm_launch_cb<EPI, NB, NT, 1024>(st, a, grid_x, grid_y);
+    if (alone) return dm_launch_cb<EPI, NB, NT, 1024>(st, a, grid_x, grid_y, S);
   if constexpr (NT == 1 && NB <= 4)
-    if (NB == 1 || alone) return dm_launch_cb<EPI, NB, NT, 512>(st, a, grid_x, grid_y);
-  return dm_launch_cb<EPI, NB, NT, 256>(st, a, grid_x, grid_y);
+    if (NB == 1 || alone) return dm_launch_cb<EPI, NB, NT, 512>(st, a, grid_x, grid_y, S);
+  return dm_launch_cb<EPI, NB, NT, 256>(st, a, grid_x, grid_y, S);
 }
 
 template <int EPI, int NB>
-static hipError_t dm_launch_nb(hipStream_t st, const DmArgs &a, int grid_x, int grid_y) {
+static hipError_t dm_launch_nb(hipStream_t st, const DmArgs &a, int grid_x, int grid_y, int S) {
   switch ((a.M + 15) / 16) {
-    case 1: return dm_launch_nt<EPI, NB, 1>(st, a, grid_x, grid_y);
-    case 2: return dm_launch_nt<EPI, NB, 2>(st, a, grid_x, grid_y);
-    case 3: return dm_launch_nt<EPI, NB, 3>(st, a, grid_x, grid_y);
+    case 1: return dm_launch_nt<EPI, NB, 1>(st, a, grid_x, grid_y, S);
+    case 2: return dm_launch_nt<EPI, NB, 2>(st, a, grid_x, grid_y, S);
+    case 3: return dm_launch_nt<EPI, NB, 3>(st, a, grid_x, grid_y, S);
     default: return hipErrorInvalidValue;
   }
 }
 
-// Row blocks per workgroup, by a model in us per 256 bytes of the rows (measured as above): 0.19 per block (4 KB at a
-// compute unit's share of the HBM rate), the activations' cutting and transfer per tile and row, and the stage's fixed
-// cost where a workgroup has its compute unit to itself.  Up to two workgroups share a unit.  (5 rows, blocks per
-// workgroup 2 / 3 / 4 / 6: 22016 x 4096 47.1 / 32.0 / 36.7 / 38.0 us, 27648 x 5120 55.6 / 58.7 / 46.8 / 57.7,
-// 35840 x 6656 91.9 / 77.9 / 88.7 / 77.5.)
-static int dm_pick_nb(int blocks, int groups, int M, int Kd, bool lm) {
+// Row blocks per workgroup and splits of the reduction axis, by a model in us (measured as above): per 256 bytes of the
+// rows 0.19 per block (4 KB at a compute unit's share of the HBM rate), the activations' cutting and transfer per tile and
+// row, and the stage's fixed cost where a workgroup has its compute unit to itself.  Up to two workgroups share a unit.
+// (5 rows, blocks per workgroup 2 / 3 / 4 / 6: 22016 x 4096 47.1 / 32.0 / 36.7 / 38.0 us, 27648 x 5120 55.6 / 58.7 /
+// 46.8 / 57.7, 35840 x 6656 91.9 / 77.9 / 88.7 / 77.5.)
+// Every workgroup reads all activations of its stages, at M * 4 bytes a column against NB * 32 of weights, and a compute
+// unit takes in 40 GB/s of the two together.  With many rows against few blocks that is the time; S workgroups with S
+// times the blocks and 1 / S of the axis each halve or quarter it, for a fold of S slabs (4 blocks
+// and 4 splits against 1 and 1, without the fold's 4.8 us: 40 rows, 4096 x 4096 34 / 16.5 us, 4096 x 11008 83 / 33, Eq. 1's
+// 4096 x 8192 50 / 25; 5 rows 13.6 / 10.7, 29 / 20, 26 / 17).
+struct DmPick { int nb, S; };
+static DmPick dm_pick(int blocks, int groups, int M, int N, int Kd, bool lm, bool may_split) {
   static const int sizes[] = {1, 2, 3, 4, 6};
   const int nt = (M + 15) / 16;
-  const double act = 0.125 * nt + 0.012 * M;
+  const double act = 0.125 * nt + 0.012 * M, chunks = Kd / 128.0;
   double best = 1e300;
-  int nb = 1;
-  for (int s : sizes) {
-    if (lm && s != 4) continue;
-    if (!lm && Kd > DM_LONG && s > DM_RUNS_NB) continue;
-    const long wgs = (long)((blocks + s - 1) / s) * groups;
-    const double fixed = (nt == 1 && s <= 4) ? 0.14 : 0.28;
-    double cost = wgs <= 256 ? 0.19 * s + act + fixed : (double)((wgs + 511) / 512) * 2 * (0.19 * s + act);
-    // two workgroups on a unit whose halves of the LDS hold only two stages each (35840 x 6656 over 24 rows: 6 blocks,
-    // two stages 140 us; 3 blocks, three stages 120 us)
-    if (wgs > 256 && 3 * (s * 4096 + M * 512 + 1024) > 80 * 1024) cost *= 1.35;
-    if (cost < best) { best = cost; nb = s; }
+  DmPick pick = {1, 1};
+  for (int S = 1; S <= (may_split ? DRAFT_MM_SPLITS : 1); S *= 2) {
+    if (S > 1 && Kd / S < 1024) break;
+    for (int s : sizes) {
+      if (lm && s != 4) continue;
+      if (!lm && Kd / S > DM_LONG && s > DM_RUNS_NB) continue;
+      const long wgs = (long)((blocks + s - 1) / s) * groups * S;
+      const double fixed = (nt == 1 && s <= 4) ? 0.14 : 0.28;
+      double cost = wgs <= 256 ? 0.19 * s + act + fixed : (double)((wgs + 511) / 512) * 2 * (0.19 * s + act);
+      // two workgroups on a unit whose halves of the LDS hold only two stages each (35840 x 6656 over 24 rows: 6 blocks,
+      // two stages 140 us; 3 blocks, three stages 120 us)
+      if (wgs > 256 && 3 * (s * 4096 + M * 512 + 1024) > 80 * 1024) cost *= 1.35;
+      cost *= chunks / S;
+      if (S > 1) cost += 5.0 + 2.0e-6 * S * M * N;           // the fold's launch, the slabs' way out and back
+      if (cost < best) { best = cost; pick = {s, S}; }
+    }
   }
-  return nb;
+  return pick;
 }
 
 template <int EPI>
 static hipError_t dm_launch(hipStream_t st, DmArgs a, int blocks, int groups) {
   if (a.M < 1 || a.M > DRAFT_MM_ROWS || a.Kd < 8 || a.Kd % 8) return hipErrorInvalidValue;
   a.blocks = blocks;
-  const int nb = dm_pick_nb(blocks, groups, a.M, a.Kd, EPI == DM_LMTOPK);
-  const int gx = (blocks + nb - 1) / nb;
-  if constexpr (EPI == DM_LMTOPK) return dm_launch_nb<EPI, 4>(st, a, gx, groups);
-  else switch (nb) {
-    case 1: return dm_launch_nb<EPI, 1>(st, a, gx, groups);
-    case 2: return dm_launch_nb<EPI, 2>(st, a, gx, groups);
-    case 3: return dm_launch_nb<EPI, 3>(st, a, gx, groups);
-    case 4: return dm_launch_nb<EPI, 4>(st, a, gx, groups);
-    default: return dm_launch_nb<EPI, 6>(st, a, gx, groups);
+  const bool may_split = (EPI == DM_LINEAR || EPI == DM_FC) && a.slabs && a.n_seg == 1 && a.seg_rows % 4 == 0 && a.ldo == a.seg_rows;
+  const DmPick p = dm_pick(blocks, groups, a.M, a.seg_rows, a.Kd, EPI == DM_LMTOPK, may_split);
+  const int gx = (blocks + p.nb - 1) / p.nb;
+  hipError_t e;
+  if constexpr (EPI == DM_LMTOPK) e = dm_launch_nb<EPI, 4>(st, a, gx, groups, 1);
+  else switch (p.nb) {
+    case 1: e = dm_launch_nb<EPI, 1>(st, a, gx, groups, p.S); break;
+    case 2: e = dm_launch_nb<EPI, 2>(st, a, gx, groups, p.S); break;
+    case 3: e = dm_launch_nb<EPI, 3>(st, a, gx, groups, p.S); break;
+    case 4: e = dm_launch_nb<EPI, 4>(st, a, gx, groups, p.S); break;
+    default: e = dm_launch_nb<EPI, 6>(st, a, gx, groups, p.S); break;
   }
+  if (e != hipSuccess || p.S == 1) return e;
+  const int n = a.M * a.seg_rows;
+  const dim3 grid((n / 4 + 255) / 256), block(256);
+  switch (p.S) {
+    case 2: hipLaunchKernelGGL((k_draft_fold<2>), grid, block, 0, st, a.slabs, n, a.res, a.o0); break;
+    case 4: hipLaunchKernelGGL((k_draft_fold<4>), grid, block, 0, st, a.slabs, n, a.res, a.o0); break;
+    default: hipLaunchKernelGGL((k_draft_fold<8>), grid, block, 0, st, a.slabs, n, a.res, a.o0); break;
+  }
+  return hipGetLastError();
 }
 
 hipError_t draft_mm_fc(hipStream_t st, const void *W, const float *u, const void *embed, const int32_t *tok, int vocab, int d, int M,
-                       float *out, uint32_t *dev_status) {
+                       float *out, uint32_t *dev_status, float *slabs) {
   if (d % 256) return hipErrorInvalidValue;               // a stage holds columns of one half of the concatenated row only
   DmArgs a{};
   a.w0 = (const bf16_t *)W; a.n_seg = 1; a.seg_rows = d; a.Kd = 2 * d; a.M = M; a.x = u; a.ldx = d; a.o0 = out; a.ldo = d;
-  a.embed = (const bf16_t *)embed; a.tok = tok; a.vocab = vocab; a.dev_status = dev_status;
+  a.embed = (const bf16_t *)embed; a.tok = tok; a.vocab = vocab; a.dev_status = dev_status; a.slabs = slabs;
   return dm_launch<DM_FC>(st, a, (d + 15) / 16, 1);
 }
 
@@ -571,10 +613,10 @@ hipError_t draft_mm_sal_qkv(hipStream_t st, const amph_layer_w &lw, const float 
 }
 
 hipError_t draft_mm_linear(hipStream_t st, const void *w0, const void *w1, const void *w2, int n_seg, int seg_rows, int Kd,
-                           const float *x, int ldx, int M, const float *res, float *o0, float *o1, float *o2, int ldo) {
+                           const float *x, int ldx, int M, const float *res, float *o0, float *o1, float *o2, int ldo, float *slabs) {
   DmArgs a{};
   a.w0 = (const bf16_t *)w0; a.w1 = (const bf16_t *)w1; a.w2 = (const bf16_t *)w2; a.n_seg = n_seg; a.seg_rows = seg_rows; a.Kd = Kd;
-  a.M = M; a.x = x; a.ldx = ldx; a.res = res; a.o0 = o0; a.o1 = o1; a.o2 = o2; a.ldo = ldo;
+  a.M = M; a.x = x; a.ldx = ldx; a.res = res; a.o0 = o0; a.o1 = o1; a.o2 = o2; a.ldo = ldo; a.slabs = slabs;
   return dm_launch<DM_LINEAR>(st, a, n_seg * ((seg_rows + 15) / 16), 1);
 }
 

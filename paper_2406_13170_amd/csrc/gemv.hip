@@ -735,10 +735,10 @@ static inline int gv_rows_per_launch(int M, size_t bytes_per_row, size_t extra) 
 
 template <typename T>
 hipError_t launch_fc_concat(hipStream_t st, const void *W, const float *u, const void *embed, const int32_t *tok,
-                            int vocab, int d, int M, float *out, uint32_t *dev_status) {
+                            int vocab, int d, int M, float *out, uint32_t *dev_status, float *slabs) {
   if (M < 1 || d % 8) return hipErrorInvalidValue;
   if (use_mm<T>(M, (size_t)d * 2 * d) && d % 256 == 0)
-    MM_CHUNKS(draft_mm_fc(st, W, u + (size_t)m0 * d, embed, tok + m0, vocab, d, m, out + (size_t)m0 * d, dev_status));
+    MM_CHUNKS(draft_mm_fc(st, W, u + (size_t)m0 * d, embed, tok + m0, vocab, d, m, out + (size_t)m0 * d, dev_status, slabs));
   int mc = gv_rows_per_launch(M, gv_xs_bytes<T>(1, 2 * d), 0);
   // rows that fit only without their other half: two launches over d columns each
   const int mch = gv_rows_per_launch(M, gv_xs_bytes<T>(1, d), 0);
@@ -784,11 +784,13 @@ hipError_t launch_sal_qkv(hipStream_t st, const amph_layer_w &lw, const float *x
 
 template <typename T>
 hipError_t launch_linear(hipStream_t st, const void *w0, const void *w1, const void *w2, int n_seg, int seg_rows, int Kd,
-                         const float *x, int ldx, int M, const float *res, float *o0, float *o1, float *o2, int ldo) {
+                         const float *x, int ldx, int M, const float *res, float *o0, float *o1, float *o2, int ldo,
+                         float *slabs) {
   if (M < 1 || Kd % 8) return hipErrorInvalidValue;
   if (use_mm<T>(M, (size_t)n_seg * seg_rows * Kd))
     MM_CHUNKS(draft_mm_linear(st, w0, w1, w2, n_seg, seg_rows, Kd, x + (size_t)m0 * ldx, ldx, m, res ? res + (size_t)m0 * ldo : nullptr,
-                              o0 + (size_t)m0 * ldo, o1 ? o1 + (size_t)m0 * ldo : nullptr, o2 ? o2 + (size_t)m0 * ldo : nullptr, ldo));
+                              o0 + (size_t)m0 * ldo, o1 ? o1 + (size_t)m0 * ldo : nullptr, o2 ? o2 + (size_t)m0 * ldo : nullptr, ldo,
+                              slabs));
   int mc = gv_rows_per_launch(M, gv_xs_bytes<T>(1, Kd), 0);
   // Rows too wide for all of them (up to 8) to sit in LDS whole: cut the reduction axis into ks slices instead of
   // the rows into more launches, each of which would read the matrix again.
@@ -915,12 +917,12 @@ size_t lmtk_ws_floats(int rows, int k) { return 2 * (size_t)rows * LMTK_MAX_WG *
 
 #define INSTANTIATE(T)                                                                                                   \
   template hipError_t launch_fc_concat<T>(hipStream_t, const void *, const float *, const void *, const int32_t *, int, \
-                                          int, int, float *, uint32_t *);                                               \
+                                          int, int, float *, uint32_t *, float *);                                             \
   template hipError_t launch_sal_qkv<T>(hipStream_t, const amph_layer_w &, const float *, int, int, int, int, float,    \
                                         float, const int32_t *, int, void *, float *, uint32_t *, int,                  \
                                         const int32_t *);                                                               \
   template hipError_t launch_linear<T>(hipStream_t, const void *, const void *, const void *, int, int, int,            \
-                                       const float *, int, int, const float *, float *, float *, float *, int);         \
+                                       const float *, int, int, const float *, float *, float *, float *, int, float *); \
   template hipError_t launch_gate_up<T>(hipStream_t, const amph_layer_w &, const float *, int, int, int, float, float *); \
   template hipError_t launch_head_mlp<T>(hipStream_t, const void *, const void *, const float *, const float *, int,    \
                                          int, int, float *);                                                            \

@@ -10,14 +10,15 @@ constexpr size_t GV_MAX_SMEM = 128 * 1024;    // dynamic LDS a GEMV workgroup ma
 // ---- gemv.hip (draft path, M <= 8 rows) ----
 template <typename T>
 hipError_t launch_fc_concat(hipStream_t st, const void *W, const float *u, const void *embed, const int32_t *tok,
-                            int vocab, int d, int M, float *out, uint32_t *dev_status);
+                            int vocab, int d, int M, float *out, uint32_t *dev_status, float *slabs);   // slabs: see draft_mm_fc
 template <typename T>
 hipError_t launch_sal_qkv(hipStream_t st, const amph_layer_w &lw, const float *x, int d, int n_heads, int d_h, int M,
                           float eps, float theta, const int32_t *sal_len, int max_kv, void *kv_stage, float *qbuf,
                           uint32_t *dev_status, int R, const int32_t *n_valid);   // rows = (batch element, new position < R)
 template <typename T>
 hipError_t launch_linear(hipStream_t st, const void *w0, const void *w1, const void *w2, int n_seg, int seg_rows, int Kd,
-                         const float *x, int ldx, int M, const float *res, float *o0, float *o1, float *o2, int ldo);
+                         const float *x, int ldx, int M, const float *res, float *o0, float *o1, float *o2, int ldo,
+                         float *slabs = nullptr);
 template <typename T>
 hipError_t launch_gate_up(hipStream_t st, const amph_layer_w &lw, const float *x, int d, int f, int M, float eps,
                           float *act);
@@ -35,14 +36,16 @@ hipError_t launch_lmhead_cands(hipStream_t st, const void *W, int V, int Kd, con
                                float *ws, int *n_cand);
 
 // ---- draft_mm.hip (draft path on the matrix cores: bf16 weights, up to DRAFT_MM_ROWS rows a launch) ----
-constexpr int DRAFT_MM_ROWS = 48;
+constexpr int DRAFT_MM_ROWS = 48, DRAFT_MM_SPLITS = 4;
+// slabs: DRAFT_MM_SPLITS * min(rows, DRAFT_MM_ROWS) * output width floats for the partial sums of a split reduction axis,
+// or NULL: it stays whole
 hipError_t draft_mm_fc(hipStream_t st, const void *W, const float *u, const void *embed, const int32_t *tok, int vocab, int d, int M,
-                       float *out, uint32_t *dev_status);
+                       float *out, uint32_t *dev_status, float *slabs);
 hipError_t draft_mm_sal_qkv(hipStream_t st, const amph_layer_w &lw, const float *x, int d, int n_heads, int d_h, int M, float eps,
                             float theta, const int32_t *sal_len, int max_kv, void *kv_stage, float *qbuf, uint32_t *dev_status,
                             int row0, int R, const int32_t *n_valid);
 hipError_t draft_mm_linear(hipStream_t st, const void *w0, const void *w1, const void *w2, int n_seg, int seg_rows, int Kd,
-                           const float *x, int ldx, int M, const float *res, float *o0, float *o1, float *o2, int ldo);
+                           const float *x, int ldx, int M, const float *res, float *o0, float *o1, float *o2, int ldo, float *slabs);
 hipError_t draft_mm_gate_up(hipStream_t st, const amph_layer_w &lw, const float *x, int d, int f, int M, float eps, float *act);
 hipError_t draft_mm_head_mlp(hipStream_t st, const void *w_mlp, const void *pe, const float *h1, const float *h2, int d, int K, int M,
                              float *Hp);
