@@ -1,6 +1,6 @@
 // GEMMs of the target's forward pass over the tree tokens (Sec. 2 "Tree Attention"): M = B*T activation rows
 // against [N, Kd] weights that stream from HBM once, on the matrix cores.  Two kernels: the skinny one
-// (described first; up to two blocks of 64 rows) and the wide one (further down; three blocks or more).
+// (described first; up to 64 rows, or row-major weights) and the wide one (further down; more than 64 rows).
 //
 // The unit of work is a ROW BLOCK: 16 weight rows that one wave keeps as matrix-core A fragments and
 // whose outputs need nothing from any other block:
@@ -404,19 +404,24 @@ __global__ __launch_bounds__(64 * (GM_MAX_NB + GM_NLW)) void k_gemm_skinny(const
 }
 
 // =====================================================================================================
-// Wide GEMM: 128 or more activation rows (batches of trees).  The skinny kernel above re-reads the weights
-// from L2 once per block of 64 rows, every math wave re-reads the whole activation chunk from LDS, and its
+// Wide GEMM: more than 64 activation rows (batches of trees, wide trees).  The skinny kernel above re-reads the
+// weights from L2 once per block of 64 rows, every math wave re-reads the whole activation chunk from LDS, and its
 // 16 x 16 matrix-core instruction runs at half the rate of the 32 x 32 one: with several blocks of rows L2, LDS
-// and the matrix cores, not HBM, set the pace.  Here a workgroup owns a group of up to 16 tiles of 32 activation
-// rows (all rows, up to 512; more rows form several groups) against NB weight row blocks, and the roles of the
-// operands are swapped:
+// and the matrix cores, not HBM, set the pace.  Here a workgroup owns a group of up to 12 (or 13 to 16) tiles of 32
+// activation rows against NB weight row blocks, and the roles of the operands are swapped:
 //   * the weights are the shared operand: two loader waves stream the workgroup's NB blocks from HBM straight
-//     into a ring of LDS stages (global-to-LDS loads, 8 steps of 64 bytes of k per stage), so they cross L2 once;
-//   * each math wave owns 2 (or 3) of the group's tiles against all NB blocks, taken in pairs (32 weight rows): per
-//     step and half-step it reads one weight fragment per pair from LDS and one activation fragment per tile from
-//     global memory (L2 hits, requested 2 or 4 steps ahead into registers) and issues one matrix-core instruction
-//     of 32 x 32 per pair and tile; one barrier per 8 steps.  Up to 8 tiles there is one math wave per SIMD (2
-//     adjacent tiles each); from 9 tiles on two per SIMD, wave w owning tiles w and w + 8.
+//     into a ring of LDS stages (global-to-LDS loads, 8 or 4 steps of 64 bytes of k per stage), so they cross L2 once;
+//   * each math wave owns one of the group's tiles (groups of 13 to 16: tiles w and w + 8) against all NB blocks, taken
+//     in pairs (32 weight rows): per step and half-step it reads one weight fragment per pair from LDS and one
+//     activation fragment per tile from global memory (L2 hits, requested 2 or 4 steps ahead into registers) and issues
+//     one matrix-core instruction of 32 x 32 per pair and tile; one barrier per stage.
+// What bounds it is what a compute unit takes in, 40 to 50 GB/s of weights and activations together: a workgroup reads its
+// group's activations for its NB blocks only, (32 gt + 16 NB) bytes against 512 gt NB products.  One tile per wave
+// halves the accumulators, so that up to ten blocks fit in the registers of eight to twelve waves, where two tiles
+// per wave ended at six: 384 rows, 35840 x 6656 (10 blocks) 229 -> 184 us = 1.0 PFLOP/s, 32000 x 6656 (8) 192 -> 167,
+// 6656 x 17920 (8, four splits) 123 -> 107; 512 rows in two groups, 32000 x 4096 (8) 158 -> 141, 12288 x 4096 (6)
+// 73 -> 64, 4096 x 11008 (8) 60 -> 52; 128 rows, against the skinny kernel, 27648 x 5120 84 -> 61, 32000 x 5120 95 -> 67,
+// 35840 x 6656 135 -> 104, 32000 x 6656 119 -> 82, 6656 x 17920 72 -> 55, but 12288 x 4096 36 -> 39.
 // A 32 x 32 instruction takes, per lane (half, r), 16 bytes of row r: the bytes [half * 16, half * 16 + 16) of
 // 32 bytes of k.  The weight fragments in LDS are the 16-row x 64-byte ones of the tiled layout, piece (g, r16)
 // at (g * 16 + r16) * 16: lane (half, r) of half-step h reads piece (2h + half, r % 16) of block r / 16 of the
@@ -425,17 +430,22 @@ __global__ __launch_bounds__(64 * (GM_MAX_NB + GM_NLW)) void k_gemm_skinny(const
 // xt[(q * m32_tiles + tile) * 1024 + lane * 16], q = index of 32 bytes of k, lane = half * 32 + row % 32, rows
 // past M as zeros (a few microseconds).
 // =====================================================================================================
-constexpr int GW_STEPS = 8;        // steps (64 bytes of k) per weight stage
+constexpr int gw_steps(int np) { return np > 3 ? 4 : 8; }   // steps (64 bytes of k) per weight stage
 constexpr int GW_R = 3;            // weight stages in the LDS ring
 constexpr int GW_NL = 2;           // loader waves
-constexpr int GW_MAX_NP = 3;       // pairs of weight row blocks per workgroup
-constexpr int GW_MAX_NW = 8;       // math waves per workgroup with 2 tiles of 32 activation rows each (two waves per SIMD)
-constexpr int GW_MAX_NW3 = 4;      // ... with 3 tiles each: one wave per SIMD (three tiles of accumulators need 222 registers)
-constexpr int GW_MAX_TW = 3;
+constexpr int GW_MAX_NP = 5;       // pairs of weight row blocks per workgroup with a tile per wave
+constexpr int GW_MAX_NP_QKV = 4;   // ... with the rotation epilogue, which needs more registers
+constexpr int GW_MAX_NP2 = 3;      // ... with two tiles per wave
+constexpr int GW_MAX_NW1 = 12;     // math waves per workgroup with a tile of 32 activation rows each (three waves per SIMD)
+constexpr int GW_MAX_NW = 8;       // ... with two tiles each (two waves per SIMD)
 constexpr int GW_XD = 4;           // steps of activations requested ahead
-constexpr int GW_MIN_MBLOCKS = 3;  // blocks of 64 activation rows from which the wide kernel is used
+constexpr int GW_MIN_MBLOCKS = 2;  // blocks of 64 activation rows from which the wide kernel is used
 constexpr int GW_AUX_NT = 2;       // cache-policy bits of the global-to-LDS load: non-temporal (the weights are read once)
-static_assert(GW_STEPS % GW_XD == 0, "the activation ring is indexed statically inside a stage");
+
+constexpr size_t gw_ct_bytes(int np) { return (size_t)32 * (32 * np + 4) * 4; }   // a wave's output tile in the epilogue
+constexpr int gw_epi_waves(int np, int nwmax) {            // waves whose output tiles fit in LDS together
+  return (int)((size_t)nwmax * gw_ct_bytes(np) <= 160 * 1024 ? nwmax : 160 * 1024 / gw_ct_bytes(np));
+}
 
 template <int N> struct GwTag { static constexpr int value = N; };
 template <int N> __device__ __forceinline__ void gw_wait_vm() {
@@ -457,10 +467,10 @@ __global__ __launch_bounds__(256) void k_tile_rows(const unsigned char *x, int M
   }
 }
 
-template <typename T, int EPI, int NP, int TW, int NWMAX>      // NWMAX = 4: one math wave per SIMD (256 registers each); 8: two (168)
+template <typename T, int EPI, int NP, int TW, int NWMAX>      // NWMAX = 8: up to two math waves per SIMD (168 registers each); 12: three (128)
 __global__ __launch_bounds__(64 * (NWMAX + GW_NL)) void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt) {
   extern __shared__ __align__(16) unsigned char gw_lds[];
-  constexpr int NB = 2 * NP, STAGE = NB * GW_STEPS * 1024, PERL = NB * GW_STEPS / GW_NL;
+  constexpr int GW_STEPS = gw_steps(NP), NB = 2 * NP, STAGE = NB * GW_STEPS * 1024, PERL = NB * GW_STEPS / GW_NL;
   static_assert(GW_R == 3 && PERL * (GW_R - 2) <= 63, "loader wave's outstanding loads");
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int NT = blockDim.x, nw = (NT >> 6) - GW_NL;       // math waves
@@ -468,13 +478,12 @@ __global__ __launch_bounds__(64 * (NWMAX + GW_NL)) void k_gemm_wide(const GemmAr
   const int id = blockIdx.x, unit = (id / 8 / mgroups) * 8 + (id & 7), mgroup = (id / 8) % mgroups;
   if (unit >= tiles * S) return;                          // padding of the last group of 8 units (whole workgroup)
   const int tile = unit / S, split = unit % S;
-  constexpr int XD = (TW == 3 || NWMAX == 8) ? 2 : GW_XD; // steps of activations requested ahead (registers)
+  constexpr int XD = TW == 2 || (NWMAX == 12 && NP > 3) ? 2 : GW_XD; // steps of activations requested ahead (registers)
   static_assert(GW_STEPS % XD == 0, "the activation ring is indexed statically inside a stage");
-  // Tiles of this group: gt of them from g0 on.  One wave per SIMD (NWMAX = 4): wave w owns the TW adjacent tiles
-  // from w * TW on.  Two waves per SIMD (NWMAX = 8): wave w owns tiles w and w + nw, so that with fewer than 2 * nw
+  // Tiles of this group: gt of them from g0 on, wave w owning tile w, and w + nw where it has two: with fewer than 2 * nw
   // tiles the waves left with one tile are the upper half, which share their SIMDs with the lower half.
   const int g0 = mgroup * gt;
-  auto tile_of = [&](int t) { return g0 + (NWMAX == 8 ? wave + t * nw : wave * TW + t); };
+  auto tile_of = [&](int t) { return g0 + wave + t * nw; };
   auto live = [&](int t) { const int x = tile_of(t); return x < g0 + gt && x < m32_tiles; };
   const int total_steps = a.Kd * (int)sizeof(T) / 64;
   const int ssh = __ffs(S) - 1;                           // S is 1, 2, 4 or 8
@@ -502,7 +511,7 @@ __global__ __launch_bounds__(64 * (NWMAX + GW_NL)) void k_gemm_wide(const GemmAr
     // bottleneck).  A ragged last stage takes the general path: steps past the slice re-read its last step and are
     // never used.
     constexpr int HS = GW_STEPS / GW_NL;
-    static_assert(GW_STEPS % GW_NL == 0 && HS == 4, "four immediate offsets per block, written out below");
+    static_assert(GW_STEPS % GW_NL == 0 && (HS == 4 || HS == 2), "the immediate offsets per block, written out below");
     const int l = wave - nw, g = lane >> 4, r16 = lane & 15;
     const unsigned char *wbase = (const unsigned char *)a.wt + r16 * 64 + g * 16;
     const unsigned char *bsrc[NB];
@@ -519,8 +528,10 @@ __global__ __launch_bounds__(64 * (NWMAX + GW_NL)) void k_gemm_wide(const GemmAr
           auto *ld = (__attribute__((address_space(3))) void *)dst;
           __builtin_amdgcn_global_load_lds(gs, ld, 16, 0, GW_AUX_NT);       // (the offset must be a literal)
           __builtin_amdgcn_global_load_lds(gs, ld, 16, 1024, GW_AUX_NT);
-          __builtin_amdgcn_global_load_lds(gs, ld, 16, 2048, GW_AUX_NT);
-          __builtin_amdgcn_global_load_lds(gs, ld, 16, 3072, GW_AUX_NT);
+          if constexpr (HS == 4) {
+            __builtin_amdgcn_global_load_lds(gs, ld, 16, 2048, GW_AUX_NT);
+            __builtin_amdgcn_global_load_lds(gs, ld, 16, 3072, GW_AUX_NT);
+          }
         }
       } else {
         #pragma unroll
@@ -543,8 +554,7 @@ __global__ __launch_bounds__(64 * (NWMAX + GW_NL)) void k_gemm_wide(const GemmAr
     }
   } else {
     // ------------------------------------------------------------------------------ math wave
-    // activation tiles TW * wave .. + TW - 1 of the group (32 rows each); the 2 * TW fragments of a step (two halves
-    // of the step's 64 bytes for every tile) are requested XD steps ahead
+    // the 2 * TW fragments of a step (two halves of its 64 bytes for every tile of 32 rows) are requested XD steps ahead
     const int half = lane >> 5, r32 = lane & 31;
     const unsigned char *xb = (const unsigned char *)a.xt + lane * 16;
     uint4 xq[XD][2][TW];
@@ -562,7 +572,7 @@ __global__ __launch_bounds__(64 * (NWMAX + GW_NL)) void k_gemm_wide(const GemmAr
     const int woff = (r32 >> 4) * (GW_STEPS * 1024) + (half * 16 + (r32 & 15)) * 16;
     #pragma unroll
     for (int i = 0; i < XD; ++i) load_x(i, xq[i]);
-    // NTL = tiles this wave multiplies: TW, or 1 for a wave of the two-per-SIMD layout whose second tile does not exist
+    // NTL = tiles this wave multiplies: TW, or 1 for a wave whose second tile does not exist
     auto run = [&](auto tag) {
       constexpr int NTL = decltype(tag)::value;
       for (int p = 0; p < P; ++p) {
@@ -589,36 +599,40 @@ __global__ __launch_bounds__(64 * (NWMAX + GW_NL)) void k_gemm_wide(const GemmAr
         }
       }
     };
-    if (NWMAX == 8 && !live(1)) run(GwTag<1>{}); else run(GwTag<TW>{});
+    if (TW > 1 && !live(1)) run(GwTag<1>{}); else run(GwTag<TW>{});
   }
 
   // ---- epilogues: every math wave handles its own activation rows through its own Ct region in LDS (the ring is
   // free by now), one tile of 32 rows at a time, the 64 lanes playing the workgroup of the shared epilogue code.
   // Lane (half, r32) holds activation row t * 32 + r32 and weight rows (i / 4) * 8 + half * 4 + (i % 4) of each pair.
   const int CT_PITCH = 16 * NB + 4;
-  __syncthreads();                                         // every wave has left the ring
-  if (wave < nw && live(0)) {                              // whole waves
-    float *Ct = reinterpret_cast<float *>(gw_lds) + (size_t)wave * 32 * CT_PITCH;
-    const int half = lane >> 5, r32 = lane & 31;
-    #pragma unroll
-    for (int t = 0; t < TW; ++t) {
-      if (!live(t)) break;                                 // (wave-uniform)
-      if (t > 0) {                                         // the lanes are done reading the tile before
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  // As many waves at a time as there is room for.
+  constexpr int EW = gw_epi_waves(NP, NWMAX);
+  for (int w0 = 0; w0 < nw; w0 += EW) {
+    __syncthreads();                                         // every wave has left the ring (the waves before, their regions)
+    if (wave >= w0 && wave < min(w0 + EW, nw) && live(0)) {  // whole waves
+      float *Ct = reinterpret_cast<float *>(gw_lds) + (size_t)(wave - w0) * 32 * CT_PITCH;
+      const int half = lane >> 5, r32 = lane & 31;
+      #pragma unroll
+      for (int t = 0; t < TW; ++t) {
+        if (!live(t)) break;                                 // (wave-uniform)
+        if (t > 0) {                                         // the lanes are done reading the tile before
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+        #pragma unroll
+        for (int pr = 0; pr < NP; ++pr)
+          #pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4) {
+            const f32x4 v = {acc[pr][t][4 * q4], acc[pr][t][4 * q4 + 1], acc[pr][t][4 * q4 + 2], acc[pr][t][4 * q4 + 3]};
+            *reinterpret_cast<f32x4 *>(Ct + r32 * CT_PITCH + pr * 32 + q4 * 8 + half * 4) = v;
+          }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the wave's LDS writes before its lanes read each other's
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        gemm_epilogue<T, EPI>(a, Ct, CT_PITCH, tile, NB, tile_of(t) * 32, split, nblk, lane, WAVE, 32);
       }
-      #pragma unroll
-      for (int pr = 0; pr < NP; ++pr)
-        #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const f32x4 v = {acc[pr][t][4 * q4], acc[pr][t][4 * q4 + 1], acc[pr][t][4 * q4 + 2], acc[pr][t][4 * q4 + 3]};
-          *reinterpret_cast<f32x4 *>(Ct + r32 * CT_PITCH + pr * 32 + q4 * 8 + half * 4) = v;
-        }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the wave's LDS writes before its lanes read each other's
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      gemm_epilogue<T, EPI>(a, Ct, CT_PITCH, tile, NB, tile_of(t) * 32, split, nblk, lane, WAVE, 32);
     }
   }
 }
@@ -721,39 +735,33 @@ GemmPlan gemm_plan(int epi, int seg_rows, int Kd, int elem_bytes, int M, int spl
   const double slab_units = fused ? 0.0 : (double)M * seg_rows * 1.0e-4 + 2.0;   // per extra split
   double best_cost = 1e300;
   best.blocks = blocks;
-  // measured at 7B shapes, ms per step skinny / wide: 2 blocks of 64 rows 5.60 / 6.49, 3 blocks 7.37 / 7.02, 4 blocks
-  // 8.23 / 7.86, 6 blocks 12.44 / 11.07, 8 blocks 14.46 / 12.40; 33B shapes, 6 blocks: 59.1 / 47.4
   best.wide = gemm_is_wide(M, tiled);
   if (best.wide) {
-    // A workgroup owns a group of tiles of 32 activation rows against nb weight row blocks.  Inside a group the
-    // tiles are dealt to math waves so that the four SIMDs carry the same matrix-core load: 2 tiles per wave, or 3
-    // per wave for 9 to 12 tiles (one wave per SIMD; six waves of two tiles kept two SIMDs twice as busy as the
-    // others), up to 8 waves of 2.  Two ways to form the groups are priced: as few groups as possible (up to 16
-    // tiles: the weights cross LDS once) or groups of at most 8 tiles (twice the workgroups: pays when the weight
-    // matrix has too few row blocks to fill the chip).  A workgroup's time goes with its steps, its nb + 2
-    // fragments per step and the tiles its busiest SIMD carries; ties go to the fewer groups.
+    // A workgroup owns a group of tiles of 32 activation rows against nb weight row blocks.  Candidates: groups of up to
+    // 12 tiles with a math wave for each, as few as possible or one more (twice the workgroups pay when the weight matrix
+    // has too few row blocks to fill the chip); groups of 13 to 16 tiles, two tiles a wave, which read the weights once.
+    // The price is in us, fitted to 500 measurements at 7B, 13B and 33B shapes over 96 to 768 rows (11 % deviation; the
+    // choice was within 3 % of the best one in 90 of 100): per step of 64 bytes of k a workgroup takes in 2 KB for every
+    // tile and 1 KB for every block, and its matrix cores and LDS reads go with blocks times tiles and with blocks.  Three
+    // waves on a SIMD come with the shorter activation ring.  A split writes, and the fold reads, one more slab.  The
+    // grid needs a round for every 256 workgroups (the LDS ring leaves room for one in a compute unit).
     const int mt = (M + 31) / 32;
-    // candidates (the later one wins ties): groups of at most 8 tiles, one wave of 2 tiles per SIMD; as few groups as
-    // possible with 3 tiles per wave (9 to 12 tiles a group); the same with two waves per SIMD (9 to 16 tiles)
     for (int cand = 0; cand < 3; ++cand) {
-      const int max_tiles = cand == 0 ? 8 : cand == 1 ? 12 : 16;
-      const int mg = (mt + max_tiles - 1) / max_tiles;
+      const int mg = cand == 2 ? (mt + 15) / 16 : (mt + GW_MAX_NW1 - 1) / GW_MAX_NW1 + cand;
       const int gt = (mt + mg - 1) / mg;                                // tiles per group
-      if (cand > 0 && gt <= 8) continue;                                // nothing new
-      const int tw = cand == 1 ? 3 : 2;
-      const int nw = cand == 2 ? GW_MAX_NW : (gt + tw - 1) / tw;
-      // tiles on the busiest SIMD; two waves on a SIMD cover part of each other's waits (measured: 23.5 against
-      // 25.7 us per tile and SIMD for gate/up at 7B shapes)
-      const double simd_tiles = cand == 2 ? 0.92 * ((gt + 3) / 4) : (double)((nw + 3) / 4) * tw;
+      if (cand == 2 ? gt <= GW_MAX_NW1 : mg > mt) continue;
+      const int tw = cand == 2 ? 2 : 1, nw = cand == 2 ? GW_MAX_NW : gt;
+      const double waves = cand == 2 ? 1.08 : gt > 8 ? 1.2 : 1.0;
+      const int max_np = tw == 2 ? GW_MAX_NP2 : epi == EPI_QKV_ROPE ? GW_MAX_NP_QKV : GW_MAX_NP;
       for (int s = 1; s <= 8; s *= 2) {
         if (split_req > 0 && s != split_req) continue;
-        if (split_req == 0 && (fused ? s > 1 : (s > 1 && total_steps / s < 2 * GW_STEPS))) continue;
-        for (int nb = 2; nb <= 2 * GW_MAX_NP; nb += 2) {      // blocks are taken in pairs
+        if (split_req == 0 && (fused ? s > 1 : (s > 1 && total_steps / s < 16))) continue;
+        for (int nb = 2; nb <= 2 * max_np; nb += 2) {         // blocks are taken in pairs
           if (nb > std::max(blocks, 2)) break;
           const int tiles = (blocks + nb - 1) / nb;
-          const long wgs = (long)tiles * s * mg;
-          const long rounds = (wgs + 255) / 256;
-          const double cost = (double)rounds * ((total_steps + s - 1) / s) * (nb + 2) * (simd_tiles / 2) + slab_units * (s - 1);
+          const long rounds = ((long)tiles * s * mg + 255) / 256;
+          const double step = 0.006 * (2 * gt + nb) + 0.0031 * nb * gt + 0.0235 * nb;
+          const double cost = (double)rounds * (((total_steps + s - 1) / s) * step * waves + 4.0) + (fused ? 0.0 : 1.1e-6 * M * seg_rows * s);
           if (cost <= best_cost) {
             best_cost = cost; best.nb = nb; best.split = s; best.tiles = tiles;
             best.mgroups = mg; best.nw = nw; best.tw = tw; best.gt = gt;
@@ -789,11 +797,12 @@ size_t gemm_xt_bytes(int M, int Kd, int elem_bytes) { return (size_t)((M + 31) /
 template <typename T, int EPI, int NP, int TW, int NWMAX>
 static hipError_t launch_wide_np(hipStream_t st, const GemmArgs &a, const GemmPlan &pl, int m32_tiles, dim3 grid, dim3 block,
                                  hipEvent_t ev_start, hipEvent_t ev_stop) {
-  // the weight ring, or (afterwards, in the same memory) one float32 output tile of 64 rows per math wave
-  constexpr size_t ring = (size_t)GW_R * 2 * NP * GW_STEPS * 1024, ct_wave = (size_t)32 * (32 * NP + 4) * 4;
-  constexpr size_t smem_max = ring > NWMAX * ct_wave ? ring : NWMAX * ct_wave;
+  // the weight ring, or (afterwards, in the same memory) the float32 output tiles (32 rows) of as many math waves as fit
+  constexpr size_t ring = (size_t)GW_R * 2 * NP * gw_steps(NP) * 1024, ct_wave = gw_ct_bytes(NP);
+  constexpr int epi_waves = gw_epi_waves(NP, NWMAX);
+  constexpr size_t smem_max = ring > epi_waves * ct_wave ? ring : epi_waves * ct_wave;
   static_assert(smem_max <= 160 * 1024, "LDS of one workgroup");
-  const size_t smem = std::max(ring, (size_t)pl.nw * ct_wave);
+  const size_t smem = std::max(ring, (size_t)std::min(pl.nw, epi_waves) * ct_wave);
   static bool attr_set = false;                           // once per instantiation and process
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute((const void *)k_gemm_wide<T, EPI, NP, TW, NWMAX>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_max);
@@ -809,7 +818,7 @@ static hipError_t launch_wide_np(hipStream_t st, const GemmArgs &a, const GemmPl
 
 template <typename T, int EPI>
 static hipError_t launch_wide(hipStream_t st, const GemmArgs &a, const GemmPlan &pl, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  if (!a.wt || !a.xt || pl.nw < 1 || pl.nw > (pl.tw == 3 ? GW_MAX_NW3 : GW_MAX_NW) || pl.tw < 2 || pl.tw > GW_MAX_TW || pl.nb < 2 ||
+  if (!a.wt || !a.xt || pl.nw < 1 || pl.nw > (pl.tw == 2 ? GW_MAX_NW : GW_MAX_NW1) || pl.tw < 1 || pl.tw > 2 || pl.nb < 2 ||
       pl.nb > 2 * GW_MAX_NP || pl.nb % 2)
     return hipErrorInvalidValue;
   if ((long long)pl.mgroups * pl.gt * 32 < a.M || pl.gt > pl.nw * pl.tw) return hipErrorInvalidValue;   // groups cover every row, waves every tile
@@ -823,13 +832,24 @@ static hipError_t launch_wide(hipStream_t st, const GemmArgs &a, const GemmPlan 
   if (wgs > 0x7fffffffLL) return hipErrorInvalidValue;
   const dim3 grid((unsigned)wgs), block(64 * (pl.nw + GW_NL));
   #define GW_LAUNCH(NP_)                                                                                            \
-    return pl.tw == 3 ? launch_wide_np<T, EPI, NP_, 3, 4>(st, aw, pl, m32_tiles, grid, block, ev_start, ev_stop)   \
-         : pl.nw > 4  ? launch_wide_np<T, EPI, NP_, 2, 8>(st, aw, pl, m32_tiles, grid, block, ev_start, ev_stop)   \
-                      : launch_wide_np<T, EPI, NP_, 2, 4>(st, aw, pl, m32_tiles, grid, block, ev_start, ev_stop)
+    return pl.nw > 8 ? launch_wide_np<T, EPI, NP_, 1, GW_MAX_NW1>(st, aw, pl, m32_tiles, grid, block, ev_start, ev_stop)   \
+                     : launch_wide_np<T, EPI, NP_, 1, 8>(st, aw, pl, m32_tiles, grid, block, ev_start, ev_stop)
+  if (pl.tw == 2) {
+    switch (pl.nb / 2) {
+      case 1: return launch_wide_np<T, EPI, 1, 2, GW_MAX_NW>(st, aw, pl, m32_tiles, grid, block, ev_start, ev_stop);
+      case 2: return launch_wide_np<T, EPI, 2, 2, GW_MAX_NW>(st, aw, pl, m32_tiles, grid, block, ev_start, ev_stop);
+      case 3: return launch_wide_np<T, EPI, 3, 2, GW_MAX_NW>(st, aw, pl, m32_tiles, grid, block, ev_start, ev_stop);
+      default: return hipErrorInvalidValue;
+    }
+  }
   switch (pl.nb / 2) {
     case 1: GW_LAUNCH(1);
     case 2: GW_LAUNCH(2);
-    default: GW_LAUNCH(3);
+    case 3: GW_LAUNCH(3);
+    case 4: GW_LAUNCH(4);
+    default:
+      if constexpr (EPI == EPI_QKV_ROPE) return hipErrorInvalidValue;   // more pairs than GW_MAX_NP_QKV
+      else GW_LAUNCH(5);
   }
   #undef GW_LAUNCH
 }

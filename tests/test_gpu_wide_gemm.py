@@ -1,0 +1,32 @@
+"""The target's projections over more than 64 rows at the widths where a workgroup takes eight or ten row blocks of the weights
+(more than 24000 rows of them): ragged tiles, ragged stages, several epilogue rounds and several row groups, against the oracle."""
+import pytest
+
+import synth_inputs as si
+from gpu_common import say
+from test_gpu_step import check_target, run_target
+
+pytestmark = pytest.mark.gpu
+
+# 2063 and 2052 row blocks: ten a workgroup, the last one ragged (W_down then has 513 steps, an odd number, in eight splits)
+TEN = si.with_(si.MINI, name="mini_ten_blocks", vocab=33003, d_ffn=16416)
+# 2000 row blocks: eight a workgroup
+EIGHT = si.with_(si.MINI, name="mini_eight_blocks", vocab=32000, d_ffn=16000)
+# 960 row blocks of Q, K and V: eight a workgroup over two row groups; W_o splits its axis over eight blocks
+QKV = si.with_(si.MINI, name="mini_wide_qkv", d_model=5120, n_heads=40, d_ffn=512, vocab=512)
+TEN_F32 = si.with_(si.TINY, name="tiny_ten_blocks", vocab=33003, d_ffn=16416)
+
+
+@pytest.mark.parametrize("cfg,T,caps,L,Bsz", [
+    (TEN, 13, (10,) * 4, 40, 5),        # 65 rows: three tiles, one row in the last
+    (TEN, 96, (10,) * 5, 30, 3),        # 288 rows: nine waves, seven output tiles at a time
+    (EIGHT, 64, (10,) * 4, 20, 2),      # 128 rows: four waves
+    (EIGHT, 64, (10,) * 4, 20, 6),      # 384 rows: twelve waves, nine output tiles at a time
+    (EIGHT, 43, (10,) * 4, 33, 9),      # 387 rows: thirteen tiles, two groups of seven
+    (QKV, 64, (10,) * 4, 20, 8),        # 512 rows: two groups of eight
+    (TEN_F32, 32, (10,) * 4, 17, 6),    # float32, 192 rows
+])
+def test_target_forward_over_wide_matrices(cfg, T, caps, L, Bsz):
+    say(f"target_forward {cfg.name} T={T} L={L} batch={Bsz} (M = {T * Bsz})")
+    cfgx, refs, got, _ = run_target(cfg, 1, T, caps, L, Bsz=Bsz, tiled=True)
+    check_target(cfgx, refs, got)
