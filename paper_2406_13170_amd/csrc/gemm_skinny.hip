@@ -243,6 +243,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const float *Ct
   }
 }
 
+template <int N> struct GemmTag { static constexpr int value = N; };
+
 template <typename T, int EPI, bool TILED>
 __global__ __launch_bounds__(64 * (GM_MAX_NB + GM_NLW)) void k_gemm_skinny(const GemmArgs a, int tiles) {
   __shared__ __align__(16) unsigned char lds[GM_LDS_BYTES];
@@ -299,21 +301,34 @@ __global__ __launch_bounds__(64 * (GM_MAX_NB + GM_NLW)) void k_gemm_skinny(const
     };
     load_w(0, aw[0]);
     __syncthreads();
-    for (int c = 0; c < nch2; c += 2) {
-      #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        load_w(c + u + 1, aw[u ^ 1]);
-        const unsigned char *buf = lds + u * GM_STAGE;
+    // Only the 16-row tiles that hold rows of the call are multiplied: in float32 a tile is 128 clocks of matrix core per
+    // step, which is what a small tree's launch lasts (16 rows, us: QKV 768 x 256 9.6 -> 6.9, 256 x 688 12.9 -> 7.3).
+    auto run = [&](auto tag) {
+      constexpr int MB = decltype(tag)::value;
+      for (int c = 0; c < nch2; c += 2) {
         #pragma unroll
-        for (int s = 0; s < GM_STEPS; ++s) {
+        for (int u = 0; u < 2; ++u) {
+          load_w(c + u + 1, aw[u ^ 1]);
+          const unsigned char *buf = lds + u * GM_STAGE;
           #pragma unroll
-          for (int mb = 0; mb < 4; ++mb) {
-            const uint4 bfrag = *reinterpret_cast<const uint4 *>(buf + (mb * 16 + r16) * GM_PITCH + s * 64 + g * 16);
-            acc[mb] = mma16<T>(aw[u][s], bfrag, acc[mb]);
+          for (int s = 0; s < GM_STEPS; ++s) {
+            #pragma unroll
+            for (int mb = 0; mb < MB; ++mb) {
+              const uint4 bfrag = *reinterpret_cast<const uint4 *>(buf + (mb * 16 + r16) * GM_PITCH + s * 64 + g * 16);
+              acc[mb] = mma16<T>(aw[u][s], bfrag, acc[mb]);
+            }
           }
+          __syncthreads();
         }
-        __syncthreads();
       }
+    };
+    // In bf16 a tile is 16 clocks a step and the weights set the pace.
+    if (sizeof(T) == 2) run(GemmTag<4>{});
+    else switch ((min(a.M - m_base, GM_BM) + 15) / 16) {    // (uniform)
+      case 1: run(GemmTag<1>{}); break;
+      case 2: run(GemmTag<2>{}); break;
+      case 3: run(GemmTag<3>{}); break;
+      default: run(GemmTag<4>{}); break;
     }
   } else {
     // ----------------------------------------------------------------------------- loader wave
@@ -447,7 +462,6 @@ constexpr int gw_epi_waves(int np, int nwmax) {            // waves whose output
   return (int)((size_t)nwmax * gw_ct_bytes(np) <= 160 * 1024 ? nwmax : 160 * 1024 / gw_ct_bytes(np));
 }
 
-template <int N> struct GwTag { static constexpr int value = N; };
 template <int N> __device__ __forceinline__ void gw_wait_vm() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
 }
@@ -599,7 +613,7 @@ __global__ __launch_bounds__(64 * (NWMAX + GW_NL)) void k_gemm_wide(const GemmAr
         }
       }
     };
-    if (TW > 1 && !live(1)) run(GwTag<1>{}); else run(GwTag<TW>{});
+    if (TW > 1 && !live(1)) run(GemmTag<1>{}); else run(GemmTag<TW>{});
   }
 
   // ---- epilogues: every math wave handles its own activation rows through its own Ct region in LDS (the ring is

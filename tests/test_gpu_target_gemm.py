@@ -1,5 +1,6 @@
-"""The target's projections over more than 64 rows at the widths where a workgroup takes eight or ten row blocks of the weights
-(more than 24000 rows of them): ragged tiles, ragged stages, several epilogue rounds and several row groups, against the oracle."""
+"""The target's projections where the row tiles of a launch can go wrong, against the oracle: float32 trees around every count
+of 16-row tiles, and more than 64 rows at the widths where a workgroup takes eight or ten row blocks of the weights (more than
+24000 rows of them), with ragged tiles, ragged stages, several epilogue rounds and several row groups."""
 import pytest
 
 import synth_inputs as si
@@ -29,4 +30,12 @@ TEN_F32 = si.with_(si.TINY, name="tiny_ten_blocks", vocab=33003, d_ffn=16416)
 def test_target_forward_over_wide_matrices(cfg, T, caps, L, Bsz):
     say(f"target_forward {cfg.name} T={T} L={L} batch={Bsz} (M = {T * Bsz})")
     cfgx, refs, got, _ = run_target(cfg, 1, T, caps, L, Bsz=Bsz, tiled=True)
+    check_target(cfgx, refs, got)
+
+
+@pytest.mark.parametrize("T", [2, 16, 17, 32, 33, 48, 49, 64])
+@pytest.mark.parametrize("tiled", [True, False])
+def test_float32_target_forward_over_few_rows(T, tiled):
+    say(f"target_forward tiny T={T} tiled={tiled}")
+    cfgx, refs, got, _ = run_target(si.TINY, 1, T, (10,) * 4, 21, tiled=tiled)
     check_target(cfgx, refs, got)
