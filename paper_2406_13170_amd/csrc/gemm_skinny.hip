@@ -592,9 +592,10 @@ __global__ __launch_bounds__(64 * (NWMAX + GW_NL)) void k_gemm_wide(const GemmAr
       for (int p = 0; p < P; ++p) {
         // Stage p is in LDS (pairs with the loaders' barrier).  A bare barrier: __syncthreads() would also wait for this
         // wave's outstanding activation loads (the fence it carries counts them since the kernel contains global-to-LDS
-        // loads) and drain the prefetch ring at every stage.  The "memory" clobber keeps the LDS reads below it; the
-        // reads of stage p - 1 are complete because the matrix-core instructions that used them have been issued.
-        asm volatile("s_barrier" ::: "memory");
+        // loads) and drain the prefetch ring at every stage.  The "memory" clobber keeps the LDS reads below it.  The reads
+        // of stage p - 1, whose slot the loaders refill behind the barrier, are waited for here: the clobber does not hold
+        // back the matrix-core instructions that use them, so the compiler's own wait may come to lie behind the barrier.
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         const unsigned char *sb = gw_lds + (p % GW_R) * STAGE + woff;
         #pragma unroll
         for (int s = 0; s < GW_STEPS; ++s) {
