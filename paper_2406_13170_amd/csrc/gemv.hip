@@ -787,7 +787,9 @@ hipError_t launch_linear(hipStream_t st, const void *w0, const void *w1, const v
                          const float *x, int ldx, int M, const float *res, float *o0, float *o1, float *o2, int ldo,
                          float *slabs) {
   if (M < 1 || Kd % 8) return hipErrorInvalidValue;
-  if (use_mm<T>(M, (size_t)n_seg * seg_rows * Kd))
+  // (its rows travel in 16-byte pieces straight into LDS; the vector kernel takes them from any float address)
+  const bool x_pieces = ((uintptr_t)x & 15) == 0 && ldx % 4 == 0;
+  if (use_mm<T>(M, (size_t)n_seg * seg_rows * Kd) && x_pieces)
     MM_CHUNKS(draft_mm_linear(st, w0, w1, w2, n_seg, seg_rows, Kd, x + (size_t)m0 * ldx, ldx, m, res ? res + (size_t)m0 * ldo : nullptr,
                               o0 + (size_t)m0 * ldo, o1 ? o1 + (size_t)m0 * ldo : nullptr, o2 ? o2 + (size_t)m0 * ldo : nullptr, ldo,
                               slabs));

@@ -31,6 +31,23 @@ def test_projection_error_against_64_bits(M, N, K):
     assert err < 5e-7, err
 
 
+# rows that begin at any float: one matrix that is small, one that is not
+@pytest.mark.parametrize("N,K", [(515, 520), (4100, 1032)])
+@pytest.mark.parametrize("M", [1, 5, 8])
+@pytest.mark.parametrize("shift", [1, 2, 3])
+def test_projection_of_rows_off_the_16_byte_grid(M, N, K, shift):
+    say(f"projection M={M} N={N} K={K} shift={shift}")
+    g = torch.Generator(device=DEV).manual_seed(N + K + shift)
+    W = (torch.randn((N, K), generator=g, device=DEV) * 0.02).bfloat16()
+    x = torch.randn((M * K + shift,), generator=g, device=DEV)[shift:].view(M, K)
+    assert x.data_ptr() % 16 == 4 * shift
+    y = torch.full((M, N), float("nan"), device=DEV)
+    make_ctx(si.MINI).amph_gemv(x, W, y, M, N, K)
+    ref = x.double() @ W.double().t()
+    err = float((y.double() - ref).norm() / ref.norm())
+    assert err < 5e-7, err                                    # the bound of the aligned rows above
+
+
 @pytest.mark.parametrize("M", [5])
 def test_projection_of_infinities_and_nan(M):
     N, K = 48, 520
