@@ -278,8 +278,9 @@ amph_status amph_target_forward(amph_ctx *ctx, const amph_tree *tree, const amph
  * amph_pack_weights: writes it (asynchronously, on the context's stream) from the row-major device
  * matrices: QKV takes (wq, wk, wv), GATEUP takes (w_gate, w_up, NULL), the others (w, NULL, NULL).
  * dst must be 16-byte aligned and must not overlap the sources.  The results of amph_target_forward
- * over up to 64 tree rows (B * T) are bit-identical with and without tiling: only addresses change, never the
- * order of the sums.  Over more rows tiled weights take another kernel, with the same precision. */
+ * over up to 128 tree rows (B * T) are bit-identical with and without tiling: the order of the sums is the same,
+ * whichever kernel takes which matrix.  Over more rows tiled weights may cut a reduction axis into other slabs than
+ * row-major ones, with the same precision. */
 typedef enum { AMPH_PACK_QKV = 0, AMPH_PACK_WO, AMPH_PACK_GATEUP, AMPH_PACK_DOWN, AMPH_PACK_LMHEAD, AMPH_PACK_COUNT } amph_pack_role;
 amph_status amph_tiled_bytes(const amph_ctx *ctx, int role, size_t *bytes /* host */);
 amph_status amph_pack_weights(amph_ctx *ctx, int role, const void *w0, const void *w1, const void *w2, void *dst);

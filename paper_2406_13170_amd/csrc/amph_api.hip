@@ -305,6 +305,7 @@ amph_status target_impl(amph_ctx *ctx, const amph_tree *tree, const amph_layer_w
     while (s > 1 && (size_t)s * slab > ctx->ws.slabs_floats) s /= 2;
     return s;
   };
+  auto wide = [&](int epi, int rows, int Kd, const void *tiled_w) { return gemm_is_wide(epi, rows, Kd, (int)sizeof(T), M, tiled_w != nullptr); };
   RopeTable rope_req;                     // written by the kernel that gathers the embeddings
   rope_req.pos = tree_pos; rope_req.d_h = d_h; rope_req.theta = c.rope_theta; rope_req.cs = rope_cs;
   int pending = 0;                        // slabs of the previous GEMM still to be added to the residual stream
@@ -312,12 +313,13 @@ amph_status target_impl(amph_ctx *ctx, const amph_tree *tree, const amph_layer_w
     const amph_layer_w &lw = layers[li];
     const amph_layer_tiled lt = tiled ? tiled[li] : amph_layer_tiled{nullptr, nullptr, nullptr, nullptr};
     void *kc = (T *)k_caches + (size_t)li * cache_layer, *vc = (T *)v_caches + (size_t)li * cache_layer;
-    const int s_wo = split_for(d, d, lt.wo != nullptr), s_down = split_for(d, f, lt.down != nullptr);
     // Where the consumer of an activation tensor is the wide GEMM (enough rows, tiled weights), its producer writes
     // it in that kernel's tiled layout straight away instead of leaving a copy to be made.
     const int xt_tiles = (M + 31) / 32;
-    const bool w_qkv = gemm_is_wide(M, lt.qkv != nullptr), w_wo = gemm_is_wide(M, lt.wo != nullptr);
-    const bool w_gu = gemm_is_wide(M, lt.gate_up != nullptr), w_down = gemm_is_wide(M, lt.down != nullptr);
+    const bool w_qkv = wide(EPI_QKV_ROPE, d, d, lt.qkv), w_wo = wide(EPI_STORE, d, d, lt.wo);
+    const bool w_gu = wide(EPI_SWIGLU, f, d, lt.gate_up);
+    const bool w_down = wide(EPI_STORE, d, f, lt.down);
+    const int s_wo = split_for(d, d, lt.wo != nullptr), s_down = split_for(d, f, lt.down != nullptr);
     PROF_TRY(ctx, AMPH_K_T_RMSNORM, launch_norm_fold<T>(st, xres, embed, li == 0 ? tree_tok : nullptr, V, slabs, pending,
                                                         slab, lw.rms1, M, d, c.rms_eps, xn, nullptr, ctx->dev_status,
                                                         w_qkv ? xt_tiles : 0, li == 0 ? rope_req : RopeTable{}));
@@ -346,7 +348,7 @@ amph_status target_impl(amph_ctx *ctx, const amph_tree *tree, const amph_layer_w
     PROF_GEMM(ctx, AMPH_K_T_DOWN, T, st, EPI_STORE, a);
     pending = s_down;
   }
-  const bool w_lm = gemm_is_wide(M, lm_head_tiled != nullptr);
+  const bool w_lm = wide(EPI_ARGMAX, V, d, lm_head_tiled);
   PROF_TRY(ctx, AMPH_K_T_RMSNORM, launch_norm_fold<T>(st, xres, embed, n_layers == 0 ? tree_tok : nullptr, V, slabs, pending,
                                                       slab, final_norm, M, d, c.rms_eps, xn, hidden_out, ctx->dev_status,
                                                       w_lm ? (M + 31) / 32 : 0));

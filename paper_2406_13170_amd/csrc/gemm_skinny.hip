@@ -454,7 +454,6 @@ constexpr int GW_MAX_NP2 = 3;      // ... with two tiles per wave
 constexpr int GW_MAX_NW1 = 12;     // math waves per workgroup with a tile of 32 activation rows each (three waves per SIMD)
 constexpr int GW_MAX_NW = 8;       // ... with two tiles each (two waves per SIMD)
 constexpr int GW_XD = 4;           // steps of activations requested ahead
-constexpr int GW_MIN_MBLOCKS = 2;  // blocks of 64 activation rows from which the wide kernel is used
 constexpr int GW_AUX_NT = 2;       // cache-policy bits of the global-to-LDS load: non-temporal (the weights are read once)
 
 constexpr size_t gw_ct_bytes(int np) { return (size_t)32 * (32 * np + 4) * 4; }   // a wave's output tile in the epilogue
@@ -736,12 +735,12 @@ hipError_t launch_argmax_fold(hipStream_t st, const float *amax_val, const int32
   return hipGetLastError();
 }
 
-// Tile height and reduction split for one GEMM.  Model, in units of one weight fragment: a workgroup's
+// Tile height and reduction split of the skinny kernel for one GEMM.  Model, in units of one weight fragment: a workgroup's
 // time is its steps times (nb fragments + 2 for its share of the activation chunk); the kernel's time
 // is that times the number of rounds the grid needs on 256 CUs; every split beyond the first costs the
 // write and the later read of one more float32 slab.  The two constants are fitted to measurements of
 // the 7B shapes (Wo: 4 blocks x 4 splits beats 2 x 2 and 8 x 8; down: 4 x 4 beats 8 x 8).
-GemmPlan gemm_plan(int epi, int seg_rows, int Kd, int elem_bytes, int M, int split_req, bool tiled) {
+static GemmPlan plan_skinny(int epi, int seg_rows, int Kd, int elem_bytes, int M, int split_req) {
   GemmPlan best{};
   const int blocks = gemm_blocks(epi, seg_rows);
   const int total_steps = Kd * elem_bytes / 64;
@@ -750,42 +749,6 @@ GemmPlan gemm_plan(int epi, int seg_rows, int Kd, int elem_bytes, int M, int spl
   const double slab_units = fused ? 0.0 : (double)M * seg_rows * 1.0e-4 + 2.0;   // per extra split
   double best_cost = 1e300;
   best.blocks = blocks;
-  best.wide = gemm_is_wide(M, tiled);
-  if (best.wide) {
-    // A workgroup owns a group of tiles of 32 activation rows against nb weight row blocks.  Candidates: groups of up to
-    // 12 tiles with a math wave for each, as few as possible or one more (twice the workgroups pay when the weight matrix
-    // has too few row blocks to fill the chip); groups of 13 to 16 tiles, two tiles a wave, which read the weights once.
-    // The price is in us, fitted to 500 measurements at 7B, 13B and 33B shapes over 96 to 768 rows (11 % deviation; the
-    // choice was within 3 % of the best one in 90 of 100): per step of 64 bytes of k a workgroup takes in 2 KB for every
-    // tile and 1 KB for every block, and its matrix cores and LDS reads go with blocks times tiles and with blocks.  Three
-    // waves on a SIMD come with the shorter activation ring.  A split writes, and the fold reads, one more slab.  The
-    // grid needs a round for every 256 workgroups (the LDS ring leaves room for one in a compute unit).
-    const int mt = (M + 31) / 32;
-    for (int cand = 0; cand < 3; ++cand) {
-      const int mg = cand == 2 ? (mt + 15) / 16 : (mt + GW_MAX_NW1 - 1) / GW_MAX_NW1 + cand;
-      const int gt = (mt + mg - 1) / mg;                                // tiles per group
-      if (cand == 2 ? gt <= GW_MAX_NW1 : mg > mt) continue;
-      const int tw = cand == 2 ? 2 : 1, nw = cand == 2 ? GW_MAX_NW : gt;
-      const double waves = cand == 2 ? 1.08 : gt > 8 ? 1.2 : 1.0;
-      const int max_np = tw == 2 ? GW_MAX_NP2 : epi == EPI_QKV_ROPE ? GW_MAX_NP_QKV : GW_MAX_NP;
-      for (int s = 1; s <= 8; s *= 2) {
-        if (split_req > 0 && s != split_req) continue;
-        if (split_req == 0 && (fused ? s > 1 : (s > 1 && total_steps / s < 16))) continue;
-        for (int nb = 2; nb <= 2 * max_np; nb += 2) {         // blocks are taken in pairs
-          if (nb > std::max(blocks, 2)) break;
-          const int tiles = (blocks + nb - 1) / nb;
-          const long rounds = ((long)tiles * s * mg + 255) / 256;
-          const double step = 0.006 * (2 * gt + nb) + 0.0031 * nb * gt + 0.0235 * nb;
-          const double cost = (double)rounds * (((total_steps + s - 1) / s) * step * waves + 4.0) + (fused ? 0.0 : 1.1e-6 * M * seg_rows * s);
-          if (cost <= best_cost) {
-            best_cost = cost; best.nb = nb; best.split = s; best.tiles = tiles;
-            best.mgroups = mg; best.nw = nw; best.tw = tw; best.gt = gt;
-          }
-        }
-      }
-    }
-    return best;
-  }
   best.mgroups = mblocks;
   best.nw = 1;
   best.tw = 2;
@@ -805,7 +768,85 @@ GemmPlan gemm_plan(int epi, int seg_rows, int Kd, int elem_bytes, int M, int spl
   return best;
 }
 
-bool gemm_is_wide(int M, bool tiled) { return tiled && (M + GM_BM - 1) / GM_BM >= GW_MIN_MBLOCKS; }
+// The wide kernel's tiles for a given split: a workgroup owns a group of tiles of 32 activation rows against nb weight row
+// blocks.  Candidates: groups of up to 12 tiles with a math wave for each, as few as possible or one more (twice the
+// workgroups pay when the weight matrix has too few row blocks to fill the chip); groups of 13 to 16 tiles, two tiles a
+// wave, which read the weights once.  The price is in us, fitted to 500 measurements at 7B, 13B and 33B shapes over 96 to
+// 768 rows (11 % deviation): per step of 64 bytes of k a workgroup takes in 2 KB for every tile and 1 KB for every block,
+// and its matrix cores and LDS reads go with blocks times tiles and with blocks.  Three waves on a SIMD come with the
+// shorter activation ring.  The grid needs a round for every 256 workgroups (the LDS ring leaves room for one in a
+// compute unit).
+static GemmPlan plan_wide(int epi, int seg_rows, int Kd, int elem_bytes, int M, int split) {
+  GemmPlan best{};
+  const int blocks = gemm_blocks(epi, seg_rows);
+  const int steps = (Kd * elem_bytes / 64 + split - 1) / split;
+  double best_cost = 1e300;
+  best.blocks = blocks;
+  best.wide = true;
+  best.split = split;
+  const int mt = (M + 31) / 32;
+  for (int cand = 0; cand < 3; ++cand) {
+    const int mg = cand == 2 ? (mt + 15) / 16 : (mt + GW_MAX_NW1 - 1) / GW_MAX_NW1 + cand;
+    const int gt = (mt + mg - 1) / mg;                                // tiles per group
+    if (cand == 2 ? gt <= GW_MAX_NW1 : mg > mt) continue;
+    const int tw = cand == 2 ? 2 : 1, nw = cand == 2 ? GW_MAX_NW : gt;
+    const double waves = cand == 2 ? 1.08 : gt > 8 ? 1.2 : 1.0;
+    const int max_np = tw == 2 ? GW_MAX_NP2 : epi == EPI_QKV_ROPE ? GW_MAX_NP_QKV : GW_MAX_NP;
+    for (int nb = 2; nb <= 2 * max_np; nb += 2) {           // blocks are taken in pairs
+      if (nb > std::max(blocks, 2)) break;
+      const int tiles = (blocks + nb - 1) / nb;
+      const long rounds = ((long)tiles * split * mg + 255) / 256;
+      const double step = 0.006 * (2 * gt + nb) + 0.0031 * nb * gt + 0.0235 * nb;
+      const double cost = (double)rounds * (steps * step * waves + 4.0);
+      if (cost <= best_cost) {
+        best_cost = cost; best.nb = nb; best.tiles = tiles;
+        best.mgroups = mg; best.nw = nw; best.tw = tw; best.gt = gt;
+      }
+    }
+  }
+  return best;
+}
+
+// Slabs that the reduction axis of a matrix is cut into.  The one choice of a plan that the result depends on: inside a
+// slab both kernels add the same products in the same order (bf16; the float32 fragments are dealt out differently), so
+// their bits are the same.  Therefore it is a rule on the shape alone.  Up to 128 rows it is the skinny kernel's, for
+// whichever kernel runs and however the weights are stored: tiled and row-major weights give the same bits there.  Beyond
+// (tiled weights) it weighs, in units of a weight fragment, a workgroup's steps times its fragments per step and the tiles
+// that its busiest SIMD carries, for groups of up to 8, 12 (three a wave) or 16 tiles, against the slabs' way out and back.
+// Finer splits would gain a little with the wide kernel's present tiles (us, GEMM and fold together: W_down at 384 rows,
+// 33B, four slabs instead of two 129 + 11 against 138 + 6; 512 rows, 7B, 59 + 9 against 63 + 5) and change every result.
+static int gemm_split(int epi, int seg_rows, int Kd, int elem_bytes, int M, bool tiled) {
+  if (epi != EPI_STORE) return 1;                           // fused epilogues need complete sums
+  if (!tiled || M <= 2 * GM_BM) return plan_skinny(epi, seg_rows, Kd, elem_bytes, M, 0).split;
+  const int blocks = gemm_blocks(epi, seg_rows), steps = Kd * elem_bytes / 64, mt = (M + 31) / 32;
+  double best_cost = 1e300;
+  int best = 1;
+  for (int most = 8; most <= 16; most += 4) {
+    const int mg = (mt + most - 1) / most, gt = (mt + mg - 1) / mg;
+    if (most > 8 && gt <= 8) continue;
+    const double simd_tiles = most == 16 ? 0.92 * ((gt + 3) / 4) : most == 12 ? ((gt + 2) / 3 + 3) / 4 * 3 : ((gt + 1) / 2 + 3) / 4 * 2;
+    for (int s = 1; s <= 8 && (s == 1 || steps / s >= 16); s *= 2)
+      for (int nb = 2; nb <= 6 && nb <= std::max(blocks, 2); nb += 2) {
+        const long rounds = ((long)((blocks + nb - 1) / nb) * s * mg + 255) / 256;
+        const double cost = (double)rounds * ((steps + s - 1) / s) * (nb + 2) * (simd_tiles / 2) + ((double)M * seg_rows * 1.0e-4 + 2.0) * (s - 1);
+        if (cost <= best_cost) { best_cost = cost; best = s; }
+      }
+  }
+  return best;
+}
+
+// Which kernel.  Up to 64 rows the skinny one, from 65 on the wide one; float32 keeps to the skinny one up to 128 rows, whose
+// sums row-major weights have.
+bool gemm_is_wide(int epi, int seg_rows, int Kd, int elem_bytes, int M, bool tiled) {
+  const int mblocks = (M + GM_BM - 1) / GM_BM;
+  return tiled && mblocks >= (elem_bytes == 4 ? 3 : 2);
+}
+
+GemmPlan gemm_plan(int epi, int seg_rows, int Kd, int elem_bytes, int M, int split_req, bool tiled) {
+  const int split = split_req > 0 ? split_req : gemm_split(epi, seg_rows, Kd, elem_bytes, M, tiled);
+  return gemm_is_wide(epi, seg_rows, Kd, elem_bytes, M, tiled) ? plan_wide(epi, seg_rows, Kd, elem_bytes, M, split)
+                                                               : plan_skinny(epi, seg_rows, Kd, elem_bytes, M, split);
+}
 
 size_t gemm_xt_bytes(int M, int Kd, int elem_bytes) { return (size_t)((M + 31) / 32) * 32 * (size_t)Kd * elem_bytes; }
 

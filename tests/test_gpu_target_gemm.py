@@ -1,9 +1,13 @@
 """The target's projections where the row tiles of a launch can go wrong, against the oracle: float32 trees around every count
 of 16-row tiles, and more than 64 rows at the widths where a workgroup takes eight or ten row blocks of the weights (more than
 24000 rows of them), with ragged tiles, ragged stages, several epilogue rounds and several row groups."""
+import numpy as np
 import pytest
+import torch
 
 import synth_inputs as si
+from paper_2406_13170_amd import device as D
+
 from gpu_common import say
 from test_gpu_step import check_target, run_target
 
@@ -31,6 +35,38 @@ def test_target_forward_over_wide_matrices(cfg, T, caps, L, Bsz):
     say(f"target_forward {cfg.name} T={T} L={L} batch={Bsz} (M = {T * Bsz})")
     cfgx, refs, got, _ = run_target(cfg, 1, T, caps, L, Bsz=Bsz, tiled=True)
     check_target(cfgx, refs, got)
+
+
+# 65 to 128 rows: bf16 with tiled weights runs on the wide kernel, row-major weights and float32 on the skinny one
+DOWN = si.with_(si.MINI, name="mini_down", d_model=1024, n_heads=8, d_ffn=4608, vocab=512)
+
+
+@pytest.mark.parametrize("cfg,n_layers,T,caps,L,Bsz", [
+    (si.MINI, 2, 64, (10,) * 4, 40, 2),
+    (EIGHT, 1, 32, (10,) * 4, 33, 4),
+    (TEN, 2, 13, (10,) * 4, 40, 5),
+    (QKV, 1, 13, (10,) * 4, 20, 5),
+    (QKV, 1, 64, (10,) * 4, 20, 2),
+    (DOWN, 1, 13, (10,) * 4, 20, 5),
+    (si.V7B, 1, 40, (10,) * 4, 64, 2),
+    (TEN_F32, 1, 16, (10,) * 4, 17, 5),
+    (si.TINY, 2, 16, (4, 2, 2, 2), 9, 8),
+])
+def test_target_forward_over_two_blocks_of_rows(cfg, n_layers, T, caps, L, Bsz):
+    """Against the oracle, and tiled against row-major weights: the same bits, whichever kernel took which matrix."""
+    say(f"target_forward {cfg.name} T={T} batch={Bsz} (M = {T * Bsz})")
+    runs = {}
+    for tiled in (True, False):
+        cfgx, refs, got, _ = run_target(cfg, n_layers, T, caps, L, Bsz=Bsz, tiled=tiled, oracle=tiled)
+        if tiled:
+            check_target(cfgx, refs, got)
+        runs[tiled] = got
+    for key in ("hidden", "logits", "tgt"):
+        assert np.array_equal(runs[True][key], runs[False][key]), key
+    bits = lambda t: t.view(torch.int16 if t.element_size() == 2 else torch.int32)
+    for key in ("k_caches", "v_caches"):
+        rows = [D.unpack_kv(r["ctx"], r["k_caches"], r["v_caches"])[key == "v_caches"][:, :, :, L:L + T] for r in runs.values()]
+        assert torch.equal(bits(rows[0]), bits(rows[1])), key
 
 
 @pytest.mark.parametrize("T", [2, 16, 17, 32, 33, 48, 49, 64])
