@@ -318,8 +318,10 @@ amph_status target_impl(amph_ctx *ctx, const amph_tree *tree, const amph_layer_w
     const int xt_tiles = (M + 31) / 32;
     const bool w_qkv = wide(EPI_QKV_ROPE, d, d, lt.qkv), w_wo = wide(EPI_STORE, d, d, lt.wo);
     const bool w_gu = wide(EPI_SWIGLU, f, d, lt.gate_up);
-    const bool w_down = wide(EPI_STORE, d, f, lt.down);
-    const int s_wo = split_for(d, d, lt.wo != nullptr), s_down = split_for(d, f, lt.down != nullptr);
+    // Up to 128 rows the two kernels are close, and W_down's input as a copy (5.5 us) would cost more than the choice gives.
+    const void *down_t = (w_gu || mblocks > 2) ? lt.down : nullptr;
+    const bool w_down = wide(EPI_STORE, d, f, down_t);
+    const int s_wo = split_for(d, d, lt.wo != nullptr), s_down = split_for(d, f, down_t != nullptr);
     PROF_TRY(ctx, AMPH_K_T_RMSNORM, launch_norm_fold<T>(st, xres, embed, li == 0 ? tree_tok : nullptr, V, slabs, pending,
                                                         slab, lw.rms1, M, d, c.rms_eps, xn, nullptr, ctx->dev_status,
                                                         w_qkv ? xt_tiles : 0, li == 0 ? rope_req : RopeTable{}));
@@ -345,6 +347,7 @@ amph_status target_impl(amph_ctx *ctx, const amph_tree *tree, const amph_layer_w
     a = g;
     a.w0 = lw.w_down; a.wt = lt.down; a.n_seg = 1; a.seg_rows = d; a.Kd = f; a.x = actb; a.out = slabs; a.split_k = s_down;
     a.x_tiled = w_gu && w_down;
+    if (!down_t) a.xt = nullptr;
     PROF_GEMM(ctx, AMPH_K_T_DOWN, T, st, EPI_STORE, a);
     pending = s_down;
   }

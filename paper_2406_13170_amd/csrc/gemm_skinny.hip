@@ -1,6 +1,7 @@
 // GEMMs of the target's forward pass over the tree tokens (Sec. 2 "Tree Attention"): M = B*T activation rows
 // against [N, Kd] weights that stream from HBM once, on the matrix cores.  Two kernels: the skinny one
-// (described first; up to 64 rows, or row-major weights) and the wide one (further down; more than 64 rows).
+// (described first; up to 64 rows, or row-major weights) and the wide one (further down; more than 128 rows, and the
+// matrices that suit it from 65 on).
 //
 // The unit of work is a ROW BLOCK: 16 weight rows that one wave keeps as matrix-core A fragments and
 // whose outputs need nothing from any other block:
@@ -419,7 +420,7 @@ __global__ __launch_bounds__(64 * (GM_MAX_NB + GM_NLW)) void k_gemm_skinny(const
 }
 
 // =====================================================================================================
-// Wide GEMM: more than 64 activation rows (batches of trees, wide trees).  The skinny kernel above re-reads the
+// Wide GEMM: more than 64 activation rows (batches of trees, wide trees; gemm_is_wide).  The skinny kernel above re-reads the
 // weights from L2 once per block of 64 rows, every math wave re-reads the whole activation chunk from LDS, and its
 // 16 x 16 matrix-core instruction runs at half the rate of the 32 x 32 one: with several blocks of rows L2, LDS
 // and the matrix cores, not HBM, set the pace.  Here a workgroup owns a group of up to 12 (or 13 to 16) tiles of 32
@@ -835,11 +836,25 @@ static int gemm_split(int epi, int seg_rows, int Kd, int elem_bytes, int M, bool
   return best;
 }
 
-// Which kernel.  Up to 64 rows the skinny one, from 65 on the wide one; float32 keeps to the skinny one up to 128 rows, whose
-// sums row-major weights have.
+// Which kernel.  Up to 64 rows the skinny one, from 129 on the wide one.  In between (two blocks of 64 rows, or three and
+// four tiles of 32) it depends on the matrix: the skinny kernel still does well where the weights are one round of its
+// workgroups (us, skinny / wide, 128 rows: 7B QKV 12288 x 4096 36 / 39, 9216 x 3072 25 / 29, 13B W_o 5120 x 5120 21 / 25;
+// but 27648 x 5120 84 / 63, 32000 x 4096 80 / 62, 35840 x 6656 134 / 101).  Prices in us for equal slabs, 6 and 8 % off over
+// 105 pairs of measurements at model widths from 2048 to 8192 and 65 to 128 rows: always the wide kernel loses 60 us over
+// all of them against the better choice, always the skinny one 968, this rule 10.  float32 keeps to the skinny kernel,
+// whose sums row-major weights have.
 bool gemm_is_wide(int epi, int seg_rows, int Kd, int elem_bytes, int M, bool tiled) {
   const int mblocks = (M + GM_BM - 1) / GM_BM;
-  return tiled && mblocks >= (elem_bytes == 4 ? 3 : 2);
+  if (!tiled || mblocks < 2) return false;
+  if (mblocks > 2) return true;
+  if (elem_bytes == 4) return false;
+  const int split = gemm_split(epi, seg_rows, Kd, elem_bytes, M, tiled);
+  const GemmPlan s = plan_skinny(epi, seg_rows, Kd, elem_bytes, M, split), w = plan_wide(epi, seg_rows, Kd, elem_bytes, M, split);
+  const double steps = (double)(Kd * elem_bytes / 64) / split, slab = epi == EPI_STORE ? 1.0e-6 * M * seg_rows * split : 0.0;
+  auto rounds = [split](int tiles, int groups) { return (double)(((long)tiles * split * groups + 255) / 256); };
+  const double us_s = rounds(s.tiles, mblocks) * (5.0 + steps * (0.030 * s.nb + 0.050)) + 2.1 * slab;
+  const double us_w = rounds(w.tiles, w.mgroups) * (4.7 + steps * (0.036 * w.nb + 0.020 * w.gt + 0.040)) + 2.4 * slab;
+  return us_w < us_s;
 }
 
 GemmPlan gemm_plan(int epi, int seg_rows, int Kd, int elem_bytes, int M, int split_req, bool tiled) {

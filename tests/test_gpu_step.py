@@ -345,7 +345,7 @@ def test_target_forward_batch_two():
 
 
 @pytest.mark.parametrize("cfg,n_layers,T,caps,L,Bsz", [
-    (si.MINI, 2, 64, (10,) * 4, 100, 2),           # M = 128: 4 tiles of 32 rows
+    (si.MINI, 2, 64, (10,) * 4, 100, 2),           # M = 128: two blocks of 64 rows, still the skinny kernel at these widths
     (si.MINI, 2, 64, (10,) * 4, 90, 3),            # M = 192: 6 tiles of 32 rows
     (si.MINI, 2, 64, (10,) * 4, 77, 5),            # M = 320: 10 tiles, up to three math waves per SIMD
     (si.MINI, 1, 35, (10,) * 4, 61, 10),           # M = 350: 11 tiles, the last one ragged
@@ -356,7 +356,7 @@ def test_target_forward_batch_two():
     (si.MINI, 1, 64, (10,) * 4, 12, 9),            # M = 576: 18 tiles, two groups of 9
 ])
 def test_target_forward_batches_on_tiled_weights(cfg, n_layers, T, caps, L, Bsz):
-    """More than 64 activation rows with tiled weights take the wide GEMM (groups of up to 16 tiles of 32 rows of a
+    """More than 128 activation rows with tiled weights take the wide GEMM (groups of up to 16 tiles of 32 rows of a
     weight tile in one workgroup, 32 x 32 matrix-core tiles, one to three math waves per SIMD); the same inputs
     with row-major weights take the skinny one.  Both against the oracle."""
     say(f"target_forward {cfg.name} layers={n_layers} T={T} L={L} batch={Bsz} (M = {T * Bsz}), tiled weights")

@@ -23,9 +23,9 @@ TEN_F32 = si.with_(si.TINY, name="tiny_ten_blocks", vocab=33003, d_ffn=16416)
 
 
 @pytest.mark.parametrize("cfg,T,caps,L,Bsz", [
-    (TEN, 13, (10,) * 4, 40, 5),        # 65 rows: three tiles, one row in the last
+    (TEN, 13, (10,) * 4, 40, 5),        # 65 rows: three tiles, one row in the last (gate/up and the head)
     (TEN, 96, (10,) * 5, 30, 3),        # 288 rows: nine waves, seven output tiles at a time
-    (EIGHT, 64, (10,) * 4, 20, 2),      # 128 rows: four waves
+    (EIGHT, 64, (10,) * 4, 20, 2),      # 128 rows: four waves (gate/up and the head)
     (EIGHT, 64, (10,) * 4, 20, 6),      # 384 rows: twelve waves, nine output tiles at a time
     (EIGHT, 43, (10,) * 4, 33, 9),      # 387 rows: thirteen tiles, two groups of seven
     (QKV, 64, (10,) * 4, 20, 8),        # 512 rows: two groups of eight
@@ -37,20 +37,21 @@ def test_target_forward_over_wide_matrices(cfg, T, caps, L, Bsz):
     check_target(cfgx, refs, got)
 
 
-# 65 to 128 rows: bf16 with tiled weights runs on the wide kernel, row-major weights and float32 on the skinny one
+# 65 to 128 rows, where each matrix goes to the kernel that suits it (gemm_is_wide).  Of the projections into Q, K and V, W_o,
+# gate/up, W_down and the LM head, those of tiled weights on the wide kernel:
 DOWN = si.with_(si.MINI, name="mini_down", d_model=1024, n_heads=8, d_ffn=4608, vocab=512)
 
 
 @pytest.mark.parametrize("cfg,n_layers,T,caps,L,Bsz", [
-    (si.MINI, 2, 64, (10,) * 4, 40, 2),
-    (EIGHT, 1, 32, (10,) * 4, 33, 4),
-    (TEN, 2, 13, (10,) * 4, 40, 5),
-    (QKV, 1, 13, (10,) * 4, 20, 5),
-    (QKV, 1, 64, (10,) * 4, 20, 2),
-    (DOWN, 1, 13, (10,) * 4, 20, 5),
-    (si.V7B, 1, 40, (10,) * 4, 64, 2),
-    (TEN_F32, 1, 16, (10,) * 4, 17, 5),
-    (si.TINY, 2, 16, (4, 2, 2, 2), 9, 8),
+    (si.MINI, 2, 64, (10,) * 4, 40, 2),    # none
+    (EIGHT, 1, 32, (10,) * 4, 33, 4),      # gate/up, which then writes rows for a skinny W_down, and the head
+    (TEN, 2, 13, (10,) * 4, 40, 5),        # the same over 65 rows, two layers
+    (QKV, 1, 13, (10,) * 4, 20, 5),        # Q, K, V and W_o
+    (QKV, 1, 64, (10,) * 4, 20, 2),        # Q, K, V
+    (DOWN, 1, 13, (10,) * 4, 20, 5),       # none: W_down would be, but its input comes from a skinny gate/up
+    (si.V7B, 1, 40, (10,) * 4, 64, 2),     # all but Q, K, V
+    (TEN_F32, 1, 16, (10,) * 4, 17, 5),    # float32: none
+    (si.TINY, 2, 16, (4, 2, 2, 2), 9, 8),  # the same, 128 rows
 ])
 def test_target_forward_over_two_blocks_of_rows(cfg, n_layers, T, caps, L, Bsz):
     """Against the oracle, and tiled against row-major weights: the same bits, whichever kernel took which matrix."""
