@@ -209,9 +209,13 @@ amph_status draft_impl(amph_ctx *ctx, const amph_draft_w *w, const float *h_new,
       HIP_TRY(ctx, launch_gather_rows(st, x, B, R, d, n_valid, x_last));
       res = x_last;
     }
+    // with few heads the attention leaves one partial result per key split: Wo folds them while it stages its rows, if it can
+    const SalParts parts = {F(ctx->ws.sal_part), sal_key_splits(B, R, last_rows_only, n_h, c.max_kv), n_h, d_h};
+    const bool to_wo = parts.S > 1 && linear_takes_parts<T>(Ms, parts);
     PROF_TRY(ctx, AMPH_K_SAL_ATTN, launch_sal_attn<T>(st, q, kv_stage, sal_len, B, n_h, d_h, c.max_kv, att, R, n_valid,
-                                                      last_rows_only ? 1 : 0, F(ctx->ws.sal_part)));
-    PROF_TRY(ctx, AMPH_K_SAL_WO, launch_linear<T>(st, w->sal[s].wo, nullptr, nullptr, 1, d, d, att, d, Ms, res, y, nullptr, nullptr, d, slabs));
+                                                      last_rows_only ? 1 : 0, F(ctx->ws.sal_part), !to_wo));
+    PROF_TRY(ctx, AMPH_K_SAL_WO, launch_linear<T>(st, w->sal[s].wo, nullptr, nullptr, 1, d, d, att, d, Ms, res, y, nullptr, nullptr, d, slabs,
+                                                  to_wo ? &parts : nullptr));
     PROF_TRY(ctx, AMPH_K_SAL_GATEUP, launch_gate_up<T>(st, w->sal[s], y, d, f, Ms, c.rms_eps, act));
     PROF_TRY(ctx, AMPH_K_SAL_DOWN, launch_linear<T>(st, w->sal[s].w_down, nullptr, nullptr, 1, d, f, act, f, Ms, y, h[s], nullptr, nullptr, d, slabs));
   }

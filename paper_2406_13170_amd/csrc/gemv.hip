@@ -208,6 +208,58 @@ __device__ __forceinline__ void load_x_plain(float *xs, const float *x, int ldx,
   fill_xs<T, M, false>(xs, x, ldx, (const T *)nullptr, m_valid, Kd, nC, ss);
 }
 
+// Rows that an attention left as partial results over its key splits, folded on their way into xs as the fold kernel does
+// it (same operations, same order).  fac: M * n_heads * (SAL_MAX_SPLITS + 1) floats of LDS behind xs for each (row, head)'s
+// weights of the splits and their sum.  Every workgroup reads all the parts, from L2, in two dependent passes; against a
+// fold kernel (4.7 us, of which 4.4 are the launch) that is worth it up to GV_PARTS (row, head, split) triples: whole drafts,
+// caches of 4096 rows, 100 in use, us with the kernel / here: the float32 miniature (32 triples) 103.0 / 95.6, over five
+// positions (160) 122.3 / 118.8, in bf16 (32) 109.4 / 106.0; 7B (256) 362.7 / 362.1, 33B (416) 695 / 699.
+constexpr int GV_PARTS = 160;
+template <typename T, int M>
+__device__ __forceinline__ void load_x_parts(float *xs, float *fac, const SalParts &p, int m_valid, int Kd, int nC) {
+  constexpr int NS = SAL_MAX_SPLITS;
+  const int pitch = sal_part_pitch(p.d_h), dsh = __ffs(p.d_h) - 1, nq = nC * XLayout<T>::CH / 4;     // d_h is a power of two
+  for (int i = threadIdx.x; i < m_valid * p.n_heads; i += GV_THREADS) {
+    float2 ml[NS];
+    #pragma unroll
+    for (int s = 0; s < NS; ++s) ml[s] = *reinterpret_cast<const float2 *>(p.part + ((size_t)i * p.S + min(s, p.S - 1)) * pitch + p.d_h);
+    float mw = NEG_BIG, lw = 0.f, *fi = fac + i * (NS + 1);
+    #pragma unroll
+    for (int s = 0; s < NS; ++s) if (s < p.S) mw = fmaxf(mw, ml[s].x);
+    #pragma unroll
+    for (int s = 0; s < NS; ++s)
+      if (s < p.S) {
+        const float f = exp2f(ml[s].x - mw);
+        lw += ml[s].y * f;
+        fi[s] = f;
+      }
+    fi[NS] = lw;
+  }
+  __syncthreads();
+  float4 *xs4 = reinterpret_cast<float4 *>(xs);
+  for (int q = threadIdx.x; q < nq; q += GV_THREADS) {
+    const int k = q * 4, kk = (k < Kd) ? k : 0, h = kk >> dsh, e = kk & (p.d_h - 1);
+    #pragma unroll
+    for (int m = 0; m < M; ++m) {
+      const int i = (m < m_valid ? m : 0) * p.n_heads + h;
+      const float *src = p.part + (size_t)i * p.S * pitch + e, *fi = fac + i * (NS + 1);
+      float4 v[NS];
+      #pragma unroll
+      for (int s = 0; s < NS; ++s) v[s] = *reinterpret_cast<const float4 *>(src + (size_t)min(s, p.S - 1) * pitch);
+      float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+      #pragma unroll
+      for (int s = 0; s < NS; ++s)
+        if (s < p.S) {
+          const float f = fi[s];
+          o.x += v[s].x * f; o.y += v[s].y * f; o.z += v[s].z * f; o.w += v[s].w * f;
+        }
+      const float lw = fi[NS];
+      const bool ok = k < Kd && m < m_valid && lw > 0.f;
+      xs4[xs_quad<T>(m, nC, k)] = ok ? make_float4(o.x / lw, o.y / lw, o.z / lw, o.w / lw) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  }
+}
+
 // x[m][k] * g[k] with the row's 1/rms returned in rs[m] (applied by the caller to the dot products).
 template <typename T, int M>
 __device__ __forceinline__ void load_x_rmsnorm(float *xs, float *red, const float *x, int ldx, const T *g,
@@ -424,15 +476,17 @@ __global__ __launch_bounds__(GV_THREADS) void k_sal_qkv(const T *wq, const T *wk
 // pointers already at the slice): with add_out it adds its sums to what out_s holds, so that consecutive launches
 // over consecutive slices build the product of rows too wide to sit in LDS whole while reading the matrix once.
 // =====================================================================================================
-template <typename T, int M, bool PIPE>
-__global__ __launch_bounds__(GV_THREADS) void k_linear(const T *w0, const T *w1, const T *w2, int n_seg, int seg_rows,
-                                                       int Kd, const float *x, int ldx, int m_valid, const float *res,
-                                                       float *o0, float *o1, float *o2, int ldo, int ldw, int add_out) {
+// PARTS: the rows come as partial results of the attention over its key splits instead (Wo).
+template <typename T, int M, bool PIPE, bool PARTS>
+__device__ __forceinline__ void linear_body(const T *w0, const T *w1, const T *w2, int n_seg, int seg_rows, int Kd, const float *x,
+                                            int ldx, int m_valid, const float *res, float *o0, float *o1, float *o2, int ldo,
+                                            int ldw, int add_out, const SalParts &parts) {
   extern __shared__ __align__(16) float smem[];
   constexpr int CH = XLayout<T>::CH;
   const int nC = (Kd + CH - 1) / CH;
   float *xs = smem;
-  load_x_plain<T, M>(xs, x, ldx, m_valid, Kd, nC);
+  if constexpr (PARTS) load_x_parts<T, M>(xs, smem + (size_t)M * nC * CH, parts, m_valid, Kd, nC);
+  else load_x_plain<T, M>(xs, x, ldx, m_valid, Kd, nC);
   __syncthreads();
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int Gseg = (seg_rows + GV_R - 1) / GV_R;
@@ -468,6 +522,18 @@ __global__ __launch_bounds__(GV_THREADS) void k_linear(const T *w0, const T *w1,
       }
     }
   }
+}
+
+template <typename T, int M, bool PIPE>
+__global__ __launch_bounds__(GV_THREADS) void k_linear(const T *w0, const T *w1, const T *w2, int n_seg, int seg_rows,
+                                                       int Kd, const float *x, int ldx, int m_valid, const float *res,
+                                                       float *o0, float *o1, float *o2, int ldo, int ldw, int add_out) {
+  linear_body<T, M, PIPE, false>(w0, w1, w2, n_seg, seg_rows, Kd, x, ldx, m_valid, res, o0, o1, o2, ldo, ldw, add_out, SalParts{});
+}
+template <typename T, int M, bool PIPE>
+__global__ __launch_bounds__(GV_THREADS) void k_linear_parts(const T *w, int seg_rows, int Kd, const SalParts parts, int m_valid,
+                                                             const float *res, float *out, int ldo) {
+  linear_body<T, M, PIPE, true>(w, nullptr, nullptr, 1, seg_rows, Kd, nullptr, 0, m_valid, res, out, nullptr, nullptr, ldo, Kd, 0, parts);
 }
 
 // =====================================================================================================
@@ -782,11 +848,29 @@ hipError_t launch_sal_qkv(hipStream_t st, const amph_layer_w &lw, const float *x
   return hipGetLastError();
 }
 
+// One launch of the vector kernel serves the rows, and reading all partial results in every workgroup costs less than a
+// fold kernel of its own (see load_x_parts).  bf16 rows that the matrix cores serve arrive there by global-to-LDS loads.
+template <typename T> bool linear_takes_parts(int M, const SalParts &p) {
+  const size_t fac = (size_t)M * p.n_heads * (SAL_MAX_SPLITS + 1) * sizeof(float);
+  return (sizeof(T) == 4 || M < DRAFT_MM_MIN) && M * p.n_heads * p.S <= GV_PARTS && gv_rows_per_launch(M, gv_xs_bytes<T>(1, p.n_heads * p.d_h), fac) >= M;
+}
+
 template <typename T>
 hipError_t launch_linear(hipStream_t st, const void *w0, const void *w1, const void *w2, int n_seg, int seg_rows, int Kd,
                          const float *x, int ldx, int M, const float *res, float *o0, float *o1, float *o2, int ldo,
-                         float *slabs) {
+                         float *slabs, const SalParts *parts) {
   if (M < 1 || Kd % 8) return hipErrorInvalidValue;
+  if (parts) {
+    if (n_seg != 1 || Kd != parts->n_heads * parts->d_h || !linear_takes_parts<T>(M, *parts)) return hipErrorInvalidValue;
+    hipError_t e = hipSuccess;
+    GV_DISPATCH_M(M, {
+      if constexpr (sizeof(T) == 4 || MM < DRAFT_MM_MIN) {
+        const size_t sm = gv_xs_bytes<T>(MM, Kd) + (size_t)M * parts->n_heads * (SAL_MAX_SPLITS + 1) * sizeof(float);
+        GV_LAUNCH(k_linear_parts, gv_grid((seg_rows + 3) / 4, sm), sm, (const T *)w0, seg_rows, Kd, *parts, M, res, o0, ldo);
+      }
+    });
+    return hipGetLastError();
+  }
   // (its rows travel in 16-byte pieces straight into LDS; the vector kernel takes them from any float address)
   const bool x_pieces = ((uintptr_t)x & 15) == 0 && ldx % 4 == 0;
   if (use_mm<T>(M, (size_t)n_seg * seg_rows * Kd) && x_pieces)
@@ -924,7 +1008,9 @@ size_t lmtk_ws_floats(int rows, int k) { return 2 * (size_t)rows * LMTK_MAX_WG *
                                         float, const int32_t *, int, void *, float *, uint32_t *, int,                  \
                                         const int32_t *);                                                               \
   template hipError_t launch_linear<T>(hipStream_t, const void *, const void *, const void *, int, int, int,            \
-                                       const float *, int, int, const float *, float *, float *, float *, int, float *); \
+                                       const float *, int, int, const float *, float *, float *, float *, int, float *,  \
+                                       const SalParts *);                                                               \
+  template bool linear_takes_parts<T>(int, const SalParts &);                                                           \
   template hipError_t launch_gate_up<T>(hipStream_t, const amph_layer_w &, const float *, int, int, int, float, float *); \
   template hipError_t launch_head_mlp<T>(hipStream_t, const void *, const void *, const float *, const float *, int,    \
                                          int, int, float *);                                                            \

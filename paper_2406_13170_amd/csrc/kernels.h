@@ -15,10 +15,16 @@ template <typename T>
 hipError_t launch_sal_qkv(hipStream_t st, const amph_layer_w &lw, const float *x, int d, int n_heads, int d_h, int M,
                           float eps, float theta, const int32_t *sal_len, int max_kv, void *kv_stage, float *qbuf,
                           uint32_t *dev_status, int R, const int32_t *n_valid);   // rows = (batch element, new position < R)
+// Partial results of an attention over S key splits: [row][head][S][sal_part_pitch(d_h)] floats = d_h weighted values, the
+// running maximum (base 2) and the sum of weights.  The attention's rows are these, folded in ascending order.
+struct SalParts { const float *part; int S, n_heads, d_h; };
+__host__ __device__ constexpr int sal_part_pitch(int d_h) { return d_h + 4; }
+// parts (of M rows of Kd = n_heads * d_h) in the place of x: only where linear_takes_parts
 template <typename T>
 hipError_t launch_linear(hipStream_t st, const void *w0, const void *w1, const void *w2, int n_seg, int seg_rows, int Kd,
                          const float *x, int ldx, int M, const float *res, float *o0, float *o1, float *o2, int ldo,
-                         float *slabs = nullptr);
+                         float *slabs = nullptr, const SalParts *parts = nullptr);
+template <typename T> bool linear_takes_parts(int M, const SalParts &parts);
 template <typename T>
 hipError_t launch_gate_up(hipStream_t st, const amph_layer_w &lw, const float *x, int d, int f, int M, float eps,
                           float *act);
@@ -54,12 +60,16 @@ hipError_t draft_mm_lmhead(hipStream_t st, const void *W, int V, int Kd, const f
                            int *cand_i);
 
 // ---- small.hip (attention of the draft path, top-k, tree, accept, norms) ----
-// part: sal_part_floats(B, R, ...) floats for the key splits' partial results
 constexpr int SAL_MAX_SPLITS = 8;
 size_t sal_part_floats(int B, int R, int n_heads, int d_h, int max_kv);      // for any number of new positions up to R
+// key splits of the attention over R new positions of B sequences (last_only: over the last live one of each)
+int sal_key_splits(int B, int R, int last_only, int n_heads, int max_kv);
+// part: sal_part_floats(B, R, ...) floats for the key splits' partial results.  fold: they are folded into out; otherwise
+// (more than one split) the caller's next kernel takes them as they are.
 template <typename T>
 hipError_t launch_sal_attn(hipStream_t st, const float *qbuf, const void *kv_stage, const int32_t *sal_len, int B,
-                           int n_heads, int d_h, int max_kv, float *out, int R, const int32_t *n_valid, int last_only, float *part);
+                           int n_heads, int d_h, int max_kv, float *out, int R, const int32_t *n_valid, int last_only, float *part,
+                           bool fold);
 hipError_t launch_aeb_attn(hipStream_t st, const float *Q, const float *Kk, const float *V, int B, int K, int n_heads,
                            int d_h, float *ctx);
 // top-k of n_cand / k sorted lists of k (value, token) candidates per row (token < 0: none), one workgroup per row

@@ -191,7 +191,7 @@ __global__ __launch_bounds__(SA_WAVES * 64) void k_sal_attn(const float *qbuf, c
     if (S == 1) {
       out[(size_t)row * d + h * DH + e] = (lw > 0.f) ? ow / lw : 0.f;
     } else {
-      float *p = part + (((size_t)row * n_heads + h) * S + split) * (DH + 2);
+      float *p = part + (((size_t)row * n_heads + h) * S + split) * sal_part_pitch(DH);
       p[e] = ow;
       if (e == 0) { p[DH] = mw; p[DH + 1] = lw; }
     }
@@ -203,11 +203,11 @@ __global__ __launch_bounds__(SA_WAVES * 64) void k_sal_attn(const float *qbuf, c
 template <int DH>
 __global__ __launch_bounds__(DH) void k_sal_fold(const float *part, int n_heads, int S, float *out) {
   const int h = blockIdx.x, row = blockIdx.y, e = threadIdx.x;
-  const float *p = part + ((size_t)row * n_heads + h) * S * (DH + 2);
+  const float *p = part + ((size_t)row * n_heads + h) * S * sal_part_pitch(DH);
   float ov[SAL_MAX_SPLITS], mv[SAL_MAX_SPLITS], lv[SAL_MAX_SPLITS];
   #pragma unroll
   for (int s = 0; s < SAL_MAX_SPLITS; ++s) {
-    const float *ps = p + (size_t)min(s, S - 1) * (DH + 2);
+    const float *ps = p + (size_t)min(s, S - 1) * sal_part_pitch(DH);
     ov[s] = ps[e]; mv[s] = ps[DH]; lv[s] = ps[DH + 1];
   }
   float mw = NEG_BIG;
@@ -228,47 +228,54 @@ __global__ __launch_bounds__(DH) void k_sal_fold(const float *part, int n_heads,
 // for all but the first, and six queries' arithmetic would be the longest part: 32 heads, 5 positions, 1024 rows: five
 // workgroups per head 15.1 us, one with 8 key splits 11.8 + 4.8 for the fold), else as many as go together.
 static int sal_group(int B, int n_heads, int R) { return (R <= 1 || B * n_heads * R <= 256) ? 1 : R <= 3 ? 3 : 6; }
-// Key splits, of 128 rows or more, where they pay for the fold's launch: one workgroup per compute unit, of the small
+// Key splits, of 128 rows or more, where they pay for the fold: one workgroup per compute unit, of the small
 // ones (one position) two, from five splits on (one position, 208 workgroups of 2047 rows: 33.8 us whole, 35.6 + 4.9 in
-// two splits; 160 of 1024 rows 15.1, 11.2 + 4.9 in three; 32 of 1024 rows 15.8, 6.1 + 4.7 in eight).
+// two splits; 160 of 1024 rows 15.1, 11.2 + 4.9 in three; 32 of 1024 rows 15.8, 6.1 + 4.7 in eight).  The lengths are the
+// device's, so the rule reads the capacity, and a short context in a large cache pays for splits that it does not need
+// (whole drafts of one position, caches of 4096 rows, us whole / split: 7B, 100 rows 357 / 363, 600 367 / 367, 1000
+// 375 / 370, 4000 427 / 383; the float32 miniature 95 / 96, 106 / 99, 112 / 101, 164 / 109).
 static int sal_splits(int B, int n_groups, int n_heads, int max_kv, int rt) {
   const int s = std::min((rt == 1 ? 480 : 256) / (B * n_groups * n_heads), max_kv / 128);
   return (rt == 1 && s < 5) ? 1 : std::max(1, std::min(s, SAL_MAX_SPLITS));
+}
+int sal_key_splits(int B, int R, int last_only, int n_heads, int max_kv) {
+  const int rt = last_only ? 1 : sal_group(B, n_heads, R), n_groups = last_only ? 1 : (R + rt - 1) / rt;
+  return sal_splits(B, n_groups, n_heads, max_kv, rt);
 }
 size_t sal_part_floats(int B, int R, int n_heads, int d_h, int max_kv) {
   size_t most = 0;
   for (int r = 1; r <= R; ++r) {                            // any number of new positions up to R may be asked for
     const int rt = sal_group(B, n_heads, r), s = sal_splits(B, (r + rt - 1) / rt, n_heads, max_kv, rt);
-    if (s > 1) most = std::max(most, (size_t)B * r * n_heads * s * (d_h + 2));
+    if (s > 1) most = std::max(most, (size_t)B * r * n_heads * s * sal_part_pitch(d_h));
   }
   return most;
 }
 
 template <typename T, int DH>
 static hipError_t launch_sal_attn_dh(hipStream_t st, const float *qbuf, const T *kv_stage, const int32_t *sal_len, int B, int n_heads,
-                                     int max_kv, float *out, int R, const int32_t *n_valid, int last_only, float *part) {
+                                     int max_kv, float *out, int R, const int32_t *n_valid, int last_only, float *part, bool fold) {
   const int rt = last_only ? 1 : sal_group(B, n_heads, R), n_groups = last_only ? 1 : (R + rt - 1) / rt;
-  const int S = sal_splits(B, n_groups, n_heads, max_kv, rt);
+  const int S = sal_key_splits(B, R, last_only, n_heads, max_kv);
   const dim3 grid(n_heads, B * n_groups, S), block(SA_WAVES * 64);
   #define SA(RT_) hipLaunchKernelGGL((k_sal_attn<T, DH, RT_>), grid, block, 0, st, qbuf, kv_stage, sal_len, n_heads, max_kv, out, R, n_valid, \
                                      last_only, n_groups, part)
   if (rt == 1) SA(1); else if (rt == 3) SA(3); else SA(6);
   #undef SA
-  if (S > 1) hipLaunchKernelGGL((k_sal_fold<DH>), dim3(n_heads, last_only ? B : B * R), dim3(DH), 0, st, part, n_heads, S, out);
+  if (S > 1 && fold) hipLaunchKernelGGL((k_sal_fold<DH>), dim3(n_heads, last_only ? B : B * R), dim3(DH), 0, st, part, n_heads, S, out);
   return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_sal_attn(hipStream_t st, const float *qbuf, const void *kv_stage, const int32_t *sal_len, int B,
-                           int n_heads, int d_h, int max_kv, float *out, int R, const int32_t *n_valid, int last_only, float *part) {
-  if (d_h == 64) return launch_sal_attn_dh<T, 64>(st, qbuf, (const T *)kv_stage, sal_len, B, n_heads, max_kv, out, R, n_valid, last_only, part);
-  if (d_h == 128) return launch_sal_attn_dh<T, 128>(st, qbuf, (const T *)kv_stage, sal_len, B, n_heads, max_kv, out, R, n_valid, last_only, part);
+                           int n_heads, int d_h, int max_kv, float *out, int R, const int32_t *n_valid, int last_only, float *part, bool fold) {
+  if (d_h == 64) return launch_sal_attn_dh<T, 64>(st, qbuf, (const T *)kv_stage, sal_len, B, n_heads, max_kv, out, R, n_valid, last_only, part, fold);
+  if (d_h == 128) return launch_sal_attn_dh<T, 128>(st, qbuf, (const T *)kv_stage, sal_len, B, n_heads, max_kv, out, R, n_valid, last_only, part, fold);
   return hipErrorInvalidValue;
 }
 template hipError_t launch_sal_attn<float>(hipStream_t, const float *, const void *, const int32_t *, int, int, int, int,
-                                           float *, int, const int32_t *, int, float *);
+                                           float *, int, const int32_t *, int, float *, bool);
 template hipError_t launch_sal_attn<bf16_t>(hipStream_t, const float *, const void *, const int32_t *, int, int, int,
-                                            int, float *, int, const int32_t *, int, float *);
+                                            int, float *, int, const int32_t *, int, float *, bool);
 
 // =====================================================================================================
 // Eq. 5 core: for one (batch, head) the K x K score matrix of the K head positions, a row softmax
