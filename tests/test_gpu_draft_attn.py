@@ -46,7 +46,10 @@ def check_draft(cfg, n_new, max_kv, lens, live, check=None, seed=17):
         k0 = [rows[s][0].f32[b][:, :lens[b]] for s in range(2)]
         v0 = [rows[s][1].f32[b][:, :lens[b]] for s in range(2)]
         ref, k1, v1 = orc.draft_catchup(dwo, h[b, :live[b]], tok[b, :live[b]], k0, v0, n_h, cfg.topk, cfg.rms_eps, cfg.rope_theta)
-        worst = assert_rows_close(lg[b], ref["logits"], tol, f"logits of element {b}")
+        # float32 sums; in bf16 also the live new rows of the cache, rounded to 2^-9 of their values (the oracle keeps them whole),
+        # whose part in an attention over n rows of like weight goes with the root of their share
+        tight = 1e-5 if cfg.dtype == "f32" else 1e-5 + 3 * 2.0 ** -9 * (live[b] / (lens[b] + live[b])) ** 0.5
+        worst = assert_rows_close(lg[b], ref["logits"], tight, f"logits of element {b}")
         say(f"  element {b}: worst row error of the logits {worst:.2e}")
         for r in range(K):
             ok, bad = topk_consistent(np_of(idx)[b, r], np.asarray(ref["logits"][r]), cfg.topk, tol * np.abs(ref["logits"][r]).max())
@@ -75,3 +78,38 @@ MINI_64 = si.with_(si.MINI, name="mini_dh64", d_model=256, n_heads=4, head_dim=6
 ])
 def test_draft_with_key_splits(cfg, n_new, lens, live):
     check_draft(cfg, n_new, 1024, lens, live)
+
+
+# Many (head, sequence, position) triples: three or six positions share a workgroup's cache rows.
+def wide(name, n_h, d_h, base=si.MINI, K=4):
+    return si.with_(base, name=name, d_model=n_h * d_h, n_heads=n_h, head_dim=d_h, d_ffn=512, vocab=512, K=K)
+
+
+H16_64, H16_128 = wide("mini_16x64", 16, 64), wide("mini_16x128", 16, 128)
+F16_64, F16_128 = wide("tiny_16x64", 16, 64, si.TINY), wide("tiny_16x128", 16, 128, si.TINY)
+H16_K8 = wide("mini_16x64_k8", 16, 64, K=8)
+
+
+@pytest.mark.parametrize("cfg,n_new,max_kv,lens,live,check", [
+    # three positions together, one key split
+    (H16_64, 3, 96, [93, 0, 5, 31, 64, 17], [3, 3, 1, 2, 3, 2], None),
+    (H16_128, 3, 96, [40, 93, 1, 7, 15, 33], [2, 3, 3, 1, 3, 3], None),
+    (F16_64, 3, 96, [93, 0, 5, 31, 64, 17], [3, 3, 1, 2, 3, 2], None),
+    (F16_128, 3, 96, [40, 93, 1, 7, 15, 33], [2, 3, 3, 1, 3, 3], None),
+    # six (four, five of them taken), over four, two and one key splits
+    (H16_64, 5, 1024, [1019, 0, 700, 129], [5, 4, 1, 3], None),
+    (H16_128, 5, 512, [507, 2, 130, 61], [5, 5, 2, 4], None),
+    (F16_64, 4, 512, [508, 0, 63, 64, 200], [4, 4, 3, 2, 1], None),
+    (F16_128, 5, 256, [251, 33, 0, 128], [5, 3, 5, 1], None),
+    (H16_128, 5, 96, [91, 16, 17, 0], [5, 1, 4, 5], None),
+    # two groups of rows: six and one, six and three
+    (H16_K8, 9, 512, [503, 70], [9, 7], None),
+    (H16_K8, 9, 512, [100, 500], [6, 3], None),
+    (H16_K8, 7, 128, [121, 0, 50], [7, 6, 2], None),
+    # a batch of eight with 32 heads; one sequence of 52 heads on a long cache
+    (wide("mini_32x64", 32, 64), 5, 256, [251, 3, 100, 0, 64, 199, 17, 130], [5, 5, 1, 2, 3, 4, 5, 5], [0, 2, 3, 7]),
+    (wide("mini_52x64", 52, 64, K=5), 6, 1024, [700], [6], None),
+    (wide("mini_52x64", 52, 64, K=5), 6, 1024, [1018], [4], None),
+])
+def test_draft_with_positions_that_share_cache_rows(cfg, n_new, max_kv, lens, live, check):
+    check_draft(cfg, n_new, max_kv, lens, live, check)
