@@ -116,3 +116,69 @@ def test_draft_over_many_rows_matches_the_oracle(batch, n_new):
     args = (*args[:2], i32_to_dev(tok), *args[3:])
     ctx.amph_draft(*args, n_new=n_new, n_valid=i32_to_dev(live))
     assert ctx.device_status() == B.AMPH_DEV_BAD_TOKEN
+
+
+# Whole drafts at the widths where the launch rule takes two to six row blocks a workgroup and splits the axis, over one, two
+# and three tiles of 16 rows and over two launches.  The same values as a float32 model run on the vector kernels (which the
+# oracle's tests hold); what may differ is the bf16 rounding of the new cache rows.  Queries and keys of the adaptation layers
+# are of size 0.4, so that every row of a cache has a like weight and the new rows' rounding counts with their share; those of
+# the self-attention over the heads are small too (its softmax over rows of size 10 would magnify any difference).
+def device_draft_weights(d, n_h, f, V, K, seed):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    w = lambda *shape, std=0.02: torch.empty(shape, dtype=torch.bfloat16, device=DEV).normal_(0.0, std, generator=g)
+    small = 0.4 * d ** -0.5
+    gain = lambda: (1.0 + w(d).float() * 5).bfloat16()
+    layer = lambda: dict(rms1=gain(), wq=w(d, d, std=small), wk=w(d, d, std=small), wv=w(d, d), wo=w(d, d), rms2=gain(), w_gate=w(f, d), w_up=w(f, d), w_down=w(d, f))
+    return dict(embed=w(V, d), fc=[w(d, 2 * d) for _ in range(2)], sal=[layer() for _ in range(2)], mlp=w(K, d, d), pe=w(K, d),
+                aeb_wq=w(d, d, std=small / 10), aeb_wk=w(d, d, std=small / 10), aeb_wv=w(d, d), aeb_wo=w(d, d), lm_head=w(V, d))
+
+
+def to_float(x):
+    if isinstance(x, dict):
+        return {k: to_float(v) for k, v in x.items()}
+    return [to_float(v) for v in x] if isinstance(x, list) else x.float()
+
+
+@pytest.mark.parametrize("d,n_h,f,K,sizes", [
+    (2560, 20, 6912, 4, [(8, 5), (1, 3)]),
+    (3072, 24, 8192, 4, [(12, 4), (4, 5)]),
+    (4096, 32, 11008, 4, [(4, 5), (8, 5), (12, 4), (10, 5), (8, 1), (2, 1)]),
+    (5120, 40, 13824, 4, [(3, 5), (7, 5)]),
+    (6656, 52, 17920, 5, [(4, 6), (8, 6), (3, 1)]),
+], ids=["2560", "3072", "4096", "5120", "6656"])
+def test_draft_on_the_matrix_cores_against_the_vector_kernels(d, n_h, f, K, sizes):
+    V, topk, max_kv, d_h = 1000, 10, 416, d // n_h
+    wb = device_draft_weights(d, n_h, f, V, K, d)
+    models = {B.AMPH_BF16: wb, B.AMPH_F32: to_float(wb)}
+    for batch, n_new in sizes:
+        say(f"draft width {d}, {batch} sequences of {n_new} positions")
+        g = torch.Generator(device=DEV).manual_seed(batch * 100 + n_new)
+        lens = [400 - 37 * (b % 7) for b in range(batch)]
+        live = [1 + (3 * b + n_new - 1) % n_new for b in range(batch)]
+        h = torch.randn((batch, n_new, d), generator=g, device=DEV)
+        tok = torch.randint(0, V, (batch, n_new), generator=g, device=DEV, dtype=torch.int32)
+        cache = torch.randn((2, batch, 2, n_h, max_kv, d_h), generator=g, device=DEV).bfloat16()
+        got = {}
+        for code, w in models.items():
+            ctx = B.Context(d_model=d, n_heads=n_h, head_dim=d_h, d_ffn=f, vocab=V, K=K, topk=topk, max_tree=16, max_kv=max_kv,
+                            batch=batch, dtype=code, rms_eps=1e-6, rope_theta=10000.0, device=DEV)
+            kv, sal_len = cache.to(w["embed"].dtype), i32_to_dev(lens)
+            idx = torch.zeros((batch, K, topk), dtype=torch.int32, device=DEV)
+            val, logits = torch.zeros((batch, K, topk), device=DEV), torch.full((batch, K, V), float("nan"), device=DEV)
+            ctx.amph_draft(B.Context.draft_struct(w), h, tok, kv, sal_len, idx, val, logits, n_new=n_new, n_valid=i32_to_dev(live))
+            assert ctx.device_status() == 0
+            got[code] = (logits.double(), kv, val, idx, sal_len)
+        (lb, kb, vb, ib, nb), (lf, kf, _, _, nf) = got[B.AMPH_BF16], got[B.AMPH_F32]
+        assert torch.equal(nb, nf) and [int(n) for n in nb] == [n + r for n, r in zip(lens, live)]
+        # relative to a row's largest logit: float32 sums, and 2^-9 (three deviations) of the new rows' values by the root of their
+        # share in the attention, whose output over hundreds of rows is below a tenth of what it is added to
+        err = ((lb - lf).abs().amax(-1) / lf.abs().amax(-1)).amax()
+        say(f"  logits differ by {float(err):.2e}")
+        assert float(err) < 1e-5 + 0.1 * 3 * 2.0 ** -9 * (n_new / (min(lens) + n_new)) ** 0.5
+        assert torch.equal(vb.double(), torch.gather(lb, 2, ib.long())) and torch.equal(vb.double(), lb.topk(topk, -1).values)
+        for b in range(batch):
+            end = lens[b] + live[b]
+            a, c = kb[:, b, :, :, lens[b]:end].double(), kf[:, b, :, :, lens[b]:end].double()
+            assert float((a - c).abs().max()) <= 2.0 ** -8 * float(c.abs().max())          # the rounding to bf16 (half of it)
+            assert float((a - c).norm() / c.norm()) < 2.0 ** -8
+            assert torch.equal(kb[:, b, :, :, end:], cache[:, b, :, :, end:])              # rows of dead positions stay

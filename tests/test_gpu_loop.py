@@ -71,10 +71,9 @@ def test_commit_moves_the_accepted_rows_and_gathers_the_next_draft_inputs(cfg, T
 
 
 # ---------------------------------------------------------------------------- amph_draft over several new positions
-# five concatenated [h ; e] rows of this width do not fit in LDS as float32: Eq. 1's product then runs as two launches
-# over half the columns each
+# rows of Eq. 1 at a wide model (the vector kernels, which serve it in float32, take half its columns at a time)
 WIDE_FC = si.with_(si.MINI, name="mini_wide_fc", d_model=3584, n_heads=28, d_ffn=512, vocab=512)
-# five rows of this FFN width do not fit in LDS either: W_down's product runs as launches over slices of its columns
+# and of W_down at a wide FFN (in float32 slices of its columns)
 WIDE_FFN = si.with_(si.MINI, name="mini_wide_ffn", d_ffn=8192)
 
 

@@ -180,9 +180,8 @@ def test_draft_vicuna13b_shape():
 
 
 def test_draft_vicuna33b_shape_batch4():
-    """Configuration 5's draft module (d 6656, 52 x 128 heads, FFN 17920, K 5, batch 4, SAL cache 4096): the
-    float32 activation rows of a launch no longer fit in LDS for the widest matrices, so fc, W_down and the
-    head MLPs run as several launches over row ranges, and the 20 head rows as three groups."""
+    """Configuration 5's draft module (d 6656, 52 x 128 heads, FFN 17920, K 5, batch 4, SAL cache 4096): four rows in
+    the adaptation layers and 20 in the heads, on the matrix cores, in one pass over the weights each."""
     say("draft vicuna33b batch 4")
     cfgx, ctx, outs, got = run_draft(si.V33B, Bsz=4)
     check_draft(cfgx, outs, got)
