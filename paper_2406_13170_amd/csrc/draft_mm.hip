@@ -583,11 +583,9 @@ static hipError_t dm_launch(hipStream_t st, DmArgs a, int blocks, int groups) {
   if (e != hipSuccess || p.S == 1) return e;
   const int n = a.M * a.seg_rows;
   const dim3 grid((n / 4 + 255) / 256), block(256);
-  switch (p.S) {
-    case 2: hipLaunchKernelGGL((k_draft_fold<2>), grid, block, 0, st, a.slabs, n, a.res, a.o0); break;
-    case 4: hipLaunchKernelGGL((k_draft_fold<4>), grid, block, 0, st, a.slabs, n, a.res, a.o0); break;
-    default: hipLaunchKernelGGL((k_draft_fold<8>), grid, block, 0, st, a.slabs, n, a.res, a.o0); break;
-  }
+  static_assert(DRAFT_MM_SPLITS == 4, "the folds below");
+  if (p.S == 2) hipLaunchKernelGGL((k_draft_fold<2>), grid, block, 0, st, a.slabs, n, a.res, a.o0);
+  else hipLaunchKernelGGL((k_draft_fold<4>), grid, block, 0, st, a.slabs, n, a.res, a.o0);
   return hipGetLastError();
 }
 

@@ -742,13 +742,14 @@ static inline bool gv_pipe(int mm, int grid, size_t smem) {
     }                                                                                                       \
   } while (0)
 
-#define GV_DISPATCH_M(Mv, BODY)                                   \
-  switch (Mv) {                                                    \
-    case 1: { constexpr int MM = 1; BODY; } break;                 \
-    case 2: { constexpr int MM = 2; BODY; } break;                 \
-    case 3: case 4: { constexpr int MM = 4; BODY; } break;         \
-    case 5: { constexpr int MM = 5; BODY; } break;                 \
-    default: { constexpr int MM = 8; BODY; } break;                \
+// BODY with the instantiated row count for Mv rows; `most`: the largest that a launcher sends for its type (the rest is not built)
+#define GV_DISPATCH_M(Mv, most, BODY)                                                                    \
+  switch (Mv) {                                                                                           \
+    case 1: { constexpr int MM = 1; BODY; } break;                                                        \
+    case 2: { constexpr int MM = 2; BODY; } break;                                                        \
+    case 3: case 4: { constexpr int MM = 4; if constexpr (MM <= (most)) { BODY; } else return hipErrorInvalidValue; } break; \
+    case 5: { constexpr int MM = 5; if constexpr (MM <= (most)) { BODY; } else return hipErrorInvalidValue; } break;         \
+    default: { constexpr int MM = 8; if constexpr (MM <= (most)) { BODY; } else return hipErrorInvalidValue; } break;         \
   }
 
 template <typename T, typename Kern> static hipError_t gv_set_smem(Kern kern, size_t bytes) {
@@ -766,11 +767,12 @@ constexpr size_t DRAFT_MM_SMALL = (size_t)4 << 20;         // weights
 template <typename T> static inline bool use_mm(int M, size_t weights) {
   return sizeof(T) == 2 && (M >= DRAFT_MM_MIN || weights <= DRAFT_MM_SMALL);
 }
+template <typename T> constexpr int GV_MOST = sizeof(T) == 2 ? DRAFT_MM_MIN - 1 : 8;        // rows that are left for a vector kernel
+constexpr int LM_MOST_BF16 = 4;                            // and in the LM head
 // The LM head: its vector kernel stays ahead up to four rows as long as they leave room for two workgroups in a compute
 // unit's LDS (us over 4 rows, here / there: 32000 x 4096 45 / 52, 32000 x 6656 81 / 64).
 template <typename T> static inline bool use_mm_head(int M, int V, int Kd) {
-  return use_mm<T>(M, (size_t)V * Kd) && draft_mm_lmhead_wgs(V) <= LMTK_MAX_WG &&
-         (M > 4 || (size_t)V * Kd <= DRAFT_MM_SMALL || (size_t)M * Kd * 4 > 80 * 1024);
+  return use_mm<T>(M, (size_t)V * Kd) && (M > LM_MOST_BF16 || (size_t)V * Kd <= DRAFT_MM_SMALL || (size_t)M * Kd * 4 > 80 * 1024);
 }
 // rows of every launch when M rows are served in as few launches as possible, evenly
 static inline int mm_chunk(int M) {
@@ -815,7 +817,7 @@ hipError_t launch_fc_concat(hipStream_t st, const void *W, const float *u, const
     const int m = std::min(mc, M - m0);
     for (int half = halves ? 0 : -1; half < (halves ? 2 : 0); ++half) {
       hipError_t e = hipSuccess;
-      GV_DISPATCH_M(m, {
+      GV_DISPATCH_M(m, 8, {
         const size_t sm = gv_xs_bytes<T>(MM, halves ? d : 2 * d);
         GV_LAUNCH(k_fc_concat, gv_grid((d + 3) / 4, sm), sm, (const T *)W, u + (size_t)m0 * d, (const T *)embed, tok + m0, vocab, d, m,
                   out + (size_t)m0 * d, dev_status, half);
@@ -838,7 +840,7 @@ hipError_t launch_sal_qkv(hipStream_t st, const amph_layer_w &lw, const float *x
   for (int m0 = 0; m0 < M; m0 += mc) {
     const int m = std::min(mc, M - m0);
     hipError_t e = hipSuccess;
-    GV_DISPATCH_M(m, {
+    GV_DISPATCH_M(m, GV_MOST<T>, {
       const size_t sm = gv_xs_bytes<T>(MM, d) + 16;
       GV_LAUNCH(k_sal_qkv, gv_grid(3 * d / 4, sm), sm, (const T *)lw.wq, (const T *)lw.wk, (const T *)lw.wv, (const T *)lw.rms1,
                 x + (size_t)m0 * d, d, n_heads, d_h, m, eps, theta, sal_len, max_kv, (T *)kv_stage, qbuf + (size_t)m0 * d,
@@ -852,7 +854,7 @@ hipError_t launch_sal_qkv(hipStream_t st, const amph_layer_w &lw, const float *x
 // fold kernel of its own (see load_x_parts).  bf16 rows that the matrix cores serve arrive there by global-to-LDS loads.
 template <typename T> bool linear_takes_parts(int M, const SalParts &p) {
   const size_t fac = (size_t)M * p.n_heads * (SAL_MAX_SPLITS + 1) * sizeof(float);
-  return (sizeof(T) == 4 || M < DRAFT_MM_MIN) && M * p.n_heads * p.S <= GV_PARTS && gv_rows_per_launch(M, gv_xs_bytes<T>(1, p.n_heads * p.d_h), fac) >= M;
+  return M <= GV_MOST<T> && M * p.n_heads * p.S <= GV_PARTS && gv_rows_per_launch(M, gv_xs_bytes<T>(1, p.n_heads * p.d_h), fac) >= M;
 }
 
 template <typename T>
@@ -863,11 +865,9 @@ hipError_t launch_linear(hipStream_t st, const void *w0, const void *w1, const v
   if (parts) {
     if (n_seg != 1 || Kd != parts->n_heads * parts->d_h || !linear_takes_parts<T>(M, *parts)) return hipErrorInvalidValue;
     hipError_t e = hipSuccess;
-    GV_DISPATCH_M(M, {
-      if constexpr (sizeof(T) == 4 || MM < DRAFT_MM_MIN) {
-        const size_t sm = gv_xs_bytes<T>(MM, Kd) + (size_t)M * parts->n_heads * (SAL_MAX_SPLITS + 1) * sizeof(float);
-        GV_LAUNCH(k_linear_parts, gv_grid((seg_rows + 3) / 4, sm), sm, (const T *)w0, seg_rows, Kd, *parts, M, res, o0, ldo);
-      }
+    GV_DISPATCH_M(M, GV_MOST<T>, {
+      const size_t sm = gv_xs_bytes<T>(MM, Kd) + (size_t)M * parts->n_heads * (SAL_MAX_SPLITS + 1) * sizeof(float);
+      GV_LAUNCH(k_linear_parts, gv_grid((seg_rows + 3) / 4, sm), sm, (const T *)w0, seg_rows, Kd, *parts, M, res, o0, ldo);
     });
     return hipGetLastError();
   }
@@ -877,15 +877,15 @@ hipError_t launch_linear(hipStream_t st, const void *w0, const void *w1, const v
     MM_CHUNKS(draft_mm_linear(st, w0, w1, w2, n_seg, seg_rows, Kd, x + (size_t)m0 * ldx, ldx, m, res ? res + (size_t)m0 * ldo : nullptr,
                               o0 + (size_t)m0 * ldo, o1 ? o1 + (size_t)m0 * ldo : nullptr, o2 ? o2 + (size_t)m0 * ldo : nullptr, ldo,
                               slabs));
-  int mc = gv_rows_per_launch(M, gv_xs_bytes<T>(1, Kd), 0);
-  // Rows too wide for all of them (up to 8) to sit in LDS whole: cut the reduction axis into ks slices instead of
+  int mc = std::min(GV_MOST<T>, gv_rows_per_launch(M, gv_xs_bytes<T>(1, Kd), 0));
+  // Rows too wide for all of them (of a launch) to sit in LDS whole: cut the reduction axis into ks slices instead of
   // the rows into more launches, each of which would read the matrix again.
-  const int want = std::min(M, 8);
+  const int want = std::min(M, GV_MOST<T>);
   int ks = 1;
   if (mc < want) {
     for (int c = 2; c <= 8; c *= 2)
       if (Kd % (8 * c) == 0 && gv_rows_per_launch(M, gv_xs_bytes<T>(1, Kd / c), 0) >= want) { ks = c; break; }
-    if (ks > 1) mc = gv_rows_per_launch(M, gv_xs_bytes<T>(1, Kd / ks), 0);
+    if (ks > 1) mc = std::min(GV_MOST<T>, gv_rows_per_launch(M, gv_xs_bytes<T>(1, Kd / ks), 0));
   }
   if (mc < 1) return hipErrorInvalidValue;
   const int Kq = Kd / ks;
@@ -895,7 +895,7 @@ hipError_t launch_linear(hipStream_t st, const void *w0, const void *w1, const v
     for (int kq = 0; kq < ks; ++kq) {
       const size_t ko = (size_t)kq * Kq;
       hipError_t e = hipSuccess;
-      GV_DISPATCH_M(m, {
+      GV_DISPATCH_M(m, GV_MOST<T>, {
         const size_t sm = gv_xs_bytes<T>(MM, Kq);
         GV_LAUNCH(k_linear, gv_grid(n_seg * ((seg_rows + 3) / 4), sm), sm, (const T *)w0 + ko, w1 ? (const T *)w1 + ko : nullptr,
                   w2 ? (const T *)w2 + ko : nullptr, n_seg, seg_rows, Kq, x + (size_t)m0 * ldx + ko, ldx, m,
@@ -917,7 +917,7 @@ hipError_t launch_gate_up(hipStream_t st, const amph_layer_w &lw, const float *x
   for (int m0 = 0; m0 < M; m0 += mc) {
     const int m = std::min(mc, M - m0);
     hipError_t e = hipSuccess;
-    GV_DISPATCH_M(m, {
+    GV_DISPATCH_M(m, GV_MOST<T>, {
       const size_t sm = gv_xs_bytes<T>(MM, d) + 16;
       GV_LAUNCH(k_gate_up, gv_grid((f + 1) / 2, sm), sm, (const T *)lw.w_gate, (const T *)lw.w_up, (const T *)lw.rms2,
                 x + (size_t)m0 * d, d, f, m, eps, act + (size_t)m0 * f);
@@ -944,7 +944,7 @@ hipError_t launch_head_mlp(hipStream_t st, const void *w_mlp, const void *pe, co
       const int k0 = (by_source && part == 1) ? K / 2 : 0;
       const int nk = !by_source ? K : (part == 0 ? K / 2 : K - K / 2);
       hipError_t e = hipSuccess;
-      GV_DISPATCH_M(m, {
+      GV_DISPATCH_M(m, GV_MOST<T>, {
         const size_t sm = (by_source ? 1 : 2) * gv_xs_bytes<T>(MM, d);
         GV_LAUNCH(k_head_mlp, gv_grid(nk * ((d + 3) / 4), sm), sm, (const T *)w_mlp, (const T *)pe, h1 + (size_t)m0 * d,
                   h2 + (size_t)m0 * d, d, K, m, Hp + (size_t)m0 * K * d, k0, nk);
@@ -989,7 +989,7 @@ hipError_t launch_lmhead_cands(hipStream_t st, const void *W, int V, int Kd, con
   for (int m0 = 0; m0 < M; m0 += mc) {
     const int m = std::min(mc, M - m0);
     hipError_t e = hipSuccess;
-    GV_DISPATCH_M(m, {
+    GV_DISPATCH_M(m, (sizeof(T) == 2 ? LM_MOST_BF16 : 8), {
       const size_t sm = gv_xs_bytes<T>(MM, Kd) + (size_t)MM * Gp * GV_R * sizeof(float);
       GV_LAUNCH(k_lmhead_topk, n_wg, sm, (const T *)W, V, Kd, x + (size_t)m0 * Kd, m, Gp, k,
                 logits ? logits + (size_t)m0 * V : nullptr, cand_v + (size_t)m0 * n_wg * k, cand_i + (size_t)m0 * n_wg * k);

@@ -26,8 +26,6 @@ constexpr int SA_WAVES = 8;
 // 2^x by the hardware instruction alone: arguments here are at most 0, and what would be below the normal range may be 0
 __device__ __forceinline__ float sa_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// sum over groups of LPR adjacent lanes, in every lane: neighbour at distance 1, 2, then mirror inside 8 and inside 16
-// lanes, each one vector instruction (a cross-lane permute goes through LDS)
 template <bool V> struct BoolTag { static constexpr bool value = V; };
 // op of a lane's value and the one 16 (32) lanes further on, modulo 32 (64): the row swap of a register with itself leaves
 // the even rows (the lower half) in one result and the odd ones (the upper half) in the other
@@ -39,6 +37,8 @@ template <typename F> __device__ __forceinline__ float sa_xor32(float v, F op) {
   const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return op(__uint_as_float(p[0]), __uint_as_float(p[1]));
 }
+// sum over groups of LPR adjacent lanes, in every lane: neighbour at distance 1, 2, then mirror inside 8 and inside 16
+// lanes, each one vector instruction (a cross-lane permute goes through LDS)
 template <int LPR> __device__ __forceinline__ float sa_group_sum(float v) {
   #define SA_DPP(CTRL) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true))
   SA_DPP(0xb1);                          // quad_perm [1, 0, 3, 2]
@@ -330,77 +330,14 @@ hipError_t launch_aeb_attn(hipStream_t st, const float *Q, const float *Kk, cons
 }
 
 // =====================================================================================================
-// Per-row top-k (Eq. 6).  "Better" means a larger value, or the same value and a smaller index, so results are sorted
-// and ties deterministic.
+// Top-k of the draft's rows (Eq. 6) and argmax of the target's.  "Better" means a larger value, or the same value and a
+// smaller index, so results are sorted and ties deterministic.
 // =====================================================================================================
 // Cache length of element i after its new rows: advanced only when every new row fitted (the kernels that write
 // the rows skipped those past the limit and raised the overflow flag; the length then stays where it was).
 __device__ __forceinline__ void advance_one(int32_t *len, int i, int by, int limit) {
   const int v = len[i];
   if (v >= 0 && by >= 0 && v + by <= limit) len[i] = v + by;
-}
-
-// One workgroup of 1024 threads per row for vocabularies up to 65536: every thread keeps NPT logits (element
-// j * 1024 + tid in slot j) and its own best; k rounds of (wave butterfly, 16 wave winners through LDS, every wave
-// folds them again) pick the winners, and only the thread that owned a winner rescans its slots.
-template <int NPT>
-__global__ __launch_bounds__(1024) void k_topk_row(const float *logits, int V, int k, int32_t *idx, float *val,
-                                                   int32_t *advance, int n_advance, int advance_by,
-                                                   const int32_t *advance_each, int advance_limit) {
-  __shared__ float sm_v[16];
-  __shared__ int sm_i[16];
-  const float NEG_INF = -__builtin_huge_valf();
-  const int NONE = 0x7fffffff;
-  const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const float *src = logits + (size_t)row * V;
-  float x[NPT];
-  unsigned long long alive = 0ull;
-  #pragma unroll
-  for (int j = 0; j < NPT; ++j) {
-    const int e = j * 1024 + tid;
-    x[j] = src[min(e, V - 1)];                            // unconditional loads from clamped addresses
-    if (e < V) alive |= 1ull << j;
-  }
-  float bv; int bi;
-  auto rescan = [&]() {
-    bv = NEG_INF; bi = NONE;
-    #pragma unroll
-    for (int j = 0; j < NPT; ++j)
-      if (((alive >> j) & 1ull) && better(x[j], j * 1024 + tid, bv, bi)) { bv = x[j]; bi = j * 1024 + tid; }
-  };
-  rescan();
-  for (int r = 0; r < k; ++r) {
-    float wv = bv; int wi = bi;
-    #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      const float ov = __shfl_xor(wv, off, WAVE);
-      const int oi = __shfl_xor(wi, off, WAVE);
-      if (better(ov, oi, wv, wi)) { wv = ov; wi = oi; }
-    }
-    if (lane == 0) { sm_v[wave] = wv; sm_i[wave] = wi; }
-    __syncthreads();
-    float gv = (lane < 16) ? sm_v[lane] : NEG_INF;
-    int gi = (lane < 16) ? sm_i[lane] : NONE;
-    #pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) {
-      const float ov = __shfl_xor(gv, off, WAVE);
-      const int oi = __shfl_xor(gi, off, WAVE);
-      if (better(ov, oi, gv, gi)) { gv = ov; gi = oi; }
-    }
-    gv = __shfl(gv, 0, WAVE);
-    gi = __shfl(gi, 0, WAVE);
-    if (tid == 0) {
-      if (idx) idx[(size_t)row * k + r] = (gi == NONE) ? -1 : gi;
-      if (val) val[(size_t)row * k + r] = gv;
-    }
-    if (gi != NONE && gi == bi) {                          // this thread owned the winner: retire it and rescan
-      alive &= ~(1ull << (gi >> 10));
-      rescan();
-    }
-    __syncthreads();                                       // the wave winners are rewritten in the next round
-  }
-  if (row == 0 && advance)
-    for (int i = tid; i < n_advance; i += 1024) advance_one(advance, i, advance_each ? advance_each[i] : advance_by, advance_limit);
 }
 
 // Top-k of the candidates the fused LM head left: per row n_lists lists of k (value, token) pairs, each sorted (best
@@ -487,12 +424,44 @@ hipError_t launch_topk_merge(hipStream_t st, const float *cand_v, const int *can
   return hipGetLastError();
 }
 
+// Argmax of a row of up to 65536 logits (amph_accept with logits): 1024 threads, each the best of its NPT logits (all requested
+// before the first is used; element j * 1024 + tid in slot j), folded in the wave and through LDS.  -1 if there are only NaN.
+template <int NPT>
+__global__ __launch_bounds__(1024) void k_row_argmax(const float *logits, int V, int32_t *out) {
+  __shared__ float sm_v[16];
+  __shared__ int sm_i[16];
+  const int NONE = 0x7fffffff;
+  const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const float *src = logits + (size_t)row * V;
+  float x[NPT];
+  #pragma unroll
+  for (int j = 0; j < NPT; ++j) x[j] = src[min(j * 1024 + tid, V - 1)];        // unconditional loads from clamped addresses
+  float bv = -__builtin_huge_valf(); int bi = NONE;
+  #pragma unroll
+  for (int j = 0; j < NPT; ++j)
+    if (j * 1024 + tid < V && better(x[j], j * 1024 + tid, bv, bi)) { bv = x[j]; bi = j * 1024 + tid; }
+  auto fold = [&](int from) {
+    #pragma unroll
+    for (int off = from; off >= 1; off >>= 1) {
+      const float ov = __shfl_xor(bv, off, WAVE);
+      const int oi = __shfl_xor(bi, off, WAVE);
+      if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+    }
+  };
+  fold(32);
+  if (lane == 0) { sm_v[wave] = bv; sm_i[wave] = bi; }
+  __syncthreads();
+  if (wave > 0) return;
+  bv = sm_v[lane & 15]; bi = sm_i[lane & 15];
+  fold(8);
+  if (lane == 0) out[row] = (bi == NONE) ? -1 : bi;
+}
+
 hipError_t launch_row_argmax(hipStream_t st, const float *logits, int rows, int V, int32_t *out) {
   if (rows < 1 || V < 1 || V > 65536) return hipErrorInvalidValue;
-  #define TK_ROW(N) hipLaunchKernelGGL((k_topk_row<N>), dim3(rows), dim3(1024), 0, st, logits, V, 1, out, (float *)nullptr, \
-                                       (int32_t *)nullptr, 0, 0, (const int32_t *)nullptr, 0)
-  if (V <= 8192) TK_ROW(8); else if (V <= 16384) TK_ROW(16); else if (V <= 32768) TK_ROW(32); else TK_ROW(64);
-  #undef TK_ROW
+  #define ROW_ARGMAX(N) hipLaunchKernelGGL((k_row_argmax<N>), dim3(rows), dim3(1024), 0, st, logits, V, out)
+  if (V <= 8192) ROW_ARGMAX(8); else if (V <= 16384) ROW_ARGMAX(16); else if (V <= 32768) ROW_ARGMAX(32); else ROW_ARGMAX(64);
+  #undef ROW_ARGMAX
   return hipGetLastError();
 }
 
