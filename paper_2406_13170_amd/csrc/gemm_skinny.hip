@@ -450,7 +450,7 @@ constexpr int gw_steps(int np) { return np > 3 ? 4 : 8; }   // steps (64 bytes o
 constexpr int GW_R = 3;            // weight stages in the LDS ring
 constexpr int GW_NL = 2;           // loader waves
 constexpr int GW_MAX_NP = 5;       // pairs of weight row blocks per workgroup with a tile per wave
-constexpr int GW_MAX_NP_QKV = 4;   // ... with the rotation epilogue, which needs more registers
+constexpr int GW_MAX_NP_QKV = 4;   // ... with the rotation epilogue (five pairs are not built for it)
 constexpr int GW_MAX_NP2 = 3;      // ... with two tiles per wave
 constexpr int GW_MAX_NW1 = 12;     // math waves per workgroup with a tile of 32 activation rows each (three waves per SIMD)
 constexpr int GW_MAX_NW = 8;       // ... with two tiles each (two waves per SIMD)
@@ -621,35 +621,38 @@ __global__ __launch_bounds__(64 * (NWMAX + GW_NL)) void k_gemm_wide(const GemmAr
   // free by now), one tile of 32 rows at a time, the 64 lanes playing the workgroup of the shared epilogue code.
   // Lane (half, r32) holds activation row t * 32 + r32 and weight rows (i / 4) * 8 + half * 4 + (i % 4) of each pair.
   const int CT_PITCH = 16 * NB + 4;
-  // As many waves at a time as there is room for.
+  // As many waves at a time as there is room for, in rounds; every wave passes each round's barrier.  A wave's own part is
+  // straight-line code between its barriers: inside a loop over the rounds its accumulators would stay live across the
+  // epilogue (QKV: up to 93 registers spilled; us, inside a loop / here: 33B over 384 rows 146 / 136, 7B over 512 71 / 67,
+  // 13B over 512 97 / 95).
   constexpr int EW = gw_epi_waves(NP, NWMAX);
-  for (int w0 = 0; w0 < nw; w0 += EW) {
-    __syncthreads();                                         // every wave has left the ring (the waves before, their regions)
-    if (wave >= w0 && wave < min(w0 + EW, nw) && live(0)) {  // whole waves
-      float *Ct = reinterpret_cast<float *>(gw_lds) + (size_t)(wave - w0) * 32 * CT_PITCH;
-      const int half = lane >> 5, r32 = lane & 31;
-      #pragma unroll
-      for (int t = 0; t < TW; ++t) {
-        if (!live(t)) break;                                 // (wave-uniform)
-        if (t > 0) {                                         // the lanes are done reading the tile before
-          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-          __builtin_amdgcn_wave_barrier();
-          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        }
-        #pragma unroll
-        for (int pr = 0; pr < NP; ++pr)
-          #pragma unroll
-          for (int q4 = 0; q4 < 4; ++q4) {
-            const f32x4 v = {acc[pr][t][4 * q4], acc[pr][t][4 * q4 + 1], acc[pr][t][4 * q4 + 2], acc[pr][t][4 * q4 + 3]};
-            *reinterpret_cast<f32x4 *>(Ct + r32 * CT_PITCH + pr * 32 + q4 * 8 + half * 4) = v;
-          }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the wave's LDS writes before its lanes read each other's
+  const int rounds = EW >= NWMAX ? 1 : (nw + EW - 1) / EW, mine = wave < nw ? (EW >= NWMAX ? 0 : wave / EW) : rounds - 1;
+  for (int r = 0; r <= mine; ++r) __syncthreads();         // every wave has left the ring (the waves of the rounds before, their regions)
+  if (wave < nw && live(0)) {                              // whole waves
+    float *Ct = reinterpret_cast<float *>(gw_lds) + (size_t)(wave - mine * EW) * 32 * CT_PITCH;
+    const int half = lane >> 5, r32 = lane & 31;
+    #pragma unroll
+    for (int t = 0; t < TW; ++t) {
+      if (!live(t)) break;                                 // (wave-uniform)
+      if (t > 0) {                                         // the lanes are done reading the tile before
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        gemm_epilogue<T, EPI>(a, Ct, CT_PITCH, tile, NB, tile_of(t) * 32, split, nblk, lane, WAVE, 32);
       }
+      #pragma unroll
+      for (int pr = 0; pr < NP; ++pr)
+        #pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const f32x4 v = {acc[pr][t][4 * q4], acc[pr][t][4 * q4 + 1], acc[pr][t][4 * q4 + 2], acc[pr][t][4 * q4 + 3]};
+          *reinterpret_cast<f32x4 *>(Ct + r32 * CT_PITCH + pr * 32 + q4 * 8 + half * 4) = v;
+        }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the wave's LDS writes before its lanes read each other's
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      gemm_epilogue<T, EPI>(a, Ct, CT_PITCH, tile, NB, tile_of(t) * 32, split, nblk, lane, WAVE, 32);
     }
   }
+  for (int r = mine + 1; r < rounds; ++r) __syncthreads();
 }
 
 // Row-major -> tiled (see the layout above).  One thread per 16-byte piece of the tiled buffer.
