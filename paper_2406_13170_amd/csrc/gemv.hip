@@ -1,6 +1,7 @@
 // Weight-streaming GEMV family for the draft path (Sec. 3.1 Eq. 1, Sec. 3.2 Eq. 2-6): M <= 8
-// activation rows against a [N, Kd] weight matrix that is read exactly once from HBM.  It serves float32 weights and,
-// in bf16, one or two rows (use_mm below says where the matrix-core form of draft_mm.hip takes over).
+// activation rows against a [N, Kd] weight matrix that is read exactly once from HBM.  It serves float32 weights and, in
+// bf16, one or two rows of a large matrix, up to four in the LM head, and Eq. 1 at widths that are no multiple of 256
+// (use_mm and use_mm_head below say where the matrix-core form of draft_mm.hip takes over).
 //
 // Shape of every kernel here: a 256-thread workgroup first parks the M activation rows in LDS as
 // float32 (after the prologue: concat with the token embedding, or RMSNorm scaling), then each of
@@ -84,13 +85,14 @@ template <typename P> __device__ __forceinline__ P *pick3(int i, P *a, P *b, P *
   return (P *)v;
 }
 
-// With five or more activation rows a batch of fragments takes about as long to multiply as to fetch, and the rows
-// in LDS leave room for one workgroup per compute unit only, so nothing else would cover the fetch: those
-// instantiations keep two batches per wave and always have the next one on its way, across row groups as well
-// (measured with 5 bf16 rows at 7B shapes: gate/up 77.8 -> 62.7 us, the three SAL projections 45.2 -> 46.7, Wo / down
-// 17.5 -> 16.5).  With fewer rows several workgroups share a compute unit and a second batch per wave gains nothing
-// (1 row) or loses (4 rows: the LM head 52.9 -> 60.5 us).
-template <int M> struct GvPipe { static constexpr bool on = (M >= 5); };
+// With many activation rows a batch of fragments takes about as long to multiply as to fetch, and the rows in LDS leave room
+// for one workgroup per compute unit only, so nothing else would cover the fetch: those instantiations keep two batches per
+// wave and always have the next one on its way, across row groups as well.  In float32 from eight rows on (us, one batch /
+// two: 11264 x 2048 27.5 / 25.4, 12288 x 2560 33.2 / 31.4, though 16384 x 1024 24.1 / 27.7; five rows 20.1 / 23.7,
+// 25.1 / 29.6, 17.8 / 23.5).  In bf16, which has half the fragments a row, from five on (gate/up at 7B widths 77.8 / 62.7;
+// only Eq. 1 at widths that are no multiple of 256 comes here with so many).  With fewer rows several workgroups share a
+// compute unit and a second batch per wave gains nothing (1 row) or loses (4 rows: the LM head 52.9 / 60.5 us).
+template <typename T, int M> struct GvPipe { static constexpr bool on = M >= (sizeof(T) == 2 ? 5 : 8); };
 
 // The weight fragments a wave holds: one batch, or two when pipelined.  In the pipelined form w0 always holds (or
 // awaits) the first batch of the group that is multiplied next.
@@ -719,11 +721,10 @@ template <typename T> static inline size_t gv_xs_bytes(int M, int Kd) {
   return (size_t)M * ((Kd + CH - 1) / CH) * CH * sizeof(float);
 }
 
-// Two batches of fragments per wave (see GvPipe): always from five rows on; for fewer rows where a compute unit gets
-// a single workgroup, whose four waves would otherwise each wait out every round trip with nothing else to run:
+// Two batches of fragments per wave (see GvPipe) for fewer rows: where a compute unit gets a single workgroup, whose four waves would otherwise each wait out every round trip with nothing else to run:
 // because the matrix has so few row groups, or because the rows of a wide model fill more than half the LDS.
-static inline bool gv_pipe(int mm, int grid, size_t smem) {
-  return mm >= 5 || grid <= 256 || 2 * smem > 160 * 1024;
+static inline bool gv_pipe(int grid, size_t smem) {
+  return grid <= 256 || 2 * smem > 160 * 1024;
 }
 
 // launch KERN<T, MM, pipelined or not> (MM, e, st from the enclosing launcher)
@@ -731,11 +732,11 @@ static inline bool gv_pipe(int mm, int grid, size_t smem) {
   do {                                                                                                      \
     const int grid_ = (GRID);                                                                               \
     const size_t sm_ = (SM);                                                                                \
-    if (gv_pipe(MM, grid_, sm_)) {                                                                          \
+    if (GvPipe<T, MM>::on || gv_pipe(grid_, sm_)) {                                                                          \
       e = gv_set_smem<T>(KERN<T, MM, true>, sm_);                                                           \
       if (e != hipSuccess) return e;                                                                        \
       hipLaunchKernelGGL((KERN<T, MM, true>), dim3(grid_), dim3(GV_THREADS), sm_, st, __VA_ARGS__);         \
-    } else if constexpr (!GvPipe<MM>::on) {                                                                 \
+    } else if constexpr (!GvPipe<T, MM>::on) {                                                                 \
       e = gv_set_smem<T>(KERN<T, MM, false>, sm_);                                                          \
       if (e != hipSuccess) return e;                                                                        \
       hipLaunchKernelGGL((KERN<T, MM, false>), dim3(grid_), dim3(GV_THREADS), sm_, st, __VA_ARGS__);        \
