@@ -130,9 +130,10 @@ amph_status amph_device_status(amph_ctx *ctx, uint32_t *host_bits);
  * adaptation layers first catch up over the a + 1 new positions, oldest first (each row attends to the
  * cache and to the new rows before it); the heads read the LAST live position.
  *   h_new    [B, n_new, d] float32     tok_new [B, n_new] int32 (the token that follows each position)
- *            1 <= n_new <= K + 1.  With bf16 weights a pass over a weight matrix serves up to 48 rows (B * n_new); in
- *            float32 it serves 8 (fewer where 8 rows of the model width do not fit in 128 KB of LDS and the kernel has a
- *            fused epilogue), and a call with more rows streams the weights that many times.
+ *            1 <= n_new <= K + 1.  With bf16 weights a pass over a weight matrix serves up to 48 rows (B * n_new; Eq. 1's
+ *            matrices where d_model is a multiple of 256); in float32, and for Eq. 1 at other widths, it serves 8 (fewer
+ *            where 8 rows of the model width do not fit in 128 KB of LDS and the kernel has a fused epilogue).  A call with
+ *            more rows streams the weights that many times.
  *   n_valid  [B] int32 on the device or NULL: positions j >= n_valid[b] of element b are ignored (no
  *            cache row, no effect on the heads); NULL = all n_new live.  amph_commit writes such a triple.
  *   sal_kv   [2 stages, B, 2 (K then V), n_heads, max_kv, head_dim] T; rows sal_len[b] + j of both stages
@@ -144,7 +145,7 @@ amph_status amph_device_status(amph_ctx *ctx, uint32_t *host_bits);
  * Device-side errors: a new position j whose cache row sal_len[b] + j would lie at or beyond max_kv writes
  * no cache row and raises AMPH_DEV_SAL_OVERFLOW (rows below it are still written); sal_len[b] is then left
  * unchanged and the top-k written for element b is meaningless.  A token id outside [0, V) raises
- * AMPH_DEV_BAD_TOKEN and is read as token 0. */
+ * AMPH_DEV_BAD_TOKEN; its embedding counts as zero. */
 amph_status amph_draft(amph_ctx *ctx, const amph_draft_w *w /* host */, const float *h_new,
                        const int32_t *tok_new, int n_new, const int32_t *n_valid, void *sal_kv,
                        int32_t *sal_len, int32_t *topk_idx, float *topk_val, float *logits,
@@ -325,7 +326,9 @@ amph_status amph_profile_kind(amph_ctx *ctx, int kind, int max_launches, int eve
 amph_status amph_profile_read(amph_ctx *ctx, double *total_ms /* host */, int *launches /* host */);
 
 /* ---- single linear layers, exported for per-kernel parity tests and micro-benchmarks ------------
- * amph_gemv: y[m, n] = sum_k x[m, k] W[n, k] for m < M <= 8 (weight-streaming vector kernel).
+ * amph_gemv: y[m, n] = sum_k x[m, k] W[n, k] for m < M <= 8, as the draft's projections compute it: on the vector ALU in
+ *   float32 and, in bf16, for one or two rows against more than 4 M weights; otherwise on the matrix cores, the float32 rows
+ *   in three bf16 pieces (rows that do not begin on a 16-byte boundary: on the vector ALU, two at a time).
  *   x [M, Kd] float32, W [N, Kd] T, y [M, N] float32.  Kd must be a multiple of 8.
  * amph_gemm: same contraction on the matrix cores for any M; x [M, Kd] T, y [M, N] float32.
  *   A row of x must be a multiple of 64 bytes (Kd % 32 == 0 in bf16, % 16 in float32).

@@ -11,8 +11,11 @@
 // sum by the vector ALU, which rounds to nearest; and every other wave multiplies the negated weights, so that what is
 // left of the bias cancels in the sum over the waves.
 //
-// Shape.  A workgroup owns NB row blocks of 16 weight rows, all activation rows (NT tiles of 16) and the whole
-// reduction axis.  Its waves have two roles:
+// Weights are finite (as gemv.hip takes them to be: its padding multiplies them by zero too); an infinite or NaN activation
+// gives what it gives there.
+//
+// Shape.  A workgroup owns NB row blocks of 16 weight rows, all activation rows (NT tiles of 16) and the whole reduction axis,
+// or one of up to DRAFT_MM_SPLITS parts of it (dm_pick), whose sums k_draft_fold adds up.  Its waves have two roles:
 //   * 2 loader waves stream the weight rows from HBM and the activation rows from L2 into a ring of LDS stages
 //     (global-to-LDS loads).  A matrix-core operand fragment is 16 rows x 64 bytes; fetched from row-major rows directly
 //     it is 16 half cache lines per load, which a CU's vector L1 serves at a quarter of the rate of whole lines.  So a
@@ -20,8 +23,8 @@
 //     way in (piece p of row r at slot p ^ (r % 16)) so that the fragment reads from LDS are free of bank conflicts.
 //     The activations travel in the same ring because a CU's loads return in order: fetched into registers by the math
 //     waves they queue behind the ring's worth of weights in flight (7B W_down over 5 rows: 53 us).
-//   * KW math waves split the reduction axis: wave w takes step w (64 bytes of a weight row) of every stage, against all
-//     NB blocks and NT tiles, so each activation element is read from LDS and cut into its pieces once per workgroup.  A
+//   * KW math waves split the reduction axis: wave w takes step w (64 bytes of a weight row) of every stage (and step w + KW
+//     of a stage of 1024 bytes), against all NB blocks and NT tiles, so each activation element is read from LDS and cut into its pieces once per workgroup.  A
 //     step costs about 75 vector instructions per tile whatever NB is; that sets the pace of launches with one or two
 //     row blocks per workgroup (reading the next step's operands ahead of this one's arithmetic changed nothing).
 // The KW partial sums meet in LDS after the loop and are added in a fixed order; RMSNorm's 1/rms of a row is

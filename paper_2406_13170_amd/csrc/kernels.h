@@ -7,7 +7,7 @@ namespace amph {
 
 constexpr size_t GV_MAX_SMEM = 128 * 1024;    // dynamic LDS a GEMV workgroup may ask for (gfx950: 160 KB per workgroup)
 
-// ---- gemv.hip (draft path, M <= 8 rows) ----
+// ---- gemv.hip (draft path: any number of rows; launches of up to 8, or draft_mm.hip) ----
 template <typename T>
 hipError_t launch_fc_concat(hipStream_t st, const void *W, const float *u, const void *embed, const int32_t *tok,
                             int vocab, int d, int M, float *out, uint32_t *dev_status, float *slabs);   // slabs: see draft_mm_fc
