@@ -434,10 +434,9 @@ __global__ __launch_bounds__(64 * (GM_MAX_NB + GM_NLW)) void k_gemm_skinny(const
 // What bounds it is what a compute unit takes in, 40 to 50 GB/s of weights and activations together: a workgroup reads its
 // group's activations for its NB blocks only, (32 gt + 16 NB) bytes against 512 gt NB products.  One tile per wave
 // halves the accumulators, so that up to ten blocks fit in the registers of eight to twelve waves, where two tiles
-// per wave ended at six: 384 rows, 35840 x 6656 (10 blocks) 229 -> 184 us = 1.0 PFLOP/s, 32000 x 6656 (8) 192 -> 167,
-// 6656 x 17920 (8, four splits) 123 -> 107; 512 rows in two groups, 32000 x 4096 (8) 158 -> 141, 12288 x 4096 (6)
-// 73 -> 64, 4096 x 11008 (8) 60 -> 52; 128 rows, against the skinny kernel, 27648 x 5120 84 -> 61, 32000 x 5120 95 -> 67,
-// 35840 x 6656 135 -> 104, 32000 x 6656 119 -> 82, 6656 x 17920 72 -> 55, but 12288 x 4096 36 -> 39.
+// per wave ended at six: 384 rows, 35840 x 6656 (10 blocks) 224 -> 182 us = 1.0 PFLOP/s, 32000 x 6656 (8) 189 -> 160;
+// 512 rows in two groups, 32000 x 4096 (8) 152 -> 134, 12288 x 4096 (6) 70 -> 66; 128 rows, against the skinny kernel,
+// 27648 x 5120 84 -> 63, 32000 x 5120 97 -> 67, 35840 x 6656 134 -> 100, 32000 x 6656 121 -> 82.
 // A 32 x 32 instruction takes, per lane (half, r), 16 bytes of row r: the bytes [half * 16, half * 16 + 16) of
 // 32 bytes of k.  The weight fragments in LDS are the 16-row x 64-byte ones of the tiled layout, piece (g, r16)
 // at (g * 16 + r16) * 16: lane (half, r) of half-step h reads piece (2h + half, r % 16) of block r / 16 of the
@@ -817,8 +816,8 @@ static GemmPlan plan_wide(int epi, int seg_rows, int Kd, int elem_bytes, int M, 
 // whichever kernel runs and however the weights are stored: tiled and row-major weights give the same bits there.  Beyond
 // (tiled weights) it weighs, in units of a weight fragment, a workgroup's steps times its fragments per step and the tiles
 // that its busiest SIMD carries, for groups of up to 8, 12 (three a wave) or 16 tiles, against the slabs' way out and back.
-// Finer splits would gain a little with the wide kernel's present tiles (us, GEMM and fold together: W_down at 384 rows,
-// 33B, four slabs instead of two 129 + 11 against 138 + 6; 512 rows, 7B, 59 + 9 against 63 + 5) and change every result.
+// Finer splits would suit the wide kernel's present tiles (us: W_down at 384 rows, 33B, four slabs 110, two 122, each fold
+// 16 against 14; 512 rows, 7B, 52 and 62, folds 13 against 12) and change every result.
 static int gemm_split(int epi, int seg_rows, int Kd, int elem_bytes, int M, bool tiled) {
   if (epi != EPI_STORE) return 1;                           // fused epilogues need complete sums
   if (!tiled || M <= 2 * GM_BM) return plan_skinny(epi, seg_rows, Kd, elem_bytes, M, 0).split;
