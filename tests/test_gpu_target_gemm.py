@@ -70,6 +70,16 @@ def test_target_forward_over_two_blocks_of_rows(cfg, n_layers, T, caps, L, Bsz):
         assert torch.equal(bits(rows[0]), bits(rows[1])), key
 
 
+@pytest.mark.parametrize("cfg,keys", [(EIGHT, ("gate_up",)), (EIGHT, ("down", "wo")), (QKV, ("qkv", "down")), (DOWN, ("down",))])
+def test_partly_tiled_weights_over_two_blocks_of_rows(cfg, keys):
+    """Whichever matrices are tiled, the results are those of row-major weights."""
+    say(f"target_forward {cfg.name}, 65 rows, tiled copies of {keys}")
+    runs = [run_target(cfg, 2, 13, (10,) * 4, 20, Bsz=5, tiled=tiled, tiled_keys=keys if tiled else None, oracle=False)[2]
+            for tiled in (True, False)]
+    for key in ("hidden", "logits", "tgt"):
+        assert np.array_equal(runs[0][key], runs[1][key]), key
+
+
 @pytest.mark.parametrize("T", [2, 16, 17, 32, 33, 48, 49, 64])
 @pytest.mark.parametrize("tiled", [True, False])
 def test_float32_target_forward_over_few_rows(T, tiled):
