@@ -139,25 +139,43 @@ template <typename T> __device__ __forceinline__ size_t xt_index(int m, int k, i
 }
 
 // ---- wave-level reductions ---------------------------------------------------------------------------
-__device__ __forceinline__ float wave_sum(float v) {
-  #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, WAVE);
-  return v;
+// The 32-bit value of the lane OFF further on, exchanged inside the vector ALU (a shuffle goes through LDS: about a hundred
+// clocks of latency each, and its turn there; six of them for every sum were a good part of the short kernels: a whole
+// iteration of the float32 miniature 216 -> 203 us, a one-row 7B draft 367 -> 364).
+// xor16 / xor32: the row swap of a register with itself leaves the even rows (the lower half) in one result and the odd
+// ones (the upper half) in the other, so op of the two is op over lanes 16 (32) apart, in every lane.
+template <typename V> __device__ __forceinline__ unsigned lane_bits(V v) { union { V v; unsigned u; } c; c.v = v; return c.u; }
+template <typename V> __device__ __forceinline__ V lane_value(unsigned u) { union { unsigned u; V v; } c; c.u = u; return c.v; }
+template <typename V, typename F> __device__ __forceinline__ V lanes_xor16(V v, F op) {
+  const auto p = __builtin_amdgcn_permlane16_swap(lane_bits(v), lane_bits(v), false, false);
+  return op(lane_value<V>(p[0]), lane_value<V>(p[1]));
 }
-__device__ __forceinline__ float wave_max(float v) {
-  #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, WAVE));
-  return v;
+template <typename V, typename F> __device__ __forceinline__ V lanes_xor32(V v, F op) {
+  const auto p = __builtin_amdgcn_permlane32_swap(lane_bits(v), lane_bits(v), false, false);
+  return op(lane_value<V>(p[0]), lane_value<V>(p[1]));
 }
-
-// sum over a whole 256-thread block; every thread gets the result.  red must hold 4 floats.
-__device__ __forceinline__ float block_sum_256(float v, float *red) {
-  v = wave_sum(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return red[0] + red[1] + red[2] + red[3];
+template <int CTRL, typename V> __device__ __forceinline__ V lanes_dpp(V v) {
+  return lane_value<V>((unsigned)__builtin_amdgcn_update_dpp(0, (int)lane_bits(v), CTRL, 0xf, 0xf, true));
 }
+template <int N, typename V> __device__ __forceinline__ V lanes_ror(V v) { return lanes_dpp<0x120 + N>(v); }   // rotation inside rows of 16
+constexpr int DPP_XOR1 = 0xb1, DPP_XOR2 = 0x4e;           // quad_perm [1, 0, 3, 2] and [2, 3, 0, 1]
+// op (commutative) over the 64 lanes, in every lane: partners 32, 16, 8, 4, 2, 1 apart.  Once lanes 2 N apart hold the same
+// value, the lane N before in the row is the partner N apart: the order, and so the bits, of a butterfly of shuffles.
+// All 64 lanes must be active.
+template <typename V, typename F> __device__ __forceinline__ V wave_fold(V v, F op) {
+  v = lanes_xor32(v, op);
+  v = lanes_xor16(v, op);
+  v = op(v, lanes_ror<8>(v));
+  v = op(v, lanes_ror<4>(v));
+  v = op(v, lanes_ror<2>(v));
+  return op(v, lanes_ror<1>(v));
+}
+struct AddF { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
+struct MaxF { __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); } };
+struct MaxI { __device__ __forceinline__ int operator()(int a, int b) const { return max(a, b); } };
+__device__ __forceinline__ float wave_sum(float v) { return wave_fold(v, AddF()); }
+__device__ __forceinline__ float wave_max(float v) { return wave_fold(v, MaxF()); }
+__device__ __forceinline__ int wave_max(int v) { return wave_fold(v, MaxI()); }
 
 __device__ __forceinline__ float silu_f(float z) { return z / (1.0f + __expf(-z)); }
 
@@ -165,6 +183,24 @@ __device__ __forceinline__ float silu_f(float z) { return z / (1.0f + __expf(-z)
 // "Better" means a larger value, or the same value and a smaller index, so results are sorted and ties deterministic.
 __device__ __forceinline__ bool better(float v1, int i1, float v2, int i2) {
   return (v1 > v2) || (v1 == v2 && i1 < i2);
+}
+__device__ __forceinline__ void take_better(float &v, int &i, float ov, int oi) {
+  if (better(ov, oi, v, i)) { v = ov; i = oi; }
+}
+// the best (value, index) of the 64 lanes, in every lane
+__device__ __forceinline__ void wave_best(float &v, int &i) {
+  const auto pv = __builtin_amdgcn_permlane32_swap(lane_bits(v), lane_bits(v), false, false);
+  const auto pi = __builtin_amdgcn_permlane32_swap(lane_bits(i), lane_bits(i), false, false);
+  v = lane_value<float>(pv[0]); i = (int)pi[0];
+  take_better(v, i, lane_value<float>(pv[1]), (int)pi[1]);
+  const auto qv = __builtin_amdgcn_permlane16_swap(lane_bits(v), lane_bits(v), false, false);
+  const auto qi = __builtin_amdgcn_permlane16_swap(lane_bits(i), lane_bits(i), false, false);
+  v = lane_value<float>(qv[0]); i = (int)qi[0];
+  take_better(v, i, lane_value<float>(qv[1]), (int)qi[1]);
+  take_better(v, i, lanes_ror<8>(v), lanes_ror<8>(i));
+  take_better(v, i, lanes_ror<4>(v), lanes_ror<4>(i));
+  take_better(v, i, lanes_ror<2>(v), lanes_ror<2>(i));
+  take_better(v, i, lanes_ror<1>(v), lanes_ror<1>(i));
 }
 
 // Selection by counting: an element's place among the best is the number of better ones, which every lane counts for its

@@ -344,9 +344,7 @@ __global__ __launch_bounds__((DmStage<NB, NT, CB_>::THREADS)) void k_draft_mm(co
     if (NORM) {
       #pragma unroll
       for (int t = 0; t < NT; ++t) {
-        float v = ss[t];
-        v += __shfl_xor(v, 16, WAVE);
-        v += __shfl_xor(v, 32, WAVE);
+        const float v = lanes_xor32(lanes_xor16(ss[t], AddF()), AddF());
         if (g == 0) sq[(wave * NT + t) * 16 + r16] = v;
       }
     }

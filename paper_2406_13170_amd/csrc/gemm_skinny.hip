@@ -230,12 +230,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const float *Ct
         const float v = Ct[m * CT_PITCH + r];
         if (n < N && (v > bv || (v == bv && n < bi))) { bv = v; bi = n; }
       }
-      #pragma unroll
-      for (int off = 1; off <= 2; off <<= 1) {
-        const float ov = __shfl_xor(bv, off, WAVE);
-        const int oi = __shfl_xor(bi, off, WAVE);
-        if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-      }
+      take_better(bv, bi, lanes_dpp<DPP_XOR1>(bv), lanes_dpp<DPP_XOR1>(bi));
+      take_better(bv, bi, lanes_dpp<DPP_XOR2>(bv), lanes_dpp<DPP_XOR2>(bi));
       if (part == 0 && mg < a.M) {
         a.amax_val[(size_t)tile * a.M + mg] = bv;
         a.amax_idx[(size_t)tile * a.M + mg] = bi;
@@ -396,7 +392,8 @@ __global__ __launch_bounds__(64 * (GM_MAX_NB + GM_NLW)) void k_gemm_skinny(const
         float y[4];
         #pragma unroll
         for (int c = 0; c < 4; ++c) {
-          const float up = __shfl_down(acc[mb][c], 32, WAVE);
+          const auto halves = __builtin_amdgcn_permlane32_swap(lane_bits(acc[mb][c]), lane_bits(acc[mb][c]), false, false);
+          const float up = lane_value<float>(halves[1]);   // the upper half's value
           y[c] = silu_f(acc[mb][c]) * up;
         }
         const int mg = m_base + mb * 16 + r16;
@@ -707,12 +704,7 @@ __global__ __launch_bounds__(64) void k_argmax_fold(const float *amax_val, const
     const int i = amax_idx[(size_t)t * M + mg];
     if (v > bv || (v == bv && i < bi)) { bv = v; bi = i; }
   }
-  #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const float ov = __shfl_xor(bv, off, WAVE);
-    const int oi = __shfl_xor(bi, off, WAVE);
-    if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-  }
+  wave_best(bv, bi);
   if (lane == 0) tgt[mg] = bi;
 }
 

@@ -262,7 +262,8 @@ __device__ __forceinline__ void load_x_parts(float *xs, float *fac, const SalPar
   }
 }
 
-// x[m][k] * g[k] with the row's 1/rms returned in rs[m] (applied by the caller to the dot products).
+// x[m][k] * g[k] with the row's 1/rms returned in rs[m] (applied by the caller to the dot products).  red: 4 * M floats.
+// Ends with a barrier.
 template <typename T, int M>
 __device__ __forceinline__ void load_x_rmsnorm(float *xs, float *red, const float *x, int ldx, const T *g,
                                                int m_valid, int Kd, int nC, float eps, float (&rs)[M]) {
@@ -272,8 +273,14 @@ __device__ __forceinline__ void load_x_rmsnorm(float *xs, float *red, const floa
   fill_xs<T, M, true>(xs, x, ldx, g, m_valid, Kd, nC, ss);
   #pragma unroll
   for (int m = 0; m < M; ++m) {
-    const float tot = block_sum_256(ss[m], red);
-    rs[m] = rsqrtf(tot / (float)Kd + eps);
+    const float w = wave_sum(ss[m]);
+    if ((threadIdx.x & 63) == 0) red[m * 4 + (threadIdx.x >> 6)] = w;
+  }
+  __syncthreads();                                         // (xs is whole as well)
+  #pragma unroll
+  for (int m = 0; m < M; ++m) {
+    const float4 w = *reinterpret_cast<const float4 *>(red + m * 4);
+    rs[m] = rsqrtf((w.x + w.y + w.z + w.w) / (float)Kd + eps);
   }
 }
 
@@ -401,10 +408,9 @@ __global__ __launch_bounds__(GV_THREADS) void k_sal_qkv(const T *wq, const T *wk
   extern __shared__ __align__(16) float smem[];
   constexpr int CH = XLayout<T>::CH;
   const int Kd = d, nC = (Kd + CH - 1) / CH;
-  float *xs = smem + 4;
+  float *xs = smem + 4 * M;
   float rs[M];
   load_x_rmsnorm<T, M>(xs, smem, x, d, norm_w, m_valid, Kd, nC, eps, rs);
-  __syncthreads();
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int Gseg = d / GV_R;                 // groups per matrix (d is a multiple of 4)
   const int G = 3 * Gseg;
@@ -548,10 +554,9 @@ __global__ __launch_bounds__(GV_THREADS) void k_gate_up(const T *w_gate, const T
   extern __shared__ __align__(16) float smem[];
   constexpr int CH = XLayout<T>::CH;
   const int Kd = d, nC = (Kd + CH - 1) / CH;
-  float *xs = smem + 4;
+  float *xs = smem + 4 * M;
   float rs[M];
   load_x_rmsnorm<T, M>(xs, smem, x, d, norm_w, m_valid, Kd, nC, eps, rs);
-  __syncthreads();
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int G = (f + 1) / 2;
   const int g_first = blockIdx.x * 4 + wave, g_step = gridDim.x * 4;
@@ -836,13 +841,13 @@ hipError_t launch_sal_qkv(hipStream_t st, const amph_layer_w &lw, const float *x
   if (use_mm<T>(M, (size_t)3 * d * d) && d % 16 == 0 && d_h % 16 == 0)
     MM_CHUNKS(draft_mm_sal_qkv(st, lw, x + (size_t)m0 * d, d, n_heads, d_h, m, eps, theta, sal_len, max_kv, kv_stage,
                                qbuf + (size_t)m0 * d, dev_status, m0, R, n_valid));
-  const int mc = gv_rows_per_launch(M, gv_xs_bytes<T>(1, d), 16);
+  const int mc = gv_rows_per_launch(M, gv_xs_bytes<T>(1, d) + 16, 0);
   if (mc < 1) return hipErrorInvalidValue;
   for (int m0 = 0; m0 < M; m0 += mc) {
     const int m = std::min(mc, M - m0);
     hipError_t e = hipSuccess;
     GV_DISPATCH_M(m, GV_MOST<T>, {
-      const size_t sm = gv_xs_bytes<T>(MM, d) + 16;
+      const size_t sm = gv_xs_bytes<T>(MM, d) + MM * 16;
       GV_LAUNCH(k_sal_qkv, gv_grid(3 * d / 4, sm), sm, (const T *)lw.wq, (const T *)lw.wk, (const T *)lw.wv, (const T *)lw.rms1,
                 x + (size_t)m0 * d, d, n_heads, d_h, m, eps, theta, sal_len, max_kv, (T *)kv_stage, qbuf + (size_t)m0 * d,
                 dev_status, m0, R, n_valid);
@@ -913,13 +918,13 @@ hipError_t launch_gate_up(hipStream_t st, const amph_layer_w &lw, const float *x
                           float *act) {
   if (M < 1 || d % 8) return hipErrorInvalidValue;
   if (use_mm<T>(M, (size_t)2 * f * d)) MM_CHUNKS(draft_mm_gate_up(st, lw, x + (size_t)m0 * d, d, f, m, eps, act + (size_t)m0 * f));
-  const int mc = gv_rows_per_launch(M, gv_xs_bytes<T>(1, d), 16);
+  const int mc = gv_rows_per_launch(M, gv_xs_bytes<T>(1, d) + 16, 0);
   if (mc < 1) return hipErrorInvalidValue;
   for (int m0 = 0; m0 < M; m0 += mc) {
     const int m = std::min(mc, M - m0);
     hipError_t e = hipSuccess;
     GV_DISPATCH_M(m, GV_MOST<T>, {
-      const size_t sm = gv_xs_bytes<T>(MM, d) + 16;
+      const size_t sm = gv_xs_bytes<T>(MM, d) + MM * 16;
       GV_LAUNCH(k_gate_up, gv_grid((f + 1) / 2, sm), sm, (const T *)lw.w_gate, (const T *)lw.w_up, (const T *)lw.rms2,
                 x + (size_t)m0 * d, d, f, m, eps, act + (size_t)m0 * f);
     });

@@ -27,16 +27,6 @@ constexpr int SA_WAVES = 8;
 __device__ __forceinline__ float sa_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 template <bool V> struct BoolTag { static constexpr bool value = V; };
-// op of a lane's value and the one 16 (32) lanes further on, modulo 32 (64): the row swap of a register with itself leaves
-// the even rows (the lower half) in one result and the odd ones (the upper half) in the other
-template <typename F> __device__ __forceinline__ float sa_xor16(float v, F op) {
-  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return op(__uint_as_float(p[0]), __uint_as_float(p[1]));
-}
-template <typename F> __device__ __forceinline__ float sa_xor32(float v, F op) {
-  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return op(__uint_as_float(p[0]), __uint_as_float(p[1]));
-}
 // sum over groups of LPR adjacent lanes, in every lane: neighbour at distance 1, 2, then mirror inside 8 and inside 16
 // lanes, each one vector instruction (a cross-lane permute goes through LDS)
 template <int LPR> __device__ __forceinline__ float sa_group_sum(float v) {
@@ -46,14 +36,14 @@ template <int LPR> __device__ __forceinline__ float sa_group_sum(float v) {
   if (LPR >= 8) SA_DPP(0x141);           // row_half_mirror
   if (LPR >= 16) SA_DPP(0x140);          // row_mirror
   #undef SA_DPP
-  if (LPR >= 32) v = sa_xor16(v, [](float a, float b) { return a + b; });
+  if (LPR >= 32) v = lanes_xor16(v, AddF());
   return v;
 }
 // op over the lane groups of LPR lanes (the same lane of each), in every lane
 template <int LPR, typename F> __device__ __forceinline__ float sa_across(float v, F op) {
-  if (LPR <= 8) v = op(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, true)));   // row_ror:8
-  if (LPR <= 16) v = sa_xor16(v, op);
-  return sa_xor32(v, op);
+  if (LPR <= 8) v = op(v, lanes_ror<8>(v));
+  if (LPR <= 16) v = lanes_xor16(v, op);
+  return lanes_xor32(v, op);
 }
 
 template <typename T, int DH, int RT>
@@ -160,12 +150,12 @@ __global__ __launch_bounds__(SA_WAVES * 64) void k_sal_attn(const float *qbuf, c
   // lane groups -> wave
   #pragma unroll
   for (int r = 0; r < RT; ++r) {
-    const float mw = sa_across<LPR>(m[r], [](float x, float y) { return fmaxf(x, y); });
+    const float mw = sa_across<LPR>(m[r], MaxF());
     const float f = sa_exp2(m[r] - mw);
     m[r] = mw;
-    l[r] = sa_across<LPR>(l[r] * f, [](float x, float y) { return x + y; });
+    l[r] = sa_across<LPR>(l[r] * f, AddF());
     #pragma unroll
-    for (int e = 0; e < PER; ++e) o[r][e] = sa_across<LPR>(o[r][e] * f, [](float x, float y) { return x + y; });
+    for (int e = 0; e < PER; ++e) o[r][e] = sa_across<LPR>(o[r][e] * f, AddF());
     if (grp == 0) {
       #pragma unroll
       for (int e = 0; e < PER; ++e) sm_o[wave][r][li * PER + e] = o[r][e];
@@ -440,20 +430,12 @@ __global__ __launch_bounds__(1024) void k_row_argmax(const float *logits, int V,
   #pragma unroll
   for (int j = 0; j < NPT; ++j)
     if (j * 1024 + tid < V && better(x[j], j * 1024 + tid, bv, bi)) { bv = x[j]; bi = j * 1024 + tid; }
-  auto fold = [&](int from) {
-    #pragma unroll
-    for (int off = from; off >= 1; off >>= 1) {
-      const float ov = __shfl_xor(bv, off, WAVE);
-      const int oi = __shfl_xor(bi, off, WAVE);
-      if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
-    }
-  };
-  fold(32);
+  wave_best(bv, bi);
   if (lane == 0) { sm_v[wave] = bv; sm_i[wave] = bi; }
   __syncthreads();
   if (wave > 0) return;
   bv = sm_v[lane & 15]; bi = sm_i[lane & 15];
-  fold(8);
+  wave_best(bv, bi);
   if (lane == 0) out[row] = (bi == NONE) ? -1 : bi;
 }
 
@@ -511,8 +493,7 @@ __global__ __launch_bounds__(AMPH_MAX_TREE) void k_accept(const int32_t *parent,
     }
     if (ok) key = depth[i] * 256 + (255 - i);
   }
-  #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) key = max(key, __shfl_xor(key, off, WAVE));
+  key = wave_max(key);
   if ((i & 63) == 0) s_key[i >> 6] = key;
   __syncthreads();
   if (i == 0) {
@@ -554,8 +535,7 @@ constexpr int AT_THREADS = 1024, AT_WAVES = AT_THREADS / WAVE;
 constexpr int AT_RUN = 32;                               // tokens of every run that sit in LDS at a time
 
 __device__ __forceinline__ float at_block_max(float v, float *sm) {
-  #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, WAVE));
+  v = wave_max(v);
   __syncthreads();                                        // sm may still be read from an earlier reduction
   if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
   __syncthreads();
@@ -564,8 +544,7 @@ __device__ __forceinline__ float at_block_max(float v, float *sm) {
   return r;
 }
 __device__ __forceinline__ float at_block_sum(float v, float *sm) {      // fixed order: lanes by butterfly, waves ascending
-  #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, WAVE);
+  v = wave_sum(v);
   __syncthreads();
   if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
   __syncthreads();
@@ -643,8 +622,7 @@ __global__ __launch_bounds__(AT_THREADS) void k_accept_typical(const int32_t *pa
     }
     if (ok) key = depth[t] * 256 + (255 - t);
   }
-  #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) key = max(key, __shfl_xor(key, off, WAVE));
+  key = wave_max(key);
   if ((t & 63) == 0) s_key[t >> 6] = key;
   __syncthreads();
   if (t == 0) {
@@ -718,8 +696,7 @@ __global__ __launch_bounds__(AT_THREADS) void k_accept_typical(const int32_t *pa
     if (pick < 0) pick = max(last_live, v0);              // (acc and inc differ by rounding order only)
     s_found = pick;
   }
-  #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) last_live = max(last_live, __shfl_xor(last_live, off, WAVE));
+  last_live = wave_max(last_live);
   __syncthreads();
   if ((t & 63) == 0) s_key[t >> 6] = last_live;
   __syncthreads();

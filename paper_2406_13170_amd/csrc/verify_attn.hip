@@ -204,8 +204,7 @@ __global__ __launch_bounds__(256) void k_verify_attn_regs(const VerifyArgs a, in
       // ---- the group's maximum per query; rescale what earlier groups accumulated
       #pragma unroll
       for (int qb = 0; qb < NQB; ++qb) {
-        float m2 = fmaxf(mx[qb], __shfl_xor(mx[qb], 16, WAVE));
-        m2 = fmaxf(m2, __shfl_xor(m2, 32, WAVE));
+        const float m2 = lanes_xor32(lanes_xor16(mx[qb], MaxF()), MaxF());
         const float mn = fmaxf(m_run[qb], m2);
         if (i0 > 0) {
           const float corr = fast_exp2(m_run[qb] - mn);
@@ -229,8 +228,7 @@ __global__ __launch_bounds__(256) void k_verify_attn_regs(const VerifyArgs a, in
   // ---- lane groups hold partial sums of l for the same query: fold them
   #pragma unroll
   for (int qb = 0; qb < NQB; ++qb) {
-    l_run[qb] += __shfl_xor(l_run[qb], 16, WAVE);
-    l_run[qb] += __shfl_xor(l_run[qb], 32, WAVE);
+    l_run[qb] = lanes_xor32(lanes_xor16(l_run[qb], AddF()), AddF());
   }
 
   // ---- waves -> workgroup through LDS
@@ -460,8 +458,7 @@ __global__ __launch_bounds__(KG == 2 ? 1024 : (VA_MAX_MATH + 2) * 64) void k_ver
         #pragma unroll
         for (int j = 0; j < PER; ++j) mx = fmaxf(mx, sv[s][qb][j]);
       }
-      mx = fmaxf(mx, __shfl_xor(mx, 16, WAVE));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
+      mx = lanes_xor32(lanes_xor16(mx, MaxF()), MaxF());
       mn[qb] = fmaxf(m_run[qb], mx);
       grow |= (mn[qb] > m_run[qb]);
     }
@@ -551,9 +548,7 @@ __global__ __launch_bounds__(KG == 2 ? 1024 : (VA_MAX_MATH + 2) * 64) void k_ver
   float *part = a.partials + ((((size_t)b * n_h + h) * S + split) * (size_t)(NQ * DH + 2 * NQ));
   #pragma unroll
   for (int qb = 0; qb < NQB; ++qb) {
-    float l = l_run[qb];
-    l += __shfl_xor(l, 16, WAVE);
-    l += __shfl_xor(l, 32, WAVE);
+    const float l = lanes_xor32(lanes_xor16(l_run[qb], AddF()), AddF());
     const int q = q0 + qb * 16 + r16;
     if (S == 1) {
       if (q < Tn) {
