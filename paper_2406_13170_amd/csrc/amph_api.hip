@@ -43,7 +43,7 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 struct WsLayout {   // byte offsets into the caller's workspace
   size_t x, q, att, y, act, h[2], Hp, Qa, Ka, Va, ctxa, attn_o, logits, topk_ws, sal_part, dslabs;  // draft
-  size_t xres, xn, qb, attb, actb, slabs, amax_val, amax_idx, ver_part, tgt_tmp, row_stats, rope_cs, xt;  // target
+  size_t xres, xn, qb, attb, actb, slabs, amax_val, amax_idx, ver_part, tgt_tmp, row_stats, row_runs, rope_cs, xt;  // target
   size_t slabs_floats, ver_part_floats;
   size_t total;
 };
@@ -152,6 +152,7 @@ WsLayout make_layout(const amph_config &c) {
   w.ver_part_floats = vfl;
   w.tgt_tmp = take(M * 4);
   w.row_stats = take(M * 16);
+  w.row_runs = take(accept_runs_floats((int)M) * 4);
   w.rope_cs = take(M * (size_t)(c.head_dim / 2) * 8);
   w.total = at;
   return w;
@@ -646,7 +647,8 @@ amph_status amph_accept_typical(amph_ctx *ctx, const amph_tree *tree, const int3
   if (amph_status s = check_tree(ctx, tree, "amph_accept_typical")) return s;
   HIP_TRY(ctx, launch_accept_typical(ctx->stream, tree->d_parent, tree->d_depth, tree->T, ctx->cfg.batch, ctx->cfg.K,
                                      ctx->cfg.vocab, tree_tok, tgt_logits, temperature, eps, delta, u, accept_len, accept_path,
-                                     next_tok, best_node, (float *)((char *)workspace + ctx->ws.row_stats)));
+                                     next_tok, best_node, (float *)((char *)workspace + ctx->ws.row_stats),
+                                     (float *)((char *)workspace + ctx->ws.row_runs)));
   return AMPH_OK;
 }
 

@@ -526,13 +526,15 @@ hipError_t launch_accept(hipStream_t st, const int32_t *parent, const int32_t *d
 // order) at the caller's uniform number.
 //   k_row_softmax_stats: one workgroup per tree node: m = max l, Z = sum exp((l - m) / t),
 //     H = ln Z - sum(e x) / Z with x = (l - m) / t, e = exp(x)            -> stats[row] = (m, Z, H, 0)
+//     and the row's 1024 run sums (run r: the e of C = ceil(V / 1024) consecutive tokens, added in order) -> runs[row]
 //   k_accept_typical: one workgroup per batch element: the pass flags, the winner as in k_accept, then the draw:
-//     thread t sums its run of consecutive tokens, a scan over the threads finds the run where the cumulative
-//     sum first exceeds u * Z, and that thread walks its run.  If rounding leaves no such token (u * Z at or
-//     above the total), the last token of non-zero probability is taken.
+//     a scan over the winner's run sums finds the run where the cumulative sum first exceeds u * Z, and one wave
+//     walks that run's tokens.  If rounding leaves no such token (u * Z at or above the total), the last token of
+//     non-zero probability is taken.
 // =====================================================================================================
 constexpr int AT_THREADS = 1024, AT_WAVES = AT_THREADS / WAVE;
-constexpr int AT_RUN = 32;                               // tokens of every run that sit in LDS at a time
+constexpr int AT_PIECE = 32;                             // logits of a thread whose exponentials sit in LDS at a time
+constexpr int AT_MAX_RUN = 64;                           // tokens of a run, at most: one lane each
 
 __device__ __forceinline__ float at_block_max(float v, float *sm) {
   v = wave_max(v);
@@ -543,22 +545,18 @@ __device__ __forceinline__ float at_block_max(float v, float *sm) {
   for (int w = 1; w < AT_WAVES; ++w) r = fmaxf(r, sm[w]);
   return r;
 }
-__device__ __forceinline__ float at_block_sum(float v, float *sm) {      // fixed order: lanes by butterfly, waves ascending
-  v = wave_sum(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
-  __syncthreads();
-  float r = sm[0];
-  for (int w = 1; w < AT_WAVES; ++w) r += sm[w];
-  return r;
-}
 
 // A row is read once: its NPT * 1024 logits are all requested before the first is used and stay in registers between the
-// maximum and the sums (two strided loops over memory took 23.5 us for 256 rows of 32000, this 12.8; the rows' 33 MB
-// are 7 us).  Threads keep the elements they always had (t, t + 1024, ...), so the sums' bits do not change.
+// maximum and the sums (two strided loops over memory took 23.5 us for 256 rows of 32000; the rows' 33 MB are 7 us).
+// Then it is the exponentials that last, 20 vector instructions for each of 32 elements of 16 waves: 5 us of a compute
+// unit.  So the draw does not take them again: the run sums leave from here, over LDS, where a thread's elements (t,
+// t + 1024, ...) and its run (t C, t C + 1, ...) are different tokens.  That is 1.3 us here for all rows, and 5 us less in
+// k_accept_typical, whose one workgroup a sequence fetched a whole row and took its exponentials.
 template <int NPT>
-__global__ __launch_bounds__(AT_THREADS) void k_row_softmax_stats(const float *logits, int V, float inv_temp, float4 *stats) {
-  __shared__ float sm[AT_WAVES];
+__global__ __launch_bounds__(AT_THREADS) void k_row_softmax_stats(const float *logits, int V, float inv_temp, float4 *stats, float *runs) {
+  constexpr int PIECE = NPT < AT_PIECE ? NPT : AT_PIECE;
+  __shared__ float sm[AT_WAVES], sm2[AT_WAVES];
+  __shared__ float s_e[PIECE * AT_THREADS / 32 * 33];      // token v of the piece at v + v / 32: few lanes of a walk meet in one bank
   const float *l = logits + (size_t)blockIdx.x * V;
   const int t = threadIdx.x;
   float x[NPT];
@@ -568,49 +566,68 @@ __global__ __launch_bounds__(AT_THREADS) void k_row_softmax_stats(const float *l
   #pragma unroll
   for (int j = 0; j < NPT; ++j) m = fmaxf(m, x[j]);       // (the clamped repeats change no maximum)
   m = at_block_max(m, sm);
-  float z = 0.f, sx = 0.f;
+  const int C = (V + AT_THREADS - 1) / AT_THREADS, v0 = min(t * C, V), v1 = min(v0 + C, V);      // this thread's run
+  float z = 0.f, sx = 0.f, run = 0.f;
   #pragma unroll
-  for (int j = 0; j < NPT; ++j) {
-    if (j * AT_THREADS + t < V) {
-      const float y = (x[j] - m) * inv_temp, e = expf(y);
+  for (int p = 0; p < NPT; p += PIECE) {
+    if (p > 0) __syncthreads();
+    #pragma unroll
+    for (int j = 0; j < PIECE; ++j) {
+      const int i = j * AT_THREADS + t, v = p * AT_THREADS + i;
+      // straight-line code: a repeat past the row's end is a token of probability zero, and such a token adds nothing
+      // to sum(e y) (0 * -infinity)
+      const float y = v < V ? (x[p + j] - m) * inv_temp : -__builtin_huge_valf(), e = expf(y);
       z += e;
-      if (e > 0.f) sx += e * y;                           // a token of probability zero adds nothing (0 * -inf)
+      const float f = fmaf(y, e, sx);
+      sx = e > 0.f ? f : sx;
+      s_e[i + (i >> 5)] = e;
     }
+    __syncthreads();
+    const int a = max(v0, p * AT_THREADS) - p * AT_THREADS, b = min(v1, (p + PIECE) * AT_THREADS) - p * AT_THREADS;
+    for (int i = a; i < b; ++i) run += s_e[i + (i >> 5)];
   }
-  z = at_block_sum(z, sm);
-  sx = at_block_sum(sx, sm);
-  if (t == 0) stats[blockIdx.x] = make_float4(m, z, logf(z) - sx / z, 0.f);
+  runs[(size_t)blockIdx.x * AT_THREADS + t] = run;
+  z = wave_sum(z);                                         // fixed order: lanes by butterfly, waves ascending
+  sx = wave_sum(sx);
+  if ((t & 63) == 0) { sm[t >> 6] = z; sm2[t >> 6] = sx; }
+  __syncthreads();
+  if (t == 0) {
+    z = sm[0]; sx = sm2[0];
+    for (int w = 1; w < AT_WAVES; ++w) { z += sm[w]; sx += sm2[w]; }
+    stats[blockIdx.x] = make_float4(m, z, logf(z) - sx / z, 0.f);
+  }
 }
 
 __global__ __launch_bounds__(AT_THREADS) void k_accept_typical(const int32_t *parent, const int32_t *depth, int T, int K, int V,
                                                                const int32_t *tree_tok, const float *logits, const float4 *stats,
-                                                               float inv_temp, float eps, float delta, const float *u,
+                                                               const float *runs, float inv_temp, float eps, float delta, const float *u,
                                                                int32_t *accept_len, int32_t *accept_path, int32_t *next_tok,
                                                                int32_t *best_node) {
   __shared__ float sm[AT_WAVES];
   __shared__ int s_pass[AMPH_MAX_TREE], s_parent[AMPH_MAX_TREE];
   __shared__ int s_key[AT_WAVES];
-  __shared__ int s_best, s_found;
-  __shared__ float s_e[AT_THREADS][AT_RUN + 1];           // one piece of every thread's run (pitch: no two lanes in one bank)
-  const int b = blockIdx.x, t = threadIdx.x;
+  __shared__ int s_best, s_run;
+  __shared__ float s_exc;
+  const int b = blockIdx.x, t = threadIdx.x, lane = t & 63;
   const int32_t *tok = tree_tok + (size_t)b * T;
+  const float ub = u[b];
+  int dep = 0;
   if (t < T) {
     int pass = 1;                                          // the root
-    const int j = parent[t];
+    const int j = parent[t], tk = tok[t];
+    dep = depth[t];
     s_parent[t] = j;                                       // (the walks up the tree below would each be a chain of global loads)
     if (t > 0) {
-      const int tk = tok[t];
       const size_t row = (size_t)b * T + j;
       const float4 st = stats[row];
-      pass = 0;
-      if (tk >= 0 && tk < V) {
-        const float p = expf((logits[row * V + tk] - st.x) * inv_temp) / st.y;
-        pass = p > fminf(eps, delta * expf(-st.z));
-      }
+      const bool known = tk >= 0 && tk < V;
+      const float lt = logits[row * V + (known ? tk : 0)];
+      const float p = expf((lt - st.x) * inv_temp) / st.y;
+      pass = known && p > fminf(eps, delta * expf(-st.z));
     }
     s_pass[t] = pass;
   }
-  if (t == 0) s_found = -1;
+  if (t == 0) s_run = -1;
   __syncthreads();
   int key = -1;
   if (t < T) {
@@ -620,180 +637,167 @@ __global__ __launch_bounds__(AT_THREADS) void k_accept_typical(const int32_t *pa
       if (!s_pass[j]) { ok = false; break; }
       j = s_parent[j];
     }
-    if (ok) key = depth[t] * 256 + (255 - t);
+    if (ok) key = dep * 256 + (255 - t);
   }
   key = wave_max(key);
-  if ((t & 63) == 0) s_key[t >> 6] = key;
+  if (lane == 0) s_key[t >> 6] = key;
   __syncthreads();
+  int best_key = s_key[0];
+  #pragma unroll
+  for (int w = 1; w < (AMPH_MAX_TREE + WAVE - 1) / WAVE; ++w) best_key = max(best_key, s_key[w]);    // (the other waves hold no node)
+  const int a = best_key >> 8, best = 255 - (best_key & 255);       // the root always qualifies
+  // ---- the draw from p_best
+  const size_t row = (size_t)b * T + best;
+  const float *l = logits + row * V;
+  const float4 st = stats[row];
+  const float run = runs[row * AT_THREADS + t];
   if (t == 0) {
-    int best_key = s_key[0];
-    for (int w = 1; w < AT_WAVES; ++w) best_key = max(best_key, s_key[w]);
-    const int a = best_key >> 8, best = 255 - (best_key & 255);     // the root always qualifies
     accept_len[b] = a;
     best_node[b] = best;
-    s_best = best;
-    for (int dd = 0; dd <= K; ++dd) accept_path[(size_t)b * (K + 1) + dd] = -1;
+    for (int dd = a + 1; dd <= K; ++dd) accept_path[(size_t)b * (K + 1) + dd] = -1;
     int j = best;
     for (int dd = a; dd >= 0 && j >= 0; --dd) { accept_path[(size_t)b * (K + 1) + dd] = j; j = s_parent[j]; }
   }
-  __syncthreads();
-  // ---- the draw from p_best
-  const size_t row = (size_t)b * T + s_best;
-  const float *l = logits + row * V;
-  const float4 st = stats[row];
-  const float target = u[b] * st.y;
-  const int C = (V + AT_THREADS - 1) / AT_THREADS, v0 = min(t * C, V), v1 = min(v0 + C, V);
-  // Thread t's run is C consecutive tokens, added up in order; read that way every load would touch 64 lines (with the
-  // walks above through global memory 21.3 us for 4 rows, this 11.8).  So the runs come in pieces of AT_RUN tokens through
-  // LDS: consecutive lanes fetch consecutive tokens, then each thread adds its own.
-  float run = 0.f;
-  int last_live = -1;
-  for (int c0 = 0; c0 < C; c0 += AT_RUN) {
-    if (c0 > 0) __syncthreads();
-    float x[AT_RUN];
-    #pragma unroll
-    for (int i = 0; i < AT_RUN; ++i) {
-      const int q = i * AT_THREADS + t;                    // piece of run q / AT_RUN, token q % AT_RUN of it
-      x[i] = l[min((q / AT_RUN) * C + c0 + q % AT_RUN, V - 1)];
-    }
-    #pragma unroll
-    for (int i = 0; i < AT_RUN; ++i) {
-      const int q = i * AT_THREADS + t;
-      s_e[q / AT_RUN][q % AT_RUN] = expf((x[i] - st.x) * inv_temp);
-    }
-    __syncthreads();
-    for (int i = 0; i < AT_RUN; ++i) {
-      const int v = v0 + c0 + i;
-      if (c0 + i < C && v < v1) {
-        const float e = s_e[t][i];
-        run += e;
-        if (e > 0.f) last_live = v;
-      }
-    }
-  }
+  const float target = ub * st.y;
+  const int C = (V + AT_THREADS - 1) / AT_THREADS;
   // inclusive scan of the runs: inside a wave, then over the wave totals (ascending)
   float inc = run;
   #pragma unroll
   for (int off = 1; off < WAVE; off <<= 1) {
     const float o = __shfl_up(inc, off, WAVE);
-    if ((t & 63) >= off) inc += o;
+    if (lane >= off) inc += o;
   }
-  if ((t & 63) == 63) sm[t >> 6] = inc;
+  if (lane == 63) sm[t >> 6] = inc;
   __syncthreads();
   float base = 0.f;
   for (int w = 0; w < (t >> 6); ++w) base += sm[w];
   inc += base;
   const float prev = __shfl_up(inc, 1, WAVE);
-  const float exc = (t & 63) ? prev : base;               // exactly the thread before's inclusive sum
+  const float exc = lane ? prev : base;                   // exactly the thread before's inclusive sum
   // the sums never decrease with t and exc(t + 1) = inc(t): at most one thread sees the crossing inside its run
-  if (exc <= target && inc > target) {
-    float acc = exc;
-    int pick = -1;
-    for (int v = v0; v < v1; ++v) {
-      acc += C <= AT_RUN ? s_e[t][v - v0] : expf((l[v] - st.x) * inv_temp);
-      if (acc > target) { pick = v; break; }
-    }
-    if (pick < 0) pick = max(last_live, v0);              // (acc and inc differ by rounding order only)
-    s_found = pick;
-  }
-  last_live = wave_max(last_live);
+  if (exc <= target && inc > target) { s_run = t; s_exc = exc; }
   __syncthreads();
-  if ((t & 63) == 0) s_key[t >> 6] = last_live;
+  const int r = s_run;
+  if (r >= 0) {                                            // (uniform over the workgroup)
+    if (t >= WAVE) return;
+    // one wave walks the run: a token per lane, added up in order
+    const int v0 = min(r * C, V), n = min(v0 + C, V) - v0;
+    const float e = lane < n ? expf((l[min(v0 + lane, V - 1)] - st.x) * inv_temp) : 0.f;
+    const unsigned long long live = __ballot(e > 0.f);
+    float acc = s_exc;
+    int pick = -1;
+    for (int i = 0; i < n; ++i) {
+      acc += __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(e), i));
+      if (acc > target) { pick = v0 + i; break; }
+    }
+    if (pick < 0) pick = live ? v0 + 63 - __clzll(live) : v0;      // (acc and inc differ by rounding order only)
+    if (t == 0) next_tok[b] = min(max(pick, 0), V - 1);
+    return;
+  }
+  // no run crosses: the last token of non-zero probability
+  int last_live = -1;
+  for (int v = t; v < V; v += AT_THREADS)
+    if (expf((l[v] - st.x) * inv_temp) > 0.f) last_live = v;
+  last_live = wave_max(last_live);
+  if (lane == 0) s_key[t >> 6] = last_live;
   __syncthreads();
   if (t == 0) {
-    int pick = s_found;
-    if (pick < 0) {
-      pick = s_key[0];
-      for (int w = 1; w < AT_WAVES; ++w) pick = max(pick, s_key[w]);
-    }
+    int pick = s_key[0];
+    for (int w = 1; w < AT_WAVES; ++w) pick = max(pick, s_key[w]);
     next_tok[b] = min(max(pick, 0), V - 1);
   }
 }
 
+size_t accept_runs_floats(int rows) { return (size_t)rows * AT_THREADS; }
+
 hipError_t launch_accept_typical(hipStream_t st, const int32_t *parent, const int32_t *depth, int T, int B, int K, int V,
                                  const int32_t *tree_tok, const float *logits, float temperature, float eps, float delta,
                                  const float *u, int32_t *accept_len, int32_t *accept_path, int32_t *next_tok,
-                                 int32_t *best_node, float *stats_ws) {
+                                 int32_t *best_node, float *stats_ws, float *runs_ws) {
   if (T < 1 || T > AMPH_MAX_TREE || V < 1 || !(temperature > 0.f)) return hipErrorInvalidValue;
   const float inv_temp = 1.0f / temperature;
-  if (V > 64 * AT_THREADS) return hipErrorInvalidValue;
-  #define AT_STATS(N) hipLaunchKernelGGL((k_row_softmax_stats<N>), dim3(B * T), dim3(AT_THREADS), 0, st, logits, V, inv_temp, (float4 *)stats_ws)
+  if (V > AT_MAX_RUN * AT_THREADS) return hipErrorInvalidValue;
+  #define AT_STATS(N) hipLaunchKernelGGL((k_row_softmax_stats<N>), dim3(B * T), dim3(AT_THREADS), 0, st, logits, V, inv_temp, (float4 *)stats_ws, runs_ws)
   if (V <= 8 * AT_THREADS) AT_STATS(8); else if (V <= 32 * AT_THREADS) AT_STATS(32); else AT_STATS(64);
   #undef AT_STATS
   hipLaunchKernelGGL(k_accept_typical, dim3(B), dim3(AT_THREADS), 0, st, parent, depth, T, K, V, tree_tok, logits,
-                     (const float4 *)stats_ws, inv_temp, eps, delta, u, accept_len, accept_path, next_tok, best_node);
+                     (const float4 *)stats_ws, (const float *)runs_ws, inv_temp, eps, delta, u, accept_len, accept_path, next_tok, best_node);
   return hipGetLastError();
 }
 
 // =====================================================================================================
 // The loop around the step (Sec. 2 "Speculative Decoding"; Eq. 1 keeps one adaptation-layer cache row per
 // committed position).
-//   k_kv_commit: for one (layer, batch element, head), the K/V rows of the accepted path's nodes 1..a move
+//   k_commit: for one (layer, batch element, head), the K/V rows of the accepted path's nodes 1..a move
 //     from tree slots kv_len + node to kv_len + j (node 0, the root, already sits at kv_len).  All sources
-//     are read before the first write (a destination may be another node's source).
-//   k_gather_advance: row j <= a of h_new is the target's hidden state at path node j, tok_new[j] the
-//     token that follows it (the next path node's token, or next_tok after the last); n_new = a + 1; and
-//     kv_len += a + 1: a launch after the one above, whose workgroups have all read kv_len by then.
+//     are read before the first write (a destination may be another node's source).  In one more layer of the grid,
+//     row j <= a of h_new is the target's hidden state at path node j, tok_new[j] the token that follows it (the next
+//     path node's token, or next_tok after the last), rows past a are zero, and n_new = a + 1;
+//   k_advance: kv_len += a + 1: a launch after the one above, whose workgroups have all read kv_len by then.
 //   k_gather_rows: out[b] = rows[b * R + (n_valid ? n_valid[b] : R) - 1] (the last live row of each element).
+// A chain of latencies, so what can be asked for at once is: the lengths together with the whole path, then every source
+// (eight 7B layers, four sequences, by the kernel trace: 6.6 + 3.9 us as the path's rows element by element behind the
+// lengths, and the hidden states' rows with kv_len in a second launch; now 7.1 + 1.4.  The
+// values are 64-byte lines touched for 2 bytes each, some 30 MB there, which is what is left).
 // =====================================================================================================
 template <typename T>
-__global__ __launch_bounds__(256) void k_kv_commit(T *k_caches, T *v_caches, int B, int n_heads, int d_h, int max_kv,
-                                                   int T_nodes, const int32_t *kv_len, const int32_t *accept_len,
-                                                   const int32_t *accept_path, int K) {
-  const int h = blockIdx.x, b = blockIdx.y, li = blockIdx.z;
-  const int L = kv_len[b];
-  int a = accept_len[b];
-  if (L < 0 || L + T_nodes > max_kv || a < 0) return;       // the target pass wrote nothing (flagged there)
-  if (a > K) a = K;
+__global__ __launch_bounds__(256) void k_commit(T *k_caches, T *v_caches, int n_layers, int B, int n_heads, int d_h, int max_kv,
+                                                int T_nodes, const int32_t *kv_len, const int32_t *accept_len,
+                                                const int32_t *accept_path, int K, int d, const float *hidden, const int32_t *tree_tok,
+                                                const int32_t *next_tok, float *h_new, int32_t *tok_new, int32_t *n_new) {
+  constexpr int PER = Elem<T>::PER;
+  const int h = blockIdx.x, b = blockIdx.y, li = blockIdx.z, t = threadIdx.x;
+  const int32_t *path = accept_path + (size_t)b * (K + 1);
+  if (li == n_layers) {                                      // the draft's next rows
+    const int a = min(max(accept_len[b], 0), K);
+    for (int j = h; j <= K; j += n_heads) {
+      const int node = min(max(path[j], 0), T_nodes - 1), node1 = min(max(path[min(j + 1, K)], 0), T_nodes - 1);
+      float *dst = h_new + ((size_t)b * (K + 1) + j) * d;
+      const float *src = hidden + ((size_t)b * T_nodes + node) * d;
+      for (int k = t * 4; k < d; k += 256 * 4) {
+        float4 v = *reinterpret_cast<const float4 *>(src + k);
+        if (j > a) v = make_float4(0.f, 0.f, 0.f, 0.f);
+        *reinterpret_cast<float4 *>(dst + k) = v;
+      }
+      if (t == 0) {
+        tok_new[(size_t)b * (K + 1) + j] = j < a ? tree_tok[(size_t)b * T_nodes + node1] : j == a ? next_tok[b] : 0;
+        if (j == 0) n_new[b] = a + 1;
+      }
+    }
+    return;
+  }
+  // Thread t moves the 16-byte piece kp of key row kj, and of up to MAXI value rows vj + i * VR the dim ve (a row's dims lie
+  // 64 bytes apart).
+  const int kpr = d_h / PER, kj = 1 + t / kpr, kp = t % kpr;          // K * d_h / PER <= 256
+  const int VR = 256 / d_h, vj = 1 + t / d_h, ve = t % d_h;
+  constexpr int MAXI = AMPH_MAX_HEADS_K * 128 / 256;
+  const int L = kv_len[b], a_raw = accept_len[b];
+  const int kn = path[min(kj, K)];
+  int vn[MAXI];
+  #pragma unroll
+  for (int i = 0; i < MAXI; ++i) vn[i] = path[min(vj + i * VR, K)];
+  if (L < 0 || L + T_nodes > max_kv || a_raw < 0) return;   // the target pass wrote nothing (flagged there)
+  const int a = min(a_raw, K);
   const size_t head = (((size_t)li * B + b) * n_heads + h) * (size_t)max_kv * d_h;
   T *kc = k_caches + head, *vc = v_caches + head;
-  constexpr int MAXE = (AMPH_MAX_HEADS_K * 128 + 255) / 256;     // elements per thread: a * d_h <= 8 * 128
-  T kr[MAXE], vr[MAXE];
+  // (unconditional loads: a path's unused places name some row of the tree)
+  const uint4 kr = ldg16(kc + k_tiled_index<T>(L + min(max(kn, 0), T_nodes - 1), kp * PER, d_h));
+  T vr[MAXI];
   #pragma unroll
-  for (int i = 0; i < MAXE; ++i) {
-    const int idx = threadIdx.x + i * 256, j = idx / d_h + 1, e = idx % d_h;
-    if (j <= a) {
-      int node = accept_path[(size_t)b * (K + 1) + j];
-      node = min(max(node, 0), T_nodes - 1);
-      kr[i] = kc[k_tiled_index<T>(L + node, e, d_h)];
-      vr[i] = vc[v_tiled_index<T>(L + node, e, d_h)];
-    }
-  }
+  for (int i = 0; i < MAXI; ++i)
+    if (i * VR < K) vr[i] = vc[v_tiled_index<T>(L + min(max(vn[i], 0), T_nodes - 1), ve, d_h)];
   __syncthreads();
+  if (kj <= a) stg16(kc + k_tiled_index<T>(L + kj, kp * PER, d_h), kr);
   #pragma unroll
-  for (int i = 0; i < MAXE; ++i) {
-    const int idx = threadIdx.x + i * 256, j = idx / d_h + 1, e = idx % d_h;
-    if (j <= a) {
-      kc[k_tiled_index<T>(L + j, e, d_h)] = kr[i];
-      vc[v_tiled_index<T>(L + j, e, d_h)] = vr[i];
-    }
-  }
+  for (int i = 0; i < MAXI; ++i)
+    if (i * VR < K && vj + i * VR <= a) vc[v_tiled_index<T>(L + vj + i * VR, ve, d_h)] = vr[i];
 }
 
-__global__ __launch_bounds__(256) void k_gather_advance(const float *hidden, const int32_t *tree_tok, int T_nodes, int d,
-                                                        int K, const int32_t *accept_len, const int32_t *accept_path,
-                                                        const int32_t *next_tok, float *h_new, int32_t *tok_new,
-                                                        int32_t *n_new, int32_t *kv_len, int max_kv) {
-  const int j = blockIdx.x, b = blockIdx.y;
-  const int a = min(max(accept_len[b], 0), K);
-  if (j == 0 && threadIdx.x == 0) {
-    const int L = kv_len[b];
-    if (L >= 0 && L + T_nodes <= max_kv) kv_len[b] = L + a + 1;
-  }
-  if (!h_new) return;
-  const int32_t *path = accept_path + (size_t)b * (K + 1);
-  float *dst = h_new + ((size_t)b * (K + 1) + j) * d;
-  if (j <= a) {
-    const int node = min(max(path[j], 0), T_nodes - 1);
-    const float *src = hidden + ((size_t)b * T_nodes + node) * d;
-    for (int k = threadIdx.x * 4; k < d; k += 256 * 4) *reinterpret_cast<float4 *>(dst + k) = *reinterpret_cast<const float4 *>(src + k);
-    if (threadIdx.x == 0)
-      tok_new[(size_t)b * (K + 1) + j] = (j < a) ? tree_tok[(size_t)b * T_nodes + min(max(path[j + 1], 0), T_nodes - 1)] : next_tok[b];
-  } else {
-    for (int k = threadIdx.x * 4; k < d; k += 256 * 4) *reinterpret_cast<float4 *>(dst + k) = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (threadIdx.x == 0) tok_new[(size_t)b * (K + 1) + j] = 0;
-  }
-  if (j == 0 && threadIdx.x == 0) n_new[b] = a + 1;
+__global__ __launch_bounds__(64) void k_advance(const int32_t *accept_len, int B, int K, int T_nodes, int max_kv, int32_t *kv_len) {
+  const int b = threadIdx.x;                                // B <= 64
+  if (b >= B) return;
+  const int a = accept_len[b], L = kv_len[b];
+  if (L >= 0 && L + T_nodes <= max_kv) kv_len[b] = L + min(max(a, 0), K) + 1;
 }
 
 __global__ __launch_bounds__(256) void k_gather_rows(const float *rows, int R, int d, const int32_t *n_valid, float *out) {
@@ -810,12 +814,12 @@ hipError_t launch_commit(hipStream_t st, void *k_caches, void *v_caches, int n_l
                          int T_nodes, int d, int K, int32_t *kv_len, const int32_t *accept_len, const int32_t *accept_path,
                          const int32_t *next_tok, const int32_t *tree_tok, const float *hidden, float *h_new, int32_t *tok_new,
                          int32_t *n_new) {
-  if (K < 1 || K > AMPH_MAX_HEADS_K || d_h > 128 || d % 4) return hipErrorInvalidValue;
-  if (n_layers > 0)
-    hipLaunchKernelGGL((k_kv_commit<T>), dim3(n_heads, B, n_layers), dim3(256), 0, st, (T *)k_caches, (T *)v_caches, B, n_heads,
-                       d_h, max_kv, T_nodes, kv_len, accept_len, accept_path, K);
-  hipLaunchKernelGGL(k_gather_advance, dim3(h_new ? K + 1 : 1, B), dim3(256), 0, st, hidden, tree_tok, T_nodes, d, K, accept_len,
-                     accept_path, next_tok, h_new, tok_new, n_new, kv_len, max_kv);
+  if (K < 1 || K > AMPH_MAX_HEADS_K || (d_h != 64 && d_h != 128) || d % 4 || B > 64) return hipErrorInvalidValue;
+  const int nz = n_layers + (h_new ? 1 : 0);
+  if (nz > 0)
+    hipLaunchKernelGGL((k_commit<T>), dim3(n_heads, B, nz), dim3(256), 0, st, (T *)k_caches, (T *)v_caches, n_layers, B, n_heads, d_h,
+                       max_kv, T_nodes, kv_len, accept_len, accept_path, K, d, hidden, tree_tok, next_tok, h_new, tok_new, n_new);
+  hipLaunchKernelGGL(k_advance, dim3(1), dim3(64), 0, st, accept_len, B, K, T_nodes, max_kv, kv_len);
   return hipGetLastError();
 }
 template hipError_t launch_commit<float>(hipStream_t, void *, void *, int, int, int, int, int, int, int, int, int32_t *,
