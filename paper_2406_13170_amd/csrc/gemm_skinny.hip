@@ -1,7 +1,7 @@
 // GEMMs of the target's forward pass over the tree tokens (Sec. 2 "Tree Attention"): M = B*T activation rows
 // against [N, Kd] weights that stream from HBM once, on the matrix cores.  Two kernels: the skinny one
-// (described first; up to 64 rows, or row-major weights) and the wide one (further down; more than 128 rows, and the
-// matrices that suit it from 65 on).
+// (described first; up to 64 rows, or row-major weights) and the wide one (further down; more than 128 rows, and most
+// matrices from 65 on).
 //
 // The unit of work is a ROW BLOCK: 16 weight rows that one wave keeps as matrix-core A fragments and
 // whose outputs need nothing from any other block:
@@ -87,9 +87,9 @@ __device__ __forceinline__ RowMap map_block(const GemmArgs &a, int b, int r16) {
 // Epilogue of one 64-row block of a workgroup's output tile: Ct[m][r] (float32, pitch CT_PITCH) holds rows
 // m_base .. m_base + 63 of the activations against the tile's nb row blocks (BN = 16 * nb columns).  Every thread
 // of the workgroup (NT of them) takes part.
-template <typename T, int EPI>
+template <typename T, int EPI, int rows>                   // rows of Ct that are live: 32 or 64
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const float *Ct, int CT_PITCH, int tile, int nb, int m_base,
-                                              int split, int nblk, int tid, int NT, int rows = GM_BM) {   // rows of Ct that are live
+                                              int split, int nblk, int tid, int NT) {
   const int BN = 16 * nb;
   if (EPI == EPI_STORE) {
     // out is [split_k][M][N]: slab `split` receives this workgroup's partial sums
@@ -136,10 +136,10 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const float *Ct
     auto seg_of = [&](int b) { return (b >= 2 * bps) ? 2 : (b >= bps) ? 1 : 0; };
     // q and k blocks: one (block, token) per thread = 8 rotation pairs.  Everything the item needs from global
     // memory (64 bytes of the cos/sin table, the committed length) is requested first, for up to QK_U items of the
-    // thread at once: a wave of the wide kernel walks several items, and stores in between would keep the next item's
+    // thread at once: a wave of the wide kernel walks several items (up to 8), and stores in between would keep the next item's
     // loads from starting early.  The 8 + 8 results leave as 16-byte pieces: dims e0 .. e0+7 (and their partners at
     // + d_h/2) are adjacent in q and inside a fragment of the tiled K cache.
-    constexpr int QK_U = 3;
+    constexpr int QK_U = rows == 32 ? 5 : 3;
     for (int base = tid; base < nb * rows; base += QK_U * NT) {
       float4 tab[QK_U][4];
       int Lb[QK_U];
@@ -190,26 +190,26 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const float *Ct
         store4<T>(dst2, y2); store4<T>(dst2 + 4, y2 + 4);
       }
     }
-    // v blocks: 8 * rows items per row block (8 dims x the live tokens).  rows (32 or 64) divides the number of
-    // threads, so a thread keeps its token through the loop: its committed length is read once, ahead of the stores,
-    // and consecutive threads write consecutive tree rows, which are adjacent inside a step-tiled piece.
+    // v blocks: a thread takes 8 of a block's 16 dims for one token.  rows divides the number of threads, so a thread keeps
+    // its token through the loop: its committed length is read once, ahead of the stores, and consecutive threads write
+    // consecutive tree rows, which are adjacent inside a step-tiled piece.  A block's dims are adjacent pieces, so its
+    // addresses are one base and constants (computed for each element they took longer than the stores).
     {
+      constexpr int PIECE = 64 / (int)sizeof(T);
       const int m = tid % rows, mg = m_base + m;
       const bool row_ok = mg < a.M;
       const int bb = row_ok ? mg / a.T_nodes : 0, node = row_ok ? mg % a.T_nodes : 0;
       const int L = a.kv_len[bb];
       if (row_ok && L >= 0 && L + a.T_nodes <= a.max_kv) {
-        for (int q = tid / rows; q < nb * 8; q += NT / rows) {
-          const int w = q >> 3, j = q & 7, b = tile * nb + w;
-          if (b >= nblk) continue;
-          const int seg = seg_of(b), bl = b - seg * bps;
-          if (seg < 2) continue;
+        T *vb = (T *)a.v_cache + (size_t)bb * a.n_heads * (size_t)a.max_kv * d_h;
+        const size_t at = v_tiled_index<T>(L + node, 0, d_h);
+        for (int q = tid / rows; q < nb * 2; q += NT / rows) {
+          const int w = q >> 1, hh = q & 1, b = tile * nb + w, bl = b - 2 * bps;
+          if (b >= nblk || bl < 0) continue;
+          T *dst = vb + (size_t)(bl >> bsh) * (size_t)a.max_kv * d_h + at + ((bl & (bph - 1)) * 16 + hh * 8) * PIECE;
+          const float *c = Ct + m * CT_PITCH + w * 16 + hh * 8;
           #pragma unroll
-          for (int hh = 0; hh < 2; ++hh) {
-            const int head = bl >> bsh, e = ((bl & (bph - 1)) << 4) + j + 8 * hh;
-            T *vc = (T *)a.v_cache + ((size_t)bb * a.n_heads + head) * (size_t)a.max_kv * d_h;
-            vc[v_tiled_index<T>(L + node, e, d_h)] = Elem<T>::from_f32(Ct[m * CT_PITCH + w * 16 + j + 8 * hh]);
-          }
+          for (int j = 0; j < 8; ++j) dst[j * PIECE] = Elem<T>::from_f32(c[j]);
         }
       }
     }
@@ -413,54 +413,52 @@ __global__ __launch_bounds__(64 * (GM_MAX_NB + GM_NLW)) void k_gemm_skinny(const
   }
   __syncthreads();
 
-  gemm_epilogue<T, EPI>(a, Ct, CT_PITCH, tile, nb, m_base, split, nblk, tid, NT);
+  gemm_epilogue<T, EPI, GM_BM>(a, Ct, CT_PITCH, tile, nb, m_base, split, nblk, tid, NT);
 }
 
 // =====================================================================================================
 // Wide GEMM: more than 64 activation rows (batches of trees, wide trees; gemm_is_wide).  The skinny kernel above re-reads the
 // weights from L2 once per block of 64 rows, every math wave re-reads the whole activation chunk from LDS, and its
 // 16 x 16 matrix-core instruction runs at half the rate of the 32 x 32 one: with several blocks of rows L2, LDS
-// and the matrix cores, not HBM, set the pace.  Here a workgroup owns a group of up to 12 (or 13 to 16) tiles of 32
-// activation rows against NB weight row blocks, and the roles of the operands are swapped:
-//   * the weights are the shared operand: two loader waves stream the workgroup's NB blocks from HBM straight
-//     into a ring of LDS stages (global-to-LDS loads, 8 or 4 steps of 64 bytes of k per stage), so they cross L2 once;
-//   * each math wave owns one of the group's tiles (groups of 13 to 16: tiles w and w + 8) against all NB blocks, taken
-//     in pairs (32 weight rows): per step and half-step it reads one weight fragment per pair from LDS and one
-//     activation fragment per tile from global memory (L2 hits, requested 2 or 4 steps ahead into registers) and issues
-//     one matrix-core instruction of 32 x 32 per pair and tile; one barrier per stage.
-// What bounds it is what a compute unit takes in, 40 to 50 GB/s of weights and activations together: a workgroup reads its
-// group's activations for its NB blocks only, (32 gt + 16 NB) bytes against 512 gt NB products.  One tile per wave
-// halves the accumulators, so that up to ten blocks fit in the registers of eight to twelve waves, where two tiles
-// per wave ended at six: 384 rows, 35840 x 6656 (10 blocks) 224 -> 182 us = 1.0 PFLOP/s, 32000 x 6656 (8) 189 -> 160;
-// 512 rows in two groups, 32000 x 4096 (8) 152 -> 134, 12288 x 4096 (6) 70 -> 66; 128 rows, against the skinny kernel,
-// 27648 x 5120 84 -> 63, 32000 x 5120 97 -> 67, 35840 x 6656 134 -> 100, 32000 x 6656 121 -> 82.
+// and the matrix cores, not HBM, set the pace.  Here a workgroup of four waves, one for each SIMD, owns a group of gt <= 12 tiles
+// of 32 activation rows against NB = 2 NP weight row blocks; wave w owns tiles w, w + 4, w + 8 of the group against all blocks,
+// taken in pairs (32 weight rows).
+//   * The weights are the shared operand: of every block of a stage (4 steps of 64 bytes of k) a wave brings in one step, through
+//     registers (requested a stage ahead) into one of two LDS slots.
+//   * The activations go from global memory (L2 hits) straight into the registers of the one wave that needs them, 3.5 steps ahead.
+//   * A half-step reads one weight fragment per pair from LDS and issues one 32 x 32 matrix-core instruction per pair and tile.
+//     The fragments of the next half-step are read, the activations requested and the next stage written between these
+//     instructions, in an order laid down by hand; the barrier lies ahead of a stage's last half-step, whose operands are in
+//     registers by then, and the next stage's first fragments are read behind it, so that it costs nothing either.
+// Why four waves: with one wave a SIMD its 512 registers hold up to 16 accumulators of 32 x 32, so an LDS fragment is used for two
+// or three tiles and the rows of a group are read again once for up to 16 blocks.  Before, eight to twelve math waves had a tile
+// each (10 blocks at most) or two (6 blocks), beside two waves that did nothing but load: a tile a wave reads 8 clocks of LDS
+// for 8 clocks of matrix core on its compute unit, and 512 x 96 outputs take in 38 KB a step where 256 x 192 take 28.
+// What bounds it: matrix-core clocks (a loop without any loads: 67 us of the 85 below; the clock drops under
+// such a load: 54 us on a quarter of the chip), then what the weights' way through registers and LDS adds (16 us) and the activations' (7).
+// Measured (us, before / now): 512 rows 22016 x 4096 99 / 85 (1.08 PFLOP/s), 32000 x 4096 144 / 116, 12288 x 4096 58 / 52;
+// 384 rows 35840 x 6656 218 / 169, 32000 x 6656 177 / 137 (1.2 PFLOP/s); 256 rows 22016 x 4096 62 / 53; 128 rows 27648 x 5120
+// 63 / 57, 5120 x 13824 43 / 34; all of a layer's matrices and the LM head at 7B, 13B and 33B widths over 80 to 768 rows 12.5 / 11.0 ms.
+// Tried: weights two stages ahead, activations 7.5 steps ahead (more registers, no gain); five pairs and more with a tile a
+// wave (LDS-bound).
 // A 32 x 32 instruction takes, per lane (half, r), 16 bytes of row r: the bytes [half * 16, half * 16 + 16) of
-// 32 bytes of k.  The weight fragments in LDS are the 16-row x 64-byte ones of the tiled layout, piece (g, r16)
-// at (g * 16 + r16) * 16: lane (half, r) of half-step h reads piece (2h + half, r % 16) of block r / 16 of the
-// pair, 16 lanes per 256 contiguous bytes.  The activations must be tiled to match (a fragment gathered from
+// 32 bytes of k: piece (2h + half) of row r % 16 of block r / 16 of the pair, for half-step h.  The activations must be
+// tiled to match (a fragment gathered from
 // row-major rows is the slow many-half-lines load): k_tile_rows rewrites [M, Kd] as
 // xt[(q * m32_tiles + tile) * 1024 + lane * 16], q = index of 32 bytes of k, lane = half * 32 + row % 32, rows
 // past M as zeros (a few microseconds).
 // =====================================================================================================
-constexpr int gw_steps(int np) { return np > 3 ? 4 : 8; }   // steps (64 bytes of k) per weight stage
-constexpr int GW_R = 3;            // weight stages in the LDS ring
-constexpr int GW_NL = 2;           // loader waves
-constexpr int GW_MAX_NP = 5;       // pairs of weight row blocks per workgroup with a tile per wave
-constexpr int GW_MAX_NP_QKV = 4;   // ... with the rotation epilogue (five pairs are not built for it)
-constexpr int GW_MAX_NP2 = 3;      // ... with two tiles per wave
-constexpr int GW_MAX_NW1 = 12;     // math waves per workgroup with a tile of 32 activation rows each (three waves per SIMD)
-constexpr int GW_MAX_NW = 8;       // ... with two tiles each (two waves per SIMD)
-constexpr int GW_XD = 4;           // steps of activations requested ahead
-constexpr int GW_AUX_NT = 2;       // cache-policy bits of the global-to-LDS load: non-temporal (the weights are read once)
+constexpr int GW_W = 4;            // waves, one per SIMD
+constexpr int GW_ST = 4;           // steps (64 bytes of k) per weight stage
+constexpr int GW_MAX_TW = 3;       // tiles of 32 activation rows per wave
 
+// pairs of weight row blocks that are built for tw tiles a wave (float32, bound by its matrix cores at any tile: two sizes, two tiles at most)
+constexpr bool gw_built(int elem_bytes, int np, int tw) {
+  if (elem_bytes == 4) return tw <= 2 && (np == 2 || np == 4);
+  return np >= 2 && (np <= 5 || (tw == 2 && (np == 6 || np == 8)));
+}
+constexpr int GW_MAX_NP = 8;
 constexpr size_t gw_ct_bytes(int np) { return (size_t)32 * (32 * np + 4) * 4; }   // a wave's output tile in the epilogue
-constexpr int gw_epi_waves(int np, int nwmax) {            // waves whose output tiles fit in LDS together
-  return (int)((size_t)nwmax * gw_ct_bytes(np) <= 160 * 1024 ? nwmax : 160 * 1024 / gw_ct_bytes(np));
-}
-
-template <int N> __device__ __forceinline__ void gw_wait_vm() {
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
-}
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_tile_rows(const unsigned char *x, int M, int row_bytes, int m32_tiles, unsigned char *xt) {
@@ -477,29 +475,24 @@ __global__ __launch_bounds__(256) void k_tile_rows(const unsigned char *x, int M
   }
 }
 
-template <typename T, int EPI, int NP, int TW, int NWMAX>      // NWMAX = 8: up to two math waves per SIMD (168 registers each); 12: three (128)
-__global__ __launch_bounds__(64 * (NWMAX + GW_NL)) void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt) {
+template <typename T, int EPI, int NP, int TW>
+__global__ __launch_bounds__(64 * GW_W) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt) {
   extern __shared__ __align__(16) unsigned char gw_lds[];
-  constexpr int GW_STEPS = gw_steps(NP), NB = 2 * NP, STAGE = NB * GW_STEPS * 1024, PERL = NB * GW_STEPS / GW_NL;
-  static_assert(GW_R == 3 && PERL * (GW_R - 2) <= 63, "loader wave's outstanding loads");
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int NT = blockDim.x, nw = (NT >> 6) - GW_NL;       // math waves
+  constexpr int NB = 2 * NP, STAGE = NB * GW_ST * 1024, XD = GW_ST;    // XD: steps in the ring of activations
+  static_assert(GW_ST == GW_W, "a wave brings in one step of every block of a stage");
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, r32 = lane & 31;
   const int S = a.split_k;
   const int id = blockIdx.x, unit = (id / 8 / mgroups) * 8 + (id & 7), mgroup = (id / 8) % mgroups;
   if (unit >= tiles * S) return;                          // padding of the last group of 8 units (whole workgroup)
   const int tile = unit / S, split = unit % S;
-  constexpr int XD = TW == 2 || (NWMAX == 12 && NP > 3) ? 2 : GW_XD; // steps of activations requested ahead (registers)
-  static_assert(GW_STEPS % XD == 0, "the activation ring is indexed statically inside a stage");
-  // Tiles of this group: gt of them from g0 on, wave w owning tile w, and w + nw where it has two: with fewer than 2 * nw
-  // tiles the waves left with one tile are the upper half, which share their SIMDs with the lower half.
-  const int g0 = mgroup * gt;
-  auto tile_of = [&](int t) { return g0 + wave + t * nw; };
-  auto live = [&](int t) { const int x = tile_of(t); return x < g0 + gt && x < m32_tiles; };
+  const int g0 = mgroup * gt, g1 = min(g0 + gt, m32_tiles);
+  auto tile_of = [&](int t) { return g0 + wave + t * GW_W; };
   const int total_steps = a.Kd * (int)sizeof(T) / 64;
   const int ssh = __ffs(S) - 1;                           // S is 1, 2, 4 or 8
   const int s0 = (total_steps * split) >> ssh, s1 = (total_steps * (split + 1)) >> ssh;
   const int n = s1 - s0;
-  const int P = (n + GW_STEPS - 1) / GW_STEPS;             // weight stages
+  const int P = (n + GW_ST - 1) / GW_ST;                   // stages
   const int nblk = gemm_blocks(EPI, a.seg_rows);
 
   f32x16 acc[NP][TW];
@@ -510,145 +503,147 @@ __global__ __launch_bounds__(64 * (NWMAX + GW_NL)) void k_gemm_wide(const GemmAr
       #pragma unroll
       for (int i = 0; i < 16; ++i) acc[p][t][i] = 0.f;
 
-  if (wave >= nw) {
-    // ---------------------------------------------------------------------------- loader wave
-    // Loader l takes steps l * HS .. + HS - 1 of every block of a stage (fragment f = block * GW_STEPS + step lies at
-    // f * 1024 of the stage).  Lane (g, r16) fetches piece g of row r16, which lands at (g * 16 + r16) * 16 of the
-    // fragment's KB in LDS.  Those HS fragments are adjacent both in memory and in LDS, so they share one address and
-    // one LDS base and differ in the instruction's immediate offset (applied to both sides): a load costs the wave one
-    // instruction instead of a dozen.  That matters because the loader shares its SIMD's issue port with a math wave
-    // whose matrix-core instructions keep it busy (measured before: 233 clocks per load, the weight ring the
-    // bottleneck).  A ragged last stage takes the general path: steps past the slice re-read its last step and are
-    // never used.
-    constexpr int HS = GW_STEPS / GW_NL;
-    static_assert(GW_STEPS % GW_NL == 0 && (HS == 4 || HS == 2), "the immediate offsets per block, written out below");
-    const int l = wave - nw, g = lane >> 4, r16 = lane & 15;
-    const unsigned char *wbase = (const unsigned char *)a.wt + r16 * 64 + g * 16;
-    const unsigned char *bsrc[NB];
+  // Weights: this wave's step of every block of a stage, contiguous 1 KB pieces.  Lane l has piece l % 4 of row l / 4; in LDS a row's
+  // pieces are permuted (piece g at g ^ (row / 4)), which leaves the fragment reads free of bank conflicts.  Blocks past the
+  // end re-read the last one and are never stored, steps past the slice its last one and are never multiplied.
+  const unsigned char *wt = (const unsigned char *)a.wt + (size_t)tile * NB * total_steps * 1024 + lane * 16;
+  const int wdst = wave * 1024 + (lane >> 2) * 64 + (((lane & 3) ^ (lane >> 4)) & 3) * 16;
+  uint4 wr[NB];
+  auto load_w = [&](int b, int p) {
+    const int st = s0 + min(p * GW_ST + wave, n - 1);
+    return ldg16_stream(wt + (unsigned)(min(b, nblk - 1 - tile * NB) * total_steps + st) * 1024u);
+  };
+  auto store_w = [&](int b, int slot, const uint4 &w) { *reinterpret_cast<uint4 *>(gw_lds + slot * STAGE + b * (GW_ST * 1024) + wdst) = w; };
+  // Activations: tiles past the end re-read the last one and are never stored, steps past the slice the last one
+  const unsigned char *xb = (const unsigned char *)a.xt + lane * 16;
+  uint4 xq[XD][2][TW];
+  auto load_x = [&](int i, int h, uint4 (&xf)[TW]) {
+    const size_t row = (size_t)(2 * (s0 + min(i, n - 1)) + h) * m32_tiles;
     #pragma unroll
-    for (int b = 0; b < NB; ++b) bsrc[b] = wbase + ((size_t)min(tile * NB + b, nblk - 1) * total_steps + s0 + l * HS) * 1024;
-    auto issue = [&](int p) {
-      unsigned char *lp = gw_lds + (p % GW_R) * STAGE;
-      if ((p + 1) * GW_STEPS <= n) {                       // a whole stage (wave-uniform)
-        #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-          const unsigned char *src = bsrc[b] + (size_t)p * (GW_STEPS * 1024);
-          unsigned char *dst = lp + (b * GW_STEPS + l * HS) * 1024;
-          const auto *gs = (const __attribute__((address_space(1))) void *)src;
-          auto *ld = (__attribute__((address_space(3))) void *)dst;
-          __builtin_amdgcn_global_load_lds(gs, ld, 16, 0, GW_AUX_NT);       // (the offset must be a literal)
-          __builtin_amdgcn_global_load_lds(gs, ld, 16, 1024, GW_AUX_NT);
-          if constexpr (HS == 4) {
-            __builtin_amdgcn_global_load_lds(gs, ld, 16, 2048, GW_AUX_NT);
-            __builtin_amdgcn_global_load_lds(gs, ld, 16, 3072, GW_AUX_NT);
-          }
-        }
-      } else {
-        #pragma unroll
-        for (int j = 0; j < PERL; ++j) {
-          const int b = j / HS, s = l * HS + j % HS, f = b * GW_STEPS + s;
-          const int blk = min(tile * NB + b, nblk - 1);
-          const int st = min(s0 + p * GW_STEPS + s, s1 - 1);
-          const unsigned char *src = wbase + ((size_t)blk * total_steps + st) * 1024;
-          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
-                                           (__attribute__((address_space(3))) void *)(lp + f * 1024), 16, 0, GW_AUX_NT);
-        }
-      }
-    };
-    const int pro = P < GW_R - 1 ? P : GW_R - 1;
-    for (int p = 0; p < pro; ++p) issue(p);
-    for (int p = 0; p < P; ++p) {
-      if (p + 1 < P) gw_wait_vm<PERL>(); else gw_wait_vm<0>();   // stage p has landed (one younger stage may be in flight)
-      __builtin_amdgcn_s_barrier();                        // math waves may read stage p; they are done with stage p - 1
-      if (p + GW_R - 1 < P) issue(p + GW_R - 1);           // into the slot of stage p - 1
-    }
-  } else {
-    // ------------------------------------------------------------------------------ math wave
-    // the 2 * TW fragments of a step (two halves of its 64 bytes for every tile of 32 rows) are requested XD steps ahead
-    const int half = lane >> 5, r32 = lane & 31;
-    const unsigned char *xb = (const unsigned char *)a.xt + lane * 16;
-    uint4 xq[XD][2][TW];
-    auto load_x = [&](int i, uint4 (&xf)[2][TW]) {
-      const int st = s0 + max(min(i, n - 1), 0);           // unconditional: steps past the slice re-read the last one
-      #pragma unroll
-      for (int h = 0; h < 2; ++h)
-        #pragma unroll
-        for (int t = 0; t < TW; ++t) {
-          const int mt = min(tile_of(t), m32_tiles - 1);   // tiles past the end (last wave) re-read the last tile; never stored
-          xf[h][t] = ldg16(xb + ((size_t)(2 * st + h) * m32_tiles + mt) * 1024);
-        }
-    };
-    // weight piece of this lane inside a pair's two fragments of a step, for half-step h: + h * 512
-    const int woff = (r32 >> 4) * (GW_STEPS * 1024) + (half * 16 + (r32 & 15)) * 16;
+    for (int t = 0; t < TW; ++t) xf[t] = ldg16(xb + (row + min(tile_of(t), m32_tiles - 1)) * 1024);
+  };
+  const int r16 = r32 & 15, woff = (r32 >> 4) * (GW_ST * 1024) + r16 * 64;
+  const int pc0 = ((half ^ (r16 >> 2)) & 3) * 16, pc1 = (((2 + half) ^ (r16 >> 2)) & 3) * 16;
+  uint4 wf[2][NP];
+  auto read_w = [&](int u, int j, uint4 (&w)[NP]) {        // the fragments of half-step j of the stage in slot u
+    const unsigned char *sb = gw_lds + u * STAGE + woff + ((j & 1) ? pc1 : pc0) + (j >> 1) * 1024;
     #pragma unroll
-    for (int i = 0; i < XD; ++i) load_x(i, xq[i]);
-    // NTL = tiles this wave multiplies: TW, or 1 for a wave whose second tile does not exist
-    auto run = [&](auto tag) {
-      constexpr int NTL = decltype(tag)::value;
-      for (int p = 0; p < P; ++p) {
-        // Stage p is in LDS (pairs with the loaders' barrier).  A bare barrier: __syncthreads() would also wait for this
-        // wave's outstanding activation loads (the fence it carries counts them since the kernel contains global-to-LDS
-        // loads) and drain the prefetch ring at every stage.  The "memory" clobber keeps the LDS reads below it.  The reads
-        // of stage p - 1, whose slot the loaders refill behind the barrier, are waited for here: the clobber does not hold
-        // back the matrix-core instructions that use them, so the compiler's own wait may come to lie behind the barrier.
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        const unsigned char *sb = gw_lds + (p % GW_R) * STAGE + woff;
-        #pragma unroll
-        for (int s = 0; s < GW_STEPS; ++s) {
-          const int i = p * GW_STEPS + s;
-          if (i < n) {                                     // wave-uniform
-            #pragma unroll
-            for (int h = 0; h < 2; ++h)
-              #pragma unroll
-              for (int pr = 0; pr < NP; ++pr) {
-                const uint4 wf = *reinterpret_cast<const uint4 *>(sb + (2 * pr * GW_STEPS + s) * 1024 + h * 512);
-                #pragma unroll
-                for (int t = 0; t < NTL; ++t) acc[pr][t] = mma32<T>(wf, xq[s % XD][h][t], acc[pr][t]);
-              }
-          }
-          load_x(i + XD, xq[s % XD]);
-        }
-      }
-    };
-    if (TW > 1 && !live(1)) run(GemmTag<1>{}); else run(GemmTag<TW>{});
-  }
+    for (int pr = 0; pr < NP; ++pr) w[pr] = *reinterpret_cast<const uint4 *>(sb + 2 * pr * GW_ST * 1024);
+  };
 
-  // ---- epilogues: every math wave handles its own activation rows through its own Ct region in LDS (the ring is
-  // free by now), one tile of 32 rows at a time, the 64 lanes playing the workgroup of the shared epilogue code.
-  // Lane (half, r32) holds activation row t * 32 + r32 and weight rows (i / 4) * 8 + half * 4 + (i % 4) of each pair.
-  const int CT_PITCH = 16 * NB + 4;
-  // As many waves at a time as there is room for, in rounds; every wave passes each round's barrier.  A wave's own part is
-  // straight-line code between its barriers: inside a loop over the rounds its accumulators would stay live across the
-  // epilogue (QKV: up to 93 registers spilled; us, inside a loop / here: 33B over 384 rows 146 / 136, 7B over 512 71 / 67,
-  // 13B over 512 97 / 95).
-  constexpr int EW = gw_epi_waves(NP, NWMAX);
-  const int rounds = EW >= NWMAX ? 1 : (nw + EW - 1) / EW, mine = wave < nw ? (EW >= NWMAX ? 0 : wave / EW) : rounds - 1;
-  for (int r = 0; r <= mine; ++r) __syncthreads();         // every wave has left the ring (the waves of the rounds before, their regions)
-  if (wave < nw && live(0)) {                              // whole waves
-    float *Ct = reinterpret_cast<float *>(gw_lds) + (size_t)(wave - mine * EW) * 32 * CT_PITCH;
-    const int half = lane >> 5, r32 = lane & 31;
+  auto run = [&](auto tag) {                               // tag: tiles that this wave multiplies, TW or one less
+    constexpr int NTL = decltype(tag)::value;
     #pragma unroll
-    for (int t = 0; t < TW; ++t) {
-      if (!live(t)) break;                                 // (wave-uniform)
-      if (t > 0) {                                         // the lanes are done reading the tile before
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (int b = 0; b < NB; ++b) wr[b] = load_w(b, 0);
+    #pragma unroll
+    for (int i = 0; i < XD; ++i) { load_x(i, 0, xq[i][0]); load_x(i, 1, xq[i][1]); }
+    #pragma unroll
+    for (int b = 0; b < NB; ++b) store_w(b, 0, wr[b]);
+    #pragma unroll
+    for (int b = 0; b < NB; ++b) wr[b] = load_w(b, 1);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    read_w(0, 0, wf[0]);
+    constexpr int HSN = 2 * GW_ST, W0 = 1, WN = 4, WB = (NB + WN - 1) / WN;      // half-steps of a stage; the WN from W0 on write the next one
+    auto stage = [&](int p, auto utag, auto whole) {       // utag: slot p % 2; whole: all its steps are in the slice
+      constexpr int u = decltype(utag)::value;
+      #pragma unroll
+      for (int j = 0; j < HSN; ++j) {
+        const int i = p * GW_ST + (j >> 1);
+        if (j == HSN - 1) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the next stage is whole, this one read
+        if (j < HSN - 1) read_w(u, j + 1, wf[(j + 1) & 1]); else read_w(u ^ 1, 0, wf[0]);
+        // into the registers of the half-step before
+        constexpr int XH = 2 * XD;
+        const int xj = (p * HSN + j + XH - 1) >> 1, xr = ((u * HSN + j + XH - 1) % XH);
+        load_x(xj, xr & 1, xq[xr >> 1][xr & 1]);
+        #pragma unroll
+        for (int b = 0; b < NB; ++b)
+          if (j >= W0 && b / WB == j - W0) {
+            store_w(b, u ^ 1, wr[b]);
+            wr[b] = load_w(b, p + 2);
+          }
+        if (decltype(whole)::value || i < n) {
+          #pragma unroll
+          for (int pr = 0; pr < NP; ++pr)
+            #pragma unroll
+            for (int t = 0; t < NTL; ++t) acc[pr][t] = mma32<T>(wf[j & 1][pr], xq[(j >> 1) % XD][j & 1][t], acc[pr][t]);
+        }
+        if (decltype(whole)::value) {
+          #pragma unroll
+          for (int pr = 0; pr < NP; ++pr) {
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                 // an LDS read,
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                 // a matrix instruction,
+            __builtin_amdgcn_sched_group_barrier(0x220, 1, 0);                 // a load or an LDS write
+            if (NTL > 1) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x220, 1, 0);
+            if (NTL > 2) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
+    };
+    int p = 0;
+    for (; (p + 2) * GW_ST <= n; p += 2) {
+      stage(p, GemmTag<0>{}, GemmTag<1>{});
+      stage(p + 1, GemmTag<1>{}, GemmTag<1>{});
+    }
+    if (p < P) stage(p, GemmTag<0>{}, GemmTag<0>{});
+    if (p + 1 < P) stage(p + 1, GemmTag<1>{}, GemmTag<0>{});
+  };
+  if (TW > 1 && tile_of(TW - 1) >= g1) run(GemmTag<(TW > 1 ? TW - 1 : 1)>{}); else run(GemmTag<TW>{});
+
+  // ---- epilogues.  Lane (half, r32) holds activation row t * 32 + r32 and weight rows (i / 4) * 8 + half * 4 + (i % 4) of each pair.
+  // The row argmax needs nothing but these registers (through LDS, four lanes to a row, it took 16 us of 135 over 512 rows of
+  // 32000 x 4096); everything else goes through the wave's own Ct region in LDS (the ring is free by now), one tile of 32 rows at
+  // a time, the 64 lanes playing the workgroup of the shared epilogue code.
+  const int CT_PITCH = 16 * NB + 4;
+  __syncthreads();                                         // every wave has left the ring
+  float *Ct = reinterpret_cast<float *>(gw_lds) + (size_t)wave * 32 * CT_PITCH;
+  #pragma unroll
+  for (int t = 0; t < TW; ++t) {
+    if (tile_of(t) >= g1) break;                           // (wave-uniform)
+    if (EPI == EPI_ARGMAX) {
+      float bv = -__builtin_huge_valf(); int bi = 0x7fffffff;
       #pragma unroll
       for (int pr = 0; pr < NP; ++pr)
         #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const f32x4 v = {acc[pr][t][4 * q4], acc[pr][t][4 * q4 + 1], acc[pr][t][4 * q4 + 2], acc[pr][t][4 * q4 + 3]};
-          *reinterpret_cast<f32x4 *>(Ct + r32 * CT_PITCH + pr * 32 + q4 * 8 + half * 4) = v;
+        for (int i = 0; i < 16; ++i) {
+          const int nn = tile * 16 * NB + pr * 32 + (i >> 2) * 8 + half * 4 + (i & 3);
+          const float v = acc[pr][t][i];
+          if (nn < a.seg_rows && (v > bv || (v == bv && nn < bi))) { bv = v; bi = nn; }
         }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the wave's LDS writes before its lanes read each other's
+      const auto ov = __builtin_amdgcn_permlane32_swap(lane_bits(bv), lane_bits(bv), false, false);
+      const auto oi = __builtin_amdgcn_permlane32_swap((unsigned)bi, (unsigned)bi, false, false);
+      const int mg = tile_of(t) * 32 + r32;
+      take_better(bv, bi, lane_value<float>(ov[1]), (int)oi[1]);   // (lanes of the lower half: the upper half's best)
+      if (half == 0 && mg < a.M) {
+        a.amax_val[(size_t)tile * a.M + mg] = bv;
+        a.amax_idx[(size_t)tile * a.M + mg] = bi;
+      }
+      if (!a.logits) continue;
+    }
+    if (t > 0) {                                           // the lanes are done reading the tile before
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      gemm_epilogue<T, EPI>(a, Ct, CT_PITCH, tile, NB, tile_of(t) * 32, split, nblk, lane, WAVE, 32);
+    }
+    #pragma unroll
+    for (int pr = 0; pr < NP; ++pr)
+      #pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const f32x4 v = {acc[pr][t][4 * q4], acc[pr][t][4 * q4 + 1], acc[pr][t][4 * q4 + 2], acc[pr][t][4 * q4 + 3]};
+        *reinterpret_cast<f32x4 *>(Ct + r32 * CT_PITCH + pr * 32 + q4 * 8 + half * 4) = v;
+      }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the wave's LDS writes before its lanes read each other's
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (EPI == EPI_ARGMAX) {
+      GemmArgs al = a;
+      al.out = a.logits;
+      gemm_epilogue<T, EPI_STORE, 32>(al, Ct, CT_PITCH, tile, NB, tile_of(t) * 32, 0, nblk, lane, WAVE);
+    } else {
+      gemm_epilogue<T, EPI, 32>(a, Ct, CT_PITCH, tile, NB, tile_of(t) * 32, split, nblk, lane, WAVE);
     }
   }
-  for (int r = mine + 1; r < rounds; ++r) __syncthreads();
 }
 
 // Row-major -> tiled (see the layout above).  One thread per 16-byte piece of the tiled buffer.
@@ -745,9 +740,6 @@ static GemmPlan plan_skinny(int epi, int seg_rows, int Kd, int elem_bytes, int M
   double best_cost = 1e300;
   best.blocks = blocks;
   best.mgroups = mblocks;
-  best.nw = 1;
-  best.tw = 2;
-  best.gt = 2;
   for (int s = 1; s <= 8; s *= 2) {
     if (split_req > 0 && s != split_req) continue;
     if (split_req == 0 && (fused ? s > 1 : (s > 1 && total_steps / s < 2 * GM_STEPS))) continue;
@@ -763,40 +755,33 @@ static GemmPlan plan_skinny(int epi, int seg_rows, int Kd, int elem_bytes, int M
   return best;
 }
 
-// The wide kernel's tiles for a given split: a workgroup owns a group of tiles of 32 activation rows against nb weight row
-// blocks.  Candidates: groups of up to 12 tiles with a math wave for each, as few as possible or one more (twice the
-// workgroups pay when the weight matrix has too few row blocks to fill the chip); groups of 13 to 16 tiles, two tiles a
-// wave, which read the weights once.  The price is in us, fitted to 500 measurements at 7B, 13B and 33B shapes over 96 to
-// 768 rows (11 % deviation): per step of 64 bytes of k a workgroup takes in 2 KB for every tile and 1 KB for every block,
-// and its matrix cores and LDS reads go with blocks times tiles and with blocks.  Three waves on a SIMD come with the
-// shorter activation ring.  The grid needs a round for every 256 workgroups (the LDS ring leaves room for one in a
-// compute unit).
+// The wide kernel's tiles for a given split: groups of gt tiles of 32 activation rows (up to three a wave) against nb weight row
+// blocks.  The price is in us, fitted to 2840 measurements at 7B, 13B and 33B widths over 80 to 768 rows (5 % deviation; its picks take
+// 11.02 ms over them where the best ones take 10.98): per step of 64 bytes of k the matrix cores take their time for the blocks
+// and tiles of the busiest wave, and the workgroup takes in 2 KB for every tile and 1 KB for every block (of which several
+// groups share the way from HBM), faster on a chip that is not full.  A compute unit has one workgroup at a time, and the workgroups are dealt to the XCDs in
+// eights: 252 of them in three groups can mean 33 on one XCD and a second round (6656 x 17920 over 320 rows: 172 us against 106).
+// float32 takes eight times as long for a step's matrix-core work.
 static GemmPlan plan_wide(int epi, int seg_rows, int Kd, int elem_bytes, int M, int split) {
   GemmPlan best{};
   const int blocks = gemm_blocks(epi, seg_rows);
-  const int steps = (Kd * elem_bytes / 64 + split - 1) / split;
-  double best_cost = 1e300;
+  const double steps = (double)(Kd * elem_bytes / 64 + split - 1) / split;
   best.blocks = blocks;
   best.wide = true;
   best.split = split;
-  const int mt = (M + 31) / 32;
-  for (int cand = 0; cand < 3; ++cand) {
-    const int mg = cand == 2 ? (mt + 15) / 16 : (mt + GW_MAX_NW1 - 1) / GW_MAX_NW1 + cand;
-    const int gt = (mt + mg - 1) / mg;                                // tiles per group
-    if (cand == 2 ? gt <= GW_MAX_NW1 : mg > mt) continue;
-    const int tw = cand == 2 ? 2 : 1, nw = cand == 2 ? GW_MAX_NW : gt;
-    const double waves = cand == 2 ? 1.08 : gt > 8 ? 1.2 : 1.0;
-    const int max_np = tw == 2 ? GW_MAX_NP2 : epi == EPI_QKV_ROPE ? GW_MAX_NP_QKV : GW_MAX_NP;
-    for (int nb = 2; nb <= 2 * max_np; nb += 2) {           // blocks are taken in pairs
-      if (nb > std::max(blocks, 2)) break;
-      const int tiles = (blocks + nb - 1) / nb;
-      const long rounds = ((long)tiles * split * mg + 255) / 256;
-      const double step = 0.006 * (2 * gt + nb) + 0.0031 * nb * gt + 0.0235 * nb;
-      const double cost = (double)rounds * (steps * step * waves + 4.0);
-      if (cost <= best_cost) {
-        best_cost = cost; best.nb = nb; best.tiles = tiles;
-        best.mgroups = mg; best.nw = nw; best.tw = tw; best.gt = gt;
-      }
+  best.cost = 1e300;
+  const int mt = (M + 31) / 32, most = GW_W * (elem_bytes == 4 ? 2 : GW_MAX_TW);
+  for (int mg = (mt + most - 1) / most; mg <= (mt + 2) / 3; ++mg) {   // (three tiles or more a group)
+    const int gt = (mt + mg - 1) / mg, tw = (gt + GW_W - 1) / GW_W;
+    if ((mg - 1) * gt >= mt) continue;                                // fewer groups of as many tiles do
+    for (int np = 2; np <= GW_MAX_NP; ++np) {
+      if (!gw_built(elem_bytes, np, tw)) continue;
+      const int nb = 2 * np, tiles = (blocks + nb - 1) / nb;
+      const long on_xcd = (long)((tiles * split + 7) / 8) * mg, rounds = (on_xcd + 31) / 32;
+      const double full = (double)on_xcd / (32.0 * rounds);
+      const double step = 0.0176 * np * tw * (elem_bytes == 4 ? 8 : 1) + (0.0137 * gt + 0.0204 * nb * (mg > 1 ? 0.75 : 1.0)) * (0.47 + 0.53 * full) + 0.045;
+      const double cost = (double)rounds * (steps * step + 2.1 + 0.78 * np * tw) * (np == 2 && tw > 1 ? 1.03 : 1.0);
+      if (cost < best.cost) { best.cost = cost; best.nb = nb; best.tiles = tiles; best.mgroups = mg; best.tw = tw; best.gt = gt; }
     }
   }
   return best;
@@ -807,9 +792,8 @@ static GemmPlan plan_wide(int epi, int seg_rows, int Kd, int elem_bytes, int M, 
 // their bits are the same.  Therefore it is a rule on the shape alone.  Up to 128 rows it is the skinny kernel's, for
 // whichever kernel runs and however the weights are stored: tiled and row-major weights give the same bits there.  Beyond
 // (tiled weights) it weighs, in units of a weight fragment, a workgroup's steps times its fragments per step and the tiles
-// that its busiest SIMD carries, for groups of up to 8, 12 (three a wave) or 16 tiles, against the slabs' way out and back.
-// Finer splits would suit the wide kernel's present tiles (us: W_down at 384 rows, 33B, four slabs 110, two 122, each fold
-// 16 against 14; 512 rows, 7B, 52 and 62, folds 13 against 12) and change every result.
+// that its busiest SIMD carries, for groups of up to 8, 12 or 16 tiles in pairs of blocks up to three, against the slabs' way out
+// and back; another count would change every result.
 static int gemm_split(int epi, int seg_rows, int Kd, int elem_bytes, int M, bool tiled) {
   if (epi != EPI_STORE) return 1;                           // fused epilogues need complete sums
   if (!tiled || M <= 2 * GM_BM) return plan_skinny(epi, seg_rows, Kd, elem_bytes, M, 0).split;
@@ -831,12 +815,12 @@ static int gemm_split(int epi, int seg_rows, int Kd, int elem_bytes, int M, bool
 }
 
 // Which kernel.  Up to 64 rows the skinny one, from 129 on the wide one.  In between (two blocks of 64 rows, or three and
-// four tiles of 32) it depends on the matrix: the skinny kernel still does well where the weights are one round of its
-// workgroups (us, skinny / wide, 128 rows: 7B QKV 12288 x 4096 36 / 39, 9216 x 3072 25 / 29, 13B W_o 5120 x 5120 21 / 25;
-// but 27648 x 5120 84 / 63, 32000 x 4096 80 / 62, 35840 x 6656 134 / 101).  Prices in us for equal slabs, 6 and 8 % off over
-// 105 pairs of measurements at model widths from 2048 to 8192 and 65 to 128 rows: always the wide kernel loses 60 us over
-// all of them against the better choice, always the skinny one 968, this rule 10.  float32 keeps to the skinny kernel,
-// whose sums row-major weights have.
+// four tiles of 32) mostly the wide one; the skinny kernel still does better where the matrix is small, or one round of its
+// workgroups with a split axis (us, skinny / wide, 128 rows: 2048 x 2048 7.0 / 9.0, 6144 x 2048 13.0 / 15.5, 4096 x 4096
+// 13.7 / 15.9, 5120 x 5120 18.1 / 20.6; but 12288 x 4096 36 / 34, 5120 x 13824 45 / 34, 27648 x 5120 84 / 57, 32000 x 4096 80 / 50).  Prices in
+// us for equal slabs, 5 % off over 90 pairs of measurements at model widths from 2048 to 8192 and 65 to 128 rows: always the
+// wide kernel takes 3890 us over all of them, always the skinny one 5042, this rule 3864, the better choice each time 3861.
+// float32 keeps to the skinny kernel, whose sums row-major weights have.
 bool gemm_is_wide(int epi, int seg_rows, int Kd, int elem_bytes, int M, bool tiled) {
   const int mblocks = (M + GM_BM - 1) / GM_BM;
   if (!tiled || mblocks < 2) return false;
@@ -845,10 +829,8 @@ bool gemm_is_wide(int epi, int seg_rows, int Kd, int elem_bytes, int M, bool til
   const int split = gemm_split(epi, seg_rows, Kd, elem_bytes, M, tiled);
   const GemmPlan s = plan_skinny(epi, seg_rows, Kd, elem_bytes, M, split), w = plan_wide(epi, seg_rows, Kd, elem_bytes, M, split);
   const double steps = (double)(Kd * elem_bytes / 64) / split, slab = epi == EPI_STORE ? 1.0e-6 * M * seg_rows * split : 0.0;
-  auto rounds = [split](int tiles, int groups) { return (double)(((long)tiles * split * groups + 255) / 256); };
-  const double us_s = rounds(s.tiles, mblocks) * (5.0 + steps * (0.030 * s.nb + 0.050)) + 2.1 * slab;
-  const double us_w = rounds(w.tiles, w.mgroups) * (4.7 + steps * (0.036 * w.nb + 0.020 * w.gt + 0.040)) + 2.4 * slab;
-  return us_w < us_s;
+  const double us_s = (double)(((long)s.tiles * split * mblocks + 255) / 256) * (3.5 + steps * (0.0254 * s.nb + 0.0654)) + 0.36 * slab;
+  return 1.06 * w.cost + 0.2 < us_s;
 }
 
 GemmPlan gemm_plan(int epi, int seg_rows, int Kd, int elem_bytes, int M, int split_req, bool tiled) {
@@ -859,35 +841,30 @@ GemmPlan gemm_plan(int epi, int seg_rows, int Kd, int elem_bytes, int M, int spl
 
 size_t gemm_xt_bytes(int M, int Kd, int elem_bytes) { return (size_t)((M + 31) / 32) * 32 * (size_t)Kd * elem_bytes; }
 
-template <typename T, int EPI, int NP, int TW, int NWMAX>
-static hipError_t launch_wide_np(hipStream_t st, const GemmArgs &a, const GemmPlan &pl, int m32_tiles, dim3 grid, dim3 block,
-                                 hipEvent_t ev_start, hipEvent_t ev_stop) {
-  // the weight ring, or (afterwards, in the same memory) the float32 output tiles (32 rows) of as many math waves as fit
-  constexpr size_t ring = (size_t)GW_R * 2 * NP * gw_steps(NP) * 1024, ct_wave = gw_ct_bytes(NP);
-  constexpr int epi_waves = gw_epi_waves(NP, NWMAX);
-  constexpr size_t smem_max = ring > epi_waves * ct_wave ? ring : epi_waves * ct_wave;
-  static_assert(smem_max <= 160 * 1024, "LDS of one workgroup");
-  const size_t smem = std::max(ring, (size_t)std::min(pl.nw, epi_waves) * ct_wave);
+template <typename T, int EPI, int NP, int TW>
+static hipError_t launch_wide_np(hipStream_t st, const GemmArgs &a, const GemmPlan &pl, int m32_tiles, dim3 grid, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  // two stages of weights, or (afterwards, in the same memory) the float32 output tiles (32 rows) of the waves
+  constexpr size_t ring = (size_t)2 * 2 * NP * GW_ST * 1024, ct = GW_W * gw_ct_bytes(NP), smem = ring > ct ? ring : ct;
+  static_assert(smem <= 160 * 1024, "LDS of one workgroup");
+  const dim3 block(64 * GW_W);
   static bool attr_set = false;                           // once per instantiation and process
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void *)k_gemm_wide<T, EPI, NP, TW, NWMAX>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_max);
+    hipError_t e = hipFuncSetAttribute((const void *)k_gemm_wide<T, EPI, NP, TW>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
   if (ev_start && ev_stop)
-    hipExtLaunchKernelGGL((k_gemm_wide<T, EPI, NP, TW, NWMAX>), grid, block, smem, st, ev_start, ev_stop, 0, a, pl.tiles, pl.mgroups, m32_tiles, pl.gt);
+    hipExtLaunchKernelGGL((k_gemm_wide<T, EPI, NP, TW>), grid, block, smem, st, ev_start, ev_stop, 0, a, pl.tiles, pl.mgroups, m32_tiles, pl.gt);
   else
-    hipLaunchKernelGGL((k_gemm_wide<T, EPI, NP, TW, NWMAX>), grid, block, smem, st, a, pl.tiles, pl.mgroups, m32_tiles, pl.gt);
+    hipLaunchKernelGGL((k_gemm_wide<T, EPI, NP, TW>), grid, block, smem, st, a, pl.tiles, pl.mgroups, m32_tiles, pl.gt);
   return hipGetLastError();
 }
 
 template <typename T, int EPI>
 static hipError_t launch_wide(hipStream_t st, const GemmArgs &a, const GemmPlan &pl, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  if (!a.wt || !a.xt || pl.nw < 1 || pl.nw > (pl.tw == 2 ? GW_MAX_NW : GW_MAX_NW1) || pl.tw < 1 || pl.tw > 2 || pl.nb < 2 ||
-      pl.nb > 2 * GW_MAX_NP || pl.nb % 2)
-    return hipErrorInvalidValue;
-  if ((long long)pl.mgroups * pl.gt * 32 < a.M || pl.gt > pl.nw * pl.tw) return hipErrorInvalidValue;   // groups cover every row, waves every tile
+  if (!a.wt || !a.xt || pl.gt < 1 || pl.tw != (pl.gt + GW_W - 1) / GW_W) return hipErrorInvalidValue;
   const int m32_tiles = (a.M + 31) / 32, row_bytes = a.Kd * (int)sizeof(T);
+  if ((long long)pl.mgroups * pl.gt < m32_tiles) return hipErrorInvalidValue;   // groups cover every row
   const size_t pieces = (size_t)(row_bytes / 32) * m32_tiles * 64;
   GemmArgs aw = a;
   if (a.x_tiled) aw.xt = const_cast<void *>(a.x);         // the producer of x wrote it tiled
@@ -895,28 +872,15 @@ static hipError_t launch_wide(hipStream_t st, const GemmArgs &a, const GemmPlan 
                           (const unsigned char *)a.x, a.M, row_bytes, m32_tiles, (unsigned char *)a.xt);
   const long long wgs = (long long)((pl.tiles * a.split_k + 7) / 8) * pl.mgroups * 8;
   if (wgs > 0x7fffffffLL) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)wgs), block(64 * (pl.nw + GW_NL));
-  #define GW_LAUNCH(NP_)                                                                                            \
-    return pl.nw > 8 ? launch_wide_np<T, EPI, NP_, 1, GW_MAX_NW1>(st, aw, pl, m32_tiles, grid, block, ev_start, ev_stop)   \
-                     : launch_wide_np<T, EPI, NP_, 1, 8>(st, aw, pl, m32_tiles, grid, block, ev_start, ev_stop)
-  if (pl.tw == 2) {
-    switch (pl.nb / 2) {
-      case 1: return launch_wide_np<T, EPI, 1, 2, GW_MAX_NW>(st, aw, pl, m32_tiles, grid, block, ev_start, ev_stop);
-      case 2: return launch_wide_np<T, EPI, 2, 2, GW_MAX_NW>(st, aw, pl, m32_tiles, grid, block, ev_start, ev_stop);
-      case 3: return launch_wide_np<T, EPI, 3, 2, GW_MAX_NW>(st, aw, pl, m32_tiles, grid, block, ev_start, ev_stop);
-      default: return hipErrorInvalidValue;
-    }
-  }
-  switch (pl.nb / 2) {
-    case 1: GW_LAUNCH(1);
-    case 2: GW_LAUNCH(2);
-    case 3: GW_LAUNCH(3);
-    case 4: GW_LAUNCH(4);
-    default:
-      if constexpr (EPI == EPI_QKV_ROPE) return hipErrorInvalidValue;   // more pairs than GW_MAX_NP_QKV
-      else GW_LAUNCH(5);
-  }
+  const dim3 grid((unsigned)wgs);
+  #define GW_LAUNCH(NP_, TW_)                                                                                   \
+    if constexpr (gw_built((int)sizeof(T), NP_, TW_))                                                            \
+      if (pl.nb == 2 * NP_ && pl.tw == TW_) return launch_wide_np<T, EPI, NP_, TW_>(st, aw, pl, m32_tiles, grid, ev_start, ev_stop)
+  GW_LAUNCH(2, 1); GW_LAUNCH(3, 1); GW_LAUNCH(4, 1); GW_LAUNCH(5, 1);
+  GW_LAUNCH(2, 2); GW_LAUNCH(3, 2); GW_LAUNCH(4, 2); GW_LAUNCH(5, 2); GW_LAUNCH(6, 2); GW_LAUNCH(8, 2);
+  GW_LAUNCH(2, 3); GW_LAUNCH(3, 3); GW_LAUNCH(4, 3); GW_LAUNCH(5, 3);
   #undef GW_LAUNCH
+  return hipErrorInvalidValue;
 }
 
 template <typename T>

@@ -144,7 +144,7 @@ struct GemmArgs {
 // the plan choose (fused epilogues always 1), else the caller's split; tiled: the launch will have both GemmArgs::wt
 // and GemmArgs::xt (then gemm_is_wide says which kernel).  The same call must be used to size
 // whatever depends on the plan (partial slabs: split; per-tile argmax candidates: tiles).
-struct GemmPlan { int nb, split, tiles, blocks; bool wide; int mgroups, nw, tw, gt; };   // wide: mgroups groups of gt tiles of 32 rows, nw math waves x up to tw tiles
+struct GemmPlan { int nb, split, tiles, blocks; bool wide; int mgroups, tw, gt; double cost; };   // wide: mgroups groups of gt tiles of 32 rows, up to tw a wave; expected us
 GemmPlan gemm_plan(int epi, int seg_rows, int Kd, int elem_bytes, int M, int split_req, bool tiled);
 size_t gemm_xt_bytes(int M, int Kd, int elem_bytes);
 bool gemm_is_wide(int epi, int seg_rows, int Kd, int elem_bytes, int M, bool tiled);   // whether gemm_plan sends the matrix to the wide kernel
