@@ -192,24 +192,22 @@ amph_status draft_impl(amph_ctx *ctx, const amph_draft_w *w, const float *h_new,
   auto F = [&](size_t off) { return (float *)(ws + off); };
   float *x = F(ctx->ws.x), *q = F(ctx->ws.q), *att = F(ctx->ws.att), *y = F(ctx->ws.y), *act = F(ctx->ws.act);
   float *h[2] = {F(ctx->ws.h[0]), F(ctx->ws.h[1])}, *slabs = F(ctx->ws.dslabs);
+  float *h1_last = F(ctx->ws.ctxa);         // the first stage's last live rows; that buffer's own use comes after the heads have read them
   const size_t stage_stride = (size_t)B * 2 * n_h * c.max_kv * d_h;      // elements of T
   for (int s = 0; s < c.n_stages; ++s) {
     const float *u = (s == 0) ? h_new : h[0];
     void *kv_stage = (T *)sal_kv + s * stage_stride;
-    PROF_TRY(ctx, AMPH_K_FC, launch_fc_concat<T>(st, w->fc[s], u, w->embed, tok_new, V, d, M, x, ctx->dev_status, slabs));
-    PROF_TRY(ctx, AMPH_K_SAL_QKV, launch_sal_qkv<T>(st, w->sal[s], x, d, n_h, d_h, M, c.rms_eps, c.rope_theta, sal_len, c.max_kv, kv_stage,
-                                   q, ctx->dev_status, R, n_valid));
     // Nothing reads the LAST stage's output at any but the last live position of a sequence (the heads read that one;
-    // the earlier positions only have to leave their cache rows, which the projections above wrote): there the
+    // the earlier positions only have to leave their cache rows, which the projections of q, k and v write): there the
     // attention, Wo and the FFN run over one row per sequence instead of R.
     const bool last_rows_only = (R > 1 && s == c.n_stages - 1);
     const int Ms = last_rows_only ? B : M;
-    const float *res = x;
-    if (last_rows_only) {
-      float *x_last = att + (size_t)B * d;        // att holds B * (K + 1) rows and the attention now fills the first B only
-      HIP_TRY(ctx, launch_gather_rows(st, x, B, R, d, n_valid, x_last));
-      res = x_last;
-    }
+    float *x_last = att + (size_t)B * d;          // att holds B * (K + 1) rows and that attention fills the first B only
+    PROF_TRY(ctx, AMPH_K_FC, launch_fc_concat<T>(st, w->fc[s], u, w->embed, tok_new, V, d, M, x, ctx->dev_status, slabs,
+                                                 last_rows_only ? LastRows{x_last, n_valid, R, 0} : LastRows{}));
+    PROF_TRY(ctx, AMPH_K_SAL_QKV, launch_sal_qkv<T>(st, w->sal[s], x, d, n_h, d_h, M, c.rms_eps, c.rope_theta, sal_len, c.max_kv, kv_stage,
+                                   q, ctx->dev_status, R, n_valid));
+    const float *res = last_rows_only ? x_last : x;
     // with few heads the attention leaves one partial result per key split: Wo folds them while it stages its rows, if it can
     const SalParts parts = {F(ctx->ws.sal_part), sal_key_splits(B, R, last_rows_only, n_h, c.max_kv), n_h, d_h};
     const bool to_wo = parts.S > 1 && linear_takes_parts<T>(Ms, parts);
@@ -218,19 +216,12 @@ amph_status draft_impl(amph_ctx *ctx, const amph_draft_w *w, const float *h_new,
     PROF_TRY(ctx, AMPH_K_SAL_WO, launch_linear<T>(st, w->sal[s].wo, nullptr, nullptr, 1, d, d, att, d, Ms, res, y, nullptr, nullptr, d, slabs,
                                                   to_wo ? &parts : nullptr));
     PROF_TRY(ctx, AMPH_K_SAL_GATEUP, launch_gate_up<T>(st, w->sal[s], y, d, f, Ms, c.rms_eps, act));
-    PROF_TRY(ctx, AMPH_K_SAL_DOWN, launch_linear<T>(st, w->sal[s].w_down, nullptr, nullptr, 1, d, f, act, f, Ms, y, h[s], nullptr, nullptr, d, slabs));
+    PROF_TRY(ctx, AMPH_K_SAL_DOWN, launch_linear<T>(st, w->sal[s].w_down, nullptr, nullptr, 1, d, f, act, f, Ms, y, h[s], nullptr, nullptr, d, slabs,
+                                                    nullptr, R > 1 && !last_rows_only ? LastRows{h1_last, n_valid, R, 0} : LastRows{}));
   }
   // the heads (Eq. 2-6) read the last live position of every batch element; with one adaptation layer every
   // head reads that layer's output.  After a catch-up the last stage's output already is one row per sequence.
-  const float *h1 = h[0], *h2 = h[c.n_stages - 1];
-  if (R > 1) {
-    if (c.n_stages == 2) {
-      HIP_TRY(ctx, launch_gather_rows(st, h[0], B, R, d, n_valid, x));
-      h1 = x;
-    } else {
-      h1 = h2;
-    }
-  }
+  const float *h2 = h[c.n_stages - 1], *h1 = R > 1 ? (c.n_stages == 2 ? h1_last : h2) : h[0];
   float *Hp = F(ctx->ws.Hp), *Qa = F(ctx->ws.Qa), *Ka = F(ctx->ws.Ka), *Va = F(ctx->ws.Va), *ctxa = F(ctx->ws.ctxa);
   float *attn_o = F(ctx->ws.attn_o);
   PROF_TRY(ctx, AMPH_K_HEAD_MLP, launch_head_mlp<T>(st, w->mlp, w->pe, h1, h2, d, K, B, Hp));

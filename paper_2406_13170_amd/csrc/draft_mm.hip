@@ -49,6 +49,7 @@ struct DmArgs {
   float *o0, *o1, *o2;            // outputs [M, ldo] per segment
   int ldo;
   const float *res;               // DM_LINEAR: residual [M, ldo] or NULL
+  LastRows last;                  // DM_LINEAR, DM_FC with one matrix
   // DM_FC
   const bf16_t *embed; const int32_t *tok; int vocab;
   // DM_SALQKV
@@ -442,9 +443,14 @@ __global__ __launch_bounds__((DmStage<NB, NT, CB_>::THREADS)) void k_draft_mm(co
         }
         float *out = (seg == 0 ? a.o0 : seg == 1 ? a.o1 : a.o2) + (size_t)m * a.ldo + n0;
         const float *res = a.res ? a.res + (size_t)m * a.ldo + n0 : nullptr;
+        const int last_b = last_row_of(a.last, m);
         #pragma unroll
         for (int j = 0; j < 4; ++j)
-          if (n0 + j < a.seg_rows) out[j] = res ? v[j] + res[j] : v[j];
+          if (n0 + j < a.seg_rows) {
+            const float y = res ? v[j] + res[j] : v[j];
+            out[j] = y;
+            if (last_b >= 0) a.last.out[(size_t)last_b * a.ldo + n0 + j] = y;
+          }
       }
     }
   }
@@ -466,16 +472,19 @@ __global__ __launch_bounds__((DmStage<NB, NT, CB_>::THREADS)) void k_draft_mm(co
 
 // out[m][n] = (res ? res[m][n] : 0) + sum_s slabs[s][m][n], s ascending; everything is requested before the first use.
 template <int S>
-__global__ __launch_bounds__(256) void k_draft_fold(const float *slabs, int n, const float *res, float *out) {
+__global__ __launch_bounds__(256) void k_draft_fold(const float *slabs, int n, const float *res, float *out, int ld, const LastRows last) {
   const int i = (blockIdx.x * 256 + threadIdx.x) * 4;
   if (i >= n) return;
+  const int m = i / ld, last_b = last_row_of(last, m);     // (ld is a multiple of 4)
   f32x4 v[S], r = (f32x4){0.f, 0.f, 0.f, 0.f};
   #pragma unroll
   for (int s = 0; s < S; ++s) v[s] = *reinterpret_cast<const f32x4 *>(slabs + (size_t)s * n + i);
   if (res) r = *reinterpret_cast<const f32x4 *>(res + i);
   #pragma unroll
   for (int s = 1; s < S; ++s) v[0] += v[s];
-  *reinterpret_cast<f32x4 *>(out + i) = v[0] + r;
+  v[0] += r;
+  *reinterpret_cast<f32x4 *>(out + i) = v[0];
+  if (last_b >= 0) *reinterpret_cast<f32x4 *>(last.out + (size_t)last_b * ld + (i - m * ld)) = v[0];
 }
 
 // ---- host side --------------------------------------------------------------------------------------
@@ -585,17 +594,18 @@ static hipError_t dm_launch(hipStream_t st, DmArgs a, int blocks, int groups) {
   const int n = a.M * a.seg_rows;
   const dim3 grid((n / 4 + 255) / 256), block(256);
   static_assert(DRAFT_MM_SPLITS == 4, "the folds below");
-  if (p.S == 2) hipLaunchKernelGGL((k_draft_fold<2>), grid, block, 0, st, a.slabs, n, a.res, a.o0);
-  else hipLaunchKernelGGL((k_draft_fold<4>), grid, block, 0, st, a.slabs, n, a.res, a.o0);
+  if (p.S == 2) hipLaunchKernelGGL((k_draft_fold<2>), grid, block, 0, st, a.slabs, n, a.res, a.o0, a.ldo, a.last);
+  else hipLaunchKernelGGL((k_draft_fold<4>), grid, block, 0, st, a.slabs, n, a.res, a.o0, a.ldo, a.last);
   return hipGetLastError();
 }
 
 hipError_t draft_mm_fc(hipStream_t st, const void *W, const float *u, const void *embed, const int32_t *tok, int vocab, int d, int M,
-                       float *out, uint32_t *dev_status, float *slabs) {
+                       float *out, uint32_t *dev_status, float *slabs, const LastRows &last) {
   if (d % 256) return hipErrorInvalidValue;               // a stage holds columns of one half of the concatenated row only
   DmArgs a{};
   a.w0 = (const bf16_t *)W; a.n_seg = 1; a.seg_rows = d; a.Kd = 2 * d; a.M = M; a.x = u; a.ldx = d; a.o0 = out; a.ldo = d;
   a.embed = (const bf16_t *)embed; a.tok = tok; a.vocab = vocab; a.dev_status = dev_status; a.slabs = slabs;
+  a.last = last;
   return dm_launch<DM_FC>(st, a, (d + 15) / 16, 1);
 }
 
@@ -612,10 +622,11 @@ hipError_t draft_mm_sal_qkv(hipStream_t st, const amph_layer_w &lw, const float 
 }
 
 hipError_t draft_mm_linear(hipStream_t st, const void *w0, const void *w1, const void *w2, int n_seg, int seg_rows, int Kd,
-                           const float *x, int ldx, int M, const float *res, float *o0, float *o1, float *o2, int ldo, float *slabs) {
+                           const float *x, int ldx, int M, const float *res, float *o0, float *o1, float *o2, int ldo, float *slabs,
+                           const LastRows &last) {
   DmArgs a{};
   a.w0 = (const bf16_t *)w0; a.w1 = (const bf16_t *)w1; a.w2 = (const bf16_t *)w2; a.n_seg = n_seg; a.seg_rows = seg_rows; a.Kd = Kd;
-  a.M = M; a.x = x; a.ldx = ldx; a.res = res; a.o0 = o0; a.o1 = o1; a.o2 = o2; a.ldo = ldo; a.slabs = slabs;
+  a.M = M; a.x = x; a.ldx = ldx; a.res = res; a.o0 = o0; a.o1 = o1; a.o2 = o2; a.ldo = ldo; a.slabs = slabs; a.last = last;
   return dm_launch<DM_LINEAR>(st, a, n_seg * ((seg_rows + 15) / 16), 1);
 }
 

@@ -293,7 +293,7 @@ __device__ __forceinline__ void load_x_rmsnorm(float *xs, float *red, const floa
 template <typename T, int M, bool PIPE>
 __global__ __launch_bounds__(GV_THREADS) void k_fc_concat(const T *W, const float *u, const T *embed,
                                                           const int32_t *tok, int vocab, int d, int m_valid,
-                                                          float *out, uint32_t *dev_status, int half) {
+                                                          float *out, uint32_t *dev_status, int half, const LastRows last) {
   extern __shared__ __align__(16) float smem[];
   constexpr int CH = XLayout<T>::CH;
   const int ldw = 2 * d, k_lo = (half == 1) ? d : 0;       // weight row length; first column of this launch
@@ -347,6 +347,7 @@ __global__ __launch_bounds__(GV_THREADS) void k_fc_concat(const T *W, const floa
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int G = (d + GV_R - 1) / GV_R;
   const int g_first = blockIdx.x * 4 + wave, g_step = gridDim.x * 4;
+  const int last_b = last_row_of(last, min(lane / GV_R, m_valid - 1));
   auto set_rows = [&](int g, const T *(&rw)[GV_R]) {
     #pragma unroll
     for (int r = 0; r < GV_R; ++r) rw[r] = W + (size_t)min(g * GV_R + r, d - 1) * ldw + k_lo;
@@ -369,6 +370,7 @@ __global__ __launch_bounds__(GV_THREADS) void k_fc_concat(const T *W, const floa
       if (m < m_valid && n < d) {
         if (half == 1) v += out[(size_t)m * d + n];
         out[(size_t)m * d + n] = v;
+        if (last_b >= 0) last.out[(size_t)last_b * d + n] = v;
       }
     }
   }
@@ -488,7 +490,7 @@ __global__ __launch_bounds__(GV_THREADS) void k_sal_qkv(const T *wq, const T *wk
 template <typename T, int M, bool PIPE, bool PARTS>
 __device__ __forceinline__ void linear_body(const T *w0, const T *w1, const T *w2, int n_seg, int seg_rows, int Kd, const float *x,
                                             int ldx, int m_valid, const float *res, float *o0, float *o1, float *o2, int ldo,
-                                            int ldw, int add_out, const SalParts &parts) {
+                                            int ldw, int add_out, const SalParts &parts, const LastRows &last) {
   extern __shared__ __align__(16) float smem[];
   constexpr int CH = XLayout<T>::CH;
   const int nC = (Kd + CH - 1) / CH;
@@ -500,6 +502,7 @@ __device__ __forceinline__ void linear_body(const T *w0, const T *w1, const T *w
   const int Gseg = (seg_rows + GV_R - 1) / GV_R;
   const int G = n_seg * Gseg;
   const int g_first = blockIdx.x * 4 + wave, g_step = gridDim.x * 4;
+  const int last_b = last_row_of(last, min(lane / GV_R, m_valid - 1));
   auto set_rows = [&](int g, const T *(&rw)[GV_R]) {
     const int seg = g / Gseg, gl = g % Gseg;
     const T *Wm = pick3(seg, w0, w1, w2);
@@ -527,6 +530,7 @@ __device__ __forceinline__ void linear_body(const T *w0, const T *w1, const T *w
         if (res) v += res[(size_t)m * ldo + n];
         if (add_out) v += om[(size_t)m * ldo + n];
         om[(size_t)m * ldo + n] = v;
+        if (last_b >= 0) last.out[(size_t)last_b * ldo + n] = v;
       }
     }
   }
@@ -535,13 +539,13 @@ __device__ __forceinline__ void linear_body(const T *w0, const T *w1, const T *w
 template <typename T, int M, bool PIPE>
 __global__ __launch_bounds__(GV_THREADS) void k_linear(const T *w0, const T *w1, const T *w2, int n_seg, int seg_rows,
                                                        int Kd, const float *x, int ldx, int m_valid, const float *res,
-                                                       float *o0, float *o1, float *o2, int ldo, int ldw, int add_out) {
-  linear_body<T, M, PIPE, false>(w0, w1, w2, n_seg, seg_rows, Kd, x, ldx, m_valid, res, o0, o1, o2, ldo, ldw, add_out, SalParts{});
+                                                       float *o0, float *o1, float *o2, int ldo, int ldw, int add_out, const LastRows last) {
+  linear_body<T, M, PIPE, false>(w0, w1, w2, n_seg, seg_rows, Kd, x, ldx, m_valid, res, o0, o1, o2, ldo, ldw, add_out, SalParts{}, last);
 }
 template <typename T, int M, bool PIPE>
 __global__ __launch_bounds__(GV_THREADS) void k_linear_parts(const T *w, int seg_rows, int Kd, const SalParts parts, int m_valid,
                                                              const float *res, float *out, int ldo) {
-  linear_body<T, M, PIPE, true>(w, nullptr, nullptr, 1, seg_rows, Kd, nullptr, 0, m_valid, res, out, nullptr, nullptr, ldo, Kd, 0, parts);
+  linear_body<T, M, PIPE, true>(w, nullptr, nullptr, 1, seg_rows, Kd, nullptr, 0, m_valid, res, out, nullptr, nullptr, ldo, Kd, 0, parts, LastRows{});
 }
 
 // =====================================================================================================
@@ -809,10 +813,10 @@ static inline int gv_rows_per_launch(int M, size_t bytes_per_row, size_t extra) 
 
 template <typename T>
 hipError_t launch_fc_concat(hipStream_t st, const void *W, const float *u, const void *embed, const int32_t *tok,
-                            int vocab, int d, int M, float *out, uint32_t *dev_status, float *slabs) {
+                            int vocab, int d, int M, float *out, uint32_t *dev_status, float *slabs, const LastRows &last) {
   if (M < 1 || d % 8) return hipErrorInvalidValue;
   if (use_mm<T>(M, (size_t)d * 2 * d) && d % 256 == 0)
-    MM_CHUNKS(draft_mm_fc(st, W, u + (size_t)m0 * d, embed, tok + m0, vocab, d, m, out + (size_t)m0 * d, dev_status, slabs));
+    MM_CHUNKS(draft_mm_fc(st, W, u + (size_t)m0 * d, embed, tok + m0, vocab, d, m, out + (size_t)m0 * d, dev_status, slabs, last.from(m0)));
   int mc = gv_rows_per_launch(M, gv_xs_bytes<T>(1, 2 * d), 0);
   // rows that fit only without their other half: two launches over d columns each
   const int mch = gv_rows_per_launch(M, gv_xs_bytes<T>(1, d), 0);
@@ -826,7 +830,7 @@ hipError_t launch_fc_concat(hipStream_t st, const void *W, const float *u, const
       GV_DISPATCH_M(m, 8, {
         const size_t sm = gv_xs_bytes<T>(MM, halves ? d : 2 * d);
         GV_LAUNCH(k_fc_concat, gv_grid((d + 3) / 4, sm), sm, (const T *)W, u + (size_t)m0 * d, (const T *)embed, tok + m0, vocab, d, m,
-                  out + (size_t)m0 * d, dev_status, half);
+                  out + (size_t)m0 * d, dev_status, half, last.from(m0));
       });
     }
   }
@@ -866,10 +870,10 @@ template <typename T> bool linear_takes_parts(int M, const SalParts &p) {
 template <typename T>
 hipError_t launch_linear(hipStream_t st, const void *w0, const void *w1, const void *w2, int n_seg, int seg_rows, int Kd,
                          const float *x, int ldx, int M, const float *res, float *o0, float *o1, float *o2, int ldo,
-                         float *slabs, const SalParts *parts) {
-  if (M < 1 || Kd % 8) return hipErrorInvalidValue;
+                         float *slabs, const SalParts *parts, const LastRows &last) {
+  if (M < 1 || Kd % 8 || (last.R > 0 && n_seg != 1)) return hipErrorInvalidValue;
   if (parts) {
-    if (n_seg != 1 || Kd != parts->n_heads * parts->d_h || !linear_takes_parts<T>(M, *parts)) return hipErrorInvalidValue;
+    if (n_seg != 1 || last.R > 0 || Kd != parts->n_heads * parts->d_h || !linear_takes_parts<T>(M, *parts)) return hipErrorInvalidValue;
     hipError_t e = hipSuccess;
     GV_DISPATCH_M(M, GV_MOST<T>, {
       const size_t sm = gv_xs_bytes<T>(MM, Kd) + (size_t)M * parts->n_heads * (SAL_MAX_SPLITS + 1) * sizeof(float);
@@ -882,7 +886,7 @@ hipError_t launch_linear(hipStream_t st, const void *w0, const void *w1, const v
   if (use_mm<T>(M, (size_t)n_seg * seg_rows * Kd) && x_pieces)
     MM_CHUNKS(draft_mm_linear(st, w0, w1, w2, n_seg, seg_rows, Kd, x + (size_t)m0 * ldx, ldx, m, res ? res + (size_t)m0 * ldo : nullptr,
                               o0 + (size_t)m0 * ldo, o1 ? o1 + (size_t)m0 * ldo : nullptr, o2 ? o2 + (size_t)m0 * ldo : nullptr, ldo,
-                              slabs));
+                              slabs, last.from(m0)));
   int mc = std::min(GV_MOST<T>, gv_rows_per_launch(M, gv_xs_bytes<T>(1, Kd), 0));
   // Rows too wide for all of them (of a launch) to sit in LDS whole: cut the reduction axis into ks slices instead of
   // the rows into more launches, each of which would read the matrix again.
@@ -906,7 +910,7 @@ hipError_t launch_linear(hipStream_t st, const void *w0, const void *w1, const v
         GV_LAUNCH(k_linear, gv_grid(n_seg * ((seg_rows + 3) / 4), sm), sm, (const T *)w0 + ko, w1 ? (const T *)w1 + ko : nullptr,
                   w2 ? (const T *)w2 + ko : nullptr, n_seg, seg_rows, Kq, x + (size_t)m0 * ldx + ko, ldx, m,
                   (res && kq == 0) ? res + oo : nullptr, o0 + oo, o1 ? o1 + oo : nullptr, o2 ? o2 + oo : nullptr, ldo, Kd,
-                  kq > 0 ? 1 : 0);
+                  kq > 0 ? 1 : 0, last.from(m0));
       });
     }
   }
@@ -1009,13 +1013,13 @@ size_t lmtk_ws_floats(int rows, int k) { return 2 * (size_t)rows * LMTK_MAX_WG *
 
 #define INSTANTIATE(T)                                                                                                   \
   template hipError_t launch_fc_concat<T>(hipStream_t, const void *, const float *, const void *, const int32_t *, int, \
-                                          int, int, float *, uint32_t *, float *);                                             \
+                                          int, int, float *, uint32_t *, float *, const LastRows &);                           \
   template hipError_t launch_sal_qkv<T>(hipStream_t, const amph_layer_w &, const float *, int, int, int, int, float,    \
                                         float, const int32_t *, int, void *, float *, uint32_t *, int,                  \
                                         const int32_t *);                                                               \
   template hipError_t launch_linear<T>(hipStream_t, const void *, const void *, const void *, int, int, int,            \
                                        const float *, int, int, const float *, float *, float *, float *, int, float *,  \
-                                       const SalParts *);                                                               \
+                                       const SalParts *, const LastRows &);                                             \
   template bool linear_takes_parts<T>(int, const SalParts &);                                                           \
   template hipError_t launch_gate_up<T>(hipStream_t, const amph_layer_w &, const float *, int, int, int, float, float *); \
   template hipError_t launch_head_mlp<T>(hipStream_t, const void *, const void *, const float *, const float *, int,    \

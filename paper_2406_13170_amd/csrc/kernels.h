@@ -8,9 +8,22 @@ namespace amph {
 constexpr size_t GV_MAX_SMEM = 128 * 1024;    // dynamic LDS a GEMV workgroup may ask for (gfx950: 160 KB per workgroup)
 
 // ---- gemv.hip (draft path: any number of rows; launches of up to 8, or draft_mm.hip) ----
+// Rows of a launch are (batch element, new position < R); the kernels that write them put the last live position's row of every
+// element into out [B, ld] as well (R = 0: no such copy).  Read back by a kernel of its own it cost a launch (4.7 us) each time.
+struct LastRows {
+  float *out; const int32_t *n_valid; int R, row0;
+  LastRows from(int m0) const { return {out, n_valid, R, row0 + m0}; }
+};
+// the batch element whose last live row the launch's row m is, or -1
+__device__ __forceinline__ int last_row_of(const LastRows &l, int m) {
+  if (l.R == 0) return -1;
+  const int r = l.row0 + m, b = r / l.R, n = l.n_valid ? l.n_valid[b] : l.R;
+  return r - b * l.R == min(max(n, 1), l.R) - 1 ? b : -1;
+}
 template <typename T>
 hipError_t launch_fc_concat(hipStream_t st, const void *W, const float *u, const void *embed, const int32_t *tok,
-                            int vocab, int d, int M, float *out, uint32_t *dev_status, float *slabs);   // slabs: see draft_mm_fc
+                            int vocab, int d, int M, float *out, uint32_t *dev_status, float *slabs,   // slabs: see draft_mm_fc
+                            const LastRows &last = {});
 template <typename T>
 hipError_t launch_sal_qkv(hipStream_t st, const amph_layer_w &lw, const float *x, int d, int n_heads, int d_h, int M,
                           float eps, float theta, const int32_t *sal_len, int max_kv, void *kv_stage, float *qbuf,
@@ -23,7 +36,7 @@ __host__ __device__ constexpr int sal_part_pitch(int d_h) { return d_h + 4; }
 template <typename T>
 hipError_t launch_linear(hipStream_t st, const void *w0, const void *w1, const void *w2, int n_seg, int seg_rows, int Kd,
                          const float *x, int ldx, int M, const float *res, float *o0, float *o1, float *o2, int ldo,
-                         float *slabs = nullptr, const SalParts *parts = nullptr);
+                         float *slabs = nullptr, const SalParts *parts = nullptr, const LastRows &last = {});   // last: one matrix
 template <typename T> bool linear_takes_parts(int M, const SalParts &parts);
 template <typename T>
 hipError_t launch_gate_up(hipStream_t st, const amph_layer_w &lw, const float *x, int d, int f, int M, float eps,
@@ -46,12 +59,13 @@ constexpr int DRAFT_MM_ROWS = 48, DRAFT_MM_SPLITS = 4;
 // slabs: DRAFT_MM_SPLITS * min(rows, DRAFT_MM_ROWS) * output width floats for the partial sums of a split reduction axis,
 // or NULL: it stays whole
 hipError_t draft_mm_fc(hipStream_t st, const void *W, const float *u, const void *embed, const int32_t *tok, int vocab, int d, int M,
-                       float *out, uint32_t *dev_status, float *slabs);
+                       float *out, uint32_t *dev_status, float *slabs, const LastRows &last);
 hipError_t draft_mm_sal_qkv(hipStream_t st, const amph_layer_w &lw, const float *x, int d, int n_heads, int d_h, int M, float eps,
                             float theta, const int32_t *sal_len, int max_kv, void *kv_stage, float *qbuf, uint32_t *dev_status,
                             int row0, int R, const int32_t *n_valid);
 hipError_t draft_mm_linear(hipStream_t st, const void *w0, const void *w1, const void *w2, int n_seg, int seg_rows, int Kd,
-                           const float *x, int ldx, int M, const float *res, float *o0, float *o1, float *o2, int ldo, float *slabs);
+                           const float *x, int ldx, int M, const float *res, float *o0, float *o1, float *o2, int ldo, float *slabs,
+                           const LastRows &last);
 hipError_t draft_mm_gate_up(hipStream_t st, const amph_layer_w &lw, const float *x, int d, int f, int M, float eps, float *act);
 hipError_t draft_mm_head_mlp(hipStream_t st, const void *w_mlp, const void *pe, const float *h1, const float *h2, int d, int K, int M,
                              float *Hp);
@@ -100,7 +114,6 @@ hipError_t launch_commit(hipStream_t st, void *k_caches, void *v_caches, int n_l
 template <typename T>
 hipError_t launch_kv_layout(hipStream_t st, const void *k_src, const void *v_src, void *k_dst, void *v_dst, int n_caches,
                             int max_kv, int d_h, bool to_tiled);
-hipError_t launch_gather_rows(hipStream_t st, const float *rows, int B, int R, int d, const int32_t *n_valid, float *out);
 // x[m] (+)= sum_s slabs[s][m] (or x[m] = embed[tok[m]] when tok != NULL); xn[m] = RMSNorm(x[m]) * g as T;
 // hidden_out (float32, optional) receives the same normalised rows.  xn_tiles != 0: xn is written in the tiled
 // activation layout of the wide GEMM (xn_tiles = number of 32-row tiles).

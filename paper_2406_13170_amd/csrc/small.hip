@@ -734,7 +734,6 @@ hipError_t launch_accept_typical(hipStream_t st, const int32_t *parent, const in
 //     row j <= a of h_new is the target's hidden state at path node j, tok_new[j] the token that follows it (the next
 //     path node's token, or next_tok after the last), rows past a are zero, and n_new = a + 1;
 //   k_advance: kv_len += a + 1: a launch after the one above, whose workgroups have all read kv_len by then.
-//   k_gather_rows: out[b] = rows[b * R + (n_valid ? n_valid[b] : R) - 1] (the last live row of each element).
 // A chain of latencies, so what can be asked for at once is: the lengths together with the whole path, then every source
 // (eight 7B layers, four sequences, by the kernel trace: 6.6 + 3.9 us as the path's rows element by element behind the
 // lengths, and the hidden states' rows with kv_len in a second launch; now 7.1 + 1.4.  The
@@ -800,15 +799,6 @@ __global__ __launch_bounds__(64) void k_advance(const int32_t *accept_len, int B
   if (L >= 0 && L + T_nodes <= max_kv) kv_len[b] = L + min(max(a, 0), K) + 1;
 }
 
-__global__ __launch_bounds__(256) void k_gather_rows(const float *rows, int R, int d, const int32_t *n_valid, float *out) {
-  const int b = blockIdx.x;
-  int r = n_valid ? n_valid[b] : R;
-  r = min(max(r, 1), R) - 1;
-  const float *src = rows + ((size_t)b * R + r) * d;
-  for (int k = threadIdx.x * 4; k < d; k += 256 * 4)
-    *reinterpret_cast<float4 *>(out + (size_t)b * d + k) = *reinterpret_cast<const float4 *>(src + k);
-}
-
 template <typename T>
 hipError_t launch_commit(hipStream_t st, void *k_caches, void *v_caches, int n_layers, int B, int n_heads, int d_h, int max_kv,
                          int T_nodes, int d, int K, int32_t *kv_len, const int32_t *accept_len, const int32_t *accept_path,
@@ -828,12 +818,6 @@ template hipError_t launch_commit<float>(hipStream_t, void *, void *, int, int, 
 template hipError_t launch_commit<bf16_t>(hipStream_t, void *, void *, int, int, int, int, int, int, int, int, int32_t *,
                                           const int32_t *, const int32_t *, const int32_t *, const int32_t *, const float *,
                                           float *, int32_t *, int32_t *);
-
-hipError_t launch_gather_rows(hipStream_t st, const float *rows, int B, int R, int d, const int32_t *n_valid, float *out) {
-  if (d % 4) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_gather_rows, dim3(B), dim3(256), 0, st, rows, R, d, n_valid, out);
-  return hipGetLastError();
-}
 
 // =====================================================================================================
 // Row-major [max_kv, d_h] caches <-> the step-tiled storage of the verification attention (formulas: header of
