@@ -730,32 +730,38 @@ hipError_t launch_accept_typical(hipStream_t st, const int32_t *parent, const in
 // committed position).
 //   k_commit: for one (layer, batch element, head), the K/V rows of the accepted path's nodes 1..a move
 //     from tree slots kv_len + node to kv_len + j (node 0, the root, already sits at kv_len).  All sources
-//     are read before the first write (a destination may be another node's source).  In one more layer of the grid,
-//     row j <= a of h_new is the target's hidden state at path node j, tok_new[j] the token that follows it (the next
-//     path node's token, or next_tok after the last), rows past a are zero, and n_new = a + 1;
+//     are read before the first write (a destination may be another node's source).  In one more layer of the grid (the
+//     first: its few workgroups have the longest way), row j <= a of h_new is the target's hidden state at path node j,
+//     tok_new[j] the token that follows it (the next path node's token, or next_tok after the last), rows past a are zero,
+//     and n_new = a + 1;
 //   k_advance: kv_len += a + 1: a launch after the one above, whose workgroups have all read kv_len by then.
-// A chain of latencies, so what can be asked for at once is: the lengths together with the whole path, then every source
-// (eight 7B layers, four sequences, by the kernel trace: 6.6 + 3.9 us as the path's rows element by element behind the
-// lengths, and the hidden states' rows with kv_len in a second launch; now 7.1 + 1.4.  The
-// values are 64-byte lines touched for 2 bytes each, some 30 MB there, which is what is left).
+// A chain of latencies, so what can be asked for at once is: the lengths together with the whole path, then every accepted
+// source.  Over deep caches it is bound by the values: lines of which two bytes move, read and written.  Measured (us by the
+// kernel trace, k_commit; k_advance takes 1.3 behind it where the commits follow each other, up to 5 at the end of a long
+// step), for 0, 1, 2, 3 and all nodes accepted in every sequence, against a version that read a source for every place of
+// the path, accepted or not: 8 layers of 7B width, batch 4: 2.9 4.8 5.2 6.0 6.7 (4.3 6.0 6.4 6.9 7.4); 40 layers of 13B,
+// batch 4: 3.6 19.4 20.7 22.4 29.5 (13.1 20.6 22.1 25.0 31.3); 60 layers of 33B, batch 4: 5.2 35.5 37.5 41.8 81.5
+// (27.5 38.8 42.4 48.6 87.5).
 // =====================================================================================================
-template <typename T>
-__global__ __launch_bounds__(256) void k_commit(T *k_caches, T *v_caches, int n_layers, int B, int n_heads, int d_h, int max_kv,
-                                                int T_nodes, const int32_t *kv_len, const int32_t *accept_len,
-                                                const int32_t *accept_path, int K, int d, const float *hidden, const int32_t *tree_tok,
-                                                const int32_t *next_tok, float *h_new, int32_t *tok_new, int32_t *n_new) {
+template <int N> struct RowTag { static constexpr int value = N; };
+
+template <typename T, int DH>
+__global__ __launch_bounds__(256) void k_commit(T *k_caches, T *v_caches, int B, int n_heads, int max_kv, int T_nodes,
+                                                const int32_t *kv_len, const int32_t *accept_len, const int32_t *accept_path, int K,
+                                                int d, const float *hidden, const int32_t *tree_tok, const int32_t *next_tok,
+                                                float *h_new, int32_t *tok_new, int32_t *n_new) {
   constexpr int PER = Elem<T>::PER;
-  const int h = blockIdx.x, b = blockIdx.y, li = blockIdx.z, t = threadIdx.x;
+  const int h = blockIdx.x, b = blockIdx.y, li = (int)blockIdx.z - (h_new ? 1 : 0), t = threadIdx.x;
   const int32_t *path = accept_path + (size_t)b * (K + 1);
-  if (li == n_layers) {                                      // the draft's next rows
+  if (li < 0) {                                              // the draft's next rows
     const int a = min(max(accept_len[b], 0), K);
     for (int j = h; j <= K; j += n_heads) {
       const int node = min(max(path[j], 0), T_nodes - 1), node1 = min(max(path[min(j + 1, K)], 0), T_nodes - 1);
       float *dst = h_new + ((size_t)b * (K + 1) + j) * d;
       const float *src = hidden + ((size_t)b * T_nodes + node) * d;
       for (int k = t * 4; k < d; k += 256 * 4) {
-        float4 v = *reinterpret_cast<const float4 *>(src + k);
-        if (j > a) v = make_float4(0.f, 0.f, 0.f, 0.f);
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (j <= a) v = *reinterpret_cast<const float4 *>(src + k);      // (uniform over the workgroup)
         *reinterpret_cast<float4 *>(dst + k) = v;
       }
       if (t == 0) {
@@ -765,31 +771,41 @@ __global__ __launch_bounds__(256) void k_commit(T *k_caches, T *v_caches, int n_
     }
     return;
   }
-  // Thread t moves the 16-byte piece kp of key row kj, and of up to MAXI value rows vj + i * VR the dim ve (a row's dims lie
-  // 64 bytes apart).
-  const int kpr = d_h / PER, kj = 1 + t / kpr, kp = t % kpr;          // K * d_h / PER <= 256
-  const int VR = 256 / d_h, vj = 1 + t / d_h, ve = t % d_h;
-  constexpr int MAXI = AMPH_MAX_HEADS_K * 128 / 256;
-  const int L = kv_len[b], a_raw = accept_len[b];
-  const int kn = path[min(kj, K)];
+  // Thread t moves the 16-byte piece kp of key row kj, and of value rows vj, vj + VR, ... (the same for a whole wave) the dim ve
+  // (a row's dims lie 64 bytes apart).
+  constexpr int KPR = DH / PER, VR = 256 / DH, MAXI = AMPH_MAX_HEADS_K / VR;
+  static_assert(AMPH_MAX_HEADS_K * KPR <= 256 && DH % WAVE == 0, "a thread for every piece of the keys; a wave for one value row");
+  const int kj = 1 + t / KPR, kp = t % KPR, vj = 1 + __builtin_amdgcn_readfirstlane(t / DH), ve = t % DH;
+  const int L = kv_len[b], a = min(accept_len[b], K);
+  const int kn = path[min(kj, K)], first = path[1];
   int vn[MAXI];
   #pragma unroll
   for (int i = 0; i < MAXI; ++i) vn[i] = path[min(vj + i * VR, K)];
-  if (L < 0 || L + T_nodes > max_kv || a_raw < 0) return;   // the target pass wrote nothing (flagged there)
-  const int a = min(a_raw, K);
-  const size_t head = (((size_t)li * B + b) * n_heads + h) * (size_t)max_kv * d_h;
+  if (L < 0 || L + T_nodes > max_kv || a < 1) return;       // the target pass wrote nothing (flagged there), or nothing moves
+  const size_t head = (((size_t)li * B + b) * n_heads + h) * (size_t)max_kv * DH;
   T *kc = k_caches + head, *vc = v_caches + head;
-  // (unconditional loads: a path's unused places name some row of the tree)
-  const uint4 kr = ldg16(kc + k_tiled_index<T>(L + min(max(kn, 0), T_nodes - 1), kp * PER, d_h));
-  T vr[MAXI];
-  #pragma unroll
-  for (int i = 0; i < MAXI; ++i)
-    if (i * VR < K) vr[i] = vc[v_tiled_index<T>(L + min(max(vn[i], 0), T_nodes - 1), ve, d_h)];
-  __syncthreads();
-  if (kj <= a) stg16(kc + k_tiled_index<T>(L + kj, kp * PER, d_h), kr);
-  #pragma unroll
-  for (int i = 0; i < MAXI; ++i)
-    if (i * VR < K && vj + i * VR <= a) vc[v_tiled_index<T>(L + vj + i * VR, ve, d_h)] = vr[i];
+  auto slot = [&](int node) { return L + min(max(node, 0), T_nodes - 1); };
+  // Only what was accepted is read (a value row is DH lines): N value rows in this wave, in code without branches, as each
+  // would have its loads wait for those before it.  Lanes without a key row re-read the first one's.
+  auto move = [&](auto tag) {
+    constexpr int N = decltype(tag)::value;
+    const uint4 kr = ldg16(kc + k_tiled_index<T>(slot(kj <= a ? kn : first), kp * PER, DH));
+    T vr[N > 0 ? N : 1];
+    #pragma unroll
+    for (int i = 0; i < N; ++i) vr[i] = vc[v_tiled_index<T>(slot(vn[i]), ve, DH)];
+    __syncthreads();
+    if (kj <= a) stg16(kc + k_tiled_index<T>(L + kj, kp * PER, DH), kr);
+    #pragma unroll
+    for (int i = 0; i < N; ++i) vc[v_tiled_index<T>(L + vj + i * VR, ve, DH)] = vr[i];
+  };
+  static_assert(MAXI == 2 || MAXI == 4, "the cases below");
+  switch (a < vj ? 0 : (a - vj) / VR + 1) {
+    case 0: move(RowTag<0>{}); break;
+    case 1: move(RowTag<1>{}); break;
+    case 2: move(RowTag<2>{}); break;
+    case 3: move(RowTag<MAXI == 4 ? 3 : 2>{}); break;
+    default: move(RowTag<MAXI>{}); break;
+  }
 }
 
 __global__ __launch_bounds__(64) void k_advance(const int32_t *accept_len, int B, int K, int T_nodes, int max_kv, int32_t *kv_len) {
@@ -806,9 +822,11 @@ hipError_t launch_commit(hipStream_t st, void *k_caches, void *v_caches, int n_l
                          int32_t *n_new) {
   if (K < 1 || K > AMPH_MAX_HEADS_K || (d_h != 64 && d_h != 128) || d % 4 || B > 64) return hipErrorInvalidValue;
   const int nz = n_layers + (h_new ? 1 : 0);
-  if (nz > 0)
-    hipLaunchKernelGGL((k_commit<T>), dim3(n_heads, B, nz), dim3(256), 0, st, (T *)k_caches, (T *)v_caches, n_layers, B, n_heads, d_h,
-                       max_kv, T_nodes, kv_len, accept_len, accept_path, K, d, hidden, tree_tok, next_tok, h_new, tok_new, n_new);
+  #define COMMIT_LAUNCH(DH)                                                                                                      \
+    hipLaunchKernelGGL((k_commit<T, DH>), dim3(n_heads, B, nz), dim3(256), 0, st, (T *)k_caches, (T *)v_caches, B, n_heads, max_kv, \
+                       T_nodes, kv_len, accept_len, accept_path, K, d, hidden, tree_tok, next_tok, h_new, tok_new, n_new)
+  if (nz > 0) { if (d_h == 128) COMMIT_LAUNCH(128); else COMMIT_LAUNCH(64); }
+  #undef COMMIT_LAUNCH
   hipLaunchKernelGGL(k_advance, dim3(1), dim3(64), 0, st, accept_len, B, K, T_nodes, max_kv, kv_len);
   return hipGetLastError();
 }
