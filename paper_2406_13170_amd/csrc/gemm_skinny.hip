@@ -95,13 +95,14 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const float *Ct
     // out is [split_k][M][N]: slab `split` receives this workgroup's partial sums
     const int N = a.seg_rows;
     float *slab = a.out + (size_t)split * a.M * N;
-    const int Q = BN / 4;                                   // 4 adjacent columns per thread (one by one in a ragged last tile)
+    const int Q = BN / 4;                                   // 4 adjacent columns per thread (one by one in a ragged last tile, and in
+    const bool pieces = (N & 3) == 0 && ((uintptr_t)slab & 15) == 0;   // a caller's logits that begin anywhere)
     for (int idx = tid; idx < rows * Q; idx += NT) {
       const int m = idx / Q, r = (idx % Q) * 4, mg = m_base + m, n = tile * BN + r;
       if (mg >= a.M || n >= N) continue;
       const f32x4 v = *reinterpret_cast<const f32x4 *>(Ct + m * CT_PITCH + r);
       float *dst = slab + (size_t)mg * N + n;
-      if (n + 4 <= N && (N & 3) == 0) {
+      if (n + 4 <= N && pieces) {
         *reinterpret_cast<f32x4 *>(dst) = v;
       } else {
         for (int c = 0; c < 4 && n + c < N; ++c) dst[c] = v[c];

@@ -3,10 +3,11 @@ against the oracle: one to thirteen tiles of 32 rows in a group of up to three a
 axis), a ragged last tile of weights, with and without the logits."""
 import numpy as np
 import pytest
+import torch
 
 import synth_inputs as si
 
-from gpu_common import say
+from gpu_common import DEV, i32_to_dev, say
 from test_gpu_step import check_target, run_target
 
 pytestmark = pytest.mark.gpu
@@ -29,3 +30,23 @@ def test_wide_gemm_row_groups(T, Bsz):
     check_target(cfgx, refs, got)
     # the argmax that the kernel takes from its registers is that of the logits it writes, ties to the lower token
     assert np.array_equal(np.asarray(got["tgt"]).reshape(-1), np.asarray(got["logits"]).reshape(T * Bsz, -1).argmax(1))
+
+
+@pytest.mark.parametrize("cfg,T,Bsz", [(si.MINI, 64, 3), (RAGGED, 43, 3), (si.TINY, 64, 3)])
+def test_wide_gemm_writes_logits_that_begin_anywhere(cfg, T, Bsz):
+    """logits_out on a 4-byte boundary only: the same logits, and not a float before or behind them."""
+    say(f"target_forward {cfg.name} T={T} batch={Bsz} (M = {T * Bsz}), logits off a 16-byte boundary")
+    L = 37
+    cfgx, _, got, (ctx, tree, otree) = run_target(cfg, 1, T, (10,) * 5, L, Bsz=Bsz, tiled=True, oracle=False)
+    dev, n = got["dev"], Bsz * T * cfgx.vocab
+    tok = i32_to_dev(si.tokens(cfgx, 0, "tree.tok", (Bsz, T)))
+    pos = i32_to_dev(np.stack([L + otree.depth for _ in range(Bsz)]))
+    for off in (1, 2, 3):
+        buf = torch.full((n + 8,), -7.0, device=DEV)
+        tgt = torch.full((Bsz, T), -1, dtype=torch.int32, device=DEV)
+        ctx.amph_target_forward(tree, dev["structs"], dev["embed_d"], dev["fn_d"], None, tok, pos, got["k_caches"], got["v_caches"],
+                                i32_to_dev(np.full(Bsz, L)), None, buf[off:off + n], tgt, tiled_structs=dev["tiled_structs"],
+                                lm_head_tiled=dev["lm_t"])
+        out = buf.cpu().numpy()
+        assert np.array_equal(out[off:off + n], got["logits"].reshape(-1)) and np.array_equal(tgt.cpu().numpy(), got["tgt"])
+        assert np.all(out[:off] == -7.0) and np.all(out[off + n:] == -7.0)
