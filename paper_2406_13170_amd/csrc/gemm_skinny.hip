@@ -604,14 +604,22 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
     if (tile_of(t) >= g1) break;                           // (wave-uniform)
     if (EPI == EPI_ARGMAX) {
       float bv = -__builtin_huge_valf(); int bi = 0x7fffffff;
+      // Columns in descending order: at equal values the lower one comes later.  Which columns of a ragged last tile exist is asked
+      // anew for every tile of rows: shared by them, the answers were 16 NP lane masks (up to 200 scalar registers spilled, and
+      // with eight pairs 33 vector registers; us, so / now: 32000 x 4096 over 512 rows 124 / 113, 32000 x 5120 148 / 136).
+      const int n0 = tile * 16 * NB + half * 4;
+      int live = a.seg_rows - n0;
+      asm volatile("" : "+v"(live));
       #pragma unroll
-      for (int pr = 0; pr < NP; ++pr)
+      for (int pr = NP - 1; pr >= 0; --pr) {
         #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int nn = tile * 16 * NB + pr * 32 + (i >> 2) * 8 + half * 4 + (i & 3);
+        for (int i = 15; i >= 0; --i) {
+          const int nn = pr * 32 + (i >> 2) * 8 + (i & 3);
           const float v = acc[pr][t][i];
-          if (nn < a.seg_rows && (v > bv || (v == bv && nn < bi))) { bv = v; bi = nn; }
+          if (nn < live && v >= bv) { bv = v; bi = n0 + nn; }
         }
+        __builtin_amdgcn_sched_barrier(0);
+      }
       const auto ov = __builtin_amdgcn_permlane32_swap(lane_bits(bv), lane_bits(bv), false, false);
       const auto oi = __builtin_amdgcn_permlane32_swap((unsigned)bi, (unsigned)bi, false, false);
       const int mg = tile_of(t) * 32 + r32;

@@ -6,8 +6,10 @@ import pytest
 import torch
 
 import synth_inputs as si
+from paper_2406_13170_amd import binding as B
+from paper_2406_13170_amd import device as D
 
-from gpu_common import DEV, i32_to_dev, say
+from gpu_common import DEV, i32_to_dev, make_ctx, say
 from test_gpu_step import check_target, run_target
 
 pytestmark = pytest.mark.gpu
@@ -50,3 +52,33 @@ def test_wide_gemm_writes_logits_that_begin_anywhere(cfg, T, Bsz):
         out = buf.cpu().numpy()
         assert np.array_equal(out[off:off + n], got["logits"].reshape(-1)) and np.array_equal(tgt.cpu().numpy(), got["tgt"])
         assert np.all(out[:off] == -7.0) and np.all(out[off + n:] == -7.0)
+
+
+@pytest.mark.parametrize("cfg,V", [(si.MINI, 2048), (si.MINI, 16003), (si.MINI, 32000), (si.MINI, 33003), (si.TINY, 1024), (si.TINY, 1003)])
+@pytest.mark.parametrize("T,Bsz", [(43, 3), (64, 4), (96, 4)])
+def test_wide_gemm_argmax_of_ties(cfg, V, T, Bsz):
+    """A head of five different rows over and over, and one of zeros: equal logits in a lane, in its partner, in other tiles and
+    in a ragged last one.  The lowest token wins."""
+    say(f"argmax of ties {cfg.name} V={V} T={T} batch={Bsz} (M = {T * Bsz})")
+    cfgx = si.with_(cfg, vocab=V, batch=Bsz, K=5, topk=10)
+    ctx = make_ctx(cfgx, T=T, batch=Bsz, max_kv=128)
+    tree = B.Tree(si.tree_paths(T, (10,) * 5), 5)
+    tdt = D.torch_dtype(cfg.dtype)
+    g = torch.Generator().manual_seed(3)
+    embed = torch.randn((V, cfg.d_model), generator=g).to(tdt).to(DEV)
+    norm = torch.ones((cfg.d_model,), dtype=tdt, device=DEV)
+    few = torch.randn((5, cfg.d_model), generator=g).to(tdt).to(DEV)
+    tok = torch.randint(0, V, (Bsz, T), generator=g, dtype=torch.int32).to(DEV)
+    for head in (few[torch.arange(V, device=DEV) % 5].contiguous(), torch.zeros((V, cfg.d_model), dtype=tdt, device=DEV)):
+        lm_t = D.pack_lm_head(ctx, head)
+        tgt = {}
+        for with_logits in (True, False):
+            logits = torch.full((Bsz, T, V), float("nan"), device=DEV) if with_logits else None
+            tgt[with_logits] = torch.full((Bsz, T), -1, dtype=torch.int32, device=DEV)
+            ctx.amph_target_forward(tree, [], embed, norm, None, tok, torch.zeros_like(tok), None, None, i32_to_dev(np.zeros(Bsz)), None,
+                                    logits, tgt[with_logits], tiled_structs=None, lm_head_tiled=lm_t)
+            if with_logits:
+                want = logits.cpu().numpy().argmax(-1)             # (the first of equal ones)
+        assert want.max() < 5
+        for t in tgt.values():
+            assert np.array_equal(t.cpu().numpy(), want)
