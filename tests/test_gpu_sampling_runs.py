@@ -10,7 +10,7 @@ from paper_2406_13170_amd import binding as B
 from paper_2406_13170_amd import device as D
 
 import test_gpu_loop
-from gpu_common import DEV, i32_to_dev, make_ctx, say
+from gpu_common import DEV, f32_to_dev, i32_to_dev, make_ctx, say
 from test_gpu_typical import run_case
 
 pytestmark = pytest.mark.gpu
@@ -26,14 +26,56 @@ def test_draw_at_run_edges(V):
     run_case(V, T, caps, 4, 9, 0.7, 0.09, 0.3, spread=1.5, us=np.array([0.0, 0.31, 0.77, LAST], dtype=np.float32))
 
 
-def test_draw_falls_back_to_the_last_token_of_non_zero_probability():
-    """Half of the vocabulary has probability zero; u = 1 lies at or above every cumulative sum."""
+def test_draw_at_the_end_of_the_live_tokens():
+    """Half of the vocabulary has probability zero; u is the largest below 1, the draw one of the last live tokens."""
     V = 3000
     logits = np.random.default_rng(4).standard_normal((2, 1, V)).astype(np.float32)
     logits[0, 0, 1501:] = -np.inf
     logits[1, 0, ::2] = -1.0e30
     run_case(V, 1, (4, 4, 4, 4), 2, 5, 1.0, 0.09, 0.3, logits=logits, toks=np.zeros((2, 1), dtype=np.int32),
              us=np.array([LAST, LAST], dtype=np.float32))
+
+
+def emulated_draw(x):
+    """Z and the scan's total in float32, in the kernels' orders: 1024 threads a strided and a consecutive share of the exponentials."""
+    n = 1024
+    e = np.exp(x - x.max(), dtype=np.float32)
+    C = (len(e) + n - 1) // n
+    e = np.pad(e, (0, C * n - len(e)))
+    z, run = np.zeros(n, dtype=np.float32), np.zeros(n, dtype=np.float32)
+    for j in range(C):
+        z += e.reshape(C, n)[j]
+        run += e.reshape(n, C)[:, j]
+    z, inc = z.reshape(16, 64), run.reshape(16, 64)
+    lane = np.arange(64)
+    for off in (32, 16, 8, 4, 2, 1):
+        z = z + z[:, lane ^ off]
+    for off in (1, 2, 4, 8, 16, 32):
+        inc = np.where(lane >= off, inc + inc[:, np.maximum(lane - off, 0)], inc)
+    add = lambda v: np.add.accumulate(v, dtype=np.float32)[-1]  # noqa: E731
+    base = np.float32(0) if len(inc) == 1 else add(inc[:-1, 63])
+    return add(z[:, 0]), inc[-1, 63] + base
+
+
+@pytest.mark.parametrize("live", [65536, 65000, 64576])
+def test_draw_that_no_run_reaches_takes_the_last_live_token(live):
+    """One token of probability near 1 ahead of 63 small ones in its run, which it swallows there and not in the strided order of
+    Z: the run sums end 16 float32 steps and more below u * Z, no run crosses, and the last token of non-zero probability counts."""
+    V = 65536
+    x = np.full(V, -17.33, dtype=np.float32)
+    x[64512] = 0.0
+    x[live:] = -np.inf
+    z, total = emulated_draw(x)
+    assert total < LAST * z - 4 * np.spacing(z)                # (the device's exponentials may differ in the last place)
+    cfg = si.with_(si.TINY, vocab=V, batch=1, K=4, topk=4)
+    ctx = make_ctx(cfg, T=1, batch=1)
+    tree = B.Tree([], 4)
+    out = [torch.full((n,), -7, dtype=torch.int32, device=DEV) for n in (1, 5, 1, 1)]
+    ctx.amph_accept_typical(tree, i32_to_dev([0]), f32_to_dev(x[None, None]), 1.0, 0.09, 0.3, f32_to_dev(np.array([LAST])), out[0], out[1],
+                            out[2], out[3])
+    a_len, path, nxt, best = (t.tolist() for t in out)
+    assert a_len == [0] and best == [0] and path == [0, -1, -1, -1, -1]
+    assert nxt == [live - 1]
 
 
 @pytest.mark.parametrize("cfg,T,caps,L,B_", [
