@@ -345,19 +345,18 @@ def test_target_forward_batch_two():
 
 @pytest.mark.parametrize("cfg,n_layers,T,caps,L,Bsz", [
     (si.MINI, 2, 64, (10,) * 4, 100, 2),           # M = 128: two blocks of 64 rows, still the skinny kernel at these widths
-    (si.MINI, 2, 64, (10,) * 4, 90, 3),            # M = 192: 6 tiles of 32 rows
-    (si.MINI, 2, 64, (10,) * 4, 77, 5),            # M = 320: 10 tiles, up to three math waves per SIMD
-    (si.MINI, 1, 35, (10,) * 4, 61, 10),           # M = 350: 11 tiles, the last one ragged
-    (si.MINI, 1, 64, (10,) * 4, 40, 7),            # M = 448: 14 tiles, one group or two
+    (si.MINI, 2, 64, (10,) * 4, 90, 3),            # M = 192: 6 tiles of 32 rows, two groups of three
+    (si.MINI, 2, 64, (10,) * 4, 77, 5),            # M = 320: 10 tiles, four groups of three, the last one of one tile
+    (si.MINI, 1, 35, (10,) * 4, 61, 10),           # M = 350: 11 tiles, the last one ragged, four groups
+    (si.MINI, 1, 64, (10,) * 4, 40, 7),            # M = 448: 14 tiles, five groups
     (si.TINY, 2, 64, (10,) * 4, 5, 6),             # float32, M = 384: 12 tiles
-    (si.MINI, 1, 96, (10,) * 5, 30, 3),            # M = 288: 9 tiles
-    (si.MINI, 1, 64, (10,) * 4, 20, 8),            # M = 512: 16 tiles, two groups of 8 or every wave two
-    (si.MINI, 1, 64, (10,) * 4, 12, 9),            # M = 576: 18 tiles, two groups of 9
+    (si.MINI, 1, 96, (10,) * 5, 30, 3),            # M = 288: 9 tiles, three groups
+    (si.MINI, 1, 64, (10,) * 4, 20, 8),            # M = 512: 16 tiles, groups of four or three
+    (si.MINI, 1, 64, (10,) * 4, 12, 9),            # M = 576: 18 tiles, five or six groups
 ])
 def test_target_forward_batches_on_tiled_weights(cfg, n_layers, T, caps, L, Bsz):
-    """More than 128 activation rows with tiled weights take the wide GEMM (groups of up to 16 tiles of 32 rows of a
-    weight tile in one workgroup, 32 x 32 matrix-core tiles, one to three math waves per SIMD); the same inputs
-    with row-major weights take the skinny one.  Both against the oracle."""
+    """More than 128 activation rows with tiled weights take the wide GEMM (at these widths groups of three or four tiles of
+    32 rows, a tile a wave); the same inputs with row-major weights take the skinny one.  Both against the oracle."""
     say(f"target_forward {cfg.name} layers={n_layers} T={T} L={L} batch={Bsz} (M = {T * Bsz}), tiled weights")
     cfgx, refs, got, _ = run_target(cfg, n_layers, T, caps, L, Bsz=Bsz, tiled=True)
     check_target(cfgx, refs, got)
@@ -415,8 +414,8 @@ def test_target_forward_vicuna13b_two_layers():
 
 @pytest.mark.parametrize("seed", [0, 1])
 def test_target_forward_vicuna33b_one_layer_batch4(seed):
-    """Configuration 5 at full width (d 6656, FFN 17920, 52 x 128 heads, L 4096, T 96, batch 4: M = 384 rows, six
-    blocks of 64 rows per weight tile), one sampled layer + final norm + LM head, tiled weights."""
+    """Configuration 5 at full width (d 6656, FFN 17920, 52 x 128 heads, L 4096, T 96, batch 4: M = 384 rows:
+    groups of six and of twelve tiles of 32), one sampled layer + final norm + LM head, tiled weights."""
     say(f"target_forward vicuna33b 1 layer (seed {seed}), batch 4 (tiled weights)")
     cfgx, refs, got, _ = run_target(si.V33B, 1, 96, (10,) * 5, 4096, seed=seed, Bsz=4, tiled=True)
     check_target(cfgx, refs, got)

@@ -1,6 +1,6 @@
 """The target's projections where the row tiles of a launch can go wrong, against the oracle: float32 trees around every count
-of 16-row tiles, and more than 64 rows at the widths where a workgroup takes eight or ten row blocks of the weights (more than
-24000 rows of them), with ragged tiles, ragged stages, several epilogue rounds and several row groups."""
+of 16-row tiles, and more than 64 rows at the widths where a workgroup takes eight, ten or sixteen row blocks of the weights,
+with ragged tiles, ragged stages and several row groups."""
 import numpy as np
 import pytest
 import torch
@@ -13,22 +13,23 @@ from test_gpu_step import check_target, run_target
 
 pytestmark = pytest.mark.gpu
 
-# 2063 and 2052 row blocks: ten a workgroup, the last one ragged (W_down then has 513 steps, an odd number, in eight splits)
+# 2063 and 2052 row blocks (the head and gate/up): ten a workgroup, the last one ragged (W_down then has 513 steps, an odd number, in
+# eight splits)
 TEN = si.with_(si.MINI, name="mini_ten_blocks", vocab=33003, d_ffn=16416)
-# 2000 row blocks: eight a workgroup
+# 2000 row blocks: eight a workgroup, or sixteen over two row groups
 EIGHT = si.with_(si.MINI, name="mini_eight_blocks", vocab=32000, d_ffn=16000)
-# 960 row blocks of Q, K and V: eight a workgroup over two row groups; W_o splits its axis over eight blocks
+# 960 row blocks of Q, K and V: eight a workgroup over two row groups; W_o splits its axis in two, ten blocks a workgroup
 QKV = si.with_(si.MINI, name="mini_wide_qkv", d_model=5120, n_heads=40, d_ffn=512, vocab=512)
 TEN_F32 = si.with_(si.TINY, name="tiny_ten_blocks", vocab=33003, d_ffn=16416)
 
 
 @pytest.mark.parametrize("cfg,T,caps,L,Bsz", [
     (TEN, 13, (10,) * 4, 40, 5),        # 65 rows: three tiles, one row in the last (gate/up and the head)
-    (TEN, 96, (10,) * 5, 30, 3),        # 288 rows: nine waves, seven output tiles at a time
-    (EIGHT, 64, (10,) * 4, 20, 2),      # 128 rows: four waves (gate/up and the head)
-    (EIGHT, 64, (10,) * 4, 20, 6),      # 384 rows: twelve waves, nine output tiles at a time
-    (EIGHT, 43, (10,) * 4, 33, 9),      # 387 rows: thirteen tiles, two groups of seven
-    (QKV, 64, (10,) * 4, 20, 8),        # 512 rows: two groups of eight
+    (TEN, 96, (10,) * 5, 30, 3),        # 288 rows: one group of nine tiles, the first wave has three
+    (EIGHT, 64, (10,) * 4, 20, 2),      # 128 rows: a tile a wave (gate/up and the head)
+    (EIGHT, 64, (10,) * 4, 20, 6),      # 384 rows: one group of twelve tiles, three a wave
+    (EIGHT, 43, (10,) * 4, 33, 9),      # 387 rows: thirteen tiles, two groups of seven, two a wave and one
+    (QKV, 64, (10,) * 4, 20, 8),        # 512 rows: two groups of eight tiles, two a wave
     (TEN_F32, 32, (10,) * 4, 17, 6),    # float32, 192 rows
 ])
 def test_target_forward_over_wide_matrices(cfg, T, caps, L, Bsz):
@@ -39,7 +40,7 @@ def test_target_forward_over_wide_matrices(cfg, T, caps, L, Bsz):
 
 # 65 to 128 rows, where each matrix goes to the kernel that suits it (gemm_is_wide).  Of the projections into Q, K and V, W_o,
 # gate/up, W_down and the LM head, those of tiled weights on the wide kernel:
-DOWN = si.with_(si.MINI, name="mini_down", d_model=1024, n_heads=8, d_ffn=4608, vocab=512)
+DOWN = si.with_(si.MINI, name="mini_down", d_model=1664, n_heads=13, d_ffn=4608, vocab=512)
 
 
 @pytest.mark.parametrize("cfg,n_layers,T,caps,L,Bsz", [
@@ -49,7 +50,7 @@ DOWN = si.with_(si.MINI, name="mini_down", d_model=1024, n_heads=8, d_ffn=4608, 
     (QKV, 1, 13, (10,) * 4, 20, 5),        # Q, K, V and W_o
     (QKV, 1, 64, (10,) * 4, 20, 2),        # Q, K, V
     (DOWN, 1, 13, (10,) * 4, 20, 5),       # none: W_down would be, but its input comes from a skinny gate/up
-    (si.V7B, 1, 40, (10,) * 4, 64, 2),     # all but Q, K, V
+    (si.V7B, 1, 40, (10,) * 4, 64, 2),     # all but W_o
     (TEN_F32, 1, 16, (10,) * 4, 17, 5),    # float32: none
     (si.TINY, 2, 16, (4, 2, 2, 2), 9, 8),  # the same, 128 rows
 ])

@@ -1,25 +1,28 @@
-"""The wide GEMM where its groups of row tiles, its waves' shares of them, its weight stages and its row argmax can go wrong,
-against the oracle: one to thirteen tiles of 32 rows in a group of up to three a wave, ragged stages (43 steps of the reduction
-axis), a ragged last tile of weights, with and without the logits."""
+"""The wide GEMM against the oracle: the head's groups of five to thirteen row tiles (up to three a wave) beside a layer whose W_down
+has ragged stages (43 steps of the reduction axis in two slabs); the row argmax; logits that begin anywhere; and every instance that the
+plan selects, on narrow matrices that it gives them."""
 import numpy as np
 import pytest
 import torch
 
 import synth_inputs as si
+from oracle import amphista_oracle as orc
 from paper_2406_13170_amd import binding as B
 from paper_2406_13170_amd import device as D
 
-from gpu_common import DEV, i32_to_dev, make_ctx, say
+import wide_plan as wp
+from gpu_common import DEV, cfg_tensor_to_dev, f32_layers, i32_to_dev, make_ctx, np_of, say
 from test_gpu_step import check_target, run_target
 
 pytestmark = pytest.mark.gpu
 
-# 172 and 688 steps' worth of blocks: W_down has 43 steps of 64 bytes, the head 2063 row blocks (the last one ragged)
+# W_down has 43 steps of 64 bytes, the head 2063 row blocks (the last one ragged)
 RAGGED = si.with_(si.MINI, name="mini_ragged", vocab=33003, d_ffn=1376)
 
 
-@pytest.mark.parametrize("T,Bsz", [(43, 3),     # 129 rows: five tiles, one row in the last
-                                   (32, 5),     # 160: five tiles, two of them with the first wave
+# the head's groups; the layer's matrices form groups of three tiles (gate/up of four over 256 rows), a tile a wave
+@pytest.mark.parametrize("T,Bsz", [(43, 3),     # 129 rows: five tiles, one row in the last, two tiles with the first wave
+                                   (32, 5),     # 160: five tiles
                                    (24, 8),     # 192: six
                                    (64, 4),     # 256: eight, two a wave
                                    (43, 6),     # 258: nine, three of them with the first wave
@@ -82,3 +85,76 @@ def test_wide_gemm_argmax_of_ties(cfg, V, T, Bsz):
         assert want.max() < 5
         for t in tgt.values():
             assert np.array_equal(t.cpu().numpy(), want)
+
+
+# ---- every instance of the kernel, on narrow matrices that the plan gives it -----------------------------------------------
+def run_twins(case, n_layers, d, d_ffn, vocab):
+    """A pass over many sequences of which only two are different: those against the oracle, the others against their twins, bit by
+    bit (a row of a GEMM does not depend on the rows beside it)."""
+    dtype, T, Bsz, _, d_h, _, _ = case
+    L, K, seed = 20, 5, 3
+    cfg = si.with_(si.MINI if dtype == "bf16" else si.TINY, name=f"twins_{dtype}_{d}", d_model=d, n_heads=d // d_h, head_dim=d_h, d_ffn=d_ffn,
+                   vocab=vocab, batch=Bsz, K=K, topk=10)
+    n_h, max_kv = cfg.n_heads, (L + T + 31) // 32 * 32
+    ctx = make_ctx(cfg, T=T, max_kv=max_kv)
+    paths = si.tree_paths(T, (10,) * K)
+    tree, otree = B.Tree(paths, K), orc.tree_from_paths(paths, K)
+    tw = si.target_weights(cfg, seed, n_layers)
+    layers_d = [D.layer_to_device(lw, DEV) for lw in tw["layers"]]
+    packed = [D.pack_layer(ctx, l) for l in layers_d]
+    structs = [B.amph_layer_w(rms1=l["rms1"].data_ptr(), rms2=l["rms2"].data_ptr()) for l in layers_d]
+    lm_t = D.pack_lm_head(ctx, cfg_tensor_to_dev(tw["lm_head"]))
+    kv = [[si.normal(cfg, seed, f"twins{li}.{n}", (2, n_h, L, d_h), 1.0) for li in range(n_layers)] for n in "kv"]
+    caches = []
+    for rows in kv:
+        t = torch.zeros((max(n_layers, 1), Bsz, n_h, max_kv, d_h), dtype=D.torch_dtype(cfg.dtype), device=DEV)
+        for li, r in enumerate(rows):
+            t[li, :, :, :L] = cfg_tensor_to_dev(r)[torch.arange(Bsz) % 2]
+        caches.append(t)
+    k_caches, v_caches = D.pack_kv(ctx, *caches)
+    del caches
+    tok = si.tokens(cfg, seed, "twins.tok", (2, T))
+    pos = (L + otree.depth).astype(np.int32)
+    hidden = torch.full((Bsz, T, d), float("nan"), device=DEV)
+    logits = torch.full((Bsz, T, vocab), float("nan"), device=DEV)
+    tgt = torch.full((Bsz, T), -1, dtype=torch.int32, device=DEV)
+    ctx.amph_target_forward(tree, structs, cfg_tensor_to_dev(tw["embed"]), cfg_tensor_to_dev(tw["final_norm"]), None,
+                            i32_to_dev(tok[np.arange(Bsz) % 2]), i32_to_dev(np.tile(pos, (Bsz, 1))), k_caches, v_caches,
+                            i32_to_dev(np.full(Bsz, L)), hidden, logits, tgt, tiled_structs=[p[0] for p in packed], lm_head_tiled=lm_t)
+    torch.cuda.synchronize()
+    assert ctx.device_status() == 0
+    bits = lambda t: t.view(torch.int16 if t.element_size() == 2 else torch.int32)  # noqa: E731
+    rows = [t[:, :, :, L:L + T].transpose(0, 1) for t in D.unpack_kv(ctx, k_caches, v_caches)] if n_layers else []
+    for t in [hidden, logits, tgt] + rows:
+        t = bits(t.contiguous())
+        for b in range(2, Bsz):
+            assert torch.equal(t[b], t[b % 2]), f"sequence {b} differs from its twin"
+    two = dict(embed=tw["embed"].f32, layers=f32_layers(tw["layers"]), final_norm=tw["final_norm"].f32, lm_head=tw["lm_head"].f32)
+    refs = [orc.target_forward(two, tok[b], pos, otree.mask, [r.f32[b] for r in kv[0]], [r.f32[b] for r in kv[1]], n_h, cfg.rms_eps,
+                               cfg.rope_theta, keep=True) for b in range(2)]
+    check_target(cfg, refs, dict(hidden=np_of(hidden[:2]), logits=np_of(logits[:2]), tgt=np_of(tgt[:2]), k_caches=k_caches, v_caches=v_caches,
+                                 L=L, T=T, ctx=ctx))
+    assert torch.equal(logits.argmax(-1).to(torch.int32), tgt)
+
+
+ids = lambda c: "-".join(str(x) for x in c[:6])  # noqa: E731
+
+
+@pytest.mark.parametrize("case", wp.LAYERS, ids=ids)
+def test_wide_gemm_instances_of_a_layer(case):
+    say(f"wide GEMM instances {sorted(case[-1])}: {case[:6]}, M = {case[1] * case[2]}")
+    assert case[-1] <= {wp.instance(*g) for g in wp.gemms(case)}
+    run_twins(case, 1, case[3], case[5], 512)
+
+
+@pytest.mark.parametrize("case", wp.HEADS, ids=ids)
+def test_wide_gemm_instances_of_the_head(case):
+    say(f"wide GEMM instances {sorted(case[-1])}: {case[:6]}, M = {case[1] * case[2]}")
+    assert case[-1] <= {wp.instance(*g) for g in wp.gemms(case)}
+    run_twins(case, 0, case[3], 320, case[5])
+
+
+@pytest.mark.parametrize("cfg,T,Bsz", [(si.V7B, 64, 8), (si.V13B, 64, 2)])
+def test_wide_gemm_at_model_width(cfg, T, Bsz):
+    say(f"one layer of {cfg.name} over {T * Bsz} rows")
+    run_twins((cfg.dtype, T, Bsz, cfg.d_model, cfg.head_dim, cfg.d_ffn, set()), 1, cfg.d_model, cfg.d_ffn, cfg.vocab)
