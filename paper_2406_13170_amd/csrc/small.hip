@@ -846,8 +846,13 @@ template hipError_t launch_commit<bf16_t>(hipStream_t, void *, void *, int, int,
 //   values  a lane holds DH / 16 adjacent rows of PER adjacent dims and turns them round in registers: a dim's rows
 //           are adjacent in the tile.
 // (One element at a time the values' side was 2-byte accesses 64 bytes apart: 2.3 GB of pack and unpack over 32 layers
-// of 7B caches 1440 us, 1.6 TB/s; this way 413 us, 5.5 TB/s.)
+// of 7B caches 1440 us, 1.6 TB/s; this way 395 us, 5.8 TB/s.)
+// The launch asks for LDS that it does not use, so that three workgroups (six of half the bytes at 64-wide heads) share a
+// compute unit: as many as the registers allow have too many streams open (us, pack / unpack of the 7B caches, workgroups a
+// unit: 8 211 / 214, 7 210 / 208, 5 204 / 206, 4 200 / 202, 3 196 / 198; smaller conversions the same).
 // =====================================================================================================
+constexpr int kvl_lds_bytes(int d_h) { return d_h == 128 ? 52 * 1024 : 26 * 1024; }
+
 template <typename T, int DH, bool TO_TILED>
 __global__ __launch_bounds__(256) void k_kv_layout(const T *k_src, const T *v_src, T *k_dst, T *v_dst, int n_caches, int max_kv) {
   constexpr int PER = Elem<T>::PER, KSTEP = 4 * PER, UN = DH / 16, LPR = DH / PER;   // LPR lanes cover a row
@@ -910,8 +915,8 @@ hipError_t launch_kv_layout(hipStream_t st, const void *k_src, const void *v_src
   if (n_caches < 1 || n_caches > 65535 * 16 || max_kv % 32 || (d_h != 64 && d_h != 128)) return hipErrorInvalidValue;
   const long long units = (long long)n_caches * (max_kv / (4 * Elem<T>::PER)) * ((k_src && v_src) ? 2 : 1);
   const dim3 grid((unsigned)std::min<long long>((units + 3) / 4, 16384)), block(256);
-  #define KVL(DH_, W_) hipLaunchKernelGGL((k_kv_layout<T, DH_, W_>), grid, block, 0, st, (const T *)k_src, (const T *)v_src, (T *)k_dst, \
-                                          (T *)v_dst, n_caches, max_kv)
+  #define KVL(DH_, W_) hipLaunchKernelGGL((k_kv_layout<T, DH_, W_>), grid, block, kvl_lds_bytes(DH_), st, (const T *)k_src, (const T *)v_src, \
+                                          (T *)k_dst, (T *)v_dst, n_caches, max_kv)
   if (d_h == 64) { if (to_tiled) KVL(64, true); else KVL(64, false); }
   else { if (to_tiled) KVL(128, true); else KVL(128, false); }
   #undef KVL
