@@ -114,7 +114,8 @@ amph_status amph_create(const amph_config *cfg, amph_ctx **out);
 void amph_destroy(amph_ctx *ctx);
 /* hip_stream is a hipStream_t (NULL = the default stream).  The caller keeps it alive. */
 amph_status amph_set_stream(amph_ctx *ctx, void *hip_stream);
-/* Bytes of caller-provided scratch every call below needs (256-byte aligned). */
+/* Bytes of caller-provided scratch every call below needs (256-byte aligned).  Among them 4 KB for each of the
+ * batch * max_tree tree rows: the run sums that amph_accept_typical draws from. */
 size_t amph_workspace_bytes(const amph_ctx *ctx);
 /* Host string describing the last failure on this context (never NULL). */
 const char *amph_last_error(const amph_ctx *ctx);

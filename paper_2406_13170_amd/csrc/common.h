@@ -141,7 +141,7 @@ template <typename T> __device__ __forceinline__ size_t xt_index(int m, int k, i
 // ---- wave-level reductions ---------------------------------------------------------------------------
 // The 32-bit value of the lane OFF further on, exchanged inside the vector ALU (a shuffle goes through LDS: about a hundred
 // clocks of latency each, and its turn there; six of them for every sum were a good part of the short kernels: a whole
-// iteration of the float32 miniature 216 -> 203 us, a one-row 7B draft 367 -> 364).
+// iteration of the float32 miniature 216 -> 203 us; longer kernels do not show it).
 // xor16 / xor32: the row swap of a register with itself leaves the even rows (the lower half) in one result and the odd
 // ones (the upper half) in the other, so op of the two is op over lanes 16 (32) apart, in every lane.
 template <typename V> __device__ __forceinline__ unsigned lane_bits(V v) { union { V v; unsigned u; } c; c.v = v; return c.u; }

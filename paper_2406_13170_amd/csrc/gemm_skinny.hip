@@ -435,11 +435,12 @@ __global__ __launch_bounds__(64 * (GM_MAX_NB + GM_NLW)) void k_gemm_skinny(const
 // or three tiles and the rows of a group are read again once for up to 16 blocks.  Before, eight to twelve math waves had a tile
 // each (10 blocks at most) or two (6 blocks), beside two waves that did nothing but load: a tile a wave reads 8 clocks of LDS
 // for 8 clocks of matrix core on its compute unit, and 512 x 96 outputs take in 38 KB a step where 256 x 192 take 28.
-// What bounds it: matrix-core clocks (a loop without any loads: 67 us of the 85 below; the clock drops under
-// such a load: 54 us on a quarter of the chip), then what the weights' way through registers and LDS adds (16 us) and the activations' (7).
-// Measured (us, before / now): 512 rows 22016 x 4096 99 / 85 (1.08 PFLOP/s), 32000 x 4096 144 / 116, 12288 x 4096 58 / 52;
-// 384 rows 35840 x 6656 218 / 169, 32000 x 6656 177 / 137 (1.2 PFLOP/s); 256 rows 22016 x 4096 62 / 53; 128 rows 27648 x 5120
-// 63 / 57, 5120 x 13824 43 / 34; all of a layer's matrices and the LM head at 7B, 13B and 33B widths over 80 to 768 rows 12.5 / 11.0 ms.
+// What bounds it: matrix-core clocks (512 rows of 22016 x 4096 alone 85 us, a loop without any loads 67 of them; the clock drops
+// under such a load: 54 us on a quarter of the chip), then what the weights' way through registers and LDS adds (16 us) and the activations' (7).
+// Measured inside verification passes (us, before / now; gate/up, QKV, W_down, W_o, LM head): 7B over 256 rows 63 / 58, 57 / 47,
+// 45 / 43, 21 / 20, 76 / 69; over 512 rows 99 / 90 (1.03 PFLOP/s), 67 / 62, 62 / 57, 33 / 31, 140 / 116; 13B over 512 rows 158 / 137,
+// 94 / 86, 91 / 83, 40 / 38, 169 / 141; 33B over 384 rows 193 / 165 (1.1 PFLOP/s), 132 / 122, 120 / 119, 50 / 51, 167 / 142; 13B over 128
+// rows 64 / 66, 52 / 47, 45 / 40, (skinny), 68 / 64.  Alone, on a cooler chip, the same kernels are 5 to 15 % faster.
 // Tried: weights two stages ahead, activations 7.5 steps ahead (more registers, no gain); five pairs and more with a tile a
 // wave (LDS-bound).
 // A 32 x 32 instruction takes, per lane (half, r), 16 bytes of row r: the bytes [half * 16, half * 16 + 16) of
@@ -800,9 +801,11 @@ static GemmPlan plan_wide(int epi, int seg_rows, int Kd, int elem_bytes, int M, 
 // slab both kernels add the same products in the same order (bf16; the float32 fragments are dealt out differently), so
 // their bits are the same.  Therefore it is a rule on the shape alone.  Up to 128 rows it is the skinny kernel's, for
 // whichever kernel runs and however the weights are stored: tiled and row-major weights give the same bits there.  Beyond
-// (tiled weights) it weighs, in units of a weight fragment, a workgroup's steps times its fragments per step and the tiles
-// that its busiest SIMD carries, for groups of up to 8, 12 or 16 tiles in pairs of blocks up to three, against the slabs' way out
-// and back; another count would change every result.
+// (tiled weights) the rule is one that was made for an earlier form of the wide kernel (groups of up to 8, 12 or 16 tiles, at
+// most six blocks a workgroup, up to three waves a SIMD): it weighs, in units of a weight fragment, a workgroup's steps times its
+// fragments per step and the tiles of its busiest SIMD against the slabs' way out and back.  It is kept because another count
+// changes every result, not because it suits the present kernel: finer slabs measured faster with the form before this one (us:
+// W_down at 384 rows, 33B, four slabs 110, two 122, the fold 16 against 14; 512 rows, 7B, 52 and 62, the folds 13 and 12).
 static int gemm_split(int epi, int seg_rows, int Kd, int elem_bytes, int M, bool tiled) {
   if (epi != EPI_STORE) return 1;                           // fused epilogues need complete sums
   if (!tiled || M <= 2 * GM_BM) return plan_skinny(epi, seg_rows, Kd, elem_bytes, M, 0).split;
