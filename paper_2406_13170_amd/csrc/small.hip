@@ -739,9 +739,9 @@ hipError_t launch_accept_typical(hipStream_t st, const int32_t *parent, const in
 // source.  Over deep caches it is bound by the values: lines of which two bytes move, read and written.  Measured (us by the
 // kernel trace, k_commit; k_advance takes 1.3 behind it where the commits follow each other, up to 5 at the end of a long
 // step), for 0, 1, 2, 3 and all nodes accepted in every sequence, against a version that read a source for every place of
-// the path, accepted or not: 8 layers of 7B width, batch 4: 2.9 4.8 5.2 6.0 6.7 (4.3 6.0 6.4 6.9 7.4); 40 layers of 13B,
-// batch 4: 3.6 19.4 20.7 22.4 29.5 (13.1 20.6 22.1 25.0 31.3); 60 layers of 33B, batch 4: 5.2 35.5 37.5 41.8 81.5
-// (27.5 38.8 42.4 48.6 87.5).
+// the path, accepted or not: 8 layers of 7B width, batch 4: 2.7 4.7 5.3 5.9 7.2 (4.3 5.9 6.3 6.7 7.9); 40 layers of 13B,
+// batch 4: 4.9 19.3 20.2 22.1 29.0 (13.5 20.5 22.2 25.0 31.2); 60 layers of 33B, batch 4: 9.0 35.4 37.1 41.5 80.9
+// (26.5 38.7 42.5 48.3 87.8).
 // =====================================================================================================
 template <int N> struct RowTag { static constexpr int value = N; };
 
@@ -759,10 +759,14 @@ __global__ __launch_bounds__(256) void k_commit(T *k_caches, T *v_caches, int B,
       const int node = min(max(path[j], 0), T_nodes - 1), node1 = min(max(path[min(j + 1, K)], 0), T_nodes - 1);
       float *dst = h_new + ((size_t)b * (K + 1) + j) * d;
       const float *src = hidden + ((size_t)b * T_nodes + node) * d;
-      for (int k = t * 4; k < d; k += 256 * 4) {
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (j <= a) v = *reinterpret_cast<const float4 *>(src + k);      // (uniform over the workgroup)
-        *reinterpret_cast<float4 *>(dst + k) = v;
+      for (int k0 = t * 4; k0 < d; k0 += 4 * 1024) {         // four pieces are asked for before the first is stored
+        float4 v[4];
+        #pragma unroll
+        for (int i = 0; i < 4; ++i)
+          v[i] = j <= a ? *reinterpret_cast<const float4 *>(src + min(k0 + i * 1024, d - 4)) : make_float4(0.f, 0.f, 0.f, 0.f);
+        #pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (k0 + i * 1024 < d) *reinterpret_cast<float4 *>(dst + k0 + i * 1024) = v[i];
       }
       if (t == 0) {
         tok_new[(size_t)b * (K + 1) + j] = j < a ? tree_tok[(size_t)b * T_nodes + node1] : j == a ? next_tok[b] : 0;
@@ -776,11 +780,15 @@ __global__ __launch_bounds__(256) void k_commit(T *k_caches, T *v_caches, int B,
   constexpr int KPR = DH / PER, VR = 256 / DH, MAXI = AMPH_MAX_HEADS_K / VR;
   static_assert(AMPH_MAX_HEADS_K * KPR <= 256 && DH % WAVE == 0, "a thread for every piece of the keys; a wave for one value row");
   const int kj = 1 + t / KPR, kp = t % KPR, vj = 1 + __builtin_amdgcn_readfirstlane(t / DH), ve = t % DH;
-  const int L = kv_len[b], a = min(accept_len[b], K);
-  const int kn = path[min(kj, K)], first = path[1];
+  int L = kv_len[b], a = accept_len[b], kn = path[min(kj, K)], first = path[1];
   int vn[MAXI];
   #pragma unroll
   for (int i = 0; i < MAXI; ++i) vn[i] = path[min(vj + i * VR, K)];
+  asm volatile("" : "+v"(L), "+v"(a), "+v"(kn), "+v"(first));         // one round trip: all are asked for ahead of the branches
+  #pragma unroll
+  for (int i = 0; i < MAXI; ++i) asm volatile("" : "+v"(vn[i]));
+  L = __builtin_amdgcn_readfirstlane(L);
+  a = min(__builtin_amdgcn_readfirstlane(a), K);
   if (L < 0 || L + T_nodes > max_kv || a < 1) return;       // the target pass wrote nothing (flagged there), or nothing moves
   const size_t head = (((size_t)li * B + b) * n_heads + h) * (size_t)max_kv * DH;
   T *kc = k_caches + head, *vc = v_caches + head;
