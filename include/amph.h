@@ -266,7 +266,7 @@ amph_status amph_commit(amph_ctx *ctx, const amph_tree *tree, int n_layers, void
  *   k_caches, v_caches   [n_layers, B, n_heads] caches of max_kv * head_dim elements each, step-tiled as
  *              amph_verify_attn describes; the call writes the tree rows of every layer
  *   hidden_out [B, T, d] float32 (final-normed hidden states) or NULL
- *   logits_out [B, T, V] float32 or NULL
+ *   logits_out [B, T, V] float32 or NULL (any address; in 16-byte pieces where it begins on such a boundary)
  *   tgt_argmax [B, T] int32 */
 amph_status amph_target_forward(amph_ctx *ctx, const amph_tree *tree, const amph_layer_w *layers /* host */,
                                 const amph_layer_tiled *tiled /* host or NULL */, int n_layers,
