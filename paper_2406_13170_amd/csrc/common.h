@@ -99,25 +99,6 @@ template <> __device__ __forceinline__ f32x4 mma16<float>(const uint4 &a, const 
   return acc;
 }
 
-// acc[32 x 32] += A[32 rows x 32 bytes of k] * B[32 columns x 32 bytes of k]: lane (half = lane / 32, r = lane % 32)
-// holds the 16 bytes at half * 16 of row (column) r; afterwards lane (half, r) holds column r, rows
-// (i / 4) * 8 + half * 4 + (i % 4) in acc[i].  On this chip the 32 x 32 bf16 instruction runs at twice the
-// rate of the 16 x 16 one (measured: 2.3 against 1.3 PFLOP/s with every SIMD busy).
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-template <typename T> __device__ __forceinline__ f32x16 mma32(const uint4 &a, const uint4 &b, f32x16 acc);
-template <> __device__ __forceinline__ f32x16 mma32<bf16_t>(const uint4 &a, const uint4 &b, f32x16 acc) {
-  union { uint4 u; bf16x8 v; } ca, cb;
-  ca.u = a; cb.u = b;
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(ca.v, cb.v, acc, 0, 0, 0);
-}
-template <> __device__ __forceinline__ f32x16 mma32<float>(const uint4 &a, const uint4 &b, f32x16 acc) {
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
-  return acc;
-}
-
 // Element index of (row, dim) in the step-tiled K and V caches of one head (layout: header of the C ABI).
 template <typename T> __device__ __forceinline__ size_t k_tiled_index(int row, int c, int d_h) {
   constexpr int PER = Elem<T>::PER, KSTEP = 4 * PER, PIECE = 64 / (int)sizeof(T);   // elements in 64 bytes
@@ -129,12 +110,12 @@ template <typename T> __device__ __forceinline__ size_t v_tiled_index(int row, i
   return ((size_t)(row / KSTEP) * (d_h / 16) + c / 16) * (16 * PIECE) + (c % 16) * PIECE + row % KSTEP;
 }
 
-// Element index of (row m, element k) in the fragment-tiled activation layout the wide GEMM reads: 32 rows x 32 bytes
-// of k per KB, lane-linear (lane = half * 32 + m % 32 holds the 16 bytes at half * 16).  4 elements starting at a
-// multiple of 4 stay inside one 16-byte piece.
+// Element index of (row m, element k) in the fragment-tiled activation layout the wide GEMM reads: 16 rows x 64 bytes
+// of k per KB, lane-linear (lane = g * 16 + m % 16 holds the 16 bytes at g * 16), the two fragments of 32 rows side by side.
+// 4 elements starting at a multiple of 4 stay inside one 16-byte piece.
 template <typename T> __device__ __forceinline__ size_t xt_index(int m, int k, int m32_tiles) {
   const int kb = k * (int)sizeof(T);
-  const size_t byte = ((size_t)(kb >> 5) * m32_tiles + (m >> 5)) * 1024 + (size_t)((((kb >> 4) & 1) * 32 + (m & 31)) << 4) + (kb & 15);
+  const size_t byte = ((size_t)(kb >> 6) * (2 * m32_tiles) + (m >> 4)) * 1024 + (size_t)((((kb >> 4) & 3) * 16 + (m & 15)) << 4) + (kb & 15);
   return byte / sizeof(T);
 }
 

@@ -84,6 +84,16 @@ __device__ __forceinline__ RowMap map_block(const GemmArgs &a, int b, int r16) {
   return o;
 }
 
+// A dimension and its RoPE partner, rotated.  The two products that are rounded on their own are named, and hidden from the compiler,
+// which otherwise contracts now one and now the other product of a sum: a row's bits must not depend on where it is computed.
+__device__ __forceinline__ void rope_pair(float x1, float x2, float cs, float sn, float &y1, float &y2) {
+  float p1 = x2 * sn, p2 = x1 * sn;
+  asm("" : "+v"(p1));
+  asm("" : "+v"(p2));
+  y1 = fmaf(x1, cs, -p1);
+  y2 = fmaf(x2, cs, p2);
+}
+
 // Epilogue of one 64-row block of a workgroup's output tile: Ct[m][r] (float32, pitch CT_PITCH) holds rows
 // m_base .. m_base + 63 of the activations against the tile's nb row blocks (BN = 16 * nb columns).  Every thread
 // of the workgroup (NT of them) takes part.
@@ -169,9 +179,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const float *Ct
         float y1[8], y2[8];
         #pragma unroll
         for (int j = 0; j < 8; ++j) {
-          const float x1 = crow[j], x2 = crow[8 + j];
-          y1[j] = x1 * cs[j] - x2 * sn[j];
-          y2[j] = x2 * cs[j] + x1 * sn[j];
+          rope_pair(crow[j], crow[8 + j], cs[j], sn[j], y1[j], y2[j]);
         }
         T *dst1, *dst2;
         if (seg == 0) {
@@ -419,36 +427,32 @@ __global__ __launch_bounds__(64 * (GM_MAX_NB + GM_NLW)) void k_gemm_skinny(const
 
 // =====================================================================================================
 // Wide GEMM: more than 64 activation rows (batches of trees, wide trees; gemm_is_wide).  The skinny kernel above re-reads the
-// weights from L2 once per block of 64 rows, every math wave re-reads the whole activation chunk from LDS, and its
-// 16 x 16 matrix-core instruction runs at half the rate of the 32 x 32 one: with several blocks of rows L2, LDS
-// and the matrix cores, not HBM, set the pace.  Here a workgroup of four waves, one for each SIMD, owns a group of gt <= 12 tiles
-// of 32 activation rows against NB = 2 NP weight row blocks; wave w owns tiles w, w + 4, w + 8 of the group against all blocks,
-// taken in pairs (32 weight rows).
+// weights from L2 once per block of 64 rows, and every math wave re-reads the whole activation chunk from LDS: with several
+// blocks of rows L2 and LDS, not HBM, set the pace.  Here a workgroup of four waves, one for each SIMD, owns a group of gt <= 12 tiles
+// of 32 activation rows against NB = 2 NP weight row blocks; wave w owns tiles w, w + 4, w + 8 of the group against all blocks.
 //   * The weights are the shared operand: of every block of a stage (4 steps of 64 bytes of k) a wave brings in one step, through
 //     registers (requested a stage ahead) into one of two LDS slots.
-//   * The activations go from global memory (L2 hits) straight into the registers of the one wave that needs them, 3.5 steps ahead.
-//   * A half-step reads one weight fragment per pair from LDS and issues one 32 x 32 matrix-core instruction per pair and tile.
-//     The fragments of the next half-step are read, the activations requested and the next stage written between these
-//     instructions, in an order laid down by hand; the barrier lies ahead of a stage's last half-step, whose operands are in
-//     registers by then, and the next stage's first fragments are read behind it, so that it costs nothing either.
-// Why four waves: with one wave a SIMD its 512 registers hold up to 16 accumulators of 32 x 32, so an LDS fragment is used for two
-// or three tiles and the rows of a group are read again once for up to 16 blocks.  Before, eight to twelve math waves had a tile
-// each (10 blocks at most) or two (6 blocks), beside two waves that did nothing but load: a tile a wave reads 8 clocks of LDS
-// for 8 clocks of matrix core on its compute unit, and 512 x 96 outputs take in 38 KB a step where 256 x 192 take 28.
-// What bounds it: matrix-core clocks (512 rows of 22016 x 4096 alone 85 us, a loop without any loads 67 of them; the clock drops
-// under such a load: 54 us on a quarter of the chip), then what the weights' way through registers and LDS adds (16 us) and the activations' (7).
-// Measured inside verification passes (us, before / now; gate/up, QKV, W_down, W_o, LM head): 7B over 256 rows 63 / 58, 57 / 47,
-// 45 / 43, 21 / 20, 76 / 69; over 512 rows 99 / 90 (1.03 PFLOP/s), 67 / 62, 62 / 57, 33 / 31, 140 / 116; 13B over 512 rows 158 / 137,
-// 94 / 86, 91 / 83, 40 / 38, 169 / 141; 33B over 384 rows 193 / 165 (1.1 PFLOP/s), 132 / 122, 120 / 119, 50 / 51, 167 / 142; 13B over 128
-// rows 64 / 66, 52 / 47, 45 / 40, (skinny), 68 / 64.  Alone, on a cooler chip, the same kernels are 5 to 15 % faster.
+//   * The activations go from global memory (L2 hits) straight into the registers of the one wave that needs them, 3 steps ahead.
+//   * A half-step is one step against half of the blocks: a weight fragment is read from LDS for the 16 x 16 matrix instructions of
+//     all the wave's rows.  The fragments of the next half-step are read, the activations requested and the next stage written
+//     between these instructions, in an order laid down by hand; the barrier lies ahead of a stage's last half-step, whose operands
+//     are in registers by then, and the next stage's first fragments are read behind it, so that it costs nothing either.
+// Why four waves: with one wave a SIMD its 512 registers hold up to 64 accumulators of 16 x 16, so an LDS fragment is used for four
+// or six of them and the rows of a group are read again once for up to 16 blocks.
+// Why 16 x 16 x 32 and not 32 x 32 x 16: both run at the same rate (16.7 and 16.2 clocks a 16 x 16 x 32 of work), but over the whole
+// chip and on normally distributed values the clock is what the power allows, and that is more for the smaller one: 1.97 PFLOP/s
+// (2.14 GHz) against 1.79 (1.86 GHz) for endless instructions on registers.  (An earlier measurement had the smaller one at half the
+// rate: the compiler had put copies of accumulators between them, see gw_mma.)
+// What bounds it: matrix instructions are 65 to 80 % of a large shape's clocks, at a clock of 1.6 to 1.8 GHz that the power sets; the
+// rest is waiting for LDS reads and loads.  Small shapes wait for the weight stream.
+// Measured alone, sustained (us, 32 x 32 instructions with an epilogue through LDS / now; gate/up, W_down, W_o, LM head): 7B over 256 rows
+// 56 / 52, 39 / 39, 17 / 17, 69 / 65; over 512 rows 88 / 81 (1.14 PFLOP/s), 56 / 52, 28 / 28, 116 / 106 (1.27); 33B over 384 rows 166 / 152
+// (1.21), 108 / 102, 45 / 43, 145 / 132; 13B over 128 rows 61 / 59, 34 / 34, 20 / 20, 61 / 61.  QKV as the plain product of its shape: 37 / 36 (7B,
+// 256), 54 / 51 (512), 111 / 101 (33B), 40 / 40 (13B).
 // Tried: weights two stages ahead, activations 7.5 steps ahead (more registers, no gain); five pairs and more with a tile a
 // wave (LDS-bound).
-// A 32 x 32 instruction takes, per lane (half, r), 16 bytes of row r: the bytes [half * 16, half * 16 + 16) of
-// 32 bytes of k: piece (2h + half) of row r % 16 of block r / 16 of the pair, for half-step h.  The activations must be
-// tiled to match (a fragment gathered from
-// row-major rows is the slow many-half-lines load): k_tile_rows rewrites [M, Kd] as
-// xt[(q * m32_tiles + tile) * 1024 + lane * 16], q = index of 32 bytes of k, lane = half * 32 + row % 32, rows
-// past M as zeros (a few microseconds).
+// The activations must be tiled to match (a fragment gathered from row-major rows is the slow many-half-lines load): k_tile_rows
+// rewrites [M, Kd] in the order of xt_index, rows past M as zeros (a few microseconds).
 // =====================================================================================================
 constexpr int GW_W = 4;            // waves, one per SIMD
 constexpr int GW_ST = 4;           // steps (64 bytes of k) per weight stage
@@ -460,21 +464,60 @@ constexpr bool gw_built(int elem_bytes, int np, int tw) {
   return np >= 2 && (np <= 5 || (tw == 2 && (np == 6 || np == 8)));
 }
 constexpr int GW_MAX_NP = 8;
-constexpr size_t gw_ct_bytes(int np) { return (size_t)32 * (32 * np + 4) * 4; }   // a wave's output tile in the epilogue
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_tile_rows(const unsigned char *x, int M, int row_bytes, int m32_tiles, unsigned char *xt) {
-  const int qn = row_bytes / 32;
-  const size_t pieces = (size_t)qn * m32_tiles * 64;
+  const int m16_tiles = 2 * m32_tiles;
+  const size_t pieces = (size_t)(row_bytes / 64) * m16_tiles * 64;
   for (size_t p = (size_t)blockIdx.x * 256 + threadIdx.x; p < pieces; p += (size_t)gridDim.x * 256) {
-    const int lane = (int)(p & 63), half = lane >> 5, r32 = lane & 31;
+    const int lane = (int)(p & 63);
     const size_t frag = p >> 6;
-    const int mt = (int)(frag % m32_tiles), q = (int)(frag / m32_tiles);
-    const int m = mt * 32 + r32;
+    const int m = (int)(frag % m16_tiles) * 16 + (lane & 15), st = (int)(frag / m16_tiles);
     uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (m < M) v = ldg16(x + (size_t)m * row_bytes + (size_t)q * 32 + half * 16);
+    if (m < M) v = ldg16(x + (size_t)m * row_bytes + (size_t)st * 64 + (lane >> 4) * 16);
     stg16(xt + p * 16, v);
   }
+}
+
+// D += A B as mma16 has it, in place.  Written as asm because the compiler, left to itself, gives the 16 x 16 instruction another
+// register for its result than for its addend and copies accumulators around the loop (140 copies beside 192 matrix instructions).
+// The operands are those of ordinary loads, which the compiler waits for; nothing but these instructions touches an accumulator
+// between its first zero and the wait behind the loop.
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t gw_rsrc(const void *p, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00020000);
+}
+template <typename T> __device__ __forceinline__ void gw_mma(f32x4 &d, const u32x4 &w, const u32x4 &x) {
+  if constexpr (sizeof(T) == 2) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(w), "v"(x));
+  } else {
+    #pragma unroll
+    for (int j = 0; j < 4; ++j) asm volatile("v_mfma_f32_16x16x4_f32 %0, %1, %2, %0" : "+a"(d) : "v"(w[j]), "v"(x[j]));
+  }
+}
+
+// ---- epilogues of the wide kernel, straight from the accumulators (through a tile in LDS they took 9 to 19 thousand clocks of 80 to
+// 270).  A wave's tile of 32 rows is two accumulators of 16 x 16 a block: lane (g, r16) holds activation rows r16 and 16 + r16 against
+// weight rows g * 4 .. + 3.  Where a block pairs its rows (gate with up, a dimension with its RoPE partner, 8 rows further on: two
+// lane groups) the upper half of one accumulator changes places with the lower half of the other: then lane (hh, gl, r16) holds row
+// hh * 16 + r16 against weight rows gl * 4 .. + 3 in the first and 8 + gl * 4 .. + 3 in the second.
+__device__ __forceinline__ void gw_pair(f32x4 &a, f32x4 &b) {
+  #pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const auto s = __builtin_amdgcn_permlane32_swap(lane_bits(a[i]), lane_bits(b[i]), false, false);
+    a[i] = lane_value<float>(s[0]);
+    b[i] = lane_value<float>(s[1]);
+  }
+}
+// 4 adjacent outputs of block 0 in y0 and of block 1 in y1 (lane gl holds outputs gl * 4 .. + 3 of the 8 of its row): afterwards lane gl
+// holds the 8 outputs of block gl, 16 bytes of bf16.
+__device__ __forceinline__ uint4 gw_join(const float (&y0)[4], const float (&y1)[4]) {
+  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  union { bf16x4 v; unsigned u[2]; } a, b;
+  #pragma unroll
+  for (int i = 0; i < 4; ++i) { a.v[i] = (bf16_t)y0[i]; b.v[i] = (bf16_t)y1[i]; }
+  const auto p = __builtin_amdgcn_permlane16_swap(a.u[0], b.u[0], false, false), q = __builtin_amdgcn_permlane16_swap(a.u[1], b.u[1], false, false);
+  return make_uint4(p[0], q[0], p[1], q[1]);
 }
 
 template <typename T, int EPI, int NP, int TW>
@@ -483,7 +526,7 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
   extern __shared__ __align__(16) unsigned char gw_lds[];
   constexpr int NB = 2 * NP, STAGE = NB * GW_ST * 1024, XD = GW_ST;    // XD: steps in the ring of activations
   static_assert(GW_ST == GW_W, "a wave brings in one step of every block of a stage");
-  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, r32 = lane & 31;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, r16 = lane & 15;
   const int S = a.split_k;
   const int id = blockIdx.x, unit = (id / 8 / mgroups) * 8 + (id & 7), mgroup = (id / 8) % mgroups;
   if (unit >= tiles * S) return;                          // padding of the last group of 8 units (whole workgroup)
@@ -497,90 +540,109 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
   const int P = (n + GW_ST - 1) / GW_ST;                   // stages
   const int nblk = gemm_blocks(EPI, a.seg_rows);
 
-  f32x16 acc[NP][TW];
-  #pragma unroll
-  for (int p = 0; p < NP; ++p)
-    #pragma unroll
-    for (int t = 0; t < TW; ++t)
-      #pragma unroll
-      for (int i = 0; i < 16; ++i) acc[p][t][i] = 0.f;
-
+  // Loads go through buffer descriptors: per block (tile) a lane's offset that stays, and one scalar offset that moves along the reduction
+  // axis (added up in vector registers for every load, the addresses took as many issue slots as the matrix instructions).
   // Weights: this wave's step of every block of a stage, contiguous 1 KB pieces.  Lane l has piece l % 4 of row l / 4; in LDS a row's
   // pieces are permuted (piece g at g ^ (row / 4)), which leaves the fragment reads free of bank conflicts.  Blocks past the
   // end re-read the last one and are never stored, steps past the slice its last one and are never multiplied.
-  const unsigned char *wt = (const unsigned char *)a.wt + (size_t)tile * NB * total_steps * 1024 + lane * 16;
+  const int blocks_here = min(NB, nblk - tile * NB);
+  const auto w_rsrc = gw_rsrc((const unsigned char *)a.wt + (size_t)tile * NB * total_steps * 1024, (unsigned)blocks_here * total_steps * 1024u);
   const int wdst = wave * 1024 + (lane >> 2) * 64 + (((lane & 3) ^ (lane >> 4)) & 3) * 16;
-  uint4 wr[NB];
-  auto load_w = [&](int b, int p) {
-    const int st = s0 + min(p * GW_ST + wave, n - 1);
-    return ldg16_stream(wt + (unsigned)(min(b, nblk - 1 - tile * NB) * total_steps + st) * 1024u);
-  };
-  auto store_w = [&](int b, int slot, const uint4 &w) { *reinterpret_cast<uint4 *>(gw_lds + slot * STAGE + b * (GW_ST * 1024) + wdst) = w; };
+  constexpr bool WO = NP < 6;                               // a block's offset in a vector register of its own, or (where these are scarce) a scalar one
+  int wo[NB];
+  #pragma unroll
+  for (int b = 0; b < NB; ++b) wo[b] = min(b, blocks_here - 1) * total_steps * 1024 + (WO ? lane * 16 : 0);
+  u32x4 wr[NB];
+  auto w_at = [&](int p) { return (s0 + min(p * GW_ST + wave, n - 1)) * 1024; };
+  auto load_w = [&](int at, int b) { return WO ? __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, wo[b], at, 2) : __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, lane * 16, at + wo[b], 2); };   // non-temporal
+  auto store_w = [&](int b, int slot, const u32x4 &w) { *reinterpret_cast<u32x4 *>(gw_lds + slot * STAGE + b * (GW_ST * 1024) + wdst) = w; };
   // Activations: tiles past the end re-read the last one and are never stored, steps past the slice the last one
-  const unsigned char *xb = (const unsigned char *)a.xt + lane * 16;
-  uint4 xq[XD][2][TW];
-  auto load_x = [&](int i, int h, uint4 (&xf)[TW]) {
-    const size_t row = (size_t)(2 * (s0 + min(i, n - 1)) + h) * m32_tiles;
-    #pragma unroll
-    for (int t = 0; t < TW; ++t) xf[t] = ldg16(xb + (row + min(tile_of(t), m32_tiles - 1)) * 1024);
-  };
-  const int r16 = r32 & 15, woff = (r32 >> 4) * (GW_ST * 1024) + r16 * 64;
-  const int pc0 = ((half ^ (r16 >> 2)) & 3) * 16, pc1 = (((2 + half) ^ (r16 >> 2)) & 3) * 16;
-  uint4 wf[2][NP];
-  auto read_w = [&](int u, int j, uint4 (&w)[NP]) {        // the fragments of half-step j of the stage in slot u
-    const unsigned char *sb = gw_lds + u * STAGE + woff + ((j & 1) ? pc1 : pc0) + (j >> 1) * 1024;
-    #pragma unroll
-    for (int pr = 0; pr < NP; ++pr) w[pr] = *reinterpret_cast<const uint4 *>(sb + 2 * pr * GW_ST * 1024);
-  };
+  const auto x_rsrc = gw_rsrc((const unsigned char *)a.xt, (unsigned)total_steps * (unsigned)m32_tiles * 2048u);
+  int xo[TW];
+  #pragma unroll
+  for (int t = 0; t < TW; ++t) xo[t] = min(tile_of(t), m32_tiles - 1) * 2048 + lane * 16;
+  u32x4 xq[XD][TW][2];
+  auto x_at = [&](int i) { return (s0 + min(i, n - 1)) * m32_tiles * 2048; };
+  auto load_x = [&](int at, int t, int c) { return __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, xo[t] + c * 1024, at, 0); };   // the upper or lower 16 rows of tile t
+  const int woff = r16 * 64 + ((g ^ (r16 >> 2)) & 3) * 16;
+  u32x4 wf[2][NP];
+  // fragment b of half-step j of the stage in slot u: half of the blocks against one step
+  auto read_w = [&](int u, int j, int b) { return *reinterpret_cast<const u32x4 *>(gw_lds + woff + u * STAGE + ((j & 1) * NP + b) * (GW_ST * 1024) + (j >> 1) * 1024); };
 
   auto run = [&](auto tag) {                               // tag: tiles that this wave multiplies, TW or one less
     constexpr int NTL = decltype(tag)::value;
+    f32x4 acc[NB][NTL][2];                                    // [block][tile][upper or lower 16 of its rows]
     #pragma unroll
-    for (int b = 0; b < NB; ++b) wr[b] = load_w(b, 0);
-    #pragma unroll
-    for (int i = 0; i < XD; ++i) { load_x(i, 0, xq[i][0]); load_x(i, 1, xq[i][1]); }
-    #pragma unroll
-    for (int b = 0; b < NB; ++b) store_w(b, 0, wr[b]);
-    #pragma unroll
-    for (int b = 0; b < NB; ++b) wr[b] = load_w(b, 1);
+    for (int b = 0; b < NB; ++b)
+      #pragma unroll
+      for (int t = 0; t < NTL; ++t)
+        #pragma unroll
+        for (int c = 0; c < 2; ++c) { acc[b][t][c] = (f32x4){0.f, 0.f, 0.f, 0.f}; asm volatile("" : "+a"(acc[b][t][c])); }
+    {
+      const int w0 = w_at(0), w1 = w_at(1);
+      #pragma unroll
+      for (int b = 0; b < NB; ++b) wr[b] = load_w(w0, b);
+      #pragma unroll
+      for (int i = 0; i < XD - 1; ++i)
+        #pragma unroll
+        for (int t = 0; t < TW; ++t) { const int at = x_at(i); xq[i][t][0] = load_x(at, t, 0); xq[i][t][1] = load_x(at, t, 1); }
+      #pragma unroll
+      for (int b = 0; b < NB; ++b) store_w(b, 0, wr[b]);
+      #pragma unroll
+      for (int b = 0; b < NB; ++b) wr[b] = load_w(w1, b);
+    }
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    read_w(0, 0, wf[0]);
+    #pragma unroll
+    for (int b = 0; b < NP; ++b) wf[0][b] = read_w(0, 0, b);
     constexpr int HSN = 2 * GW_ST, W0 = 1, WN = 4, WB = (NB + WN - 1) / WN;      // half-steps of a stage; the WN from W0 on write the next one
     auto stage = [&](int p, auto utag, auto whole) {       // utag: slot p % 2; whole: all its steps are in the slice
-      constexpr int u = decltype(utag)::value;
+      constexpr int u = decltype(utag)::value, MN = NP * NTL * 2;
+      const int wp = w_at(p + 2);
+      int xp = 0;
       #pragma unroll
       for (int j = 0; j < HSN; ++j) {
         const int i = p * GW_ST + (j >> 1);
+        if (!decltype(whole)::value && (j & 1) == 0 && i >= n) return;        // (the same for every wave)
         if (j == HSN - 1) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the next stage is whole, this one read
-        if (j < HSN - 1) read_w(u, j + 1, wf[(j + 1) & 1]); else read_w(u ^ 1, 0, wf[0]);
-        // into the registers of the half-step before
-        constexpr int XH = 2 * XD;
-        const int xj = (p * HSN + j + XH - 1) >> 1, xr = ((u * HSN + j + XH - 1) % XH);
-        load_x(xj, xr & 1, xq[xr >> 1][xr & 1]);
-        #pragma unroll
-        for (int b = 0; b < NB; ++b)
-          if (j >= W0 && b / WB == j - W0) {
-            store_w(b, u ^ 1, wr[b]);
-            wr[b] = load_w(b, p + 2);
-          }
-        if (decltype(whole)::value || i < n) {
-          #pragma unroll
-          for (int pr = 0; pr < NP; ++pr)
-            #pragma unroll
-            for (int t = 0; t < NTL; ++t) acc[pr][t] = mma32<T>(wf[j & 1][pr], xq[(j >> 1) % XD][j & 1][t], acc[pr][t]);
-        }
+        if ((j & 1) == 0) xp = x_at(i + XD - 1);           // into the registers of the step before
+        // what else there is to do in this half-step, in order: the activations' loads, then every block's write and next load
+        const int nw = (j >= W0 && j - W0 < WN) ? min(WB, NB - (j - W0) * WB) : 0, ops = TW + 2 * max(nw, 0);
+        auto op = [&](int k) {
+          if (k < TW) { xq[((j >> 1) + XD - 1) % XD][k][j & 1] = load_x(xp, k, j & 1); return; }
+          const int b = (j - W0) * WB + (k - TW) / 2;
+          if ((k - TW) % 2 == 0) store_w(b, u ^ 1, wr[b]); else wr[b] = load_w(wp, b);
+        };
+        auto read = [&](int b) { wf[(j + 1) & 1][b] = j < HSN - 1 ? read_w(u, j + 1, b) : read_w(u ^ 1, 0, b); };
         if (decltype(whole)::value) {
+          // an LDS read ahead of every fragment's matrix instructions, the rest spread evenly between them
           #pragma unroll
-          for (int pr = 0; pr < NP; ++pr) {
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                 // an LDS read,
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                 // a matrix instruction,
-            __builtin_amdgcn_sched_group_barrier(0x220, 1, 0);                 // a load or an LDS write
-            if (NTL > 1) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x220, 1, 0);
-            if (NTL > 2) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          for (int b = 0; b < NP; ++b) {
+            read(b);
+            #pragma unroll
+            for (int t = 0; t < NTL; ++t)
+              #pragma unroll
+              for (int c = 0; c < 2; ++c) {
+                const int m = (b * NTL + t) * 2 + c;
+                gw_mma<T>(acc[(j & 1) * NP + b][t][c], wf[j & 1][b], xq[(j >> 1) % XD][t][c]);
+                #pragma unroll
+                for (int k = 0; k < TW + 2 * WB; ++k)
+                  if (k < ops && (k * MN) / ops == m) op(k);
+                __builtin_amdgcn_sched_barrier(0);
+              }
           }
+        } else {
+          #pragma unroll
+          for (int b = 0; b < NP; ++b) read(b);
+          #pragma unroll
+          for (int k = 0; k < TW + 2 * WB; ++k) if (k < ops) op(k);
+          #pragma unroll
+          for (int b = 0; b < NP; ++b)
+            #pragma unroll
+            for (int t = 0; t < NTL; ++t)
+              #pragma unroll
+              for (int c = 0; c < 2; ++c) gw_mma<T>(acc[(j & 1) * NP + b][t][c], wf[j & 1][b], xq[(j >> 1) % XD][t][c]);
+          __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_sched_barrier(0);
       }
     };
     int p = 0;
@@ -590,70 +652,205 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
     }
     if (p < P) stage(p, GemmTag<0>{}, GemmTag<0>{});
     if (p + 1 < P) stage(p + 1, GemmTag<1>{}, GemmTag<0>{});
+    // the last matrix instructions finish before anything else reads their accumulators (the compiler does not know what is in the asm)
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    #pragma unroll
+    for (int b = 0; b < NB; ++b)
+      #pragma unroll
+      for (int t = 0; t < NTL; ++t)
+        #pragma unroll
+        for (int c = 0; c < 2; ++c) asm volatile("" : "+a"(acc[b][t][c]));
+
+    const int gl = g & 1, b0 = tile * NB;                    // first row block of the workgroup
+    #pragma unroll
+    for (int t = 0; t < NTL; ++t) {
+      if (tile_of(t) >= g1) break;                           // (wave-uniform)
+      const int mt = tile_of(t) * 32;
+      if (EPI == EPI_ARGMAX) {
+        // Which columns of a ragged last tile exist is asked anew for every tile of rows: shared by them, the answers were 16 NP
+        // lane masks (up to 200 scalar registers spilled).
+        #pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          float bv = -__builtin_huge_valf(); int bi = 0x7fffffff;
+          // Columns in descending order: at equal values the lower one comes later
+          const int n0 = b0 * 16 + g * 4;
+          int live = a.seg_rows - n0;
+          asm volatile("" : "+v"(live));
+          #pragma unroll
+          for (int b = NB - 1; b >= 0; --b) {
+            #pragma unroll
+            for (int i = 3; i >= 0; --i) {
+              const float v = acc[b][t][c][i];
+              if (b * 16 + i < live && v >= bv) { bv = v; bi = n0 + b * 16 + i; }
+            }
+            if (b % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+          }
+          const auto ov = __builtin_amdgcn_permlane16_swap(lane_bits(bv), lane_bits(bv), false, false);
+          const auto oi = __builtin_amdgcn_permlane16_swap((unsigned)bi, (unsigned)bi, false, false);
+          bv = lane_value<float>(ov[0]); bi = (int)oi[0];
+          take_better(bv, bi, lane_value<float>(ov[1]), (int)oi[1]);
+          const auto pv = __builtin_amdgcn_permlane32_swap(lane_bits(bv), lane_bits(bv), false, false);
+          const auto pi = __builtin_amdgcn_permlane32_swap((unsigned)bi, (unsigned)bi, false, false);
+          bv = lane_value<float>(pv[0]); bi = (int)pi[0];
+          take_better(bv, bi, lane_value<float>(pv[1]), (int)pi[1]);
+          const int mg = mt + c * 16 + r16;
+          if (g == 0 && mg < a.M) {
+            a.amax_val[(size_t)tile * a.M + mg] = bv;
+            a.amax_idx[(size_t)tile * a.M + mg] = bi;
+          }
+        }
+      }
+      if (EPI == EPI_STORE || (EPI == EPI_ARGMAX && a.logits)) {
+        // [split_k][M][N] partial sums (one slab of them: the logits): 4 adjacent columns a lane, one by one in a ragged last tile
+        // and in a caller's logits that begin anywhere
+        const int N = a.seg_rows;
+        float *slab = EPI == EPI_STORE ? a.out + (size_t)split * a.M * N : a.logits;
+        const bool pieces = (N & 3) == 0 && ((uintptr_t)slab & 15) == 0;
+        #pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          const int m = mt + c * 16 + r16;
+          if (m >= a.M) continue;
+          float *dst = slab + (size_t)m * N + b0 * 16 + g * 4;
+          const int left = N - (b0 * 16 + g * 4);
+          #pragma unroll
+          for (int b = 0; b < NB; ++b) {
+            const f32x4 v = acc[b][t][c];
+            if (pieces && left - b * 16 >= 4) {
+              *reinterpret_cast<f32x4 *>(dst + b * 16) = v;
+            } else {
+              #pragma unroll
+              for (int i = 0; i < 4; ++i)
+                if (b * 16 + i < left) dst[b * 16 + i] = v[i];
+            }
+          }
+        }
+      }
+      if (EPI == EPI_SWIGLU) {
+        const int f = a.seg_rows, m = mt + (lane >> 5) * 16 + r16;
+        T *act = (T *)a.act;
+        #pragma unroll
+        for (int pr = 0; pr < NP; ++pr) {
+          float y[2][4];
+          #pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            f32x4 &gt_ = acc[2 * pr + e][t][0], &up = acc[2 * pr + e][t][1];
+            gw_pair(gt_, up);
+            #pragma unroll
+            for (int i = 0; i < 4; ++i) y[e][i] = silu_f(gt_[i]) * up[i];
+          }
+          if constexpr (sizeof(T) == 2) {
+            const uint4 v = gw_join(y[0], y[1]);
+            const int j0 = (b0 + 2 * pr + gl) * 8;
+            if (m >= a.M || j0 >= f) continue;
+            T *dst = act + (size_t)m * f + j0;
+            if (a.act_tiles) {                               // tiled for the wide GEMM that follows (f is a multiple of 16)
+              stg16(act + xt_index<T>(m, j0, a.act_tiles), v);
+            } else if (j0 + 8 <= f && (f & 3) == 0) {
+              *reinterpret_cast<uint2 *>(dst) = make_uint2(v.x, v.y);
+              *reinterpret_cast<uint2 *>(dst + 4) = make_uint2(v.z, v.w);
+            } else {
+              const unsigned w4[4] = {v.x, v.y, v.z, v.w};
+              #pragma unroll
+              for (int i = 0; i < 8; ++i)
+                if (j0 + i < f) reinterpret_cast<unsigned short *>(dst)[i] = (unsigned short)(w4[i / 2] >> (16 * (i & 1)));
+            }
+          } else {
+            #pragma unroll
+            for (int e = 0; e < 2; ++e) {
+              const int j0 = (b0 + 2 * pr + e) * 8 + gl * 4;
+              if (m >= a.M || j0 >= f) continue;
+              if (a.act_tiles) store4<T>(act + xt_index<T>(m, j0, a.act_tiles), y[e]);
+              else if (j0 + 4 <= f && (f & 3) == 0) store4<T>(act + (size_t)m * f + j0, y[e]);
+              else
+                for (int i = 0; i < 4 && j0 + i < f; ++i) act[(size_t)m * f + j0 + i] = Elem<T>::from_f32(y[e][i]);
+            }
+          }
+        }
+      }
+      if (EPI == EPI_QKV_ROPE) {
+        // d_h is a power of two (checked at launch): heads and dims come from shifts.  What a lane needs from global memory
+        // (32 bytes of the cos/sin table a block) is requested QB blocks ahead of the stores.
+        constexpr int QB = NB % 4 ? 2 : 4, PIECE = 64 / (int)sizeof(T);
+        const int d_h = a.d_h, d = a.n_heads * d_h, bps = d >> 4, bph = d_h >> 4, bsh = __ffs(bph) - 1, half = d_h >> 1;
+        const int m = mt + (lane >> 5) * 16 + r16;
+        const bool row_ok = m < a.M;
+        const int bb = row_ok ? m / a.T_nodes : 0, node = row_ok ? m - bb * a.T_nodes : 0, L = a.kv_len[bb];
+        const bool kv_ok = row_ok && L >= 0 && L + a.T_nodes <= a.max_kv;
+        if (row_ok && !kv_ok && node == 0) atomicOr(a.dev_status, 2u);
+        const size_t cache = (size_t)a.max_kv * d_h;
+        T *q_row = (T *)a.q_out + (size_t)(row_ok ? m : 0) * d, *kb = (T *)a.k_cache + (size_t)bb * a.n_heads * cache, *vb = (T *)a.v_cache + (size_t)bb * a.n_heads * cache;
+        const size_t v_at = v_tiled_index<T>(kv_ok ? L + node : 0, 0, d_h);
+        const float2 *cs_row = a.rope_cs + (size_t)(row_ok ? m : 0) * half + gl * 4;
+        auto seg_of = [&](int b) { return (b >= 2 * bps) ? 2 : (b >= bps) ? 1 : 0; };
+        float4 tab[2][QB][2];
+        auto load_tab = [&](int q, float4 (&tb)[QB][2]) {
+          #pragma unroll
+          for (int k = 0; k < QB; ++k) {
+            const int b = min(b0 + q * QB + k, nblk - 1), bl = b - seg_of(b) * bps;
+            const float4 *p = reinterpret_cast<const float4 *>(cs_row + (bl & (bph - 1)) * 8);
+            tb[k][0] = p[0]; tb[k][1] = p[1];
+          }
+        };
+        load_tab(0, tab[0]);
+        #pragma unroll
+        for (int q = 0; q < NB / QB; ++q) {
+          if (q + 1 < NB / QB) load_tab(q + 1, tab[(q + 1) & 1]);
+          #pragma unroll
+          for (int k = 0; k < QB; k += 2) {
+            const int lb = q * QB + k, b = b0 + lb;
+            if (b >= nblk) continue;
+            float y[2][2][4];                                // [block][dims, partners]
+            #pragma unroll
+            for (int e = 0; e < 2; ++e) {
+              f32x4 &lo = acc[lb + e][t][0], &hi = acc[lb + e][t][1];
+              gw_pair(lo, hi);
+              const float4 c0 = tab[q & 1][k + e][0], c1 = tab[q & 1][k + e][1];
+              const float cs[4] = {c0.x, c0.z, c1.x, c1.z}, sn[4] = {c0.y, c0.w, c1.y, c1.w};
+              const bool rot = seg_of(b + e) < 2;            // (uniform)
+              #pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                float y1, y2;
+                rope_pair(lo[i], hi[i], cs[i], sn[i], y1, y2);
+                y[e][0][i] = rot ? y1 : lo[i];
+                y[e][1][i] = rot ? y2 : hi[i];
+              }
+            }
+            // where 8 outputs from block bl's dim e0 on go (q and k): e0 and e0 + d_h / 2
+            auto dst_of = [&](int seg, int bl, int e0, T *&d1, T *&d2) {
+              const int head = bl >> bsh;
+              if (seg == 0) { d1 = q_row + head * d_h + e0; d2 = d1 + half; }
+              else { T *kc = kb + (size_t)head * cache; d1 = kc + k_tiled_index<T>(L + node, e0, d_h); d2 = kc + k_tiled_index<T>(L + node, e0 + half, d_h); }
+            };
+            const int s0_ = seg_of(b), s1_ = seg_of(b + 1);
+            if (sizeof(T) == 2 && s0_ == s1_ && s0_ < 2 && b + 1 < nblk) {
+              const uint4 v1 = gw_join(y[0][0], y[1][0]), v2 = gw_join(y[0][1], y[1][1]);
+              const int bl = b + gl - s0_ * bps;
+              T *d1, *d2;
+              dst_of(s0_, bl, (bl & (bph - 1)) * 8, d1, d2);
+              if (s0_ == 0 ? row_ok : kv_ok) { stg16(d1, v1); stg16(d2, v2); }
+              continue;
+            }
+            #pragma unroll
+            for (int e = 0; e < 2; ++e) {
+              const int seg = e ? s1_ : s0_, bl = b + e - seg * bps;
+              if (b + e >= nblk) continue;
+              if (seg == 2) {
+                if (!kv_ok) continue;
+                T *dst = vb + (size_t)(bl >> bsh) * cache + v_at + ((bl & (bph - 1)) * 16 + gl * 4) * PIECE;
+                #pragma unroll
+                for (int i = 0; i < 4; ++i) { dst[i * PIECE] = Elem<T>::from_f32(y[e][0][i]); dst[(8 + i) * PIECE] = Elem<T>::from_f32(y[e][1][i]); }
+              } else {
+                T *d1, *d2;
+                dst_of(seg, bl, (bl & (bph - 1)) * 8 + gl * 4, d1, d2);
+                if (seg == 0 ? row_ok : kv_ok) { store4<T>(d1, y[e][0]); store4<T>(d2, y[e][1]); }
+              }
+            }
+          }
+        }
+      }
+    }
   };
   if (TW > 1 && tile_of(TW - 1) >= g1) run(GemmTag<(TW > 1 ? TW - 1 : 1)>{}); else run(GemmTag<TW>{});
-
-  // ---- epilogues.  Lane (half, r32) holds activation row t * 32 + r32 and weight rows (i / 4) * 8 + half * 4 + (i % 4) of each pair.
-  // The row argmax needs nothing but these registers (through LDS, four lanes to a row, it took 16 us of 135 over 512 rows of
-  // 32000 x 4096); everything else goes through the wave's own Ct region in LDS (the ring is free by now), one tile of 32 rows at
-  // a time, the 64 lanes playing the workgroup of the shared epilogue code.
-  const int CT_PITCH = 16 * NB + 4;
-  __syncthreads();                                         // every wave has left the ring
-  float *Ct = reinterpret_cast<float *>(gw_lds) + (size_t)wave * 32 * CT_PITCH;
-  #pragma unroll
-  for (int t = 0; t < TW; ++t) {
-    if (tile_of(t) >= g1) break;                           // (wave-uniform)
-    if (EPI == EPI_ARGMAX) {
-      float bv = -__builtin_huge_valf(); int bi = 0x7fffffff;
-      // Columns in descending order: at equal values the lower one comes later.  Which columns of a ragged last tile exist is asked
-      // anew for every tile of rows: shared by them, the answers were 16 NP lane masks (up to 200 scalar registers spilled, and
-      // with eight pairs 33 vector registers; us, so / now: 32000 x 4096 over 512 rows 124 / 113, 32000 x 5120 148 / 136).
-      const int n0 = tile * 16 * NB + half * 4;
-      int live = a.seg_rows - n0;
-      asm volatile("" : "+v"(live));
-      #pragma unroll
-      for (int pr = NP - 1; pr >= 0; --pr) {
-        #pragma unroll
-        for (int i = 15; i >= 0; --i) {
-          const int nn = pr * 32 + (i >> 2) * 8 + (i & 3);
-          const float v = acc[pr][t][i];
-          if (nn < live && v >= bv) { bv = v; bi = n0 + nn; }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      const auto ov = __builtin_amdgcn_permlane32_swap(lane_bits(bv), lane_bits(bv), false, false);
-      const auto oi = __builtin_amdgcn_permlane32_swap((unsigned)bi, (unsigned)bi, false, false);
-      const int mg = tile_of(t) * 32 + r32;
-      take_better(bv, bi, lane_value<float>(ov[1]), (int)oi[1]);   // (lanes of the lower half: the upper half's best)
-      if (half == 0 && mg < a.M) {
-        a.amax_val[(size_t)tile * a.M + mg] = bv;
-        a.amax_idx[(size_t)tile * a.M + mg] = bi;
-      }
-      if (!a.logits) continue;
-    }
-    if (t > 0) {                                           // the lanes are done reading the tile before
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-    #pragma unroll
-    for (int pr = 0; pr < NP; ++pr)
-      #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const f32x4 v = {acc[pr][t][4 * q4], acc[pr][t][4 * q4 + 1], acc[pr][t][4 * q4 + 2], acc[pr][t][4 * q4 + 3]};
-        *reinterpret_cast<f32x4 *>(Ct + r32 * CT_PITCH + pr * 32 + q4 * 8 + half * 4) = v;
-      }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the wave's LDS writes before its lanes read each other's
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (EPI == EPI_ARGMAX) {
-      GemmArgs al = a;
-      al.out = a.logits;
-      gemm_epilogue<T, EPI_STORE, 32>(al, Ct, CT_PITCH, tile, NB, tile_of(t) * 32, 0, nblk, lane, WAVE);
-    } else {
-      gemm_epilogue<T, EPI, 32>(a, Ct, CT_PITCH, tile, NB, tile_of(t) * 32, split, nblk, lane, WAVE);
-    }
-  }
 }
 
 // Row-major -> tiled (see the layout above).  One thread per 16-byte piece of the tiled buffer.
@@ -855,8 +1052,7 @@ size_t gemm_xt_bytes(int M, int Kd, int elem_bytes) { return (size_t)((M + 31) /
 
 template <typename T, int EPI, int NP, int TW>
 static hipError_t launch_wide_np(hipStream_t st, const GemmArgs &a, const GemmPlan &pl, int m32_tiles, dim3 grid, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  // two stages of weights, or (afterwards, in the same memory) the float32 output tiles (32 rows) of the waves
-  constexpr size_t ring = (size_t)2 * 2 * NP * GW_ST * 1024, ct = GW_W * gw_ct_bytes(NP), smem = ring > ct ? ring : ct;
+  constexpr size_t smem = (size_t)2 * 2 * NP * GW_ST * 1024;            // two stages of weights
   static_assert(smem <= 160 * 1024, "LDS of one workgroup");
   const dim3 block(64 * GW_W);
   static bool attr_set = false;                           // once per instantiation and process
@@ -877,7 +1073,7 @@ static hipError_t launch_wide(hipStream_t st, const GemmArgs &a, const GemmPlan 
   if (!a.wt || !a.xt || pl.gt < 1 || pl.tw != (pl.gt + GW_W - 1) / GW_W) return hipErrorInvalidValue;
   const int m32_tiles = (a.M + 31) / 32, row_bytes = a.Kd * (int)sizeof(T);
   if ((long long)pl.mgroups * pl.gt < m32_tiles) return hipErrorInvalidValue;   // groups cover every row
-  const size_t pieces = (size_t)(row_bytes / 32) * m32_tiles * 64;
+  const size_t pieces = (size_t)(row_bytes / 64) * m32_tiles * 128;
   GemmArgs aw = a;
   if (a.x_tiled) aw.xt = const_cast<void *>(a.x);         // the producer of x wrote it tiled
   else hipLaunchKernelGGL((k_tile_rows<T>), dim3((unsigned)std::min<size_t>((pieces + 255) / 256, 4096)), dim3(256), 0, st,
