@@ -429,7 +429,9 @@ __global__ __launch_bounds__(64 * (GM_MAX_NB + GM_NLW)) void k_gemm_skinny(const
 // Wide GEMM: more than 64 activation rows (batches of trees, wide trees; gemm_is_wide).  The skinny kernel above re-reads the
 // weights from L2 once per block of 64 rows, and every math wave re-reads the whole activation chunk from LDS: with several
 // blocks of rows L2 and LDS, not HBM, set the pace.  Here a workgroup of four waves, one for each SIMD, owns a group of gt <= 12 tiles
-// of 32 activation rows against NB = 2 NP weight row blocks; wave w owns tiles w, w + 4, w + 8 of the group against all blocks.
+// of 32 activation rows against NB = 2 NP weight row blocks; a wave owns up to six sixteens of the rows, dealt one by one, against all
+// blocks (dealt as tiles of 32, two of four waves had half the work where a group has five, six, nine or ten: the target pass over
+// 384 rows at 33B widths, QKV, W_o and W_down in groups of six, 678 -> 660 us).
 //   * The weights are the shared operand: of every block of a stage (4 steps of 64 bytes of k) a wave brings in one step, through
 //     registers (requested a stage ahead) into one of two LDS slots.
 //   * The activations go from global memory (L2 hits) straight into the registers of the one wave that needs them, 3 steps ahead.
@@ -531,8 +533,9 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
   const int id = blockIdx.x, unit = (id / 8 / mgroups) * 8 + (id & 7), mgroup = (id / 8) % mgroups;
   if (unit >= tiles * S) return;                          // padding of the last group of 8 units (whole workgroup)
   const int tile = unit / S, split = unit % S;
-  const int g0 = mgroup * gt, g1 = min(g0 + gt, m32_tiles);
-  auto tile_of = [&](int t) { return g0 + wave + t * GW_W; };
+  // the group's rows in sixteens, dealt to the waves one by one
+  const int sub0 = mgroup * gt * 2, sub1 = min(sub0 + gt * 2, (a.M + 15) >> 4);
+  auto sub_of = [&](int i) { return sub0 + wave + i * GW_W; };
   const int total_steps = a.Kd * (int)sizeof(T) / 64;
   const int ssh = __ffs(S) - 1;                           // S is 1, 2, 4 or 8
   const int s0 = (total_steps * split) >> ssh, s1 = (total_steps * (split + 1)) >> ssh;
@@ -556,36 +559,36 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
   auto w_at = [&](int p) { return (s0 + min(p * GW_ST + wave, n - 1)) * 1024; };
   auto load_w = [&](int at, int b) { return WO ? __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, wo[b], at, 2) : __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, lane * 16, at + wo[b], 2); };   // non-temporal
   auto store_w = [&](int b, int slot, const u32x4 &w) { *reinterpret_cast<u32x4 *>(gw_lds + slot * STAGE + b * (GW_ST * 1024) + wdst) = w; };
-  // Activations: tiles past the end re-read the last one and are never stored, steps past the slice the last one
+  // Activations: sixteens past the end re-read the last one and are never stored, steps past the slice the last one
   const auto x_rsrc = gw_rsrc((const unsigned char *)a.xt, (unsigned)total_steps * (unsigned)m32_tiles * 2048u);
-  int xo[TW];
-  #pragma unroll
-  for (int t = 0; t < TW; ++t) xo[t] = min(tile_of(t), m32_tiles - 1) * 2048 + lane * 16;
-  u32x4 xq[XD][TW][2];
   auto x_at = [&](int i) { return (s0 + min(i, n - 1)) * m32_tiles * 2048; };
-  auto load_x = [&](int at, int t, int c) { return __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, xo[t] + c * 1024, at, 0); };   // the upper or lower 16 rows of tile t
   const int woff = r16 * 64 + ((g ^ (r16 >> 2)) & 3) * 16;
   u32x4 wf[2][NP];
   // fragment b of half-step j of the stage in slot u: half of the blocks against one step
   auto read_w = [&](int u, int j, int b) { return *reinterpret_cast<const u32x4 *>(gw_lds + woff + u * STAGE + ((j & 1) * NP + b) * (GW_ST * 1024) + (j >> 1) * 1024); };
 
-  auto run = [&](auto tag) {                               // tag: tiles that this wave multiplies, TW or one less
-    constexpr int NTL = decltype(tag)::value;
-    f32x4 acc[NB][NTL][2];                                    // [block][tile][upper or lower 16 of its rows]
+  auto run = [&](auto tag) {                               // tag: sixteens of rows that this wave multiplies
+    constexpr int NS = decltype(tag)::value;
+    int xo[NS];
+    #pragma unroll
+    for (int i = 0; i < NS; ++i) xo[i] = min(sub_of(i), 2 * m32_tiles - 1) * 1024 + lane * 16;
+    u32x4 xq[XD][NS];
+    auto load_x = [&](int at, int i) { return __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, xo[i], at, 0); };
+    f32x4 acc[NB][NS];
     #pragma unroll
     for (int b = 0; b < NB; ++b)
       #pragma unroll
-      for (int t = 0; t < NTL; ++t)
-        #pragma unroll
-        for (int c = 0; c < 2; ++c) { acc[b][t][c] = (f32x4){0.f, 0.f, 0.f, 0.f}; asm volatile("" : "+a"(acc[b][t][c])); }
+      for (int i = 0; i < NS; ++i) { acc[b][i] = (f32x4){0.f, 0.f, 0.f, 0.f}; asm volatile("" : "+a"(acc[b][i])); }
     {
       const int w0 = w_at(0), w1 = w_at(1);
       #pragma unroll
       for (int b = 0; b < NB; ++b) wr[b] = load_w(w0, b);
       #pragma unroll
-      for (int i = 0; i < XD - 1; ++i)
+      for (int i = 0; i < XD - 1; ++i) {
+        const int at = x_at(i);
         #pragma unroll
-        for (int t = 0; t < TW; ++t) { const int at = x_at(i); xq[i][t][0] = load_x(at, t, 0); xq[i][t][1] = load_x(at, t, 1); }
+        for (int t = 0; t < NS; ++t) xq[i][t] = load_x(at, t);
+      }
       #pragma unroll
       for (int b = 0; b < NB; ++b) store_w(b, 0, wr[b]);
       #pragma unroll
@@ -595,55 +598,58 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
     #pragma unroll
     for (int b = 0; b < NP; ++b) wf[0][b] = read_w(0, 0, b);
     constexpr int HSN = 2 * GW_ST, W0 = 1, WN = 4, WB = (NB + WN - 1) / WN;      // half-steps of a stage; the WN from W0 on write the next one
-    auto stage = [&](int p, auto utag, auto whole) {       // utag: slot p % 2; whole: all its steps are in the slice
-      constexpr int u = decltype(utag)::value, MN = NP * NTL * 2;
-      const int wp = w_at(p + 2);
-      int xp = 0;
-      #pragma unroll
-      for (int j = 0; j < HSN; ++j) {
-        const int i = p * GW_ST + (j >> 1);
-        if (!decltype(whole)::value && (j & 1) == 0 && i >= n) return;        // (the same for every wave)
-        if (j == HSN - 1) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the next stage is whole, this one read
-        if ((j & 1) == 0) xp = x_at(i + XD - 1);           // into the registers of the step before
-        // what else there is to do in this half-step, in order: the activations' loads, then every block's write and next load
-        const int nw = (j >= W0 && j - W0 < WN) ? min(WB, NB - (j - W0) * WB) : 0, ops = TW + 2 * max(nw, 0);
-        auto op = [&](int k) {
-          if (k < TW) { xq[((j >> 1) + XD - 1) % XD][k][j & 1] = load_x(xp, k, j & 1); return; }
-          const int b = (j - W0) * WB + (k - TW) / 2;
-          if ((k - TW) % 2 == 0) store_w(b, u ^ 1, wr[b]); else wr[b] = load_w(wp, b);
-        };
-        auto read = [&](int b) { wf[(j + 1) & 1][b] = j < HSN - 1 ? read_w(u, j + 1, b) : read_w(u ^ 1, 0, b); };
-        if (decltype(whole)::value) {
-          // an LDS read ahead of every fragment's matrix instructions, the rest spread evenly between them
+    int xp = 0;                                            // the activations' offset in this step's loads
+    // jtag: half-step of stage p; utag: the stage's slot p % 2; whole: all the stage's steps are in the slice.  False: the slice has ended.
+    auto half_step = [&](int p, int wp, auto jtag, auto utag, auto whole) {
+      constexpr int j = decltype(jtag)::value, u = decltype(utag)::value, MN = NP * NS;
+      const int i = p * GW_ST + (j >> 1);
+      if (!decltype(whole)::value && (j & 1) == 0 && i >= n) return false;  // (the same for every wave)
+      if (j == HSN - 1) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the next stage is whole, this one read
+      if ((j & 1) == 0) xp = x_at(i + XD - 1);           // into the registers of the step before
+      // what else there is to do in this half-step, in order: the activations' loads, then every block's write and next load
+      constexpr int nw = (j >= W0 && j - W0 < WN) ? (NB - (j - W0) * WB < WB ? NB - (j - W0) * WB : WB) : 0;
+      constexpr int nx = (NS + 1 - (j & 1)) / 2, ops = nx + 2 * (nw > 0 ? nw : 0);
+      auto op = [&](int k) {
+        if (k < nx) { xq[((j >> 1) + XD - 1) % XD][2 * k + (j & 1)] = load_x(xp, 2 * k + (j & 1)); return; }
+        const int b = (j - W0) * WB + (k - nx) / 2;
+        if ((k - nx) % 2 == 0) store_w(b, u ^ 1, wr[b]); else wr[b] = load_w(wp, b);
+      };
+      auto read = [&](int b) { wf[(j + 1) & 1][b] = j < HSN - 1 ? read_w(u, j + 1, b) : read_w(u ^ 1, 0, b); };
+      if (decltype(whole)::value) {
+        // an LDS read ahead of every fragment's matrix instructions, the rest spread evenly between them
+        #pragma unroll
+        for (int b = 0; b < NP; ++b) {
+          read(b);
           #pragma unroll
-          for (int b = 0; b < NP; ++b) {
-            read(b);
-            #pragma unroll
-            for (int t = 0; t < NTL; ++t)
-              #pragma unroll
-              for (int c = 0; c < 2; ++c) {
-                const int m = (b * NTL + t) * 2 + c;
-                gw_mma<T>(acc[(j & 1) * NP + b][t][c], wf[j & 1][b], xq[(j >> 1) % XD][t][c]);
-                #pragma unroll
-                for (int k = 0; k < TW + 2 * WB; ++k)
-                  if (k < ops && (k * MN) / ops == m) op(k);
-                __builtin_amdgcn_sched_barrier(0);
-              }
+          for (int t = 0; t < NS; ++t) {
+            gw_mma<T>(acc[(j & 1) * NP + b][t], wf[j & 1][b], xq[(j >> 1) % XD][t]);
+            const int m = b * NS + t, k = (m * ops + MN - 1) / MN;           // (at most three of them fall behind one instruction)
+            if (k * MN < (m + 1) * ops) op(k);
+            if ((k + 1) * MN < (m + 1) * ops) op(k + 1);
+            if ((k + 2) * MN < (m + 1) * ops) op(k + 2);
+            __builtin_amdgcn_sched_barrier(0);
           }
-        } else {
-          #pragma unroll
-          for (int b = 0; b < NP; ++b) read(b);
-          #pragma unroll
-          for (int k = 0; k < TW + 2 * WB; ++k) if (k < ops) op(k);
-          #pragma unroll
-          for (int b = 0; b < NP; ++b)
-            #pragma unroll
-            for (int t = 0; t < NTL; ++t)
-              #pragma unroll
-              for (int c = 0; c < 2; ++c) gw_mma<T>(acc[(j & 1) * NP + b][t][c], wf[j & 1][b], xq[(j >> 1) % XD][t][c]);
-          __builtin_amdgcn_sched_barrier(0);
         }
+      } else {
+        #pragma unroll
+        for (int b = 0; b < NP; ++b) read(b);
+        #pragma unroll
+        for (int k = 0; k < ops; ++k) op(k);
+        #pragma unroll
+        for (int b = 0; b < NP; ++b)
+          #pragma unroll
+          for (int t = 0; t < NS; ++t) gw_mma<T>(acc[(j & 1) * NP + b][t], wf[j & 1][b], xq[(j >> 1) % XD][t]);
+        __builtin_amdgcn_sched_barrier(0);
       }
+      return true;
+    };
+    auto stage = [&](int p, auto utag, auto whole) {
+      const int wp = w_at(p + 2);
+      static_assert(HSN == 8, "the half-steps below");
+      (void)(half_step(p, wp, GemmTag<0>{}, utag, whole) && half_step(p, wp, GemmTag<1>{}, utag, whole) &&
+             half_step(p, wp, GemmTag<2>{}, utag, whole) && half_step(p, wp, GemmTag<3>{}, utag, whole) &&
+             half_step(p, wp, GemmTag<4>{}, utag, whole) && half_step(p, wp, GemmTag<5>{}, utag, whole) &&
+             half_step(p, wp, GemmTag<6>{}, utag, whole) && half_step(p, wp, GemmTag<7>{}, utag, whole));
     };
     int p = 0;
     for (; (p + 2) * GW_ST <= n; p += 2) {
@@ -657,20 +663,21 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
     #pragma unroll
     for (int b = 0; b < NB; ++b)
       #pragma unroll
-      for (int t = 0; t < NTL; ++t)
-        #pragma unroll
-        for (int c = 0; c < 2; ++c) asm volatile("" : "+a"(acc[b][t][c]));
+      for (int i = 0; i < NS; ++i) asm volatile("" : "+a"(acc[b][i]));
 
-    const int gl = g & 1, b0 = tile * NB;                    // first row block of the workgroup
+    const int gl = g & 1, hh = lane >> 5, b0 = tile * NB;    // b0: first row block of the workgroup
     #pragma unroll
-    for (int t = 0; t < NTL; ++t) {
-      if (tile_of(t) >= g1) break;                           // (wave-uniform)
-      const int mt = tile_of(t) * 32;
+    for (int t = 0; t < NS; t += 2) {
+      if (sub_of(t) >= sub1) break;                          // (wave-uniform)
+      // row of this lane where the two sixteens are paired (an odd last one with itself)
+      const int m = sub_of(min(t + hh, NS - 1)) * 16 + r16;
+      const bool row_ok = t + hh < NS && sub_of(t + hh) < sub1 && m < a.M;
+      auto pair_of = [&](int b, f32x4 &lo, f32x4 &hi) { lo = acc[b][t]; hi = acc[b][min(t + 1, NS - 1)]; gw_pair(lo, hi); };
       if (EPI == EPI_ARGMAX) {
         // Which columns of a ragged last tile exist is asked anew for every tile of rows: shared by them, the answers were 16 NP
         // lane masks (up to 200 scalar registers spilled).
         #pragma unroll
-        for (int c = 0; c < 2; ++c) {
+        for (int c = 0; c < 2 && t + c < NS; ++c) {
           float bv = -__builtin_huge_valf(); int bi = 0x7fffffff;
           // Columns in descending order: at equal values the lower one comes later
           const int n0 = b0 * 16 + g * 4;
@@ -680,7 +687,7 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
           for (int b = NB - 1; b >= 0; --b) {
             #pragma unroll
             for (int i = 3; i >= 0; --i) {
-              const float v = acc[b][t][c][i];
+              const float v = acc[b][t + c][i];
               if (b * 16 + i < live && v >= bv) { bv = v; bi = n0 + b * 16 + i; }
             }
             if (b % 2 == 0) __builtin_amdgcn_sched_barrier(0);
@@ -693,8 +700,8 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
           const auto pi = __builtin_amdgcn_permlane32_swap((unsigned)bi, (unsigned)bi, false, false);
           bv = lane_value<float>(pv[0]); bi = (int)pi[0];
           take_better(bv, bi, lane_value<float>(pv[1]), (int)pi[1]);
-          const int mg = mt + c * 16 + r16;
-          if (g == 0 && mg < a.M) {
+          const int mg = sub_of(t + c) * 16 + r16;
+          if (g == 0 && sub_of(t + c) < sub1 && mg < a.M) {
             a.amax_val[(size_t)tile * a.M + mg] = bv;
             a.amax_idx[(size_t)tile * a.M + mg] = bi;
           }
@@ -707,14 +714,14 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
         float *slab = EPI == EPI_STORE ? a.out + (size_t)split * a.M * N : a.logits;
         const bool pieces = (N & 3) == 0 && ((uintptr_t)slab & 15) == 0;
         #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const int m = mt + c * 16 + r16;
-          if (m >= a.M) continue;
-          float *dst = slab + (size_t)m * N + b0 * 16 + g * 4;
+        for (int c = 0; c < 2 && t + c < NS; ++c) {
+          const int mg = sub_of(t + c) * 16 + r16;
+          if (sub_of(t + c) >= sub1 || mg >= a.M) continue;
+          float *dst = slab + (size_t)mg * N + b0 * 16 + g * 4;
           const int left = N - (b0 * 16 + g * 4);
           #pragma unroll
           for (int b = 0; b < NB; ++b) {
-            const f32x4 v = acc[b][t][c];
+            const f32x4 v = acc[b][t + c];
             if (pieces && left - b * 16 >= 4) {
               *reinterpret_cast<f32x4 *>(dst + b * 16) = v;
             } else {
@@ -726,22 +733,22 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
         }
       }
       if (EPI == EPI_SWIGLU) {
-        const int f = a.seg_rows, m = mt + (lane >> 5) * 16 + r16;
+        const int f = a.seg_rows;
         T *act = (T *)a.act;
         #pragma unroll
         for (int pr = 0; pr < NP; ++pr) {
           float y[2][4];
           #pragma unroll
           for (int e = 0; e < 2; ++e) {
-            f32x4 &gt_ = acc[2 * pr + e][t][0], &up = acc[2 * pr + e][t][1];
-            gw_pair(gt_, up);
+            f32x4 gate, up;
+            pair_of(2 * pr + e, gate, up);
             #pragma unroll
-            for (int i = 0; i < 4; ++i) y[e][i] = silu_f(gt_[i]) * up[i];
+            for (int i = 0; i < 4; ++i) y[e][i] = silu_f(gate[i]) * up[i];
           }
           if constexpr (sizeof(T) == 2) {
             const uint4 v = gw_join(y[0], y[1]);
             const int j0 = (b0 + 2 * pr + gl) * 8;
-            if (m >= a.M || j0 >= f) continue;
+            if (!row_ok || j0 >= f) continue;
             T *dst = act + (size_t)m * f + j0;
             if (a.act_tiles) {                               // tiled for the wide GEMM that follows (f is a multiple of 16)
               stg16(act + xt_index<T>(m, j0, a.act_tiles), v);
@@ -758,7 +765,7 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
             #pragma unroll
             for (int e = 0; e < 2; ++e) {
               const int j0 = (b0 + 2 * pr + e) * 8 + gl * 4;
-              if (m >= a.M || j0 >= f) continue;
+              if (!row_ok || j0 >= f) continue;
               if (a.act_tiles) store4<T>(act + xt_index<T>(m, j0, a.act_tiles), y[e]);
               else if (j0 + 4 <= f && (f & 3) == 0) store4<T>(act + (size_t)m * f + j0, y[e]);
               else
@@ -772,8 +779,6 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
         // (32 bytes of the cos/sin table a block) is requested QB blocks ahead of the stores.
         constexpr int QB = NB % 4 ? 2 : 4, PIECE = 64 / (int)sizeof(T);
         const int d_h = a.d_h, d = a.n_heads * d_h, bps = d >> 4, bph = d_h >> 4, bsh = __ffs(bph) - 1, half = d_h >> 1;
-        const int m = mt + (lane >> 5) * 16 + r16;
-        const bool row_ok = m < a.M;
         const int bb = row_ok ? m / a.T_nodes : 0, node = row_ok ? m - bb * a.T_nodes : 0, L = a.kv_len[bb];
         const bool kv_ok = row_ok && L >= 0 && L + a.T_nodes <= a.max_kv;
         if (row_ok && !kv_ok && node == 0) atomicOr(a.dev_status, 2u);
@@ -802,8 +807,8 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
             float y[2][2][4];                                // [block][dims, partners]
             #pragma unroll
             for (int e = 0; e < 2; ++e) {
-              f32x4 &lo = acc[lb + e][t][0], &hi = acc[lb + e][t][1];
-              gw_pair(lo, hi);
+              f32x4 lo, hi;
+              pair_of(lb + e, lo, hi);
               const float4 c0 = tab[q & 1][k + e][0], c1 = tab[q & 1][k + e][1];
               const float cs[4] = {c0.x, c0.z, c1.x, c1.z}, sn[4] = {c0.y, c0.w, c1.y, c1.w};
               const bool rot = seg_of(b + e) < 2;            // (uniform)
@@ -850,7 +855,10 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
       }
     }
   };
-  if (TW > 1 && tile_of(TW - 1) >= g1) run(GemmTag<(TW > 1 ? TW - 1 : 1)>{}); else run(GemmTag<TW>{});
+  const int mine = (sub1 - sub0 - wave + GW_W - 1) / GW_W;   // (what a wave multiplies beyond its own is never stored)
+  if (mine >= 2 * TW) run(GemmTag<2 * TW>{});
+  else if (TW == 1 || mine == 2 * TW - 1) run(GemmTag<2 * TW - 1>{});
+  else run(GemmTag<(TW > 1 ? 2 * TW - 2 : 1)>{});
 }
 
 // Row-major -> tiled (see the layout above).  One thread per 16-byte piece of the tiled buffer.
