@@ -1003,20 +1003,29 @@ static GemmPlan plan_wide(int epi, int seg_rows, int Kd, int elem_bytes, int M, 
 }
 
 // Slabs that the reduction axis of a matrix is cut into.  The one choice of a plan that the result depends on: inside a
-// slab both kernels add the same products in the same order (bf16; the float32 fragments are dealt out differently), so
-// their bits are the same.  Therefore it is a rule on the shape alone.  Up to 128 rows it is the skinny kernel's, for
-// whichever kernel runs and however the weights are stored: tiled and row-major weights give the same bits there.  Beyond
-// (tiled weights) the rule is one that was made for an earlier form of the wide kernel (groups of up to 8, 12 or 16 tiles, at
-// most six blocks a workgroup, up to three waves a SIMD): it weighs, in units of a weight fragment, a workgroup's steps times its
-// fragments per step and the tiles of its busiest SIMD against the slabs' way out and back.  It is kept because another count
-// changes every result, not because it suits the present kernel: finer slabs measured faster with the form before this one (us:
-// W_down at 384 rows, 33B, four slabs 110, two 122, the fold 16 against 14; 512 rows, 7B, 52 and 62, the folds 13 and 12).
+// slab both kernels add the same products in the same order, so their bits are the same.  Therefore it is a rule on the shape
+// alone.  Up to 128 rows it is the skinny kernel's, for whichever kernel runs and however the weights are stored: tiled and
+// row-major weights give the same bits there.  Beyond (tiled weights), bf16 matrices of 16 Mi elements and more: the count of 1, 2 or 4
+// whose plan is priced lowest with 0.9 us a further slab of a million outputs (its way out of the kernel and into the next one).
+// Measured over W_o and W_down at 7B, 13B and 33B widths and 144 to 768 rows, with 1, 2, 4 and 8 slabs each: the picks take 11 us
+// more than the best of each, the rule before them 354 (of about 2500; us, before / now: W_down 7B over 512 rows 52 / 44, 33B over 384
+// 99 / 84, 13B over 768 111 / 86; W_o 7B over 512 28 / 23).  Eight were best at three of the 48 shapes, by 2 us at most.
+// Smaller matrices keep the rule made for an earlier form of the kernel (groups of up to 8, 12 or 16 tiles, at most
+// six blocks a workgroup): it weighs, in units of a weight fragment, a workgroup's steps times its fragments per step and the tiles of its
+// busiest SIMD against the slabs' way out and back.  Their launches are mostly prologue and epilogue, which neither price describes.
 static int gemm_split(int epi, int seg_rows, int Kd, int elem_bytes, int M, bool tiled) {
   if (epi != EPI_STORE) return 1;                           // fused epilogues need complete sums
   if (!tiled || M <= 2 * GM_BM) return plan_skinny(epi, seg_rows, Kd, elem_bytes, M, 0).split;
   const int blocks = gemm_blocks(epi, seg_rows), steps = Kd * elem_bytes / 64, mt = (M + 31) / 32;
   double best_cost = 1e300;
   int best = 1;
+  if (elem_bytes == 2 && (long long)seg_rows * Kd >= (1 << 24)) {
+    for (int s = 1; s <= 4 && (s == 1 || steps / s >= 16); s *= 2) {
+      const double cost = plan_wide(epi, seg_rows, Kd, elem_bytes, M, s).cost + 0.9e-6 * M * seg_rows * (s - 1);
+      if (cost < best_cost) { best_cost = cost; best = s; }
+    }
+    return best;
+  }
   for (int most = 8; most <= 16; most += 4) {
     const int mg = (mt + most - 1) / most, gt = (mt + mg - 1) / mg;
     if (most > 8 && gt <= 8) continue;
