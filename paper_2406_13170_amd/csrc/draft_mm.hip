@@ -85,6 +85,8 @@ template <int NB, int NT, int CB_> struct DmStage {
 constexpr int DM_RUN = 16, DM_RUNS_NB = 2, DM_LONG = 8192;
 constexpr int DM_GAIN_B = 1024;                 // RMSNorm weights of a stage
 
+template <int N> struct DmTag { static constexpr int value = N; };
+
 template <int N> __device__ __forceinline__ void dm_wait_vm() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
 }
@@ -103,22 +105,16 @@ __device__ __forceinline__ unsigned dm_hi2(float a, float b) {
   return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
 }
 
-// x = hi + mid + lo for 8 floats, each piece a bf16 fragment.  Infinities would leave NaN in the lower pieces
-// (inf - inf): they are put in hi alone.
-__device__ __forceinline__ void dm_split(const float (&x)[8], uint4 &hi, uint4 &mid, uint4 &lo) {
+// x = hi + mid + lo for 8 floats, each piece a bf16 fragment.  With weights (NORM) x is f * w, of which what lies below hi is taken
+// from the unrounded product.  Infinities would leave NaN in the lower pieces (inf - inf): INF puts them in hi alone.
+template <bool NORM, bool INF> __device__ __forceinline__ void dm_split(const float (&x)[8], const float (&f)[8], const float (&w)[8], uint4 &hi, uint4 &mid, uint4 &lo) {
   float r[8], q[8];
   #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    r[i] = x[i] - __uint_as_float(__float_as_uint(x[i]) & 0xffff0000u);
+    const float top = __uint_as_float(__float_as_uint(x[i]) & 0xffff0000u);
+    r[i] = NORM ? fmaf(f[i], w[i], -top) : x[i] - top;
     q[i] = r[i] - __uint_as_float(__float_as_uint(r[i]) & 0xffff0000u);
-  }
-  bool inf = false;
-  #pragma unroll
-  for (int i = 0; i < 8; ++i) inf |= __builtin_amdgcn_classf(x[i], 0x204);      // +-infinity
-  if (__any(inf)) {
-    #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (__builtin_amdgcn_classf(x[i], 0x204)) { r[i] = 0.f; q[i] = 0.f; }
+    if (INF && __builtin_amdgcn_classf(x[i], 0x204)) { r[i] = 0.f; q[i] = 0.f; }           // +-infinity
   }
   hi = make_uint4(dm_hi2(x[0], x[1]), dm_hi2(x[2], x[3]), dm_hi2(x[4], x[5]), dm_hi2(x[6], x[7]));
   mid = make_uint4(dm_hi2(r[0], r[1]), dm_hi2(r[2], r[3]), dm_hi2(r[4], r[5]), dm_hi2(r[6], r[7]));
@@ -289,36 +285,55 @@ __global__ __launch_bounds__((DmStage<NB, NT, CB_>::THREADS)) void k_draft_mm(co
             #pragma unroll
             for (int b = 0; b < NB; ++b) { wf[b].x ^= sgn; wf[b].y ^= sgn; wf[b].z ^= sgn; wf[b].w ^= sgn; }
           }
+          float f[NT][8], x[NT][8], top = 0.f;               // top: the largest magnitude (NaN aside)
           #pragma unroll
           for (int t = 0; t < NT; ++t) {
-            float f[8];
             const unsigned char *xr = sx + (t * 16 + r16) * XRB;
-            Elem<float>::unpack(*reinterpret_cast<const uint4 *>(xr + (((s * 8 + g * 2) ^ r16) * 16)), f);
-            Elem<float>::unpack(*reinterpret_cast<const uint4 *>(xr + (((s * 8 + g * 2 + 1) ^ r16) * 16)), f + 4);
-            if (k + 32 > a.Kd && k + g * 8 >= a.Kd) {        // past the end of the reduction axis (Kd is a multiple of 8)
+            float (&ft)[8] = f[t];
+            float lo4[4], hi4[4];
+            Elem<float>::unpack(*reinterpret_cast<const uint4 *>(xr + (((s * 8 + g * 2) ^ r16) * 16)), lo4);
+            Elem<float>::unpack(*reinterpret_cast<const uint4 *>(xr + (((s * 8 + g * 2 + 1) ^ r16) * 16)), hi4);
+            #pragma unroll
+            for (int e = 0; e < 4; ++e) { ft[e] = lo4[e]; ft[4 + e] = hi4[e]; }
+          }
+          const bool ends = k + 32 > a.Kd;                   // (uniform) the reduction axis ends in this step
+          if (ends) {
+            #pragma unroll
+            for (int t = 0; t < NT; ++t)
               #pragma unroll
-              for (int e = 0; e < 8; ++e) f[e] = 0.f;
-            }
+              for (int e = 0; e < 8; ++e) f[t][e] = k + g * 8 >= a.Kd ? 0.f : f[t][e];       // (Kd is a multiple of 8)
+          }
+          #pragma unroll
+          for (int t = 0; t < NT; ++t) {
             if (NORM) {
               #pragma unroll
-              for (int e = 0; e < 8; ++e) { ss[t] = fmaf(f[e], f[e], ss[t]); f[e] *= gk[e]; }
+              for (int e = 0; e < 8; ++e) ss[t] = fmaf(f[t][e], f[t][e], ss[t]);
             }
             if (NB > 2 * NT) {
               #pragma unroll
-              for (int e = 0; e < 8; ++e) f[e] = __uint_as_float(__float_as_uint(f[e]) ^ (sgn & 0x80000000u));
+              for (int e = 0; e < 8; ++e) f[t][e] = __uint_as_float(__float_as_uint(f[t][e]) ^ (sgn & 0x80000000u));
             }
-            uint4 hi, mid, lo;
-            dm_split(f, hi, mid, lo);
-            f32x4 d[NB];
             #pragma unroll
-            for (int b = 0; b < NB; ++b) d[b] = mma16<bf16_t>(wf[b], lo, (f32x4){0.f, 0.f, 0.f, 0.f});
-            #pragma unroll
-            for (int b = 0; b < NB; ++b) d[b] = mma16<bf16_t>(wf[b], mid, d[b]);
-            #pragma unroll
-            for (int b = 0; b < NB; ++b) d[b] = mma16<bf16_t>(wf[b], hi, d[b]);
-            #pragma unroll
-            for (int b = 0; b < NB; ++b) acc[b][t] += d[b];
+            for (int e = 0; e < 8; ++e) { x[t][e] = NORM ? f[t][e] * gk[e] : f[t][e]; top = fmaxf(top, fabsf(x[t][e])); }
           }
+          auto multiply = [&](auto tag) {
+            #pragma unroll
+            for (int t = 0; t < NT; ++t) {
+              uint4 hi, mid, lo;
+              dm_split<NORM, decltype(tag)::value != 0>(x[t], f[t], gk, hi, mid, lo);
+              f32x4 d[NB];
+              #pragma unroll
+              for (int b = 0; b < NB; ++b) d[b] = mma16<bf16_t>(wf[b], lo, (f32x4){0.f, 0.f, 0.f, 0.f});
+              #pragma unroll
+              for (int b = 0; b < NB; ++b) d[b] = mma16<bf16_t>(wf[b], mid, d[b]);
+              #pragma unroll
+              for (int b = 0; b < NB; ++b) d[b] = mma16<bf16_t>(wf[b], hi, d[b]);
+              #pragma unroll
+              for (int b = 0; b < NB; ++b) acc[b][t] += d[b];
+            }
+          };
+          // one question for all tiles of the step: asked for each, its branch kept them from overlapping
+          if (__builtin_expect(__any(top == __builtin_huge_valf()), 0)) multiply(DmTag<1>{}); else multiply(DmTag<0>{});
         }
       }
       if (RUNS && ((p + 1) % (DM_RUN / SPW) == 0 || p + 1 == P)) {
