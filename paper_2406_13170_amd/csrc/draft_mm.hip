@@ -121,22 +121,33 @@ template <bool NORM, bool INF> __device__ __forceinline__ void dm_split(const fl
   lo = make_uint4(dm_hi2(q[0], q[1]), dm_hi2(q[2], q[3]), dm_hi2(q[4], q[5]), dm_hi2(q[6], q[7]));
 }
 
-// weight row r16 of block blk: its matrix and its row in it.  Rows past the end re-read the last row; they are never
-// stored.  q and k blocks: 8 rows of a head and their 8 RoPE partners; gate/up blocks: 8 rows of each matrix.
+// 16 bytes a lane from base + off + at (off a lane's own, at the wave's) to LDS, lane by lane.  Nothing is written for a lane past `bytes`.
+template <int AUX> __device__ __forceinline__ void dm_load_lds(const void *base, unsigned bytes, unsigned char *lds, int off, int at) {
+#ifdef __HIP_DEVICE_COMPILE__                              // (the host's pass refuses 16 bytes)
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00020000),
+                                           (__attribute__((address_space(3))) void *)lds, 16, off, at, 0, AUX);
+#endif
+}
+
+// Weight rows r16, r16 + 1, .. of block blk that lie next to each other (up to a multiple of eight): their matrix, the first one's row
+// in it.  Rows past the end re-read the last row; they are never stored.  q and k blocks: 8 rows of a head and their 8 RoPE partners;
+// gate/up blocks: 8 rows of each matrix.
+struct DmRows { const bf16_t *w; int n, rows; };
 template <int EPI>
-__device__ __forceinline__ const bf16_t *dm_row(const DmArgs &a, int blk, int r16) {
-  if (EPI == DM_SWIGLU) return ((r16 >= 8) ? a.w1 : a.w0) + (size_t)min(blk * 8 + (r16 & 7), a.seg_rows - 1) * a.Kd;
+__device__ __forceinline__ DmRows dm_rows(const DmArgs &a, int blk, int r16) {
+  if (EPI == DM_SWIGLU) return {r16 >= 8 ? a.w1 : a.w0, min(blk * 8 + (r16 & 7), a.seg_rows - 1), a.seg_rows};
   const int bps = (a.seg_rows + 15) >> 4;
-  const int seg = a.n_seg == 1 ? 0 : blk / bps, bl = blk - seg * bps;
+  if (EPI == DM_HEADMLP) {                                 // (one head a workgroup)
+    const int seg = blockIdx.y;
+    return {a.w0 + (size_t)seg * a.seg_rows * a.Kd, min((blk - seg * bps) * 16 + r16, a.seg_rows - 1), a.seg_rows};
+  }
+  const int seg = a.n_seg == 1 ? 0 : (blk >= 2 * bps ? 2 : blk >= bps ? 1 : 0), bl = blk - seg * bps;
   int n = bl * 16 + r16;
   if (EPI == DM_SALQKV && seg < 2) {
     const int bph = a.d_h >> 4;
     n = (bl / bph) * a.d_h + (bl % bph) * 8 + (r16 & 7) + ((r16 >= 8) ? a.d_h / 2 : 0);
   }
-  n = min(n, a.seg_rows - 1);
-  if (EPI == DM_HEADMLP) return a.w0 + ((size_t)seg * a.seg_rows + n) * a.Kd;
-  const bf16_t *w = seg == 0 ? a.w0 : seg == 1 ? a.w1 : a.w2;
-  return w + (size_t)n * a.Kd;
+  return {seg == 0 ? a.w0 : seg == 1 ? a.w1 : a.w2, min(n, a.seg_rows - 1), a.seg_rows};
 }
 
 template <int EPI, int NB, int NT, int CB_>
@@ -155,6 +166,7 @@ __global__ __launch_bounds__((DmStage<NB, NT, CB_>::THREADS)) void k_draft_mm(co
   const int Kb = a.Kd * 2;
   const int P_all = (Kb + CB - 1) / CB;                    // stages of the whole axis; this workgroup's are [Pa, P)
   const int S = gridDim.z, Pa = (int)((unsigned)(P_all * blockIdx.z) / (unsigned)S), P = (int)((unsigned)(P_all * (blockIdx.z + 1)) / (unsigned)S);
+  const int Kx = EPI == DM_FC ? a.Kd / 2 : a.Kd;           // float32 columns
   const int Pu = EPI == DM_FC ? P_all / 2 : P_all;         // stages whose activations are float32 (DM_FC: then the embeddings, bf16)
   const int R = a.ring, SB = a.stage_bytes;
   auto blk_of = [&](int b) { return head * bps + min(b0 + b, bl_last); };
@@ -175,61 +187,62 @@ __global__ __launch_bounds__((DmStage<NB, NT, CB_>::THREADS)) void k_draft_mm(co
   if (wave >= KW) {
     // ------------------------------------------------------------------------------- loader wave
     // Loader l takes weight loads l * LPW .. and every other activation load; loader 1 also the RMSNorm weights.
+    // Its loads go through buffer descriptors: what a lane adds to a load's base stays the same through the launch, and the stage
+    // is a scalar offset.  Pieces past a row's end read what follows, past the end of the matrix nothing: what LDS holds there is not
+    // looked at.  (With a dozen vector instructions of addresses for every load, on a SIMD that a math wave keeps busy, issuing the
+    // 32 loads of a stage of 40 rows set the pace.  us, so / now: 40 rows QKV 12288 x 4096 44 / 39, W_down 4096 x 11008 32 / 27; 32 rows
+    // 12288 x 4096 36 / 28, the LM head 32000 x 4096 75 / 71; 24 rows 35840 x 6656 111 / 102; five rows the same.)
     const int l = wave - KW;
     constexpr int PPR = CB / 16, PPX = XRB / 16;           // 16-byte pieces of a weight / float32 activation row per stage
-    const unsigned char *src[LPW];
-    int pc[LPW];
+    const unsigned char *wbase[LPW];
+    unsigned wbytes[LPW];
+    int wo[LPW];
     #pragma unroll
     for (int j = 0; j < LPW; ++j) {
-      const int row = (l * LPW + j) * RPI + lane / PPR;    // row of the stage: block row / 16, row % 16 of it
-      src[j] = (const unsigned char *)dm_row<EPI>(a, blk_of(row >> 4), row & 15);
-      pc[j] = ((lane % PPR) ^ (row & 15)) * 16;            // the piece that belongs at this lane's slot
+      const int r0 = (l * LPW + j) * RPI;                  // first row of the load in the stage: block r0 / 16, row r0 % 16 of it
+      const DmRows rw = dm_rows<EPI>(a, blk_of(r0 >> 4), r0 & 15);
+      const size_t left = (size_t)(rw.rows - rw.n) * Kb;
+      wbase[j] = (const unsigned char *)rw.w + (size_t)rw.n * Kb;
+      wbytes[j] = left < 0xffffffffu ? (unsigned)left : 0xffffffffu;
+      wo[j] = min(lane / PPR, rw.rows - 1 - rw.n) * Kb + ((lane % PPR) ^ ((r0 + lane / PPR) & 15)) * 16;   // the piece that belongs at this lane's slot
     }
     const int nx = (a.M + RPX - 1) / RPX * C::LPX, ne = EPI == DM_FC ? (a.M + RPI - 1) / RPI : 0;     // activation loads per stage
-    constexpr int EMAX = EPI == DM_FC ? (DRAFT_MM_ROWS / RPI + 1) / 2 : 1;
+    constexpr int XMAX = (NT * 16 / RPX * C::LPX + 1) / 2, EMAX = EPI == DM_FC ? (NT * 16 / RPI + 1) / 2 : 1;
+    const unsigned xbytes = (unsigned)(((a.M - 1) * a.ldx + Kx) * 4);
+    int xo[XMAX];
+    #pragma unroll
+    for (int j = 0; j < XMAX; ++j) {                       // rows past the end re-read the last one; never stored
+      const int i = l + 2 * j, row = C::LPX > 1 ? i / C::LPX : i * RPX + lane / PPX, pl = C::LPX > 1 ? (i % C::LPX) * 64 + lane : lane % PPX;
+      xo[j] = min(row, a.M - 1) * a.ldx * 4 + (pl ^ (row & 15)) * 16;
+    }
     const unsigned char *esrc[EMAX];                       // DM_FC: embedding rows of this lane's loads
     if (EPI == DM_FC) {
       #pragma unroll
       for (int j = 0; j < EMAX; ++j) {
-        const int tk = a.tok[min((l + 2 * j) * RPI + lane / PPR, a.M - 1)];
-        esrc[j] = (const unsigned char *)(a.embed + (size_t)((tk < 0 || tk >= a.vocab) ? 0 : tk) * a.ldx);
+        const int row = (l + 2 * j) * RPI + lane / PPR, tk = a.tok[min(row, a.M - 1)];
+        esrc[j] = (const unsigned char *)(a.embed + (size_t)((tk < 0 || tk >= a.vocab) ? 0 : tk) * a.ldx) + ((lane % PPR) ^ (row & 15)) * 16;
       }
     }
+    const int go = min(lane % PPR, 63) * 16;
     const int cu = LPW + (nx - l + 1) / 2 + ((NORM && l == 1) ? 1 : 0), ce = LPW + (ne - l + 1) / 2;   // loads per stage
+    typedef __attribute__((address_space(3))) void Lds;
     auto issue = [&](int p, int slot) {
       unsigned char *lp = dm_lds + (size_t)slot * SB;
       #pragma unroll
-      for (int j = 0; j < LPW; ++j) {
-        const int off = min(p * CB + pc[j], Kb - 16);      // pieces past the row re-read its last one (the activations are zero there)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src[j] + off),
-                                         (__attribute__((address_space(3))) void *)(lp + (l * LPW + j) * 1024), 16, 0, 2);   // non-temporal
-      }
+      for (int j = 0; j < LPW; ++j)
+        dm_load_lds<2>(wbase[j], wbytes[j], lp + (l * LPW + j) * 1024, wo[j], p * CB);   // non-temporal
       unsigned char *xp = lp + C::WB;
       if (EPI == DM_FC && p >= Pu) {
         #pragma unroll
-        for (int j = 0; j < EMAX; ++j) {
-          const int i = l + 2 * j;
-          if (i < ne) {
-            const int row = i * RPI + lane / PPR;
-            const int off = (p - Pu) * CB + (((lane % PPR) ^ (row & 15)) * 16);
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(esrc[j] + off),
-                                             (__attribute__((address_space(3))) void *)(xp + i * 1024), 16, 0, 0);
-          }
-        }
+        for (int j = 0; j < EMAX; ++j)
+          if (l + 2 * j < ne)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(esrc[j] + (p - Pu) * CB),
+                                             (Lds *)(xp + (l + 2 * j) * 1024), 16, 0, 0);
       } else {
-        for (int i = l; i < nx; i += 2) {
-          // rows past the end re-read the last one; never stored
-          const int row = C::LPX > 1 ? i / C::LPX : i * RPX + lane / PPX, pl = C::LPX > 1 ? (i % C::LPX) * 64 + lane : lane % PPX;
-          const int off = min(p * XRB + ((pl ^ (row & 15)) * 16), a.Kd * 4 - 16);
-          const unsigned char *s = (const unsigned char *)xbase + ((size_t)min(row, a.M - 1) * a.ldx * 4 + off);
-          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)s,
-                                           (__attribute__((address_space(3))) void *)(xp + i * 1024), 16, 0, 0);
-        }
-        if (NORM && l == 1) {
-          const unsigned char *s = (const unsigned char *)a.gain + min(p * CB + (lane % PPR) * 16, Kb - 16);
-          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)s,
-                                           (__attribute__((address_space(3))) void *)(lp + SB - DM_GAIN_B), 16, 0, 0);
-        }
+        #pragma unroll
+        for (int j = 0; j < XMAX; ++j)
+          if (l + 2 * j < nx) dm_load_lds<0>(xbase, xbytes, xp + (l + 2 * j) * 1024, xo[j], p * XRB);
+        if (NORM && l == 1) dm_load_lds<0>(a.gain, Kb, lp + SB - DM_GAIN_B, go, p * CB);
       }
     };
     const int pro = P - Pa < R - 1 ? P - Pa : R - 1;
@@ -297,11 +310,15 @@ __global__ __launch_bounds__((DmStage<NB, NT, CB_>::THREADS)) void k_draft_mm(co
             for (int e = 0; e < 4; ++e) { ft[e] = lo4[e]; ft[4 + e] = hi4[e]; }
           }
           const bool ends = k + 32 > a.Kd;                   // (uniform) the reduction axis ends in this step
-          if (ends) {
+          if (ends && k + g * 8 >= a.Kd) {                   // (what lies there in LDS is anything)
+            #pragma unroll
+            for (int b = 0; b < NB; ++b) wf[b] = make_uint4(0u, 0u, 0u, 0u);
+            #pragma unroll
+            for (int e = 0; e < 8; ++e) gk[e] = 0.f;
             #pragma unroll
             for (int t = 0; t < NT; ++t)
               #pragma unroll
-              for (int e = 0; e < 8; ++e) f[t][e] = k + g * 8 >= a.Kd ? 0.f : f[t][e];       // (Kd is a multiple of 8)
+              for (int e = 0; e < 8; ++e) f[t][e] = 0.f;      // (Kd is a multiple of 8)
           }
           #pragma unroll
           for (int t = 0; t < NT; ++t) {
