@@ -97,32 +97,26 @@ __device__ __forceinline__ void rope_pair(float x1, float x2, float cs, float sn
 // Epilogue of one 64-row block of a workgroup's output tile: Ct[m][r] (float32, pitch CT_PITCH) holds rows
 // m_base .. m_base + 63 of the activations against the tile's nb row blocks (BN = 16 * nb columns).  Every thread
 // of the workgroup (NT of them) takes part.
-template <typename T, int EPI, int rows>                   // rows of Ct that are live: 32 or 64
+template <typename T, int EPI>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const float *Ct, int CT_PITCH, int tile, int nb, int m_base,
                                               int split, int nblk, int tid, int NT) {
+  constexpr int rows = GM_BM;
   const int BN = 16 * nb;
   if (EPI == EPI_STORE) {
     // out is [split_k][M][N]: slab `split` receives this workgroup's partial sums
     const int N = a.seg_rows;
     float *slab = a.out + (size_t)split * a.M * N;
-    const int Q = BN / 4;                                   // 4 adjacent columns per thread (one by one in a ragged last tile, and in
-    const bool pieces = (N & 3) == 0 && ((uintptr_t)slab & 15) == 0;   // a caller's logits that begin anywhere)
+    const int Q = BN / 4;                                   // 4 adjacent columns per thread (N is no multiple of 4: one by one)
     for (int idx = tid; idx < rows * Q; idx += NT) {
       const int m = idx / Q, r = (idx % Q) * 4, mg = m_base + m, n = tile * BN + r;
       if (mg >= a.M || n >= N) continue;
-      const f32x4 v = *reinterpret_cast<const f32x4 *>(Ct + m * CT_PITCH + r);
-      float *dst = slab + (size_t)mg * N + n;
-      if (n + 4 <= N && pieces) {
-        *reinterpret_cast<f32x4 *>(dst) = v;
-      } else {
-        for (int c = 0; c < 4 && n + c < N; ++c) dst[c] = v[c];
-      }
+      for (int c = 0; c < 4 && n + c < N; ++c) slab[(size_t)mg * N + n + c] = Ct[m * CT_PITCH + r + c];
     }
   } else if (EPI == EPI_SWIGLU) {
     // block w of the tile: columns 0..7 = gate rows, 8..15 = the same rows of up
     const int f = a.seg_rows, H = 8 * nb;
     T *act = (T *)a.act;
-    // one (token, block) per thread: 8 adjacent outputs leave as one piece (element by element in a ragged last block)
+    // one (token, block) per thread: 8 adjacent outputs
     for (int idx = tid; idx < rows * nb; idx += NT) {
       const int m = idx / nb, w = idx % nb, mg = m_base + m, j0 = tile * H + w * 8;
       if (mg >= a.M || j0 >= f) continue;
@@ -131,14 +125,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const float *Ct
       #pragma unroll
       for (int j = 0; j < 8; ++j) y[j] = silu_f(crow[j]) * crow[8 + j];
       T *dst = act + (size_t)mg * f + j0;
-      if (a.act_tiles) {                                   // tiled for the wide GEMM that follows (f is a multiple of 16)
-        store4<T>(act + xt_index<T>(mg, j0, a.act_tiles), y);
-        store4<T>(act + xt_index<T>(mg, j0 + 4, a.act_tiles), y + 4);
-      } else if (j0 + 8 <= f && (f & 7) == 0) {
-        store4<T>(dst, y); store4<T>(dst + 4, y + 4);
-      } else {
-        for (int j = 0; j < 8 && j0 + j < f; ++j) dst[j] = Elem<T>::from_f32(y[j]);
-      }
+      for (int j = 0; j < 8 && j0 + j < f; ++j) dst[j] = Elem<T>::from_f32(y[j]);      // (f is no multiple of 4)
     }
   } else if (EPI == EPI_QKV_ROPE) {
     // d_h is a power of two (checked at launch): heads and dims come from shifts; the segment of a block (q, k or v:
@@ -147,10 +134,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const float *Ct
     auto seg_of = [&](int b) { return (b >= 2 * bps) ? 2 : (b >= bps) ? 1 : 0; };
     // q and k blocks: one (block, token) per thread = 8 rotation pairs.  Everything the item needs from global
     // memory (64 bytes of the cos/sin table, the committed length) is requested first, for up to QK_U items of the
-    // thread at once: a wave of the wide kernel walks several items (up to 8), and stores in between would keep the next item's
-    // loads from starting early.  The 8 + 8 results leave as 16-byte pieces: dims e0 .. e0+7 (and their partners at
+    // thread at once: stores in between would keep the next item's loads from starting early.  The 8 + 8 results leave as 16-byte pieces: dims e0 .. e0+7 (and their partners at
     // + d_h/2) are adjacent in q and inside a fragment of the tiled K cache.
-    constexpr int QK_U = rows == 32 ? 5 : 3;
+    constexpr int QK_U = 3;
     for (int base = tid; base < nb * rows; base += QK_U * NT) {
       float4 tab[QK_U][4];
       int Lb[QK_U];
@@ -222,31 +208,19 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const float *Ct
         }
       }
     }
-  } else if (EPI == EPI_ARGMAX) {
-    const int N = a.seg_rows;
-    if (a.logits) {
-      for (int idx = tid; idx < rows * BN; idx += NT) {
-        const int m = idx / BN, r = idx % BN, mg = m_base + m, n = tile * BN + r;
-        if (mg < a.M && n < N) a.logits[(size_t)mg * N + n] = Ct[m * CT_PITCH + r];
-      }
-    }
-    // 4 threads per token row, BN/4 columns each, then a 4-lane butterfly (ties -> lower column)
-    for (int t4 = tid; t4 < 4 * rows; t4 += NT) {         // NT and 4 * rows are multiples of 64: the 4 lanes of a row stay in one wave
-      const int m = t4 >> 2, part = t4 & 3, mg = m_base + m;
-      float bv = -__builtin_huge_valf(); int bi = 0x7fffffff;
-      for (int r = part * (BN / 4); r < (part + 1) * (BN / 4); ++r) {
-        const int n = tile * BN + r;
-        const float v = Ct[m * CT_PITCH + r];
-        if (n < N && (v > bv || (v == bv && n < bi))) { bv = v; bi = n; }
-      }
-      take_better(bv, bi, lanes_dpp<DPP_XOR1>(bv), lanes_dpp<DPP_XOR1>(bi));
-      take_better(bv, bi, lanes_dpp<DPP_XOR2>(bv), lanes_dpp<DPP_XOR2>(bi));
-      if (part == 0 && mg < a.M) {
-        a.amax_val[(size_t)tile * a.M + mg] = bv;
-        a.amax_idx[(size_t)tile * a.M + mg] = bi;
-      }
-    }
   }
+}
+
+// the best (value, column) of the four lane groups of 16, in every lane
+__device__ __forceinline__ void best_of_groups(float &bv, int &bi) {
+  const auto ov = __builtin_amdgcn_permlane16_swap(lane_bits(bv), lane_bits(bv), false, false);
+  const auto oi = __builtin_amdgcn_permlane16_swap((unsigned)bi, (unsigned)bi, false, false);
+  bv = lane_value<float>(ov[0]); bi = (int)oi[0];
+  take_better(bv, bi, lane_value<float>(ov[1]), (int)oi[1]);
+  const auto pv = __builtin_amdgcn_permlane32_swap(lane_bits(bv), lane_bits(bv), false, false);
+  const auto pi = __builtin_amdgcn_permlane32_swap((unsigned)bi, (unsigned)bi, false, false);
+  bv = lane_value<float>(pv[0]); bi = (int)pi[0];
+  take_better(bv, bi, lane_value<float>(pv[1]), (int)pi[1]);
 }
 
 template <int N> struct GemmTag { static constexpr int value = N; };
@@ -411,6 +385,43 @@ __global__ __launch_bounds__(64 * (GM_MAX_NB + GM_NLW)) void k_gemm_skinny(const
     }
     return;
   }
+  // Neither does the row argmax, nor its logits: each math wave leaves the best of its 16 columns for every row, and the waves'
+  // winners are compared.  (Through a tile in LDS, a float at a time: the LM head 32000 x 4096 with logits 57 us.)
+  if (EPI == EPI_ARGMAX) {
+    const int N = a.seg_rows, n0 = tile * BN + wave * 16 + g * 4;
+    float *best_v = reinterpret_cast<float *>(lds);        // [wave][64 rows]
+    int *best_i = reinterpret_cast<int *>(lds) + GM_MAX_NB * GM_BM;
+    if (wave < nb) {
+      const bool pieces = (N & 3) == 0 && ((uintptr_t)a.logits & 15) == 0;
+      #pragma unroll
+      for (int mb = 0; mb < 4; ++mb) {
+        const int mg = m_base + mb * 16 + r16;
+        if (a.logits && mg < a.M) {                        // (a caller's logits may begin anywhere)
+          float *dst = a.logits + (size_t)mg * N + n0;
+          if (pieces && n0 < N) {
+            *reinterpret_cast<f32x4 *>(dst) = acc[mb];
+          } else {
+            #pragma unroll
+            for (int i = 0; i < 4; ++i) if (n0 + i < N) dst[i] = acc[mb][i];
+          }
+        }
+        float bv = -__builtin_huge_valf(); int bi = 0x7fffffff;
+        #pragma unroll
+        for (int i = 3; i >= 0; --i)                       // descending: at equal values the lower column comes later
+          if (n0 + i < N && acc[mb][i] >= bv) { bv = acc[mb][i]; bi = n0 + i; }
+        best_of_groups(bv, bi);
+        if (g == 0) { best_v[wave * GM_BM + mb * 16 + r16] = bv; best_i[wave * GM_BM + mb * 16 + r16] = bi; }
+      }
+    }
+    __syncthreads();
+    if (tid < GM_BM && m_base + tid < a.M) {
+      float bv = best_v[tid]; int bi = best_i[tid];
+      for (int w = 1; w < nb; ++w) take_better(bv, bi, best_v[w * GM_BM + tid], best_i[w * GM_BM + tid]);
+      a.amax_val[(size_t)tile * a.M + m_base + tid] = bv;
+      a.amax_idx[(size_t)tile * a.M + m_base + tid] = bi;
+    }
+    return;
+  }
   // accumulators -> Ct[m][r] (float32): a math lane holds rows r = wave*16 + g*4 .. +4 of column m.
   // The last barrier of the loop has passed, so nobody reads the stages any more; the one write still
   // outstanding (the loaders' zero chunk nch2) went to stage nch2 % 2 before that barrier.
@@ -422,7 +433,7 @@ __global__ __launch_bounds__(64 * (GM_MAX_NB + GM_NLW)) void k_gemm_skinny(const
   }
   __syncthreads();
 
-  gemm_epilogue<T, EPI, GM_BM>(a, Ct, CT_PITCH, tile, nb, m_base, split, nblk, tid, NT);
+  gemm_epilogue<T, EPI>(a, Ct, CT_PITCH, tile, nb, m_base, split, nblk, tid, NT);
 }
 
 // =====================================================================================================
@@ -692,14 +703,7 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
             }
             if (b % 2 == 0) __builtin_amdgcn_sched_barrier(0);
           }
-          const auto ov = __builtin_amdgcn_permlane16_swap(lane_bits(bv), lane_bits(bv), false, false);
-          const auto oi = __builtin_amdgcn_permlane16_swap((unsigned)bi, (unsigned)bi, false, false);
-          bv = lane_value<float>(ov[0]); bi = (int)oi[0];
-          take_better(bv, bi, lane_value<float>(ov[1]), (int)oi[1]);
-          const auto pv = __builtin_amdgcn_permlane32_swap(lane_bits(bv), lane_bits(bv), false, false);
-          const auto pi = __builtin_amdgcn_permlane32_swap((unsigned)bi, (unsigned)bi, false, false);
-          bv = lane_value<float>(pv[0]); bi = (int)pi[0];
-          take_better(bv, bi, lane_value<float>(pv[1]), (int)pi[1]);
+          best_of_groups(bv, bi);
           const int mg = sub_of(t + c) * 16 + r16;
           if (g == 0 && sub_of(t + c) < sub1 && mg < a.M) {
             a.amax_val[(size_t)tile * a.M + mg] = bv;
