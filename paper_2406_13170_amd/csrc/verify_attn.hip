@@ -638,8 +638,15 @@ struct VaPlan {
 };
 constexpr int VA_MAX_QB = 2;       // regs: more blocks per wave would leave no room for a second set of K/V fragments
 
+// Bytes of a head's whole cache up to which one workgroup walks it alone: splitting it saves less than the fold's launch costs (us, with
+// splits / without: whole iterations of the float32 miniature, 128 rows 190 / 186, of the bf16 one 128 rows 211 / 207, 300 rows
+// 215 / 211; target passes of two layers at 7B widths, 180 rows 278 / 274, 430 rows 277 / 274, 13B 430 rows 356 / 354; but with caches
+// of 512 KB, 900 rows, 275 / 282; in float32, whose matrix instructions take longer, half of it: 300 rows
+// of the miniature 200 / 200).  The rule reads the capacity: the lengths are the device's.
+constexpr long VA_SHORT = 256 * 1024;
+
 // force: -1 chooses by shape, 0 = registers, 1 = LDS ring
-static VaPlan va_plan(int B, int T, int n_heads, int max_kv, int elem_bytes, int force) {
+static VaPlan va_plan(int B, int T, int n_heads, int d_h, int max_kv, int elem_bytes, int force) {
   VaPlan p{};
   const int kstep = 4 * (16 / elem_bytes);
   const int max_steps = max_kv / kstep;
@@ -651,7 +658,7 @@ static VaPlan va_plan(int B, int T, int n_heads, int max_kv, int elem_bytes, int
   const int cap = (max_steps + 3) / 4;
   if (s > cap) s = cap;
   if (s > 32) s = 32;
-  if (s < 1) s = 1;
+  if (s < 1 || (long)max_kv * d_h * 2 * elem_bytes <= (elem_bytes == 4 ? VA_SHORT / 2 : VA_SHORT)) s = 1;
   // ring: when a workgroup walks a whole head anyway (no room for key splits) and the walk is long, or when the
   // register kernel would need more workgroups than there are compute units (measured: 32 heads, T = 64, L = 1024:
   // batch 1 15.4 us regs / 17.3 ring, batch 4 21.1 / 23.2, batch 8 40.6 / 31.0; 40 heads, L = 2048, batch 4: 57.8 / 46.4)
@@ -688,13 +695,13 @@ static size_t va_plan_floats(const VaPlan &p, int B, int n_heads, int d_h) {
 }
 
 size_t verify_partials_floats(int B, int T, int n_heads, int d_h, int max_kv, int elem_bytes, int kernel) {
-  return va_plan_floats(va_plan(B, T, n_heads, max_kv, elem_bytes, kernel), B, n_heads, d_h);
+  return va_plan_floats(va_plan(B, T, n_heads, d_h, max_kv, elem_bytes, kernel), B, n_heads, d_h);
 }
 
 // partial results of the larger of the two kernels' plans: the choice may be overridden per call
 size_t verify_ws_floats(int B, int T, int n_heads, int d_h, int max_kv, int elem_bytes) {
-  const size_t a = va_plan_floats(va_plan(B, T, n_heads, max_kv, elem_bytes, 0), B, n_heads, d_h);
-  const size_t b = va_plan_floats(va_plan(B, T, n_heads, max_kv, elem_bytes, 1), B, n_heads, d_h);
+  const size_t a = va_plan_floats(va_plan(B, T, n_heads, d_h, max_kv, elem_bytes, 0), B, n_heads, d_h);
+  const size_t b = va_plan_floats(va_plan(B, T, n_heads, d_h, max_kv, elem_bytes, 1), B, n_heads, d_h);
   return a > b ? a : b;
 }
 
@@ -714,7 +721,7 @@ static hipError_t launch_va_ring(hipStream_t st, const VerifyArgs &a, const VaPl
 
 template <typename T, int DH>
 static hipError_t launch_va_dh(hipStream_t st, const VerifyArgs &a) {
-  const VaPlan p = va_plan(a.B, a.T, a.n_heads, a.max_kv, (int)sizeof(T), a.kernel);
+  const VaPlan p = va_plan(a.B, a.T, a.n_heads, DH, a.max_kv, (int)sizeof(T), a.kernel);
   if (p.nqb < 1 || p.nqb > 2) return hipErrorInvalidValue;
   if (va_plan_floats(p, a.B, a.n_heads, DH) > a.partials_cap) return hipErrorInvalidValue;
   if (p.ring) {
