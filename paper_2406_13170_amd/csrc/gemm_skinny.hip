@@ -1053,7 +1053,7 @@ static int gemm_split(int epi, int seg_rows, int Kd, int elem_bytes, int M, bool
 // float32 keeps to the skinny kernel, whose sums row-major weights have.
 bool gemm_is_wide(int epi, int seg_rows, int Kd, int elem_bytes, int M, bool tiled) {
   const int mblocks = (M + GM_BM - 1) / GM_BM;
-  if (!tiled || mblocks < 2) return false;
+  if (!tiled || mblocks < 2 || gemm_xt_bytes(M, Kd, elem_bytes) > 0x7fffffffu) return false;   // (the wide kernel's offsets have 32 bits)
   if (mblocks > 2) return true;
   if (elem_bytes == 4) return false;
   const int split = gemm_split(epi, seg_rows, Kd, elem_bytes, M, tiled);
