@@ -25,8 +25,8 @@
 //     waves they queue behind the ring's worth of weights in flight (7B W_down over 5 rows: 53 us).
 //   * KW math waves split the reduction axis: wave w takes step w (64 bytes of a weight row) of every stage (and step w + KW
 //     of a stage of 1024 bytes), against all NB blocks and NT tiles, so each activation element is read from LDS and cut into its pieces once per workgroup.  A
-//     step costs about 75 vector instructions per tile whatever NB is; that sets the pace of launches with one or two
-//     row blocks per workgroup (reading the next step's operands ahead of this one's arithmetic changed nothing).
+//     step costs about 45 vector instructions per tile whatever NB is, which what a compute unit takes in mostly hides: twice the
+//     math waves, sharing the tiles, changed nothing (nor did reading the next step's operands ahead of this one's arithmetic).
 // The KW partial sums meet in LDS after the loop and are added in a fixed order; RMSNorm's 1/rms of a row is
 // applied there too (the waves collect the squares of the elements they saw).
 #include "kernels.h"
