@@ -638,12 +638,20 @@ struct VaPlan {
 };
 constexpr int VA_MAX_QB = 2;       // regs: more blocks per wave would leave no room for a second set of K/V fragments
 
-// Bytes of a head's whole cache up to which one workgroup walks it alone: splitting it saves less than the fold's launch costs (us, with
-// splits / without: whole iterations of the float32 miniature, 128 rows 190 / 186, of the bf16 one 128 rows 211 / 207, 300 rows
-// 215 / 211; target passes of two layers at 7B widths, 180 rows 278 / 274, 430 rows 277 / 274, 13B 430 rows 356 / 354; but with caches
-// of 512 KB, 900 rows, 275 / 282; in float32, whose matrix instructions take longer, half of it: 300 rows
-// of the miniature 200 / 200).  The rule reads the capacity: the lengths are the device's.
-constexpr long VA_SHORT = 256 * 1024;
+// regs: key steps of a wave up to which a workgroup walks a head's whole cache alone, because splitting it saves less than the
+// fold's launch costs.  A wave's step costs what its type and width make it cost, and the line lies where every count of heads (1 to 96
+// sequences times heads) and tree of 8 to 128 nodes was no slower without splits.  us of a call, with splits / without, at the line and
+// at the next step of a wave:
+//   bf16, 128 wide   4 (512 rows)   8 heads, T = 64 11.3 / 9.9; 32 heads 13.7 / 11.1; 640 rows 11.7 / 12.2, 13.9 / 13.8; 768 12.1 / 12.5, 14.0 / 14.6
+//   bf16, 64 wide    6 (768 rows)   8 heads, T = 64 9.9 / 9.2; 52 heads 11.4 / 10.9; 1024 rows, 32 heads 11.0 / 11.7; 52 heads 11.7 / 12.0
+//   float32, 128     2 (128 rows)   8 heads, T = 64 13.3 / 12.5; 160 rows, T = 32 12.5 / 13.5, T = 96 13.6 / 14.5
+//   float32, 64      3 (192 rows)   8 heads, T = 96 10.0 / 9.7; 256 rows 10.0 / 10.7.  But 4 where a step has few queries (T = 16 7.8 / 6.2)
+//                                   or the chip has no room to cut the walk into steps of one (24 heads, T = 96 12.0 / 10.8).
+// The rule reads the capacity: the lengths are the device's.
+static int va_alone(int T, int d_h, int elem_bytes, int splits) {
+  if (elem_bytes == 2) return d_h == 64 ? 6 : 4;
+  return d_h != 64 ? 2 : (T <= 16 || splits < 4) ? 4 : 3;
+}
 
 // force: -1 chooses by shape, 0 = registers, 1 = LDS ring
 static VaPlan va_plan(int B, int T, int n_heads, int d_h, int max_kv, int elem_bytes, int force) {
@@ -658,7 +666,7 @@ static VaPlan va_plan(int B, int T, int n_heads, int d_h, int max_kv, int elem_b
   const int cap = (max_steps + 3) / 4;
   if (s > cap) s = cap;
   if (s > 32) s = 32;
-  if (s < 1 || (long)max_kv * d_h * 2 * elem_bytes <= (elem_bytes == 4 ? VA_SHORT / 2 : VA_SHORT)) s = 1;
+  if (s < 1 || cap <= va_alone(T, d_h, elem_bytes, s)) s = 1;   // (cap: key steps of a wave without splits)
   // ring: when a workgroup walks a whole head anyway (no room for key splits) and the walk is long, or when the
   // register kernel would need more workgroups than there are compute units (measured: 32 heads, T = 64, L = 1024:
   // batch 1 15.4 us regs / 17.3 ring, batch 4 21.1 / 23.2, batch 8 40.6 / 31.0; 40 heads, L = 2048, batch 4: 57.8 / 46.4)

@@ -63,12 +63,12 @@ KERNELS = [0, 1]        # amph_verify_kernel: operands through registers / throu
 KERNEL_IDS = ["regs", "ring"]
 
 
-def verify_case(cfg, T, caps, L, B_=1, seed=21, heads=None, lens=None, kernel=-1):
+def verify_case(cfg, T, caps, L, B_=1, seed=21, heads=None, lens=None, kernel=-1, max_kv=None):
     K = len(caps)
     cfgx = si.with_(cfg, batch=B_, K=K, topk=min(16, max(caps)))
     lens = [L] * B_ if lens is None else list(lens)      # committed rows per batch element (L = the largest)
     assert max(lens) == L and len(lens) == B_
-    max_kv = (L + T + 31) // 32 * 32 + 32
+    max_kv = max_kv or (L + T + 31) // 32 * 32 + 32
     ctx = make_ctx(cfgx, T=T, batch=B_, max_kv=max_kv)
     ctx.amph_verify_kernel(kernel)
     paths = si.tree_paths(T, caps)
