@@ -554,8 +554,10 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
   const int P = (n + GW_ST - 1) / GW_ST;                   // stages
   const int nblk = gemm_blocks(EPI, a.seg_rows);
 
-  // Loads go through buffer descriptors: per block (tile) a lane's offset that stays, and one scalar offset that moves along the reduction
-  // axis (added up in vector registers for every load, the addresses took as many issue slots as the matrix instructions).
+  // Loads go through buffer descriptors: per block (tile) a lane's offset that stays, and one scalar that moves along the reduction
+  // axis (added up in vector registers for every load, the addresses took as many issue slots as the matrix instructions).  For the
+  // weights it is a 32-bit offset (gemm_is_wide leaves a workgroup's weights of 4 GiB and more to the skinny kernel), for the activations,
+  // of which there can be more, the descriptor's base.
   // Weights: this wave's step of every block of a stage, contiguous 1 KB pieces.  Lane l has piece l % 4 of row l / 4; in LDS a row's
   // pieces are permuted (piece g at g ^ (row / 4)), which leaves the fragment reads free of bank conflicts.  Blocks past the
   // end re-read the last one and are never stored, steps past the slice its last one and are never multiplied.
@@ -563,16 +565,16 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
   const auto w_rsrc = gw_rsrc((const unsigned char *)a.wt + (size_t)tile * NB * total_steps * 1024, (unsigned)blocks_here * total_steps * 1024u);
   const int wdst = wave * 1024 + (lane >> 2) * 64 + (((lane & 3) ^ (lane >> 4)) & 3) * 16;
   constexpr bool WO = NP < 6;                               // a block's offset in a vector register of its own, or (where these are scarce) a scalar one
-  int wo[NB];
+  unsigned wo[NB];
   #pragma unroll
-  for (int b = 0; b < NB; ++b) wo[b] = min(b, blocks_here - 1) * total_steps * 1024 + (WO ? lane * 16 : 0);
+  for (int b = 0; b < NB; ++b) wo[b] = (unsigned)(min(b, blocks_here - 1) * total_steps) * 1024u + (WO ? lane * 16 : 0);
   u32x4 wr[NB];
-  auto w_at = [&](int p) { return (s0 + min(p * GW_ST + wave, n - 1)) * 1024; };
-  auto load_w = [&](int at, int b) { return WO ? __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, wo[b], at, 2) : __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, lane * 16, at + wo[b], 2); };   // non-temporal
+  auto w_at = [&](int p) { return (unsigned)(s0 + min(p * GW_ST + wave, n - 1)) * 1024u; };
+  auto load_w = [&](unsigned at, int b) { return WO ? __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, wo[b], at, 2) : __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, lane * 16, at + wo[b], 2); };   // non-temporal
   auto store_w = [&](int b, int slot, const u32x4 &w) { *reinterpret_cast<u32x4 *>(gw_lds + slot * STAGE + b * (GW_ST * 1024) + wdst) = w; };
   // Activations: sixteens past the end re-read the last one and are never stored, steps past the slice the last one
-  const auto x_rsrc = gw_rsrc((const unsigned char *)a.xt, (unsigned)total_steps * (unsigned)m32_tiles * 2048u);
-  auto x_at = [&](int i) { return (s0 + min(i, n - 1)) * m32_tiles * 2048; };
+  const unsigned x_step = (unsigned)m32_tiles * 2048u;      // bytes of a step
+  auto x_at = [&](int i) { return (const unsigned char *)a.xt + (size_t)(unsigned)(s0 + min(i, n - 1)) * x_step; };
   const int woff = r16 * 64 + ((g ^ (r16 >> 2)) & 3) * 16;
   u32x4 wf[2][NP];
   // fragment b of half-step j of the stage in slot u: half of the blocks against one step
@@ -584,19 +586,19 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
     #pragma unroll
     for (int i = 0; i < NS; ++i) xo[i] = min(sub_of(i), 2 * m32_tiles - 1) * 1024 + lane * 16;
     u32x4 xq[XD][NS];
-    auto load_x = [&](int at, int i) { return __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, xo[i], at, 0); };
+    auto load_x = [&](const unsigned char *at, int i) { return __builtin_amdgcn_raw_buffer_load_b128(gw_rsrc(at, x_step), xo[i], 0, 0); };
     f32x4 acc[NB][NS];
     #pragma unroll
     for (int b = 0; b < NB; ++b)
       #pragma unroll
       for (int i = 0; i < NS; ++i) { acc[b][i] = (f32x4){0.f, 0.f, 0.f, 0.f}; asm volatile("" : "+a"(acc[b][i])); }
     {
-      const int w0 = w_at(0), w1 = w_at(1);
+      const unsigned w0 = w_at(0), w1 = w_at(1);
       #pragma unroll
       for (int b = 0; b < NB; ++b) wr[b] = load_w(w0, b);
       #pragma unroll
       for (int i = 0; i < XD - 1; ++i) {
-        const int at = x_at(i);
+        const unsigned char *at = x_at(i);
         #pragma unroll
         for (int t = 0; t < NS; ++t) xq[i][t] = load_x(at, t);
       }
@@ -609,9 +611,9 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
     #pragma unroll
     for (int b = 0; b < NP; ++b) wf[0][b] = read_w(0, 0, b);
     constexpr int HSN = 2 * GW_ST, W0 = 1, WN = 4, WB = (NB + WN - 1) / WN;      // half-steps of a stage; the WN from W0 on write the next one
-    int xp = 0;                                            // the activations' offset in this step's loads
+    const unsigned char *xp = nullptr;                     // where this half-step's loads of activations are from
     // jtag: half-step of stage p; utag: the stage's slot p % 2; whole: all the stage's steps are in the slice.  False: the slice has ended.
-    auto half_step = [&](int p, int wp, auto jtag, auto utag, auto whole) {
+    auto half_step = [&](int p, unsigned wp, auto jtag, auto utag, auto whole) {
       constexpr int j = decltype(jtag)::value, u = decltype(utag)::value, MN = NP * NS;
       const int i = p * GW_ST + (j >> 1);
       if (!decltype(whole)::value && (j & 1) == 0 && i >= n) return false;  // (the same for every wave)
@@ -655,7 +657,7 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
       return true;
     };
     auto stage = [&](int p, auto utag, auto whole) {
-      const int wp = w_at(p + 2);
+      const unsigned wp = w_at(p + 2);
       static_assert(HSN == 8, "the half-steps below");
       (void)(half_step(p, wp, GemmTag<0>{}, utag, whole) && half_step(p, wp, GemmTag<1>{}, utag, whole) &&
              half_step(p, wp, GemmTag<2>{}, utag, whole) && half_step(p, wp, GemmTag<3>{}, utag, whole) &&
@@ -1053,7 +1055,7 @@ static int gemm_split(int epi, int seg_rows, int Kd, int elem_bytes, int M, bool
 // float32 keeps to the skinny kernel, whose sums row-major weights have.
 bool gemm_is_wide(int epi, int seg_rows, int Kd, int elem_bytes, int M, bool tiled) {
   const int mblocks = (M + GM_BM - 1) / GM_BM;
-  if (!tiled || mblocks < 2 || gemm_xt_bytes(M, Kd, elem_bytes) > 0x7fffffffu) return false;   // (the wide kernel's offsets have 32 bits)
+  if (!tiled || mblocks < 2 || (long long)Kd * elem_bytes / 64 * (2 * GW_MAX_NP * 1024) > 0xffffffffLL) return false;   // (offsets in a workgroup's weights have 32 bits)
   if (mblocks > 2) return true;
   if (elem_bytes == 4) return false;
   const int split = gemm_split(epi, seg_rows, Kd, elem_bytes, M, tiled);

@@ -158,3 +158,12 @@ def test_wide_gemm_instances_of_the_head(case):
 def test_wide_gemm_at_model_width(cfg, T, Bsz):
     say(f"one layer of {cfg.name} over {T * Bsz} rows")
     run_twins((cfg.dtype, T, Bsz, cfg.d_model, cfg.head_dim, cfg.d_ffn, set()), 1, cfg.d_model, cfg.d_ffn, cfg.vocab)
+
+
+def test_wide_gemm_over_more_than_4_gib_of_activations():
+    """W_down of 128 x 278,528 over 8,192 rows, 4.6 GB of them."""
+    case = ("bf16", 128, 64, 128, 64, 278528, set())
+    down = wp.instance("bf16", wp.STORE, 128, 278528, 8192)
+    say(f"one layer of 128 x 278528 over 8192 rows: W_down on {down}")
+    assert down
+    run_twins(case, 1, 128, 278528, 512)

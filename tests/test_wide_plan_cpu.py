@@ -40,3 +40,13 @@ def test_every_instance_that_the_plan_selects_has_a_case():
 def test_two_blocks_of_rows_as_their_test_says(cfg, M, wide):
     gemms = zip(["qkv", "wo", "gate_up", "down", "head"], wp.layer_gemms(cfg.d_model, cfg.d_ffn) + [(wp.ARGMAX, cfg.vocab, cfg.d_model)])
     assert [n for n, g in gemms if wp.instance(cfg.dtype, *g, M)] == wide.split()
+
+
+@pytest.mark.parametrize("dt,epi", [("bf16", wp.STORE), ("bf16", wp.QKV), ("bf16", wp.SWIGLU), ("bf16", wp.ARGMAX), ("f32", wp.STORE)])
+def test_large_operands(dt, epi):
+    """Activations of 2 GiB and more, and of more than 4, are the wide kernel's; its offsets in a workgroup's weights have 32 bits: what
+    sixteen blocks would need more for is the skinny one's."""
+    for M in (129, 8192):
+        for row_bytes in ((1 << 18) - 64, 1 << 18, (1 << 18) + 64, 1 << 19, (1 << 19) + 64, (1 << 24) - 64):
+            assert wp.plan(dt, epi, 256, row_bytes // wp.ELEM[dt], M).wide, (M, row_bytes)
+        assert not wp.plan(dt, epi, 256, (1 << 24) // wp.ELEM[dt], M).wide
