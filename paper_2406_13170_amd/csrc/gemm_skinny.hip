@@ -636,7 +636,8 @@ void k_gemm_wide(const GemmArgs a, int tiles, int mgroups, int m32_tiles, int gt
           #pragma unroll
           for (int t = 0; t < NS; ++t) {
             gw_mma<T>(acc[(j & 1) * NP + b][t], wf[j & 1][b], xq[(j >> 1) % XD][t]);
-            const int m = b * NS + t, k = (m * ops + MN - 1) / MN;           // (at most three of them fall behind one instruction)
+            static_assert(ops <= 3 * MN, "at most three of them fall behind one instruction");
+            const int m = b * NS + t, k = (m * ops + MN - 1) / MN;
             if (k * MN < (m + 1) * ops) op(k);
             if ((k + 1) * MN < (m + 1) * ops) op(k + 1);
             if ((k + 2) * MN < (m + 1) * ops) op(k + 2);
