@@ -784,14 +784,16 @@ constexpr int LM_MOST_BF16 = 4;                            // and in the LM head
 template <typename T> static inline bool use_mm_head(int M, int V, int Kd) {
   return use_mm<T>(M, (size_t)V * Kd) && (M > LM_MOST_BF16 || (size_t)V * Kd <= DRAFT_MM_SMALL || (size_t)M * Kd * 4 > 80 * 1024);
 }
-// rows of every launch when M rows are served in as few launches as possible, evenly
-static inline int mm_chunk(int M) {
-  const int n = (M + DRAFT_MM_ROWS - 1) / DRAFT_MM_ROWS;
+// rows of every launch when M rows of `width` floats are served in as few launches as possible, evenly (a launch's offsets in its
+// activations have 31 bits)
+static inline int mm_chunk(int M, int width) {
+  const int most = (int)std::max(1LL, std::min((long long)DRAFT_MM_ROWS, 0x7fffffffLL / ((long long)width * 4)));
+  const int n = (M + most - 1) / most;
   return (M + n - 1) / n;
 }
-#define MM_CHUNKS(CALL)                                      \
+#define MM_CHUNKS(width, CALL)                               \
   do {                                                       \
-    const int ch_ = mm_chunk(M);                             \
+    const int ch_ = mm_chunk(M, width);                      \
     for (int m0 = 0; m0 < M; m0 += ch_) {                    \
       const int m = std::min(ch_, M - m0);                   \
       hipError_t e_ = (CALL);                                \
@@ -816,7 +818,7 @@ hipError_t launch_fc_concat(hipStream_t st, const void *W, const float *u, const
                             int vocab, int d, int M, float *out, uint32_t *dev_status, float *slabs, const LastRows &last) {
   if (M < 1 || d % 8) return hipErrorInvalidValue;
   if (use_mm<T>(M, (size_t)d * 2 * d) && d % 256 == 0)
-    MM_CHUNKS(draft_mm_fc(st, W, u + (size_t)m0 * d, embed, tok + m0, vocab, d, m, out + (size_t)m0 * d, dev_status, slabs, last.from(m0)));
+    MM_CHUNKS(d, draft_mm_fc(st, W, u + (size_t)m0 * d, embed, tok + m0, vocab, d, m, out + (size_t)m0 * d, dev_status, slabs, last.from(m0)));
   int mc = gv_rows_per_launch(M, gv_xs_bytes<T>(1, 2 * d), 0);
   // rows that fit only without their other half: two launches over d columns each
   const int mch = gv_rows_per_launch(M, gv_xs_bytes<T>(1, d), 0);
@@ -843,7 +845,7 @@ hipError_t launch_sal_qkv(hipStream_t st, const amph_layer_w &lw, const float *x
                           uint32_t *dev_status, int R, const int32_t *n_valid) {
   if (M < 1 || d % 8 || d_h % 4) return hipErrorInvalidValue;
   if (use_mm<T>(M, (size_t)3 * d * d) && d % 16 == 0 && d_h % 16 == 0)
-    MM_CHUNKS(draft_mm_sal_qkv(st, lw, x + (size_t)m0 * d, d, n_heads, d_h, m, eps, theta, sal_len, max_kv, kv_stage,
+    MM_CHUNKS(d, draft_mm_sal_qkv(st, lw, x + (size_t)m0 * d, d, n_heads, d_h, m, eps, theta, sal_len, max_kv, kv_stage,
                                qbuf + (size_t)m0 * d, dev_status, m0, R, n_valid));
   const int mc = gv_rows_per_launch(M, gv_xs_bytes<T>(1, d) + 16, 0);
   if (mc < 1) return hipErrorInvalidValue;
@@ -884,7 +886,7 @@ hipError_t launch_linear(hipStream_t st, const void *w0, const void *w1, const v
   // (its rows travel in 16-byte pieces straight into LDS; the vector kernel takes them from any float address)
   const bool x_pieces = ((uintptr_t)x & 15) == 0 && ldx % 4 == 0;
   if (use_mm<T>(M, (size_t)n_seg * seg_rows * Kd) && x_pieces)
-    MM_CHUNKS(draft_mm_linear(st, w0, w1, w2, n_seg, seg_rows, Kd, x + (size_t)m0 * ldx, ldx, m, res ? res + (size_t)m0 * ldo : nullptr,
+    MM_CHUNKS(ldx, draft_mm_linear(st, w0, w1, w2, n_seg, seg_rows, Kd, x + (size_t)m0 * ldx, ldx, m, res ? res + (size_t)m0 * ldo : nullptr,
                               o0 + (size_t)m0 * ldo, o1 ? o1 + (size_t)m0 * ldo : nullptr, o2 ? o2 + (size_t)m0 * ldo : nullptr, ldo,
                               slabs, last.from(m0)));
   int mc = std::min(GV_MOST<T>, gv_rows_per_launch(M, gv_xs_bytes<T>(1, Kd), 0));
@@ -921,7 +923,7 @@ template <typename T>
 hipError_t launch_gate_up(hipStream_t st, const amph_layer_w &lw, const float *x, int d, int f, int M, float eps,
                           float *act) {
   if (M < 1 || d % 8) return hipErrorInvalidValue;
-  if (use_mm<T>(M, (size_t)2 * f * d)) MM_CHUNKS(draft_mm_gate_up(st, lw, x + (size_t)m0 * d, d, f, m, eps, act + (size_t)m0 * f));
+  if (use_mm<T>(M, (size_t)2 * f * d)) MM_CHUNKS(d, draft_mm_gate_up(st, lw, x + (size_t)m0 * d, d, f, m, eps, act + (size_t)m0 * f));
   const int mc = gv_rows_per_launch(M, gv_xs_bytes<T>(1, d) + 16, 0);
   if (mc < 1) return hipErrorInvalidValue;
   for (int m0 = 0; m0 < M; m0 += mc) {
@@ -941,7 +943,7 @@ hipError_t launch_head_mlp(hipStream_t st, const void *w_mlp, const void *pe, co
                            int K, int M, float *Hp) {
   if (M < 1 || d % 8) return hipErrorInvalidValue;
   if (use_mm<T>(M, (size_t)K * d * d))
-    MM_CHUNKS(draft_mm_head_mlp(st, w_mlp, pe, h1 + (size_t)m0 * d, h2 + (size_t)m0 * d, d, K, m, Hp + (size_t)m0 * K * d));
+    MM_CHUNKS(d, draft_mm_head_mlp(st, w_mlp, pe, h1 + (size_t)m0 * d, h2 + (size_t)m0 * d, d, K, m, Hp + (size_t)m0 * K * d));
   int mc = gv_rows_per_launch(M, 2 * gv_xs_bytes<T>(1, d), 0);
   // rows that fit only with one of the two sources staged: one launch for the heads of each source
   const int mch = gv_rows_per_launch(M, gv_xs_bytes<T>(1, d), 0);
@@ -985,7 +987,7 @@ hipError_t launch_lmhead_cands(hipStream_t st, const void *W, int V, int Kd, con
     const int wgs = draft_mm_lmhead_wgs(V);
     int *ci = reinterpret_cast<int *>(ws + (size_t)M * wgs * k);
     *n_cand = wgs * k;
-    MM_CHUNKS(draft_mm_lmhead(st, W, V, Kd, x + (size_t)m0 * Kd, m, k, logits ? logits + (size_t)m0 * V : nullptr,
+    MM_CHUNKS(Kd, draft_mm_lmhead(st, W, V, Kd, x + (size_t)m0 * Kd, m, k, logits ? logits + (size_t)m0 * V : nullptr,
                               ws + (size_t)m0 * wgs * k, ci + (size_t)m0 * wgs * k));
   }
   const int mc = gv_rows_per_launch(M, gv_xs_bytes<T>(1, Kd), 8 * 64 * LMTK_NPT * sizeof(float));

@@ -31,6 +31,23 @@ def test_projection_error_against_64_bits(M, N, K):
     assert err < 5e-7, err
 
 
+def test_projection_of_more_than_4_gib_of_rows():
+    """Eight rows of 134,218,752 floats against sixteen of bf16."""
+    M, N, K = 8, 16, (1 << 27) + 1024
+    say(f"projection M={M} N={N} K={K}")
+    g = torch.Generator(device=DEV).manual_seed(7)
+    W = torch.empty((N, K), dtype=torch.bfloat16, device=DEV).normal_(0.0, 0.02, generator=g)
+    x = torch.empty((M, K), device=DEV).normal_(0.0, 1.0, generator=g)
+    y = torch.full((M, N), float("nan"), device=DEV)
+    make_ctx(si.MINI).amph_gemv(x, W, y, M, N, K)
+    ref = torch.zeros((M, N), dtype=torch.float64, device=DEV)
+    for c in range(0, K, 1 << 22):
+        ref += x[:, c:c + (1 << 22)].double() @ W[:, c:c + (1 << 22)].double().t()
+    # a wave adds 524,292 steps up in runs of 16: chains of 32,768 rounded sums, about sqrt(32768) / 2 half-ulps of the running sum
+    err = float((y.double() - ref).norm() / ref.norm())
+    assert err < 1.1e-5, err
+
+
 # rows that begin at any float: one matrix that is small, one that is not
 @pytest.mark.parametrize("N,K", [(515, 520), (4100, 1032)])
 @pytest.mark.parametrize("M", [1, 5, 8])
