@@ -977,17 +977,21 @@ static GemmPlan plan_skinny(int epi, int seg_rows, int Kd, int elem_bytes, int M
   return best;
 }
 
-// The wide kernel's tiles for a given split: groups of gt tiles of 32 activation rows (up to three a wave) against nb weight row
-// blocks.  The price is in us, fitted to 2840 measurements at 7B, 13B and 33B widths over 80 to 768 rows (5 % deviation; its picks take
-// 11.02 ms over them where the best ones take 10.98): per step of 64 bytes of k the matrix cores take their time for the blocks
-// and tiles of the busiest wave, and the workgroup takes in 2 KB for every tile and 1 KB for every block (of which several
-// groups share the way from HBM), faster on a chip that is not full.  A compute unit has one workgroup at a time, and the workgroups are dealt to the XCDs in
-// eights: 252 of them in three groups can mean 33 on one XCD and a second round (6656 x 17920 over 320 rows: 172 us against 106).
-// float32 takes eight times as long for a step's matrix-core work.
+// The wide kernel's tiles for a given split: groups of gt tiles of 32 activation rows (up to six sixteens a wave) against nb weight row
+// blocks.  The price is in us.  A step of 64 bytes of k takes what lasts longer: the matrix instructions of the busiest wave and the
+// fragments that it reads from LDS for them, at a clock that is lower the fuller the chip and the busier the other waves (in bf16, where the power
+// sets it); or what the workgroup takes in, 2 KB for every tile, from further away the more rows there are, and 1 KB for every block (of which
+// the groups share the way from HBM), faster on a chip that is not full.  A part of the shorter one does not hide behind it.  A compute
+// unit has one workgroup at a time, and the workgroups are dealt to the XCDs in eights: 252 of them in three groups can mean 33 on one
+// XCD and a second round (6656 x 17920 over 320 rows: 172 us against 106).
+// Fitted to 21,916 measurements of launches in a row (bf16 at 7B, 13B and 33B widths and 2048 over 80 to 768 rows, at nine widths from 512
+// to 8192 over 65 to 128, at four over 208 to 8192; float32 at five widths from 256 to 4096 over 144 to 768): 6 % deviation.  Over the shapes the
+// picks take 39.42 ms where the best plans take 39.18 (80 to 768 rows), 9.66 where 9.62 (65 to 128), 24.07 where 24.00 (208 to 8192), and
+// 39.73 where 39.69 (float32).  (The price of the 32 x 32 form took 39.62, 9.67, 24.14 and 41.75.)
 static GemmPlan plan_wide(int epi, int seg_rows, int Kd, int elem_bytes, int M, int split) {
   GemmPlan best{};
   const int blocks = gemm_blocks(epi, seg_rows);
-  const double steps = (double)(Kd * elem_bytes / 64 + split - 1) / split;
+  const int steps = (Kd * elem_bytes / 64 + split - 1) / split;
   best.blocks = blocks;
   best.wide = true;
   best.split = split;
@@ -996,13 +1000,16 @@ static GemmPlan plan_wide(int epi, int seg_rows, int Kd, int elem_bytes, int M, 
   for (int mg = (mt + most - 1) / most; mg <= (mt + 2) / 3; ++mg) {   // (three tiles or more a group)
     const int gt = (mt + mg - 1) / mg, tw = (gt + GW_W - 1) / GW_W;
     if ((mg - 1) * gt >= mt) continue;                                // fewer groups of as many tiles do
+    const int ns = (std::min(2 * gt, (M + 15) / 16) + GW_W - 1) / GW_W;   // sixteens of the busiest wave
     for (int np = 2; np <= GW_MAX_NP; ++np) {
       if (!gw_built(elem_bytes, np, tw)) continue;
       const int nb = 2 * np, tiles = (blocks + nb - 1) / nb;
       const long on_xcd = (long)((tiles * split + 7) / 8) * mg, rounds = (on_xcd + 31) / 32;
       const double full = (double)on_xcd / (32.0 * rounds);
-      const double step = 0.0176 * np * tw * (elem_bytes == 4 ? 8 : 1) + (0.0137 * gt + 0.0204 * nb * (mg > 1 ? 0.75 : 1.0)) * (0.47 + 0.53 * full) + 0.045;
-      const double cost = (double)rounds * (steps * step + 2.1 + 0.78 * np * tw) * (np == 2 && tw > 1 ? 1.03 : 1.0);
+      const double mma = elem_bytes == 4 ? nb * (0.0472 * ns + 0.0034) : nb * (0.0037 * ns + 0.0034) * (1.0 + full * (0.748 * gt / ns - 0.576));
+      const double intake = (0.0151 * gt * (1.0 + 0.0037 * mt) + 0.0215 * nb * (0.43 + 0.57 / mg)) * (0.65 + 0.35 * full);
+      const double step = std::max(mma, intake) + 0.309 * std::min(mma, intake) + 0.052;
+      const double cost = (double)rounds * (steps * step + 0.585 + 0.213 * nb * ns) + 1.91;
       if (cost < best.cost) { best.cost = cost; best.nb = nb; best.tiles = tiles; best.mgroups = mg; best.tw = tw; best.gt = gt; }
     }
   }
@@ -1012,47 +1019,30 @@ static GemmPlan plan_wide(int epi, int seg_rows, int Kd, int elem_bytes, int M, 
 // Slabs that the reduction axis of a matrix is cut into.  The one choice of a plan that the result depends on: inside a
 // slab both kernels add the same products in the same order, so their bits are the same.  Therefore it is a rule on the shape
 // alone.  Up to 128 rows it is the skinny kernel's, for whichever kernel runs and however the weights are stored: tiled and
-// row-major weights give the same bits there.  Beyond (tiled weights), bf16 matrices of 16 Mi elements and more: the count of 1, 2 or 4
-// whose plan is priced lowest with 0.9 us a further slab of a million outputs (its way out of the kernel and into the next one).
-// Measured over W_o and W_down at 7B, 13B and 33B widths and 144 to 768 rows, with 1, 2, 4 and 8 slabs each: the picks take 11 us
-// more than the best of each, the rule before them 354 (of about 2500; us, before / now: W_down 7B over 512 rows 52 / 44, 33B over 384
-// 99 / 84, 13B over 768 111 / 86; W_o 7B over 512 28 / 23).  Eight were best at three of the 48 shapes, by 2 us at most.
-// Smaller matrices keep the rule made for an earlier form of the kernel (groups of up to 8, 12 or 16 tiles, at most
-// six blocks a workgroup): it weighs, in units of a weight fragment, a workgroup's steps times its fragments per step and the tiles of its
-// busiest SIMD against the slabs' way out and back.  Their launches are mostly prologue and epilogue, which neither price describes.
+// row-major weights give the same bits there.  Beyond (tiled weights), the count whose plan is priced lowest with 0.6 us a further slab and 0.9
+// for every million of its outputs (its way out of the kernel and into the next one).
+// Measured with the fold behind the launch, W_o and W_down over 129 to 768 rows, ms of all shapes of a size with these picks / with the
+// best: bf16 from 512 x 512 to 1 Mi weights 0.22 / 0.20, to 4 Mi 0.40 / 0.38, to 16 Mi 1.20 / 1.18, beyond (to 6656 x 17920) 4.36 / 4.33;
+// float32 from 256 x 256 0.58 / 0.58, 0.47 / 0.47, 1.09 / 1.08, 3.37 / 3.34.
 static int gemm_split(int epi, int seg_rows, int Kd, int elem_bytes, int M, bool tiled) {
   if (epi != EPI_STORE) return 1;                           // fused epilogues need complete sums
   if (!tiled || M <= 2 * GM_BM) return plan_skinny(epi, seg_rows, Kd, elem_bytes, M, 0).split;
-  const int blocks = gemm_blocks(epi, seg_rows), steps = Kd * elem_bytes / 64, mt = (M + 31) / 32;
+  const int steps = Kd * elem_bytes / 64;
   double best_cost = 1e300;
   int best = 1;
-  if (elem_bytes == 2 && (long long)seg_rows * Kd >= (1 << 24)) {
-    for (int s = 1; s <= 4 && (s == 1 || steps / s >= 16); s *= 2) {
-      const double cost = plan_wide(epi, seg_rows, Kd, elem_bytes, M, s).cost + 0.9e-6 * M * seg_rows * (s - 1);
-      if (cost < best_cost) { best_cost = cost; best = s; }
-    }
-    return best;
-  }
-  for (int most = 8; most <= 16; most += 4) {
-    const int mg = (mt + most - 1) / most, gt = (mt + mg - 1) / mg;
-    if (most > 8 && gt <= 8) continue;
-    const double simd_tiles = most == 16 ? 0.92 * ((gt + 3) / 4) : most == 12 ? ((gt + 2) / 3 + 3) / 4 * 3 : ((gt + 1) / 2 + 3) / 4 * 2;
-    for (int s = 1; s <= 8 && (s == 1 || steps / s >= 16); s *= 2)
-      for (int nb = 2; nb <= 6 && nb <= std::max(blocks, 2); nb += 2) {
-        const long rounds = ((long)((blocks + nb - 1) / nb) * s * mg + 255) / 256;
-        const double cost = (double)rounds * ((steps + s - 1) / s) * (nb + 2) * (simd_tiles / 2) + ((double)M * seg_rows * 1.0e-4 + 2.0) * (s - 1);
-        if (cost <= best_cost) { best_cost = cost; best = s; }
-      }
+  for (int s = 1; s <= 8 && (s == 1 || steps / s >= 16); s *= 2) {
+    const double cost = plan_wide(epi, seg_rows, Kd, elem_bytes, M, s).cost + (0.9e-6 * M * seg_rows + 0.6) * (s - 1);
+    if (cost < best_cost) { best_cost = cost; best = s; }
   }
   return best;
 }
 
 // Which kernel.  Up to 64 rows the skinny one, from 129 on the wide one.  In between (two blocks of 64 rows, or three and
 // four tiles of 32) mostly the wide one; the skinny kernel still does better where the matrix is small, or one round of its
-// workgroups with a split axis (us, skinny / wide, 128 rows: 2048 x 2048 7.0 / 9.0, 6144 x 2048 13.0 / 15.5, 4096 x 4096
-// 13.7 / 15.9, 5120 x 5120 18.1 / 20.6; but 12288 x 4096 36 / 34, 5120 x 13824 45 / 34, 27648 x 5120 84 / 57, 32000 x 4096 80 / 50).  Prices in
-// us for equal slabs, 5 % off over 90 pairs of measurements at model widths from 2048 to 8192 and 65 to 128 rows: always the
-// wide kernel takes 3890 us over all of them, always the skinny one 5042, this rule 3864, the better choice each time 3861.
+// workgroups with a split axis (us, skinny / wide, 128 rows: QKV 2048 wide 13.6 / 14.4, 3072 21.6 / 22.7, W_o 4096 x 4096 13.6 / 14.3,
+// 5120 x 5120 18.0 / 19.7; but W_down 4096 x 11008 29.0 / 25.2, gate/up 2 x 11008 x 4096 44 / 38, QKV 5120 wide 46 / 40, the head
+// 32000 x 4096 73 / 48).  Prices in us for equal slabs; over 315 shapes at nine widths from 512 to 8192 and 65 to 128 rows: always the
+// wide kernel takes 9659 us over all of them, always the skinny one 12837, this rule 9585, the better choice each time 9572.
 // float32 keeps to the skinny kernel, whose sums row-major weights have.
 bool gemm_is_wide(int epi, int seg_rows, int Kd, int elem_bytes, int M, bool tiled) {
   const int mblocks = (M + GM_BM - 1) / GM_BM;
@@ -1061,9 +1051,9 @@ bool gemm_is_wide(int epi, int seg_rows, int Kd, int elem_bytes, int M, bool til
   if (elem_bytes == 4) return false;
   const int split = gemm_split(epi, seg_rows, Kd, elem_bytes, M, tiled);
   const GemmPlan s = plan_skinny(epi, seg_rows, Kd, elem_bytes, M, split), w = plan_wide(epi, seg_rows, Kd, elem_bytes, M, split);
-  const double steps = (double)(Kd * elem_bytes / 64) / split, slab = epi == EPI_STORE ? 1.0e-6 * M * seg_rows * split : 0.0;
-  const double us_s = (double)(((long)s.tiles * split * mblocks + 255) / 256) * (3.5 + steps * (0.0254 * s.nb + 0.0654)) + 0.36 * slab;
-  return 1.06 * w.cost + 0.2 < us_s;
+  const double steps = (double)(Kd * elem_bytes / 64) / split;
+  const double us_s = (double)(((long)s.tiles * split * mblocks + 255) / 256) * (2.4 + steps * (0.0273 * s.nb + 0.0446)) + 2.27;
+  return w.cost + 1.2 < us_s;
 }
 
 GemmPlan gemm_plan(int epi, int seg_rows, int Kd, int elem_bytes, int M, int split_req, bool tiled) {

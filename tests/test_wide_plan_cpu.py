@@ -50,3 +50,31 @@ def test_large_operands(dt, epi):
         for row_bytes in ((1 << 18) - 64, 1 << 18, (1 << 18) + 64, 1 << 19, (1 << 19) + 64, (1 << 24) - 64):
             assert wp.plan(dt, epi, 256, row_bytes // wp.ELEM[dt], M).wide, (M, row_bytes)
         assert not wp.plan(dt, epi, 256, (1 << 24) // wp.ELEM[dt], M).wide
+
+
+# What launches in a row took (us) with some of their plans (row blocks a workgroup, groups of rows): groups of five, six, nine and ten
+# tiles, whose busiest wave has three or five sixteens of rows; float32.
+MEASURED = [
+    ("bf16", wp.QKV, 5120, 5120, 352, 1, {(8, 2): 60.1, (4, 1): 70.2}),
+    ("bf16", wp.STORE, 5120, 13824, 144, 4, {(6, 1): 36.9, (10, 2): 42.8}),
+    ("bf16", wp.STORE, 5120, 13824, 256, 1, {(4, 3): 75.7, (4, 2): 87.7}),
+    ("bf16", wp.STORE, 6656, 17920, 352, 2, {(8, 2): 94.0, (4, 1): 108.7}),
+    ("bf16", wp.STORE, 6656, 17920, 640, 4, {(8, 2): 139.4, (10, 3): 158.1}),
+    ("bf16", wp.STORE, 6656, 6656, 512, 1, {(8, 4): 58.1, (4, 2): 65.8}),
+    ("f32", wp.QKV, 2048, 2048, 336, 1, {(4, 2): 93.0, (8, 3): 121.9}),
+    ("f32", wp.SWIGLU, 5632, 2048, 144, 1, {(4, 1): 92.6, (8, 2): 118.0}),
+    ("f32", wp.STORE, 4096, 11008, 576, 1, {(4, 4): 460.7, (8, 6): 610.1}),
+]
+
+
+@pytest.mark.parametrize("dt,epi,rows,Kd,M,split,us", MEASURED, ids=lambda x: str(x) if not isinstance(x, dict) else "")
+def test_picks_are_the_fast_plans(dt, epi, rows, Kd, M, split, us):
+    p = wp.plan(dt, epi, rows, Kd, M, split)
+    assert us.get((p.nb, p.mgroups)) == min(us.values()), (p.nb, p.mgroups)
+    assert abs(p.cost / min(us.values()) - 1) < 0.2                    # (it deviates by 6 % over thousands of them)
+
+
+@pytest.mark.parametrize("shapes", [[(2048, 8160), (2048, 8192)], [(4096, 4064), (4096, 4096), (4096, 4128)]], ids=str)
+def test_slabs_do_not_jump_between_like_shapes(shapes):
+    for M in (144, 256, 384, 512, 768):
+        assert len({wp.plan("bf16", wp.STORE, rows, Kd, M).split for rows, Kd in shapes}) == 1, M
