@@ -456,8 +456,8 @@ __global__ __launch_bounds__(64 * (GM_MAX_NB + GM_NLW)) void k_gemm_skinny(const
 // chip and on normally distributed values the clock is what the power allows, and that is more for the smaller one: 1.97 PFLOP/s
 // (2.14 GHz) against 1.79 (1.86 GHz) for endless instructions on registers.  (An earlier measurement had the smaller one at half the
 // rate: the compiler had put copies of accumulators between them, see gw_mma.)
-// What bounds it: matrix instructions are 65 to 80 % of a large shape's clocks, at a clock of 1.6 to 1.8 GHz that the power sets; the
-// rest is waiting for LDS reads and loads.  Small shapes wait for the weight stream.
+// What bounds it: matrix instructions are in flight for 64 to 71 % of a large shape's clocks (46 to 55 % of QKV's and W_o's), at a clock of
+// 1.8 to 2.0 GHz that the power sets; the rest is waiting for LDS reads and loads.  Small shapes wait for the weight stream.
 // Measured alone, sustained (us, 32 x 32 instructions with an epilogue through LDS / now; gate/up, W_down, W_o, LM head): 7B over 256 rows
 // 56 / 52, 39 / 39, 17 / 17, 69 / 65; over 512 rows 88 / 81 (1.14 PFLOP/s), 56 / 52, 28 / 28, 116 / 106 (1.27); 33B over 384 rows 166 / 152
 // (1.21), 108 / 102, 45 / 43, 145 / 132; 13B over 128 rows 61 / 59, 34 / 34, 20 / 20, 61 / 61.  QKV as the plain product of its shape: 37 / 36 (7B,

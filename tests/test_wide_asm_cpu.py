@@ -135,7 +135,7 @@ def test_the_scan_follows_branches():
     assert faults(lines_of(*far, "s_endpgm", read))[0] == []
 
 
-@pytest.mark.skipif(not os.path.exists(f"{LLVM}/llvm-objdump"), reason="no disassembler")
+@pytest.mark.skipif(not (os.path.exists(OBJ) and os.path.exists(f"{LLVM}/llvm-objdump")), reason="no built object or no disassembler")
 def test_nothing_touches_an_operand_too_early(tmp_path):
     assert bld.built_from() == bld.sources_digest(), "the built objects are not those of the sources: build again"
     kernels = 0
